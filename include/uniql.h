@@ -147,9 +147,9 @@ typedef struct uniql_keep {
  *   y_f16 : device, fp16 [M][ldy], first n_keep entries of a row are written
  *   ldx >= k_keep, ldy >= n_keep (elements); x and y must not overlap (this is not checked:
  *   with overlapping buffers the result is undefined).
- * M = 1 runs the streaming GEMV; M >= 2 the MFMA dequant-GEMM: 2..32 tokens the decode-batch
- * kernels (a wave owns 16 rows and part of K; tall matrices above 8 tokens a slab kernel), up to
- * 64 tokens tiles whose K range is split over the waves of a block, large tiles for prefill.
+ * M = 1 runs the streaming GEMV; M >= 2 the MFMA dequant-GEMMs: 2..32 tokens the decode-batch
+ * kernel (a wave owns 16 rows and part of K), more tokens, tall matrices and codes of 8, 6 and 3 bits
+ * the pipelined kernel (loads in waves of their own), long prompts 256 x 256 tiles.
  * Errors: E_NULL, E_SHAPE, E_KEEP, E_ALIGN, E_ARCH, E_HIP.  E_SHAPE also at M = 1 when the last
  * kept column lies past stored column 81920 (the block's image of the activations in LDS holds
  * 40 tiles of 2048 columns), and for codes of 8, 6 or 3 bits past column 32768 at any M.
@@ -162,9 +162,9 @@ int uniql_w4_linear(const uniql_w4_t* W, const uniql_keep_t* keep, const void* x
  * projections of a layer (Eq. 2) or gate and up (Eq. 1), which read the same x.  W, keep (or NULL
  * = all unpruned), x_f16, ldx, y_f16, ldy are host arrays of n entries; each entry follows the
  * rules of uniql_w4_linear.  At M = 1 linears that stream rows of the same length are served by
- * ONE kernel launch (a decode step is launch-latency bound), and so are the linears of a decode
- * batch (M = 2..32) when each keeps a column prefix of at least 8 columns and is one the
- * decode-batch kernel takes; otherwise they are launched one after the other on the stream.
+ * ONE kernel launch (a decode step is launch-latency bound), and so are the linears of several
+ * tokens when one kernel takes them all (the decode-batch kernel with column prefixes of at least
+ * 8 columns, or the pipelined one); otherwise they are launched one after the other on the stream.
  * Results are identical to n separate uniql_w4_linear calls.
  * Errors: E_SHAPE also for n outside 1..4; otherwise as uniql_w4_linear (nothing is launched if
  * any entry is invalid).

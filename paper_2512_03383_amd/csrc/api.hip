@@ -3,6 +3,7 @@
 // error paths behave the same on a machine without a GPU.
 #include "../../include/uniql.h"
 #include "common.h"
+#include "pipe_serves.h"
 #include <algorithm>
 #include <atomic>
 #include <cmath>
@@ -124,8 +125,34 @@ static int fill_linear(const uniql_w4_t* W, const uniql_keep_t* keep, const void
 
 constexpr int kInterleavedMaxTokens = 64;   // a matrix with head-interleaved words: tokens per call
 
+// Codes of 8, 6 and 3 bits: what the streaming kernels' staging of one token does not hold (columns past 32768) or their
+// grid and group indices do not reach is refused whatever the number of tokens.
+static bool wide_codes_refused(const LinearArgs& a) {
+  const int c = a.bits == 8 ? 16 : 96 / a.bits;   // columns per unit of staged activations
+  if ((long long)(a.km.k_span + c - 1) / c * c * 2 > 64 * 1024 || a.M > 65535) return true;
+  return a.bits != 8 && (long long)a.N_total * (a.K_total / kGroup) > 0x7fffffffLL;
+}
+
+static hipError_t launch_pipe(const LinearArgs* p, int n, hipStream_t s) {
+  switch (p[0].bits * 2 + (p[0].bf16 ? 1 : 0)) {
+    case 6: return launch_pipe_w3(p, n, s);
+    case 7: return launch_pipe_w3_bf16(p, n, s);
+    case 12: return launch_pipe_w6(p, n, s);
+    case 13: return launch_pipe_w6_bf16(p, n, s);
+    case 16: return launch_pipe_w8(p, n, s);
+    case 17: return launch_pipe_w8_bf16(p, n, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
 static int run_linear(const LinearArgs& a, hipStream_t s) {
   if (a.bits != 4) {
+    if (wide_codes_refused(a)) return UNIQL_E_SHAPE;
+    // several tokens: the matrix kernel; the streaming ones read the weights once per token
+    if (pipe_serves(a)) {
+      hipError_t ep = launch_pipe(&a, 1, s);
+      return ep == hipSuccess ? UNIQL_OK : hip_fail(ep);
+    }
     hipError_t e8 = a.bits == 8 ? launch_w8_linear(a, s) : launch_wb_linear(a, s);
     if (e8 == hipErrorInvalidValue) return UNIQL_E_SHAPE;   // more kept columns than the kernel's staging holds
     return e8 == hipSuccess ? UNIQL_OK : hip_fail(e8);
@@ -172,9 +199,9 @@ extern "C" int uniql_w4_linear_multi(int32_t n, const uniql_w4_t* W, const uniql
     if (e == hipErrorInvalidValue) return UNIQL_E_SHAPE;
     return e == hipSuccess ? UNIQL_OK : hip_fail(e);
   }
-  if (n > 1 && M <= 32) {
-    // a decode batch: one launch when the decode-batch kernel takes every member (the same format: fill_linear's
-    // entries of one call may differ in it, then they go one by one)
+  if (n > 1) {
+    // one launch when one kernel takes every member (the same format: fill_linear's entries of one call may differ in
+    // it, then they go one by one)
     bool same = true, done = false;
     for (int i = 1; i < n; ++i) same = same && a[i].bf16 == a[0].bf16;
     if (same) {

@@ -294,14 +294,24 @@ hipError_t launch_w4_mlp_fused(const LinearArgs* probs, void* scratch, hipStream
 hipError_t launch_w4_mlp_fused_bf16(const LinearArgs* probs, void* scratch, hipStream_t stream, bool* done);
 hipError_t launch_w4_gemm(const LinearArgs& a, hipStream_t stream);
 hipError_t launch_w4_gemm_bf16(const LinearArgs& a, hipStream_t stream);
-// n (2..4) linears of one decode batch in one launch where the decode-batch kernel takes them all (*done says whether)
+// n (2..4) linears of one token count in one launch where one kernel takes them all (*done says whether)
 hipError_t launch_w4_gemm_batch(const LinearArgs* a, int n, hipStream_t stream, bool* done);
 hipError_t launch_w4_gemm_batch_bf16(const LinearArgs* a, int n, hipStream_t stream, bool* done);
 // gate (p[0]) and up (p[1]) of a decode batch (2..16 tokens) with h = SiLU(g) * u in one launch (*done says whether)
 hipError_t launch_w4_gate_up_silu_batch(const LinearArgs* p, hipStream_t stream, bool* done);
 hipError_t launch_w4_gate_up_silu_batch_bf16(const LinearArgs* p, hipStream_t stream, bool* done);
+// n linears of the same token count, width, format and way (pipe_dispatch.h) in one launch of the pipelined kernel, one
+// function per code width and format
+hipError_t launch_pipe_w3(const LinearArgs* p, int n, hipStream_t stream);
+hipError_t launch_pipe_w4(const LinearArgs* p, int n, hipStream_t stream);
+hipError_t launch_pipe_w6(const LinearArgs* p, int n, hipStream_t stream);
+hipError_t launch_pipe_w8(const LinearArgs* p, int n, hipStream_t stream);
+hipError_t launch_pipe_w3_bf16(const LinearArgs* p, int n, hipStream_t stream);
+hipError_t launch_pipe_w4_bf16(const LinearArgs* p, int n, hipStream_t stream);
+hipError_t launch_pipe_w6_bf16(const LinearArgs* p, int n, hipStream_t stream);
+hipError_t launch_pipe_w8_bf16(const LinearArgs* p, int n, hipStream_t stream);
 hipError_t launch_w4_dequant(const LinearArgs& a, hipStream_t stream);
-// codes of 8 bits: the dequantised matrix, and the linear for any number of tokens
+// codes of 8 bits: the dequantised matrix, and the linear with one token per grid row
 hipError_t launch_w8_dequant(const LinearArgs& a, hipStream_t stream);
 hipError_t launch_w8_linear(const LinearArgs& a, hipStream_t stream);
 // codes of 3 and 6 bits (a.bits), packed as a bit stream: the same two operations

@@ -12,14 +12,14 @@
 //
 // A wave owns BF fragments of 16 rows and AF fragments of 16 tokens (AF*BF accumulators of 4
 // VGPRs); a dequantised weight fragment is reused by AF MFMAs, an activation fragment by BF.
-// Small M (decode batches) is HBM-bound: AF = 1 and the K range is split over KS waves of the
-// block (reduced through LDS at the end) to get enough waves; large M (prefill) is MFMA-bound:
-// AF = 8, BF = 2, eight waves side by side over 256 rows, KS = 1, two groups per slab.
+// It serves the prompts whose tiles of 128 or 64 tokens x 256 rows fill the chip better than those of the
+// pipelined kernel (pipe_kernel.h), and every column rule and size the other kernels do not take.
 #pragma once
 #define UNIQL_ANDOR_PLAIN   // and-or as plain C here: the scheduler must be able to classify it as VALU
 #include "common.h"
 #include "smallm_kernel.h"
 #include "prefill_kernel.h"
+#include "pipe_dispatch.h"
 #include <type_traits>
 
 namespace uniql {
@@ -377,62 +377,100 @@ static hipError_t launch_cfg(const LinearArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
+template <bool BF16>
+static hipError_t launch_pipe4(const LinearArgs* p, int n, hipStream_t stream) {
+  if constexpr (BF16) return launch_pipe_w4_bf16(p, n, stream);
+  else return launch_pipe_w4(p, n, stream);
+}
+
+// Which kernel a linear of 2 tokens and more takes.  It follows from the linear alone.
+enum GemmRoute { kSmallM, kPipe, kPrefill256, kTile128, kTile64, kTileSmall };
+
+// xm: staging mode of the activations (0 element by element, 1 column prefix, 2 column segments of whole 8-column units)
+static inline GemmRoute gemm_route(const LinearArgs& a, int xm) {
+  const int row_tiles = (a.km.n_keep + 15) / 16;
+  const bool pipe = xm != 0 && pipe_serves(a);
+  // Decode batches (M <= 32) are bound by the weight stream and have a kernel of their own (smallm_kernel.h), except
+  // tall matrices whose activations it cannot stage once per block: a wave that stages its own 16 x 128 activations per
+  // group costs more than the pipelined kernel's slabs (9318 x 4096 at 8 / 16 / 24 tokens 12.7 / 16.6 / 23.2 us there,
+  // 11.0 / 11.0 / 12.4 us here; with 256 row tiles it is the other way round: 4096 x 9318 at 24 tokens 18.1 against 22.6).
+  const bool tall = row_tiles >= 400 && a.M >= 5 && !(xm == 1 && smallm_pre(a));
+  if (smallm_takes(a, xm == 1) && !(pipe && tall)) return kSmallM;
+  if (!pipe && a.M <= 64) return kTileSmall;
+  if (pipe && a.M <= 64) return kPipe;
+  // More tokens: the cheapest of the tiles, from what a group of 128 columns costs one tile with the chip full and what a
+  // tile costs besides (microseconds, measured; a tile in a round of its own where the tiles do not fill one)
+  const int cus = prefill_grid_limit();
+  const float ng = (float)((a.km.k_span + kGroup - 1) / kGroup);
+  auto cost = [&](int bm, int bn, float us) {
+    const long long tiles = (long long)((a.km.n_keep + bn - 1) / bn) * ((a.M + bm - 1) / bm);
+    return 3.f + (float)((tiles + cus - 1) / cus) * (5.f + ng * us);
+  };
+  GemmRoute best = kTileSmall;
+  // (32 tokens x 128 rows, for what the pipelined kernel does not serve)
+  float best_us = pipe ? pipe_pick<4>(&a, 1).us : cost(32, 128, 1.2f);
+  if (pipe) best = kPipe;
+  auto take = [&](GemmRoute r, float us) {
+    if (us < best_us) best = r, best_us = us;
+  };
+  if (xm == 1 && prefill_serves(a)) take(kPrefill256, cost(256, 256, a.bf16 ? 4.9f : 3.75f));
+  take(kTile128, cost(128, 256, (a.bf16 ? 2.9f : 2.35f) * (xm == 2 ? 1.1f : 1.f)));
+  take(kTile64, cost(64, 256, (a.bf16 ? 1.45f : 1.30f) * (xm == 2 ? 1.15f : 1.f)));
+  return best;
+}
+
 template <int XVEC, bool BF16>
 static hipError_t launch_m(const LinearArgs& a, hipStream_t stream) {
-  // Decode batches (M <= 32) are bound by the weight stream and have a kernel of their own (smallm_kernel.h), except
-  // tall matrices at more than 8 tokens: there this kernel's slab, staged once for 64 rows, costs less than every wave
-  // staging its own activations (14336-row gate at 16 / 32 tokens, weights from HBM: 12.3 / 15.3 us here, 14.1 / 19.5 us
-  // there; 3584-row down: 16.4 / 27.3 us here, 15.9 / 21.6 us there; up to 8 tokens the other kernel wins or ties
-  // everywhere; with the activations staged once per block -- column prefixes of at most 32 groups, up to 16 tokens --
-  // the other kernel takes the tall matrices at 9..16 tokens too: 18944-row gate at 16 tokens 11.6 against 12.7 us).  What that kernel does not take falls through to this one: 16 rows per wave and the K range split over
-  // the block's 8 waves, four ways when there are many row tiles, eight ways otherwise.
-  const int row_tiles = (a.km.n_keep + 15) / 16;
-  if (smallm_takes(a, XVEC == 1)) return smallm_dispatch<XVEC, BF16>(a, stream);
-  // (many row tiles: 32 rows per wave, so that an activation fragment read from LDS serves two weight fragments,
-  // 64 rows per block; few: 16 rows per block, two groups per wave and slab, which halves the number of barriers)
-  if (a.M <= 16) return row_tiles >= 600 ? launch_cfg<BF16, 1, 2, 2, 4, 1, 2, XVEC>(a, stream) : launch_cfg<BF16, 1, 1, 1, 8, 2, 1, XVEC>(a, stream);
-  // 17..32 tokens: tall matrices 32 rows per wave and 64 per block with two groups per wave and slab (Qwen gate at 32
-  // tokens 17.0 -> 14.5 us); short ones 16 rows per block, K over eight waves
-  if (a.M <= 32) return row_tiles >= 600 ? launch_cfg<BF16, 2, 2, 2, 4, 2, 1, XVEC>(a, stream) : launch_cfg<BF16, 2, 1, 1, 8, 1, 2, XVEC>(a, stream);
-  // 33..64 tokens: K over four waves in either case, or a matrix of a few thousand rows leaves most of the chip idle
-  // (64 x 128 tiles without a K split: Qwen down 122 us, gate 33 us; now 50 us and 21 us)
-  if (a.M <= 64) return row_tiles >= 600 ? launch_cfg<BF16, 4, 2, 2, 4, 1, 2, XVEC>(a, stream) : launch_cfg<BF16, 4, 1, 2, 4, 1, 2, XVEC>(a, stream);
-  // Prefill: the largest tile that still gives the chip about a block per CU.
-  auto blocks = [&](int bm, int bn) { return (long long)((a.km.n_keep + bn - 1) / bn) * ((a.M + bm - 1) / bm); };
-  constexpr long long kEnough = 192;
-  // 128 x 256: eight waves side by side over rows, 8 x 2 fragments each, two groups per wave and slab (a block barrier per
-  // 256 columns) and two slabs of weight loads in flight
-  // (bfloat16: with the longer unpack two slabs of weight loads in flight do not fit 256 registers; one does)
-  // 256 x 256 on a persistent grid (prefill_kernel.h), where its tiles fill the chip in fewer, longer rounds than
-  // twice as many 128 x 256 tiles would: a round of it takes about 1.8 rounds of those
-  // (gate / up at 4096 tokens 412 against 472 us in the same process, down 389 against 477, gate / up at 1000 tokens 131 against 164)
-  if constexpr (XVEC == 1) {
-    if (prefill_serves(a) && blocks(256, 256) >= kEnough) {
-      const long long cus = prefill_grid_limit();
-      const long long rounds_big = (blocks(256, 256) + cus - 1) / cus, rounds_std = (blocks(128, 256) + cus - 1) / cus;
-      if (rounds_big * 18 < rounds_std * 10) return launch_prefill_cfg<BF16, 16, 2, 8, 1, 1, 8, 2, 1>(a, stream);
-    }
+  switch (gemm_route(a, XVEC)) {
+    case kSmallM: return smallm_dispatch<XVEC, BF16>(a, stream);
+    case kPipe: return launch_pipe4<BF16>(&a, 1, stream);
+    case kPrefill256:
+      if constexpr (XVEC == 1) return launch_prefill_cfg<BF16, 16, 2, 8, 1, 1, 8, 2, 1>(a, stream);
+      break;
+    // 128 x 256: eight waves side by side over rows, 8 x 2 fragments each, two groups per wave and slab (a block barrier per
+    // 256 columns) and two slabs of weight loads in flight (bfloat16: with the longer unpack two do not fit 256 registers)
+    case kTile128: return launch_cfg<BF16, 8, 2, 8, 1, 2, BF16 ? 1 : 2, XVEC>(a, stream);
+    case kTile64: return launch_cfg<BF16, 4, 2, 8, 1, 2, 2, XVEC>(a, stream);
+    default: break;
   }
-  if (blocks(128, 256) >= kEnough) {
-    if constexpr (BF16) return launch_cfg<BF16, 8, 2, 8, 1, 2, 1, XVEC>(a, stream);
-    else return launch_cfg<BF16, 8, 2, 8, 1, 2, 2, XVEC>(a, stream);
-  }
-  if (blocks(64, 256) >= kEnough) return launch_cfg<BF16, 4, 2, 8, 1, 2, 2, XVEC>(a, stream);
-  if (blocks(64, 128) >= kEnough) return launch_cfg<BF16, 4, 2, 4, 2, 2, 1, XVEC>(a, stream);   // K split over two waves
-  // few tiles whatever the shape (e.g. 4096 rows at 128 or 256 tokens): 32 tokens x 128 rows, K over two waves
-  // (down_proj at 256 tokens: 61 us against 77 us with 64 x 64 tiles)
+  // column rules and sizes that the pipelined kernel does not serve: K over eight waves up to 16 tokens, else 32 tokens x
+  // 128 rows, K over two waves
+  if (a.M <= 16) return launch_cfg<BF16, 1, 1, 1, 8, 2, 1, XVEC>(a, stream);
   return launch_cfg<BF16, 2, 2, 4, 2, 2, 1, XVEC>(a, stream);
 }
 
 // the staging mode of the activations, then the tile shape
-template <bool BF16>
-static hipError_t launch_gemm_fmt(const LinearArgs& a, hipStream_t stream) {
+static inline int gemm_xm(const LinearArgs& a) {
   // 128-bit x loads: a column prefix (global loads of any size may start on any 2-byte boundary on
   // this target, so odd leading dimensions such as k_keep = 12185 qualify), or column segments
   // whose stride is a multiple of 8 and that keep at least 8 columns each
-  if (a.km.cs_stride == 0) return a.km.k_keep >= 8 ? launch_m<1, BF16>(a, stream) : launch_m<0, BF16>(a, stream);
-  if (a.km.cs_stride % 8 == 0 && a.km.cs_keep >= 8) return launch_m<2, BF16>(a, stream);
-  return launch_m<0, BF16>(a, stream);
+  if (a.km.cs_stride == 0) return a.km.k_keep >= 8 ? 1 : 0;
+  return a.km.cs_stride % 8 == 0 && a.km.cs_keep >= 8 ? 2 : 0;
+}
+
+template <bool BF16>
+static hipError_t launch_gemm_fmt(const LinearArgs& a, hipStream_t stream) {
+  const int xm = gemm_xm(a);
+  return xm == 1 ? launch_m<1, BF16>(a, stream) : xm == 2 ? launch_m<2, BF16>(a, stream) : launch_m<0, BF16>(a, stream);
+}
+
+// n (2..4) linears of the same token count and format in one launch: a decode batch that the decode-batch kernel takes, or
+// linears that the pipelined kernel takes with the same split of K and kind of column rule.  *done = false: not such a
+// set, nothing was launched.
+template <bool BF16>
+static hipError_t launch_gemm_batch_fmt(const LinearArgs* a, int n, hipStream_t stream, bool* done) {
+  *done = false;
+  bool small = true, pipe = true;
+  for (int i = 0; i < n; ++i) {
+    const int xm = gemm_xm(a[i]);
+    const GemmRoute r = xm == 0 ? kTileSmall : gemm_route(a[i], xm);
+    small = small && r == kSmallM && xm == 1;
+    pipe = pipe && r == kPipe && xm == gemm_xm(a[0]) && pipe_way(a[i]) == pipe_way(a[0]);
+  }
+  if (small) return smallm_batch<BF16>(a, n, stream, done);
+  if (!pipe) return hipSuccess;
+  *done = true;
+  return launch_pipe4<BF16>(a, n, stream);
 }
 
 }  // namespace uniql

@@ -1,0 +1,98 @@
+// Which tile of pipe_kernel.h a linear takes, and its launch.  One translation unit per code width and format
+// (pipe_w*.hip) instantiates it.
+#pragma once
+#include "pipe_kernel.h"
+#include "pipe_serves.h"
+#include "prefill_kernel.h"   // prefill_grid_limit: compute units of the device
+
+namespace uniql {
+
+// A tile and what it costs: microseconds per slab of one tile with the chip full (measured on 2560..12185 columns; segments
+// take the masks on top)
+struct PipeTile {
+  int af, bf, wn, g;
+  float us, us_seg;
+};
+
+template <int BITS>
+static inline PipeTile pipe_pick(const LinearArgs* p, int n) {
+  // groups: 32- and 64-row tiles; mixed: 64- and 96-row tiles (96 rows x 64 tokens do not fit with 8-bit codes);
+  // halves: rows x tokens from 128 x 128 down to 64 x 64 (segments: no 128 tokens, the masks cost it its registers;
+  // 8-bit codes: no 112, its buffers)
+  static const PipeTile groups[] = {{1, 1, 2, 4, 0.55f, 0.60f}, {1, 2, 2, 4, 0.95f, 1.0f}, {2, 1, 2, 4, 0.60f, 0.70f}, {2, 2, 2, 4, 1.05f, 1.1f}};
+  static const PipeTile mixed[] = {{3, 2, 2, 2, 0.69f, 0.75f}, {3, 3, 2, 2, 0.87f, 0.95f}, {4, 2, 2, 2, 0.80f, 0.90f}, {4, 3, 2, 2, 1.0f, 1.1f}};
+  static const PipeTile halves[] = {{8, 2, 4, 1, 1.17f, 0.f}, {7, 2, 4, 1, 1.08f, 1.20f}, {6, 2, 4, 1, 0.90f, 1.0f}, {4, 2, 4, 1, 0.70f, 0.80f}, {4, 1, 4, 1, 0.46f, 0.53f}};
+  const PipeWay way = pipe_way(p[0]);
+  const bool seg = p[0].km.cs_stride != 0;
+  const PipeTile* set = way == kPipeGroups ? groups : way == kPipeMixed ? mixed : halves;
+  const int count = way == kPipeHalves ? 5 : 4, M = p[0].M;
+  int slabs = 0;
+  for (int i = 0; i < n; ++i) slabs = max(slabs, (p[i].km.k_span + kGroup - 1) / kGroup);
+  PipeTile best = {};
+  float best_us = 0.f;
+  for (int c = 0; c < count; ++c) {
+    const PipeTile& t = set[c];
+    if (way == kPipeGroups && t.af != (M <= 16 ? 1 : 2)) continue;
+    if (way == kPipeMixed && t.af != (M <= 48 ? 3 : 4)) continue;
+    if (BITS > 4 && way != kPipeGroups && ((t.af == 4 && t.bf == 3) || t.af == 7)) continue;
+    if (BITS > 4 && way == kPipeGroups && t.bf == 2) continue;
+    if (seg && t.us_seg == 0.f) continue;
+    long long tiles = 0;
+    for (int i = 0; i < n; ++i) tiles += (p[i].km.n_keep + t.wn * t.bf * 16 - 1) / (t.wn * t.bf * 16);
+    tiles *= (M + 16 * t.af - 1) / (16 * t.af);
+    const int cus = prefill_grid_limit();
+    const float us = 3.f + (float)((tiles + cus - 1) / cus) * (3.f + (float)((slabs + t.g - 1) / t.g) * (seg ? t.us_seg : t.us));
+    if (best.af == 0 || us < best_us) best = t, best_us = us;
+  }
+  best.us = best_us;
+  return best;
+}
+
+// slabs of codes in flight where the activations leave room
+constexpr int pipe_nw(int lds, int sz, int wbytes, int most) {
+  int n = (160 * 1024 - lds - sz) / wbytes;
+  n = n < most ? n : most;
+  const int counted = 63 / (wbytes / 1024) + 1;   // (n - 1 slabs of loads in flight are counted in six bits)
+  return n < counted ? n : counted;
+}
+template <int AF, int BF, int WN, int KG, int KQ, int G, int NX, int BITS, bool BF16, bool SEG>
+static hipError_t pipe_tile(const LinearArgs* p, int n, hipStream_t s) {
+  constexpr int BN = WN * BF * 16;
+  constexpr int NW = pipe_nw(NX * 16 * AF * G * 256, BN * 64, BN * G * BITS * 16, 8);
+  return pipe_launch<AF, BF, WN, KG, KQ, G, NX, NW, BITS, BF16, SEG>(p, n, s);
+}
+
+template <int BITS, bool BF16, bool SEG>
+static hipError_t pipe_run(const LinearArgs* p, int n, hipStream_t s) {
+  const PipeTile t = pipe_pick<BITS>(p, n);
+  switch (pipe_way(p[0])) {
+    case kPipeGroups:
+      if constexpr (BITS <= 4) {
+        if (t.bf == 2) return t.af == 1 ? pipe_tile<1, 2, 2, 4, 1, 4, 3, BITS, BF16, SEG>(p, n, s) : pipe_tile<2, 2, 2, 4, 1, 4, 3, BITS, BF16, SEG>(p, n, s);
+      }
+      return t.af == 1 ? pipe_tile<1, 1, 2, 4, 1, 4, 4, BITS, BF16, SEG>(p, n, s) : pipe_tile<2, 1, 2, 4, 1, 4, 3, BITS, BF16, SEG>(p, n, s);
+    case kPipeMixed:
+      if (t.af == 3) return t.bf == 2 ? pipe_tile<3, 2, 2, 2, 2, 2, BITS <= 4 ? 4 : 3, BITS, BF16, SEG>(p, n, s) : pipe_tile<3, 3, 2, 2, 2, 2, 3, BITS, BF16, SEG>(p, n, s);
+      if constexpr (BITS <= 4) {
+        if (t.bf == 3) return pipe_tile<4, 3, 2, 2, 2, 2, 3, BITS, BF16, SEG>(p, n, s);
+      }
+      return pipe_tile<4, 2, 2, 2, 2, 2, 3, BITS, BF16, SEG>(p, n, s);
+    default:
+      if constexpr (!SEG) {
+        if (t.af == 8) return pipe_tile<8, 2, 4, 1, 2, 1, 3, BITS, BF16, SEG>(p, n, s);
+      }
+      if constexpr (BITS <= 4) {
+        if (t.af == 7) return pipe_tile<7, 2, 4, 1, 2, 1, 4, BITS, BF16, SEG>(p, n, s);
+      }
+      if (t.af == 6) return pipe_tile<6, 2, 4, 1, 2, 1, BITS <= 4 ? 4 : 3, BITS, BF16, SEG>(p, n, s);
+      return t.bf == 2 ? pipe_tile<4, 2, 4, 1, 2, 1, 6, BITS, BF16, SEG>(p, n, s) : pipe_tile<4, 1, 4, 1, 2, 1, 6, BITS, BF16, SEG>(p, n, s);
+  }
+}
+
+// n linears (the same token count, format, width, way and kind of column rule; the caller checks) in one launch
+template <int BITS, bool BF16>
+static hipError_t pipe_linears(const LinearArgs* p, int n, hipStream_t s) {
+  return p[0].km.cs_stride != 0 ? pipe_run<BITS, BF16, true>(p, n, s) : pipe_run<BITS, BF16, false>(p, n, s);
+}
+
+}  // namespace uniql

@@ -1,0 +1,477 @@
+// Linears of more than a few tokens on MFMA for codes of 8, 6, 4 and 3 bits: y[M][n_keep] = x[M][k_keep] * W'^T, with the
+// loads in waves of their own.
+//
+// A block of twelve waves owns BN = WN * BF * 16 rows and BM = 16 AF tokens.  The columns go by in slabs of G groups; a slab
+// is the block's activations and packed codes of those groups.
+//  - Two waves do nothing but move activations into LDS (128-bit loads that write LDS directly: no registers, no LDS
+//    instructions), up to NX - 1 slabs ahead, and a third one codes, NW - 1 slabs ahead: loads return in order, and codes
+//    come from memory where activations come from the L2.  The next slab is there one barrier early.
+//  - One wave does the same for scales and zero points, eight groups of a row at a time, through registers.
+//  - Eight waves, WN along the rows times KG along the groups of a slab times KQ along the four steps of a group, read codes
+//    and activations from LDS, unpack in registers (codes.h) and multiply.  They never wait for memory, and the first
+//    fragments of the next slab are read before the barrier that ends the current one.
+// The point of the split: in a kernel whose waves load, stage and multiply in turn these phases add up, since all waves
+// of a block are in the same phase; here the address unit, the LDS and the matrix pipes work on different slabs at the
+// same time.  And a block's share of a packed row is fetched as contiguous runs (17 clocks of the address unit per KB)
+// instead of 16 rows per load (65 clocks).
+//
+// LDS layout: activations [token][16 G chunks of 8 columns], chunk c of token t at c ^ (t % 16); codes [row][units of 16
+// bytes], the units of a row permuted likewise where their number is a power of two: the 16 lanes of a fragment read 16
+// different bank groups.  Activations stay in memory order (codes.h gives the weights in that order).
+//
+// The partial sums of the KG x KQ waves meet in LDS and are added in order; within a wave sums run in order of the columns.  The
+// result depends on KG and KQ, not on AF, BF, WN, G, NX or NW.
+#pragma once
+#include "codes.h"
+#include <type_traits>
+
+namespace uniql {
+
+constexpr uint32_t kBufferWord3 = 0x00020000u;
+constexpr int kBeyond = (int)0x80000000u;   // as an unsigned offset: past the end of every resource below 2 GiB; reads zeros
+
+constexpr int kPipeConsumers = 8, kPipeMovers = 2;
+constexpr int kPipeThreads = (kPipeConsumers + kPipeMovers + 2) * kWave;
+constexpr int kPipeDies = 8, kPipeTokTilesPerPass = 4;
+
+// Up to four linears with the same token count and format; tiles are numbered through the whole batch.
+struct PipeBatch {
+  LinearArgs p[kMaxBatch];
+  int first[kMaxBatch];   // first tile of problem i
+  int n, tiles, ntt;      // problems, all tiles, token tiles (the same for every problem)
+};
+
+template <int AF, int BF, int WN, int KG, int KQ, int G, int NX, int NW, int BITS>
+struct PipeShape {
+  static_assert(WN * KG * KQ == kPipeConsumers && G % KG == 0 && 4 % KQ == 0, "eight waves multiply");
+  static constexpr int BM = 16 * AF, BN = WN * BF * 16, KS = KG * KQ, T = 4 / KQ, GW = G / KG;   // a wave: GW groups of a slab, T steps of each
+  static_assert(GW * T % 2 == 0, "two sets of activation fragments take turns");
+  static constexpr int U = G * BITS;                           // 16-byte units of codes per row and slab
+  static constexpr int XBytes = BM * G * 256, WBytes = BN * U * 16;
+  static constexpr int XI = XBytes / 1024, WI = (WBytes + 1023) / 1024; // loads of 64 x 16 bytes
+  static_assert(WBytes % 1024 == 0, "whole loads");
+  static constexpr int XPW = (XI + kPipeMovers - 1) / kPipeMovers;
+  static constexpr int SZ = 2 * BN * 8 * 4;                    // two windows of eight groups
+  static constexpr int W0 = NX * XBytes, SZ0 = W0 + NW * WBytes, Lds = SZ0 + SZ;
+  static_assert((NX - 1) * XPW <= 63 && (NW - 1) * WI <= 63, "loads in flight are counted in six bits");
+  static_assert(NX >= 3 && NW >= 3 && 8 % G == 0 && G <= 4, "a slab in use, one ready, one on its way; a window of scales is two slabs or more");
+  static_assert(Lds <= 160 * 1024, "the slabs fit the LDS");
+  static_assert(KS == 1 || kPipeConsumers * AF * BF * 1024 <= Lds, "so do the partial sums");
+};
+
+__device__ __forceinline__ void pipe_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+template <int AF, int BF, int WN, int KG, int KQ, int G, int NX, int NW, int BITS, bool BF16, bool SEG>
+__global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
+#ifdef __HIP_DEVICE_COMPILE__   // (the loads into LDS have no form in the host's pass)
+  typedef PipeShape<AF, BF, WN, KG, KQ, G, NX, NW, BITS> S;
+  constexpr int BM = S::BM, BN = S::BN, U = S::U, KS = S::KS;
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+
+  // Tile of this block.  Consecutive blocks go to the eight dies in turn, each with an L2 of its own: a die takes a
+  // contiguous stretch of the tiles, and inside a problem the tiles run row tile by row tile over a few token tiles at
+  // a time, so that the blocks a die runs at once share codes and activations through its L2.
+  int rt, tt, pi = 0;
+  {
+    const int b = (int)blockIdx.x, die = b % kPipeDies, nb = bt.tiles;
+    int L = die * (nb / kPipeDies) + (die < nb % kPipeDies ? die : nb % kPipeDies) + b / kPipeDies;
+#pragma unroll
+    for (int i = 1; i < kMaxBatch; ++i) pi += (i < bt.n && L >= bt.first[i]) ? 1 : 0;
+    L -= bt.first[pi];
+    const int nrt = (bt.p[pi].km.n_keep + BN - 1) / BN, ntt = bt.ntt;
+    const int full = ntt / kPipeTokTilesPerPass * kPipeTokTilesPerPass;
+    if (L < nrt * full) {
+      const int pass = L / (nrt * kPipeTokTilesPerPass), r = L - pass * (nrt * kPipeTokTilesPerPass);
+      rt = r / kPipeTokTilesPerPass;
+      tt = pass * kPipeTokTilesPerPass + (r - rt * kPipeTokTilesPerPass);
+    } else {
+      const int w = ntt - full, r = L - nrt * full;
+      rt = r / w;
+      tt = full + (r - rt * w);
+    }
+  }
+  const LinearArgs a = bt.p[pi];
+  const KeepMap& km = a.km;
+  const int n0 = rt * BN, m0 = tt * BM;
+  const int row_bytes = a.K_total / 8 * BITS, gpr = a.K_total / kGroup;
+  const int ngroups = (km.k_span + kGroup - 1) / kGroup;
+  const int nslab = (ngroups + G - 1) / G;
+  const int kv = km.k_keep & ~7;
+  // column segments: a power of two up to the group's 128 columns (the host checks), so every group has the same pattern
+  const int seg_shift = SEG ? __builtin_ctz((unsigned)km.cs_stride) : 0;
+
+  if (wave >= kPipeConsumers) {
+    __builtin_amdgcn_s_setprio(3);
+    typedef __attribute__((address_space(3))) unsigned char lds_byte;
+    typedef __attribute__((address_space(3))) void lds_void;
+    lds_byte* const lds = (lds_byte*)smem;
+    // A mover's walk: slabs 0 .. N - 2 to begin with, then, one barrier per slab, the slab that takes the buffer which
+    // everybody has left.  Before barrier `it` the slabs up to it + 1 have landed.
+    auto walk = [&](auto n, auto per, auto&& move) {
+      constexpr int N = decltype(n)::value, PER = decltype(per)::value;
+#pragma unroll
+      for (int p = 0; p < N - 1; ++p)
+        if (p < nslab) move(p, p);
+      int buf = N - 1;
+      for (int it = 0; it < nslab; ++it) {
+        if (it + N - 2 < nslab) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((N - 3) * PER) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        pipe_barrier();
+        if (it + N - 1 < nslab) move(it + N - 1, buf);
+        buf = buf + 1 == N ? 0 : buf + 1;
+      }
+      pipe_barrier();
+    };
+    if (wave < kPipeConsumers + kPipeMovers) {
+      // ---- activations
+      const int d = wave - kPipeConsumers;
+      const int mt = a.M - m0 < BM ? a.M - m0 : BM;
+      const int ldx2 = (int)a.ldx * 2;
+      // rows past the last token lie beyond the resource and read as zero
+      const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<half_t*>(a.x + (size_t)m0 * a.ldx), 0,
+                                                                          (mt - 1) * ldx2 + km.k_keep * 2, kBufferWord3);
+      // Byte offset of this lane's unit of load k in slab `slab`.  Segments divide the groups, so every group is alike: its
+      // kept columns are `kpg` consecutive ones of x, a block's kept columns its first ones, contiguous.  A slab that lies
+      // wholly in the row takes slab 0's offsets and a scalar (a load is then two instructions; a mover issues one
+      // every 60 clocks otherwise).
+      const int kpg = SEG ? (kGroup >> seg_shift) * km.cs_keep : kGroup;
+      auto unit = [&](int k, int slab) {
+        const int q0 = d + kPipeMovers * k, q = q0 < S::XI ? q0 : 0;   // (uniform; a turn with nothing left repeats the first load)
+        constexpr int CH = 16 * G;                       // chunks per token
+        const int v = q * 64;
+        const int tok = v / CH + (CH < 64 ? lane / CH : 0);
+        const int c = (CH <= 64 ? lane % CH : v % CH + lane) ^ (tok & 15);
+        const int g = slab * G + c / 16, k0 = (c % 16) * 8;   // group, column in it
+        int col = g * kpg + k0;
+        bool there = g * kGroup + k0 + 8 <= kv;          // a prefix: whole blocks below kv, the rest in the epilogue
+        if constexpr (SEG) {
+          const int off = k0 & (km.cs_stride - 1);
+          col = g * kpg + (k0 >> seg_shift) * km.cs_keep + off;
+          there = off < km.cs_keep && g < ngroups;
+        }
+        return there ? tok * ldx2 + col * 2 : kBeyond;
+      };
+      const int nwhole = SEG ? ngroups / G : kv / (G * kGroup);
+      int first[S::XPW];                                 // (of use when there is a whole slab: then slab 0 is one)
+#pragma unroll
+      for (int k = 0; k < S::XPW; ++k) first[k] = unit(k, 0);
+      walk(std::integral_constant<int, NX>(), std::integral_constant<int, S::XPW>(), [&](int slab, int buf) {
+        lds_byte* const to = lds + buf * S::XBytes + d * 1024;
+        if (slab < nwhole) {
+#pragma unroll
+          for (int k = 0; k < S::XPW; ++k)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void*)(d + kPipeMovers * k < S::XI ? to + k * (kPipeMovers * 1024) : to - d * 1024), 16,
+                                                     first[k], slab * (G * kpg * 2), 0, 0);
+        } else {
+#pragma unroll
+          for (int k = 0; k < S::XPW; ++k)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void*)(d + kPipeMovers * k < S::XI ? to + k * (kPipeMovers * 1024) : to - d * 1024), 16,
+                                                     unit(k, slab), 0, 0, 0);
+        }
+      });
+      return;
+    }
+    if (wave == kPipeConsumers + kPipeMovers) {
+      // ---- codes
+      const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(a.qweight), 0, a.N_total * row_bytes, kBufferWord3);
+      int woff[S::WI];                                   // byte offset of the lane's unit in slab 0
+#pragma unroll
+      for (int k = 0; k < S::WI; ++k) {
+        const int v = k * 64 + lane, row = v / U, j = v - row * U;
+        int js = j;
+        if constexpr ((U & (U - 1)) == 0) js = U >= 16 ? j ^ (row & 15) : j ^ ((row / (U < 16 ? 16 / U : 1)) & (U - 1));
+        int rc = n0 + row;
+        rc = rc < km.n_keep ? rc : km.n_keep - 1;       // (rows past the last one: a valid, unused load)
+        woff[k] = stored_row(km, rc) * row_bytes + js * 16;
+      }
+      walk(std::integral_constant<int, NW>(), std::integral_constant<int, S::WI>(), [&](int slab, int buf) {
+        if ((slab + 1) * G <= gpr) {
+#pragma unroll
+          for (int k = 0; k < S::WI; ++k)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_void*)(lds + S::W0 + buf * S::WBytes + k * 1024), 16, woff[k], slab * (U * 16), 0, 0);
+        } else {
+          // (a slab's groups past the row's end: the next row's codes, or nothing behind the matrix; their scale is zero)
+#pragma unroll
+          for (int k = 0; k < S::WI; ++k)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_void*)(lds + S::W0 + buf * S::WBytes + k * 1024), 16, woff[k] + slab * (U * 16), 0, 0, 0);
+        }
+      });
+      return;
+    }
+    // ---- scales and zero points: row lane (+ 64 p) of the block, windows of eight groups, scale | zero << 16.  The window
+    // never leaves the row (a load whose last word lies partly past the array comes back with that word zeroed): at the
+    // row's end it starts `back` groups earlier and is shifted.  Groups past the last one get a zero scale.
+    constexpr int P = (BN + 63) / 64, SPW = 8 / G;      // rows per lane, slabs per window
+    uint32_t* szs = reinterpret_cast<uint32_t*>(smem + S::SZ0);
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(a.scales), 0, a.N_total * gpr * 2, kBufferWord3);
+    const __amdgpu_buffer_rsrc_t rz = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(a.zeros), 0, a.zeros ? a.N_total * gpr : 0, kBufferWord3);
+    const bool has_z = a.zeros != nullptr;
+    int e0[P];
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+      int rc = n0 + p * 64 + lane;
+      rc = rc < km.n_keep ? rc : km.n_keep - 1;
+      e0[p] = stored_row(km, rc) * gpr;
+    }
+    u32x4_t s[P];
+    u32x2_t z[P];
+    auto fetch = [&](int w) {
+      const int g = 8 * w, back = g + 8 > gpr ? g + 8 - gpr : 0;
+      const bool there = g < ngroups;
+#pragma unroll
+      for (int p = 0; p < P; ++p) {
+        s[p] = __builtin_amdgcn_raw_buffer_load_b128(rs, there ? 2 * (e0[p] + g - back) : kBeyond, 0, 0);
+        z[p] = __builtin_amdgcn_raw_buffer_load_b64(rz, there ? e0[p] + g - back : kBeyond, 0, 0);
+      }
+    };
+    auto put = [&](int w) {
+      const int g = 8 * w, back = g + 8 > gpr ? (g + 8 - gpr) & 7 : 0;
+#pragma unroll
+      for (int p = 0; p < P; ++p) {
+        const unsigned __int128 sv = ((unsigned __int128)s[p].w << 96 | (unsigned __int128)s[p].z << 64 |
+                                      (unsigned __int128)s[p].y << 32 | (unsigned __int128)s[p].x) >> (16 * back);
+        const uint64_t zv = has_z ? (((uint64_t)z[p].y << 32) | z[p].x) >> (8 * back) : (uint64_t)(1u << (BITS - 1)) * 0x0101010101010101ull;
+        uint32_t o[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          o[j] = (g + j < ngroups ? (uint32_t)(sv >> (16 * j)) & 0xffffu : 0u) | ((uint32_t)(zv >> (8 * j)) & 0xffu) << 16;
+        const int row = p * 64 + lane;
+        uint4* dst = reinterpret_cast<uint4*>(szs + ((w & 1) * BN + row) * 8);
+        if (BN % 64 == 0 || row < BN) {
+          dst[0] = make_uint4(o[0], o[1], o[2], o[3]);
+          dst[1] = make_uint4(o[4], o[5], o[6], o[7]);
+        }
+      }
+    };
+    fetch(0);
+    put(0);
+    fetch(1);
+    for (int it = 0; it < nslab; ++it) {
+      pipe_barrier();
+      if (it % SPW == 0) {
+        const int w = it / SPW;
+        put(w + 1);                       // into the window before the current one
+        fetch(w + 2);
+      }
+    }
+    pipe_barrier();
+    return;
+  }
+
+  // ---- consumers
+  const int wn = wave % WN, wk = wave / WN, kg = wk / KQ, kq = wk % KQ;
+  const int n = lane & 15, ks = lane >> 4;
+  constexpr int SPW = 8 / G, T = S::T, GW = S::GW;
+  float4_t acc[AF][BF];
+#pragma unroll
+  for (int f = 0; f < AF; ++f)
+#pragma unroll
+    for (int b = 0; b < BF; ++b) acc[f][b] = float4_t{0.f, 0.f, 0.f, 0.f};
+  const CodeMagic mg = make_code_magic<BITS, BF16>();
+  // LDS byte offsets inside a slab: activations of the wave's step t of its first group (token n), codes of its slots
+  int xoff[T], wro[BF][GW];
+#pragma unroll
+  for (int t = 0; t < T; ++t) xoff[t] = (n * (16 * G) + kg * 16 + ((ks * 4 + kq * T + t) ^ n)) * 16;
+#pragma unroll
+  for (int b = 0; b < BF; ++b)
+#pragma unroll
+    for (int g = 0; g < GW; ++g) {
+      const int row = (wn * BF + b) * 16 + n, byte = (g * KG + kg) * (16 * BITS) + ks * (4 * BITS);   // of the row's codes in the slab
+      int o = byte;
+      if constexpr ((U & (U - 1)) == 0) {
+        // (8 bits: a slot is two units and the permutation may swap them, so the window's own unit is addressed)
+        const int by = byte + (BITS == 8 ? kq * (T * BITS) : 0);
+        const int sw = U >= 16 ? row & 15 : (row / (U < 16 ? 16 / U : 1)) & (U - 1);
+        o = (((by >> 4) ^ sw) << 4) | (by & 15);
+      }
+      wro[b][g] = S::W0 + row * U * 16 + o;
+    }
+  const uint32_t* szs = reinterpret_cast<const uint32_t*>(smem + S::SZ0) + (wn * BF * 16 + n) * 8 + kg;
+
+  // segments: the block that holds a segment's last kept columns arrives with the next segment's first ones (or the next
+  // token's) behind them; the masks of the lane's blocks of a group
+  uint4 mask[SEG ? T : 1];
+  if constexpr (SEG) {
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      const int k = km.cs_keep - (((ks * 4 + kq * T + t) * 8) & (km.cs_stride - 1));   // kept columns from the block's first one on
+      auto m = [&](int i) { return (k > i ? 0xffffu : 0u) | (k > i + 1 ? 0xffff0000u : 0u); };
+      mask[t] = make_uint4(m(0), m(2), m(4), m(6));
+    }
+  }
+
+  // A step multiplies one unpacked operand per row fragment with AF activation fragments.  Meanwhile the operands of the next
+  // step are unpacked between the products -- two waves share a SIMD and run in phase, so a wave that unpacks, then
+  // multiplies, leaves the matrix pipe idle while it unpacks -- and the fragments of the next step and the codes of the
+  // group after that are read from LDS.
+  typedef RawCodes<BITS, T> Raw;
+  struct Group { Raw raw[BF]; uint32_t sz[BF]; };
+  auto read_group = [&](const unsigned char* sl, int it, int g, Group& o) {   // sl: smem + offset of the slab's codes
+#pragma unroll
+    for (int b = 0; b < BF; ++b) {
+      if constexpr (BITS == 8) {
+        // a slot is two units of 16 bytes: both, one or half of one
+        if constexpr (T == 1) {
+          const u32x2_t v = *reinterpret_cast<const u32x2_t*>(sl + wro[b][g]);
+          o.raw[b].w[0] = v.x; o.raw[b].w[1] = v.y;
+        } else {
+#pragma unroll
+          for (int h = 0; h < T / 2; ++h) {
+            const uint4 v = *reinterpret_cast<const uint4*>(sl + (wro[b][g] ^ (16 * h)));
+            o.raw[b].w[4 * h] = v.x; o.raw[b].w[4 * h + 1] = v.y; o.raw[b].w[4 * h + 2] = v.z; o.raw[b].w[4 * h + 3] = v.w;
+          }
+        }
+      } else {
+        o.raw[b] = read_codes<BITS, T>(sl + wro[b][g], kq);
+      }
+      o.sz[b] = szs[(((it / SPW) & 1) * BN + b * 16) * 8 + (it % SPW) * G + g * KG];
+    }
+  };
+  auto read_a = [&](const unsigned char* sl, int g, int t, uint4 (&o)[AF]) {
+#pragma unroll
+    for (int f = 0; f < AF; ++f) o[f] = *reinterpret_cast<const uint4*>(sl + xoff[t] + (f * (16 * 16 * G) + g * (KG * 16)) * 16);
+  };
+  auto constants = [&](const Group& r, CodeGroup<BITS, BF16> (&o)[BF]) {
+#pragma unroll
+    for (int b = 0; b < BF; ++b) o[b] = make_code_group<BITS, BF16>(r.sz[b] & 0xffffu, r.sz[b] >> 16);
+  };
+  // cur: the group whose operands are being unpacked; ahead: with T > 1 the next group, with T = 1 the two after the
+  // current one take turns
+  Group cur, ahead[2];
+  CodeGroup<BITS, BF16> gq[BF];
+  uint4 av[2][AF], wf[2][BF];
+  pipe_barrier();                         // slabs 0 and 1 are in LDS
+  const unsigned char *xsl = smem, *wsl = smem;
+  read_group(wsl, 0, 0, cur);
+  read_a(xsl, 0, 0, av[0]);
+  if constexpr (T == 1) read_group(wsl, 0, 1, ahead[1]);
+  constants(cur, gq);
+#pragma unroll
+  for (int b = 0; b < BF; ++b) wf[0][b] = code_step<BITS, BF16, T>(cur.raw[b], 0, gq[b], mg);
+  int xb = 1, wb = 1;
+  for (int it = 0; it < nslab; ++it) {
+    const unsigned char *xnext = smem + xb * S::XBytes, *wnext = smem + wb * S::WBytes;
+    xb = xb + 1 == NX ? 0 : xb + 1;
+    wb = wb + 1 == NW ? 0 : wb + 1;
+#pragma unroll
+    for (int s = 0; s < GW * T; ++s) {
+      const int g = s / T, t = s % T, s1 = (s + 1) % (GW * T), p = s & 1;
+      read_a(s1 ? xsl : xnext, s1 / T, s1 % T, av[p ^ 1]);
+      if constexpr (T == 1) {
+        if (s + 2 < GW) read_group(wsl, it, s + 2, ahead[p]);
+        else read_group(wnext, it + 1, s + 2 - GW, ahead[p]);
+      } else if (t == 0) {
+        if (g + 1 < GW) read_group(wsl, it, g + 1, ahead[0]);
+        else read_group(wnext, it + 1, 0, ahead[0]);
+      }
+      __builtin_amdgcn_sched_barrier(0);   // (or the compiler moves the reads behind the products to save registers)
+      if constexpr (SEG) {
+#pragma unroll
+        for (int f = 0; f < AF; ++f) {
+          uint4& v = av[p][f];
+          v.x &= mask[t].x; v.y &= mask[t].y; v.z &= mask[t].z; v.w &= mask[t].w;
+        }
+      }
+      if (t == T - 1) {
+        cur = ahead[T == 1 ? p ^ 1 : 0];
+        constants(cur, gq);
+      }
+#pragma unroll
+      for (int b = 0; b < BF; ++b) wf[p ^ 1][b] = code_step<BITS, BF16, T>(cur.raw[b], (t + 1) % T, gq[b], mg);
+#pragma unroll
+      for (int b = 0; b < BF; ++b)
+#pragma unroll
+        for (int f = 0; f < AF; ++f) acc[f][b] = mfma_16x16x32<BF16>(wf[p][b], av[p][f], acc[f][b]);
+      // products and unpacking in turns
+      constexpr int kVec = (BF * (BITS == 6 ? 20 : 17) + (T == 1 ? 8 * BF : 0) + (SEG ? 4 * AF : 0) + AF * BF - 1) / (AF * BF);
+#pragma unroll
+      for (int i = 0; i < AF * BF; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);      // matrix instruction
+        __builtin_amdgcn_sched_group_barrier(0x002, kVec, 0);   // vector instructions
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    xsl = xnext;
+    wsl = wnext;
+    pipe_barrier();                       // slab it + 2 is in LDS, and nobody reads slab `it` any more
+  }
+
+  // ---- output.  Lane l holds, for fragment (f, b): token l % 16, rows 4 (l / 16) + v.
+  auto store = [&](int f, int b, float4_t s) {
+    const int tok = m0 + f * 16 + n, rc = n0 + (wn * BF + b) * 16 + 4 * ks;
+    if (tok >= a.M || rc >= km.n_keep) return;
+    if (!SEG && kv < km.k_keep) {
+      // the kept columns kv .. k_keep - 1 of a prefix, in fp32
+      for (int v = 0; v < 4; ++v) {
+        const size_t row = (size_t)stored_row(km, rc + v < km.n_keep ? rc + v : km.n_keep - 1);
+        for (int k = kv; k < km.k_keep; ++k)
+          s[v] = __builtin_fmaf(in16<BF16>(a.x[(size_t)tok * a.ldx + k]), code_weight<BITS, BF16>(a, row, k), s[v]);
+      }
+    }
+    half_t* y = a.y + (size_t)tok * a.ldy + rc;
+    uint16_t o[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) o[v] = __builtin_bit_cast(uint16_t, out16<BF16>(s[v]));
+    if (rc + 4 <= km.n_keep) {
+      typedef uint32_t u32x2_u2 __attribute__((ext_vector_type(2), aligned(2)));
+      u32x2_u2 pk;
+      pk.x = o[0] | ((uint32_t)o[1] << 16);
+      pk.y = o[2] | ((uint32_t)o[3] << 16);
+      *reinterpret_cast<u32x2_u2*>(y) = pk;
+    } else {
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        if (rc + v < km.n_keep) y[v] = __builtin_bit_cast(half_t, o[v]);
+    }
+  };
+  if constexpr (KS == 1) {
+#pragma unroll
+    for (int f = 0; f < AF; ++f)
+#pragma unroll
+      for (int b = 0; b < BF; ++b) store(f, b, acc[f][b]);
+  } else {
+    // partial sums through LDS (nobody reads or moves slabs any more): fragment q = f BF + b of a row position is added up
+    // over the KS waves in order and stored by wave q % KS of them
+    float4_t* red = reinterpret_cast<float4_t*>(smem);
+#pragma unroll
+    for (int f = 0; f < AF; ++f)
+#pragma unroll
+      for (int b = 0; b < BF; ++b) red[((wk * WN + wn) * AF * BF + f * BF + b) * 64 + lane] = acc[f][b];
+    pipe_barrier();
+    for (int q = wk; q < AF * BF; q += KS) {
+      float4_t s = red[(wn * AF * BF + q) * 64 + lane];
+#pragma unroll
+      for (int k2 = 1; k2 < KS; ++k2) s += red[((k2 * WN + wn) * AF * BF + q) * 64 + lane];
+      store(q / BF, q % BF, s);
+    }
+  }
+#endif
+}
+
+template <int AF, int BF, int WN, int KG, int KQ, int G, int NX, int NW, int BITS, bool BF16, bool SEG>
+static hipError_t pipe_launch(const LinearArgs* p, int n, hipStream_t stream) {
+  typedef PipeShape<AF, BF, WN, KG, KQ, G, NX, NW, BITS> S;
+  auto kern = w_pipe_kernel<AF, BF, WN, KG, KQ, G, NX, NW, BITS, BF16, SEG>;
+  if (S::Lds > 64 * 1024) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, S::Lds);
+    if (e != hipSuccess) return e;
+  }
+  PipeBatch b;
+  b.n = n;
+  b.ntt = (p[0].M + S::BM - 1) / S::BM;
+  int tiles = 0;
+  for (int i = 0; i < kMaxBatch; ++i) {
+    b.p[i] = p[i < n ? i : 0];
+    b.first[i] = tiles;
+    if (i < n) tiles += (p[i].km.n_keep + S::BN - 1) / S::BN * b.ntt;
+  }
+  b.tiles = tiles;
+  hipLaunchKernelGGL(kern, dim3(tiles), dim3(kPipeThreads), S::Lds, stream, b);
+  return hipGetLastError();
+}
+
+}  // namespace uniql

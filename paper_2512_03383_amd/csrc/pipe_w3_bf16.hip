@@ -1,0 +1,8 @@
+// The 3-bit bfloat16 instantiations of pipe_kernel.h.
+#include "pipe_dispatch.h"
+
+namespace uniql {
+
+hipError_t launch_pipe_w3_bf16(const LinearArgs* p, int n, hipStream_t stream) { return pipe_linears<3, true>(p, n, stream); }
+
+}  // namespace uniql

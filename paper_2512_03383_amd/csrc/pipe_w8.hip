@@ -1,0 +1,8 @@
+// The 8-bit fp16 instantiations of pipe_kernel.h.
+#include "pipe_dispatch.h"
+
+namespace uniql {
+
+hipError_t launch_pipe_w8(const LinearArgs* p, int n, hipStream_t stream) { return pipe_linears<8, false>(p, n, stream); }
+
+}  // namespace uniql
