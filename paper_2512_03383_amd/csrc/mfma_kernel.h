@@ -384,7 +384,7 @@ static hipError_t launch_pipe4(const LinearArgs* p, int n, hipStream_t stream) {
 }
 
 // Which kernel a linear of 2 tokens and more takes.  It follows from the linear alone.
-enum GemmRoute { kSmallM, kPipe, kPrefill256, kTile128, kTile64, kTileSmall };
+enum GemmRoute { kSmallM, kPipe, kPrefill256, kTile128, kTile64, kTile64Split, kTileSmall };
 
 // xm: staging mode of the activations (0 element by element, 1 column prefix, 2 column segments of whole 8-column units)
 static inline GemmRoute gemm_route(const LinearArgs& a, int xm) {
@@ -398,24 +398,22 @@ static inline GemmRoute gemm_route(const LinearArgs& a, int xm) {
   if (smallm_takes(a, xm == 1) && !(pipe && tall)) return kSmallM;
   if (!pipe && a.M <= 64) return kTileSmall;
   if (pipe && a.M <= 64) return kPipe;
-  // More tokens: the cheapest of the tiles, from what a group of 128 columns costs one tile with the chip full and what a
-  // tile costs besides (microseconds, measured; a tile in a round of its own where the tiles do not fill one)
-  const int cus = prefill_grid_limit();
+  // More tokens: the cheapest of the tiles (launch_cost)
   const float ng = (float)((a.km.k_span + kGroup - 1) / kGroup);
-  auto cost = [&](int bm, int bn, float us) {
-    const long long tiles = (long long)((a.km.n_keep + bn - 1) / bn) * ((a.M + bm - 1) / bm);
-    return 3.f + (float)((tiles + cus - 1) / cus) * (5.f + ng * us);
+  auto cost = [&](int bm, int bn, float far, TileCost f16, TileCost b16, TileCost f16_seg, TileCost b16_seg) {
+    const TileCost c = xm == 2 ? (a.bf16 ? b16_seg : f16_seg) : (a.bf16 ? b16 : f16);
+    return launch_cost((long long)((a.km.n_keep + bn - 1) / bn) * ((a.M + bm - 1) / bm), ng, c, a.km.k_span > 8192 ? far : 1.f);
   };
   GemmRoute best = kTileSmall;
-  // (32 tokens x 128 rows, for what the pipelined kernel does not serve)
-  float best_us = pipe ? pipe_pick<4>(&a, 1).us : cost(32, 128, 1.2f);
-  if (pipe) best = kPipe;
+  float best_us = cost(32, 128, 1.25f, {0.36f, 0.05f}, {0.47f, 0.05f}, {0.50f, 0.05f}, {0.56f, 0.05f});
   auto take = [&](GemmRoute r, float us) {
     if (us < best_us) best = r, best_us = us;
   };
-  if (xm == 1 && prefill_serves(a)) take(kPrefill256, cost(256, 256, a.bf16 ? 4.9f : 3.75f));
-  take(kTile128, cost(128, 256, (a.bf16 ? 2.9f : 2.35f) * (xm == 2 ? 1.1f : 1.f)));
-  take(kTile64, cost(64, 256, (a.bf16 ? 1.45f : 1.30f) * (xm == 2 ? 1.15f : 1.f)));
+  if (pipe) take(kPipe, pipe_pick<4>(&a, 1).us);
+  if (xm == 1 && prefill_serves(a)) take(kPrefill256, cost(256, 256, 1.05f, {2.75f, 0.8f}, {2.95f, 0.6f}, {}, {}));
+  take(kTile128, cost(128, 256, 1.05f, {1.65f, 0.5f}, {1.85f, 0.4f}, {1.95f, 0.45f}, {2.1f, 0.45f}));
+  take(kTile64, cost(64, 256, 1.05f, {1.03f, 0.22f}, {1.22f, 0.12f}, {1.2f, 0.18f}, {1.4f, 0.13f}));
+  take(kTile64Split, cost(64, 128, 1.1f, {0.57f, 0.16f}, {0.70f, 0.10f}, {0.78f, 0.14f}, {0.88f, 0.11f}));
   return best;
 }
 
@@ -431,6 +429,7 @@ static hipError_t launch_m(const LinearArgs& a, hipStream_t stream) {
     // 256 columns) and two slabs of weight loads in flight (bfloat16: with the longer unpack two do not fit 256 registers)
     case kTile128: return launch_cfg<BF16, 8, 2, 8, 1, 2, BF16 ? 1 : 2, XVEC>(a, stream);
     case kTile64: return launch_cfg<BF16, 4, 2, 8, 1, 2, 2, XVEC>(a, stream);
+    case kTile64Split: return launch_cfg<BF16, 4, 2, 4, 2, 2, 1, XVEC>(a, stream);   // 64 x 128, K over two waves
     default: break;
   }
   // column rules and sizes that the pipelined kernel does not serve: K over eight waves up to 16 tokens, else 32 tokens x

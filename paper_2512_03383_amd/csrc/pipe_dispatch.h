@@ -7,11 +7,22 @@
 
 namespace uniql {
 
-// A tile and what it costs: microseconds per slab of one tile with the chip full (measured on 2560..12185 columns; segments
-// take the masks on top)
+// What a launch costs, in microseconds: a group of 128 columns (or a slab of them) costs one tile `us` on an idle chip and
+// `slope` more with every compute unit busy (clock and L2), a round of tiles 4 besides, the launch 3.  Rows of more than
+// 8192 columns miss the L2 more often.  Fitted to 350 shapes of 2560..13260 columns, 80..4096 tokens, within 10 %.
+struct TileCost {
+  float us, slope;
+};
+static inline float launch_cost(long long tiles, float steps, TileCost c, float far) {
+  const int cus = prefill_grid_limit();
+  const float rounds = (float)((tiles + cus - 1) / cus);
+  return 3.f + rounds * (4.f + steps * (c.us + c.slope * (float)tiles / (rounds * (float)cus)) * far);
+}
+
 struct PipeTile {
   int af, bf, wn, g;
-  float us, us_seg;
+  TileCost prefix, seg;   // per slab of g groups; segments take the masks on top
+  float us;               // of the launch
 };
 
 template <int BITS>
@@ -19,32 +30,34 @@ static inline PipeTile pipe_pick(const LinearArgs* p, int n) {
   // groups: 32- and 64-row tiles; mixed: 64- and 96-row tiles (96 rows x 64 tokens do not fit with 8-bit codes);
   // halves: rows x tokens from 128 x 128 down to 64 x 64 (segments: no 128 tokens, the masks cost it its registers;
   // 8-bit codes: no 112, its buffers)
-  static const PipeTile groups[] = {{1, 1, 2, 4, 0.55f, 0.60f}, {1, 2, 2, 4, 0.95f, 1.0f}, {2, 1, 2, 4, 0.60f, 0.70f}, {2, 2, 2, 4, 1.05f, 1.1f}};
-  static const PipeTile mixed[] = {{3, 2, 2, 2, 0.69f, 0.75f}, {3, 3, 2, 2, 0.87f, 0.95f}, {4, 2, 2, 2, 0.80f, 0.90f}, {4, 3, 2, 2, 1.0f, 1.1f}};
-  static const PipeTile halves[] = {{8, 2, 4, 1, 1.17f, 0.f}, {7, 2, 4, 1, 1.08f, 1.20f}, {6, 2, 4, 1, 0.90f, 1.0f}, {4, 2, 4, 1, 0.70f, 0.80f}, {4, 1, 4, 1, 0.46f, 0.53f}};
+  static const PipeTile groups[] = {{1, 1, 2, 4, {0.50f, 0.05f}, {0.55f, 0.05f}, 0.f}, {1, 2, 2, 4, {0.90f, 0.05f}, {0.95f, 0.05f}, 0.f},
+                                    {2, 1, 2, 4, {0.55f, 0.05f}, {0.65f, 0.05f}, 0.f}, {2, 2, 2, 4, {1.0f, 0.05f}, {1.05f, 0.05f}, 0.f}};
+  static const PipeTile mixed[] = {{3, 2, 2, 2, {0.62f, 0.07f}, {0.70f, 0.05f}, 0.f}, {3, 3, 2, 2, {0.80f, 0.07f}, {0.90f, 0.05f}, 0.f},
+                                   {4, 2, 2, 2, {0.73f, 0.07f}, {0.85f, 0.05f}, 0.f}, {4, 3, 2, 2, {0.93f, 0.07f}, {1.05f, 0.05f}, 0.f}};
+  static const PipeTile halves[] = {{8, 2, 4, 1, {1.0f, 0.15f}, {0.f, 0.f}, 0.f}, {7, 2, 4, 1, {0.93f, 0.12f}, {1.0f, 0.13f}, 0.f},
+                                    {6, 2, 4, 1, {0.85f, 0.07f}, {0.95f, 0.12f}, 0.f}, {4, 2, 4, 1, {0.56f, 0.15f}, {0.62f, 0.22f}, 0.f},
+                                    {4, 1, 4, 1, {0.33f, 0.09f}, {0.39f, 0.08f}, 0.f}};
   const PipeWay way = pipe_way(p[0]);
   const bool seg = p[0].km.cs_stride != 0;
   const PipeTile* set = way == kPipeGroups ? groups : way == kPipeMixed ? mixed : halves;
   const int count = way == kPipeHalves ? 5 : 4, M = p[0].M;
-  int slabs = 0;
-  for (int i = 0; i < n; ++i) slabs = max(slabs, (p[i].km.k_span + kGroup - 1) / kGroup);
+  int span = 0;
+  for (int i = 0; i < n; ++i) span = p[i].km.k_span > span ? p[i].km.k_span : span;
+  const int ngroups = (span + kGroup - 1) / kGroup;
   PipeTile best = {};
-  float best_us = 0.f;
   for (int c = 0; c < count; ++c) {
-    const PipeTile& t = set[c];
+    PipeTile t = set[c];
     if (way == kPipeGroups && t.af != (M <= 16 ? 1 : 2)) continue;
     if (way == kPipeMixed && t.af != (M <= 48 ? 3 : 4)) continue;
     if (BITS > 4 && way != kPipeGroups && ((t.af == 4 && t.bf == 3) || t.af == 7)) continue;
     if (BITS > 4 && way == kPipeGroups && t.bf == 2) continue;
-    if (seg && t.us_seg == 0.f) continue;
+    if (seg && t.seg.us == 0.f) continue;
     long long tiles = 0;
     for (int i = 0; i < n; ++i) tiles += (p[i].km.n_keep + t.wn * t.bf * 16 - 1) / (t.wn * t.bf * 16);
     tiles *= (M + 16 * t.af - 1) / (16 * t.af);
-    const int cus = prefill_grid_limit();
-    const float us = 3.f + (float)((tiles + cus - 1) / cus) * (3.f + (float)((slabs + t.g - 1) / t.g) * (seg ? t.us_seg : t.us));
-    if (best.af == 0 || us < best_us) best = t, best_us = us;
+    t.us = launch_cost(tiles, (float)((ngroups + t.g - 1) / t.g), seg ? t.seg : t.prefix, span > 8192 ? 1.18f : 1.f);
+    if (best.af == 0 || t.us < best.us) best = t;
   }
-  best.us = best_us;
   return best;
 }
 
