@@ -15,7 +15,8 @@
 //
 // fp16 weight: (pair - (base + z)) * s in packed fp16, one rounding.  bfloat16: fma(member, s, -(base + z) s) in fp32 with
 // the fp16 operand read in place (exact: the products and their difference fit 24 bits), then a packed conversion, one
-// rounding; the members are converted one by one, so any order costs the same and the cheaper pairs (j, j + 4) of common.h
+// rounding (the second term overflows from scales of 3.2e35 on; a weight (q - z) s can from 2.2e37 on); the members are
+// converted one by one, so any order costs the same and the cheaper pairs (j, j + 4) of common.h
 // serve 4 and 6 bits.
 #pragma once
 #include "common.h"

@@ -47,7 +47,7 @@ struct LinearArgs {
   int N_total, K_total, M;
   int bf16;           // scales, x and y are bfloat16 (the weights are then rounded to bfloat16 as well)
   int il_heads;       // > 0: the row's words are stored head-interleaved over this many heads (uniql_w4_t.col_interleave)
-  int bits;           // width of a code: 4, or 8 (w8.hip serves those), or 3 / 6 (wbits.hip)
+  int bits;           // width of a code: 4, or 8 (one token: w8.hip), or 3 / 6 (wbits.hip); several tokens of any width: pipe_kernel.h
   KeepMap km;
 };
 
@@ -311,7 +311,7 @@ hipError_t launch_pipe_w4_bf16(const LinearArgs* p, int n, hipStream_t stream);
 hipError_t launch_pipe_w6_bf16(const LinearArgs* p, int n, hipStream_t stream);
 hipError_t launch_pipe_w8_bf16(const LinearArgs* p, int n, hipStream_t stream);
 hipError_t launch_w4_dequant(const LinearArgs& a, hipStream_t stream);
-// codes of 8 bits: the dequantised matrix, and the linear with one token per grid row
+// codes of 8 bits: the dequantised matrix, and the linear of one token (several: a grid row each)
 hipError_t launch_w8_dequant(const LinearArgs& a, hipStream_t stream);
 hipError_t launch_w8_linear(const LinearArgs& a, hipStream_t stream);
 // codes of 3 and 6 bits (a.bits), packed as a bit stream: the same two operations
