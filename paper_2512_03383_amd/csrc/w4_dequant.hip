@@ -9,14 +9,14 @@
 namespace uniql {
 
 // Bound by the output: 2 bytes written per half byte read.  A wave takes a row; its lanes take consecutive words, so a
-// store instruction writes 1 KB of consecutive output and a load reads 256 bytes of codes, four words per lane in flight.
-// 10752 x 4096 kept: 25 us against 59 us (3072 x 4096: 10.2 against 20.7) of one thread per word of
-// the whole matrix with eight 2-byte stores and a 64-bit division each.  A word's eight columns are written
-// at once when all are kept; the word that holds the last kept columns of the row or of a segment, and column rules whose
-// segments are not whole words, go element by element.
+// store instruction writes 1 KB of consecutive output and a load reads 256 bytes of codes, eight words per lane in flight.
+// 10752 x 4096 kept: 24.4 us against 62 us (3072 x 4096: 8.3 against 21) of one thread per word of the whole matrix with
+// eight 2-byte stores and a 64-bit division each; four words in flight 24.9 (10.3), two 28.9 (12.4).  A word's eight
+// columns are written at once when all are kept; the word that holds the last kept columns of the row or of a segment, and
+// column rules whose segments are not whole words, go element by element.
 template <bool BF16>
 __global__ __launch_bounds__(256) void w4_dequant_kernel(LinearArgs a) {
-  constexpr int U = 4;                    // words per lane and turn
+  constexpr int U = 8;                    // words per lane and turn
   const KeepMap& km = a.km;
   const int lane = threadIdx.x & 63;
   const int words_span = (km.k_span + 7) >> 3;

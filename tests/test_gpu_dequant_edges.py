@@ -1,4 +1,4 @@
-"""Bit-exact 4-bit dequantisation where a wave's turn over a row ends: rows of 63..66 and 255..258 words, rows whose output
+"""Bit-exact 4-bit dequantisation where a wave's turn over a row ends: rows of 63..66, 255..258 and 511..514 words, rows whose output
 starts at every 2-byte alignment, segments of whole and of partial words, head-interleaved words, more rows than
 one turn of the grid; nothing is written past the last element."""
 import numpy as np
@@ -22,6 +22,10 @@ pytestmark = pytest.mark.gpu
     (9, 2048, Keep(), 0),
     (9, 2176, Keep(n_keep=8, k_keep=2049), 0),
     (3, 2176, Keep(k_keep=2063), 0),
+    (5, 4096, Keep(k_keep=4081), 0),
+    (5, 4096, Keep(), 0),
+    (5, 4224, Keep(n_keep=4, k_keep=4097), 0),
+    (6, 4224, Keep(k_keep=4111), 0),
     (4, 2048, Keep(k_keep=64 * 1, col_seg_stride=32, col_seg_keep=1), 0),
     (5, 2048, Keep(k_keep=16 * 127, col_seg_stride=128, col_seg_keep=127), 0),
     (5, 2176, Keep(k_keep=64 * 33, col_seg_stride=34, col_seg_keep=33), 0),
