@@ -15,9 +15,10 @@
 //
 // fp16 weight: (pair - (base + z)) * s in packed fp16, one rounding.  bfloat16: fma(member, s, -(base + z) s) in fp32 with
 // the fp16 operand read in place (exact: the products and their difference fit 24 bits), then a packed conversion, one
-// rounding (the second term overflows from scales of 3.2e35 on; a weight (q - z) s can from 2.2e37 on); the members are
-// converted one by one, so any order costs the same and the cheaper pairs (j, j + 4) of common.h
-// serve 4 and 6 bits.
+// rounding; the members are converted one by one, so any order costs the same and the cheaper pairs (j, j + 4) of common.h
+// serve 4 and 6 bits.  The constant (base + z) s overflows from scales of 2^128 / 1279 on where a weight need not, so a group
+// with such a scale takes the wide form (member - (base + z)) * s, exact up to the rounding as well and two instructions a
+// code; code_scale_wide tells.
 #pragma once
 #include "common.h"
 
@@ -97,21 +98,24 @@ template <int BITS> struct CodeGroup<BITS, false> {
   half2_t za, zb, s2;   // base + z of the two classes, scale
 };
 template <int BITS> struct CodeGroup<BITS, true> {
-  float s, nalo, nahi, nblo, nbhi;   // scale, -(base + z) s of the two classes and halves
+  float s, nalo, nahi, nblo, nbhi;   // scale, -(base + z) s of the two classes and halves (wide: base + z)
 };
 
-template <int BITS, bool BF16>
+// a bfloat16 scale of 2^117 or more in magnitude (infinities and NaN among them): (1024 + z) s may overflow (1279 * 2^117 < 2^128)
+__device__ __forceinline__ bool code_scale_wide(uint32_t sbits) { return (sbits & 0x7f80u) >= ((127u + 117u) << 7); }
+
+template <int BITS, bool BF16, bool WIDE = false>
 __device__ __forceinline__ CodeGroup<BITS, BF16> make_code_group(uint32_t sbits, uint32_t z) {
   typedef CodeForm<BITS, BF16> F;
   CodeGroup<BITS, BF16> g;
   if constexpr (BF16) {
     // a code at bit p of its half comes with the base 1024 / 2^p
     g.s = __builtin_bit_cast(float, sbits << 16);
-    const float zf = (float)z;
-    g.nalo = -((1024.f / (1 << F::kAlo) + zf) * g.s);
-    g.nahi = -((1024.f / (1 << F::kAhi) + zf) * g.s);
-    g.nblo = -((1024.f / (1 << F::kBlo) + zf) * g.s);
-    g.nbhi = -((1024.f / (1 << F::kBhi) + zf) * g.s);
+    const float zf = (float)z, f = WIDE ? 1.f : -g.s;
+    g.nalo = (1024.f / (1 << F::kAlo) + zf) * f;
+    g.nahi = (1024.f / (1 << F::kAhi) + zf) * f;
+    g.nblo = (1024.f / (1 << F::kBlo) + zf) * f;
+    g.nbhi = (1024.f / (1 << F::kBhi) + zf) * f;
   } else {
     g.za = as_half2((z << F::kAlo) | (z << (16 + F::kAhi)) | F::kA);
     g.zb = F::kOneClass ? g.za : as_half2((z << F::kBlo) | (z << (16 + F::kBhi)) | F::kB);
@@ -167,18 +171,19 @@ __device__ __forceinline__ void code_pairs(const RawCodes<BITS, T>& r, int t, co
 }
 
 // the MFMA weight operand of step t of the window (t is a constant after unrolling), columns in memory order
-template <int BITS, bool BF16, int T>
+template <int BITS, bool BF16, int T, bool WIDE = false>
 __device__ __forceinline__ uint4 code_step(const RawCodes<BITS, T>& r, int t, const CodeGroup<BITS, BF16>& g, const CodeMagic& m) {
   typedef CodeForm<BITS, BF16> F;
   uint32_t p[4], d[4];
   code_pairs<BITS, BF16, T>(r, t, m, p);
   if constexpr (BF16) {
     float f[8];
+    auto weight = [&](float member, float c) { return WIDE ? (member - c) * g.s : __builtin_fmaf(member, g.s, c); };
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const half2_t h = as_half2(p[j]);
-      f[F::kFar ? j : 2 * j] = __builtin_fmaf((float)h.x, g.s, F::is_b(j) ? g.nblo : g.nalo);
-      f[F::kFar ? j + 4 : 2 * j + 1] = __builtin_fmaf((float)h.y, g.s, F::is_b(j) ? g.nbhi : g.nahi);
+      f[F::kFar ? j : 2 * j] = weight((float)h.x, F::is_b(j) ? g.nblo : g.nalo);
+      f[F::kFar ? j + 4 : 2 * j + 1] = weight((float)h.y, F::is_b(j) ? g.nbhi : g.nahi);
     }
 #pragma unroll
     for (int j = 0; j < 4; ++j) d[j] = pack_bf16(f[2 * j], f[2 * j + 1]);
