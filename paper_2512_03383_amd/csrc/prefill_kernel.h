@@ -23,6 +23,7 @@
 // The sums are formed in the same order as in w4_mfma_kernel: the outputs are bit-identical.
 #pragma once
 #include "common.h"
+#include <atomic>
 
 namespace uniql {
 
@@ -347,17 +348,18 @@ static inline bool prefill_serves(const LinearArgs& a) {
          a.ldx * 256 * 2 + (long long)a.K_total * 2 + 8192 < (1ll << 31);
 }
 
-// Number of compute units of the current device (the size of the persistent grid), looked up once per device.
+// Number of compute units of the current device (the size of the persistent grid), looked up once per device (0: not yet;
+// host threads may look it up at once).
 static inline int prefill_grid_limit() {
-  static int cus[64] = {0};
+  static std::atomic<int> cus[64];
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
-  if (cus[dev] == 0) {
-    int v = 0;
+  int v = cus[dev].load(std::memory_order_relaxed);
+  if (v == 0) {
     if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v <= 0) v = 256;
-    cus[dev] = v;
+    cus[dev].store(v, std::memory_order_relaxed);
   }
-  return cus[dev];
+  return v;
 }
 
 template <bool BF16, int AF, int BF, int WN, int S2, int PW, int AH = (AF > 8 ? 8 : AF), int UPP = 8, int ADB = 1>
