@@ -69,6 +69,8 @@ def lib():
         L.uniql_w4_linear_multi.restype = C.c_int
         L.uniql_w4_linear_multi.argtypes = [i32, C.POINTER(W4), C.POINTER(KeepDesc), C.POINTER(vp), C.POINTER(i64),
                                             C.POINTER(vp), C.POINTER(i64), i32, vp]
+        L.uniql_w4_linear_kernel.restype = C.c_int
+        L.uniql_w4_linear_kernel.argtypes = [C.POINTER(W4), C.POINTER(KeepDesc), i64, i32, C.POINTER(i32)]
         L.uniql_w4_dequant.restype = C.c_int
         L.uniql_w4_dequant.argtypes = [C.POINTER(W4), C.POINTER(KeepDesc), vp, vp]
         L.uniql_pruned_rope.restype = C.c_int
@@ -213,6 +215,16 @@ def kept_dims(W: QuantLinear, keep) -> tuple:
     else:
         k = kd.k_keep or W.K
     return n, k
+
+
+def uniql_w4_linear_kernel(N: int, K: int, keep, M: int, bits: int = 4, bf16: bool = False, ldx: Optional[int] = None,
+                           col_interleave: int = 0):
+    """(kernel, tile tokens, tile rows, waves along K) that uniql_w4_linear takes for a matrix of this shape, without running
+    it: kernel 0 streaming, 1 decode-batch, 2 pipelined, 3 persistent 256 x 256, 4 tiled (see include/uniql.h)."""
+    d = W4(None, None, None, N, K, 128, UNIQL_BF16 if bf16 else UNIQL_F16, col_interleave, bits)
+    kd, out = _keep_desc(keep), (C.c_int32 * 4)()
+    _check(lib().uniql_w4_linear_kernel(C.byref(d), C.byref(kd) if kd is not None else None, K if ldx is None else ldx, M, out))
+    return tuple(out)
 
 
 def uniql_w4_linear(W: QuantLinear, keep, x, y=None, stream=None):

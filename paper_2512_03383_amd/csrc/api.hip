@@ -180,6 +180,25 @@ extern "C" int uniql_w4_linear(const uniql_w4_t* W, const uniql_keep_t* keep, co
   return run_linear(a, (hipStream_t)hip_stream);
 }
 
+extern "C" int uniql_w4_linear_kernel(const uniql_w4_t* W, const uniql_keep_t* keep, int64_t ldx, int32_t M, int32_t* choice) {
+  if (!W || !choice) return UNIQL_E_NULL;
+  // host arithmetic: the data pointers of W may be NULL here
+  uniql_w4_t shape = *W;
+  static const uint32_t dummy[4] __attribute__((aligned(16))) = {0, 0, 0, 0};
+  shape.qweight = dummy;
+  shape.scales = reinterpret_cast<const uint16_t*>(dummy);
+  shape.zeros = nullptr;
+  LinearArgs a;
+  int rc = fill_linear(&shape, keep, dummy, ldx, const_cast<uint32_t*>(dummy), INT64_MAX, M, &a, true);
+  if (rc) return rc;
+  if (a.bits != 4 && wide_codes_refused(a)) return UNIQL_E_SHAPE;
+  if (a.il_heads > 0 && M > kInterleavedMaxTokens) return UNIQL_E_SHAPE;
+  for (int i = 0; i < 4; ++i) choice[i] = 0;
+  if (M == 1 || a.il_heads > 0 || (a.bits != 4 && !pipe_serves(a))) return UNIQL_OK;
+  gemm_choice(a, choice);
+  return UNIQL_OK;
+}
+
 extern "C" int uniql_w4_linear_multi(int32_t n, const uniql_w4_t* W, const uniql_keep_t* keep,
                                      const void* const* x_f16, const int64_t* ldx, void* const* y_f16,
                                      const int64_t* ldy, int32_t M, void* hip_stream) {

@@ -294,6 +294,8 @@ hipError_t launch_w4_mlp_fused(const LinearArgs* probs, void* scratch, hipStream
 hipError_t launch_w4_mlp_fused_bf16(const LinearArgs* probs, void* scratch, hipStream_t stream, bool* done);
 hipError_t launch_w4_gemm(const LinearArgs& a, hipStream_t stream);
 hipError_t launch_w4_gemm_bf16(const LinearArgs& a, hipStream_t stream);
+// which kernel and tile a linear of 2 tokens and more takes (uniql_w4_linear_kernel)
+void gemm_choice(const LinearArgs& a, int out[4]);
 // n (2..4) linears of one token count in one launch where one kernel takes them all (*done says whether)
 hipError_t launch_w4_gemm_batch(const LinearArgs* a, int n, hipStream_t stream, bool* done);
 hipError_t launch_w4_gemm_batch_bf16(const LinearArgs* a, int n, hipStream_t stream, bool* done);

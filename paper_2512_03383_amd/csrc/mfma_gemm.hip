@@ -4,6 +4,8 @@
 
 namespace uniql {
 
+void gemm_choice(const LinearArgs& a, int out[4]) { gemm_choice_of(a, out); }
+
 hipError_t launch_w4_gemm(const LinearArgs& a, hipStream_t stream) {
   if (a.bf16) return launch_w4_gemm_bf16(a, stream);
   return launch_gemm_fmt<false>(a, stream);

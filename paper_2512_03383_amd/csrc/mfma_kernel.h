@@ -13,7 +13,8 @@
 // A wave owns BF fragments of 16 rows and AF fragments of 16 tokens (AF*BF accumulators of 4
 // VGPRs); a dequantised weight fragment is reused by AF MFMAs, an activation fragment by BF.
 // It serves the prompts whose tiles of 128 or 64 tokens x 256 rows fill the chip better than those of the
-// pipelined kernel (pipe_kernel.h), and every column rule and size the other kernels do not take.
+// pipelined kernel (pipe_kernel.h), and every column rule and size the other kernels do not take: up to 64 tokens with
+// the K range split over KS waves of the block (reduced through LDS at the end).
 #pragma once
 #define UNIQL_ANDOR_PLAIN   // and-or as plain C here: the scheduler must be able to classify it as VALU
 #include "common.h"
@@ -383,8 +384,12 @@ static hipError_t launch_pipe4(const LinearArgs* p, int n, hipStream_t stream) {
   else return launch_pipe_w4(p, n, stream);
 }
 
-// Which kernel a linear of 2 tokens and more takes.  It follows from the linear alone.
-enum GemmRoute { kSmallM, kPipe, kPrefill256, kTile128, kTile64, kTile64Split, kTileSmall };
+// Which kernel a linear of 2 tokens and more takes.  It follows from the linear alone.  kTile*: w4_mfma_kernel with tiles of
+// that many tokens x rows, K over that many waves of a block.
+enum GemmRoute {
+  kSmallM, kPipe, kPrefill256, kTile128x256, kTile64x256, kTile64x128k2, kTile32x128k2,
+  kTile16x16k8, kTile16x64k4, kTile32x16k8, kTile32x64k4, kTile64x32k4, kTile64x64k4
+};
 
 // xm: staging mode of the activations (0 element by element, 1 column prefix, 2 column segments of whole 8-column units)
 static inline GemmRoute gemm_route(const LinearArgs& a, int xm) {
@@ -396,24 +401,30 @@ static inline GemmRoute gemm_route(const LinearArgs& a, int xm) {
   // 11.0 / 11.0 / 12.4 us here; with 256 row tiles it is the other way round: 4096 x 9318 at 24 tokens 18.1 against 22.6).
   const bool tall = row_tiles >= 400 && a.M >= 5 && !(xm == 1 && smallm_pre(a));
   if (smallm_takes(a, xm == 1) && !(pipe && tall)) return kSmallM;
-  if (!pipe && a.M <= 64) return kTileSmall;
   if (pipe && a.M <= 64) return kPipe;
+  // What neither takes (rows of fewer than eight groups; above the decode batches, or on tall matrices from 9 tokens on,
+  // segments that are not a power of two up to a group with an even number kept): K over four or eight waves of a block, or
+  // a matrix of a few thousand rows leaves most of the chip idle (4096 x 4096, segments of 256, 48 tokens: 19.5 us; 32 x 128
+  // tiles with K over two waves 21.7); tall matrices 64 rows per block (12288 x 896 at 8 tokens 6.4 us; 16 rows 11.4).
+  if (a.M <= 16) return row_tiles >= 600 ? kTile16x64k4 : kTile16x16k8;
+  if (a.M <= 32) return row_tiles >= 600 ? kTile32x64k4 : kTile32x16k8;
+  if (a.M <= 64) return row_tiles >= 600 ? kTile64x64k4 : kTile64x32k4;
   // More tokens: the cheapest of the tiles (launch_cost)
   const float ng = (float)((a.km.k_span + kGroup - 1) / kGroup);
   auto cost = [&](int bm, int bn, float far, TileCost f16, TileCost b16, TileCost f16_seg, TileCost b16_seg) {
     const TileCost c = xm == 2 ? (a.bf16 ? b16_seg : f16_seg) : (a.bf16 ? b16 : f16);
     return launch_cost((long long)((a.km.n_keep + bn - 1) / bn) * ((a.M + bm - 1) / bm), ng, c, a.km.k_span > 8192 ? far : 1.f);
   };
-  GemmRoute best = kTileSmall;
+  GemmRoute best = kTile32x128k2;
   float best_us = cost(32, 128, 1.25f, {0.36f, 0.05f}, {0.47f, 0.05f}, {0.50f, 0.05f}, {0.56f, 0.05f});
   auto take = [&](GemmRoute r, float us) {
     if (us < best_us) best = r, best_us = us;
   };
   if (pipe) take(kPipe, pipe_pick<4>(&a, 1).us);
   if (xm == 1 && prefill_serves(a)) take(kPrefill256, cost(256, 256, 1.05f, {2.75f, 0.8f}, {2.95f, 0.6f}, {}, {}));
-  take(kTile128, cost(128, 256, 1.05f, {1.65f, 0.5f}, {1.85f, 0.4f}, {1.95f, 0.45f}, {2.1f, 0.45f}));
-  take(kTile64, cost(64, 256, 1.05f, {1.03f, 0.22f}, {1.22f, 0.12f}, {1.2f, 0.18f}, {1.4f, 0.13f}));
-  take(kTile64Split, cost(64, 128, 1.1f, {0.57f, 0.16f}, {0.70f, 0.10f}, {0.78f, 0.14f}, {0.88f, 0.11f}));
+  take(kTile128x256, cost(128, 256, 1.05f, {1.65f, 0.5f}, {1.85f, 0.4f}, {1.95f, 0.45f}, {2.1f, 0.45f}));
+  take(kTile64x256, cost(64, 256, 1.05f, {1.03f, 0.22f}, {1.22f, 0.12f}, {1.2f, 0.18f}, {1.4f, 0.13f}));
+  take(kTile64x128k2, cost(64, 128, 1.1f, {0.57f, 0.16f}, {0.70f, 0.10f}, {0.78f, 0.14f}, {0.88f, 0.11f}));
   return best;
 }
 
@@ -427,15 +438,20 @@ static hipError_t launch_m(const LinearArgs& a, hipStream_t stream) {
       break;
     // 128 x 256: eight waves side by side over rows, 8 x 2 fragments each, two groups per wave and slab (a block barrier per
     // 256 columns) and two slabs of weight loads in flight (bfloat16: with the longer unpack two do not fit 256 registers)
-    case kTile128: return launch_cfg<BF16, 8, 2, 8, 1, 2, BF16 ? 1 : 2, XVEC>(a, stream);
-    case kTile64: return launch_cfg<BF16, 4, 2, 8, 1, 2, 2, XVEC>(a, stream);
-    case kTile64Split: return launch_cfg<BF16, 4, 2, 4, 2, 2, 1, XVEC>(a, stream);   // 64 x 128, K over two waves
-    default: break;
+    case kTile128x256: return launch_cfg<BF16, 8, 2, 8, 1, 2, BF16 ? 1 : 2, XVEC>(a, stream);
+    case kTile64x256: return launch_cfg<BF16, 4, 2, 8, 1, 2, 2, XVEC>(a, stream);
+    case kTile64x128k2: return launch_cfg<BF16, 4, 2, 4, 2, 2, 1, XVEC>(a, stream);
+    case kTile32x128k2: return launch_cfg<BF16, 2, 2, 4, 2, 2, 1, XVEC>(a, stream);
+    // (few row tiles: two groups per wave and slab, which halves the number of barriers; many: 32 rows per wave, so that an
+    // activation fragment read from LDS serves two weight fragments)
+    case kTile16x16k8: return launch_cfg<BF16, 1, 1, 1, 8, 2, 1, XVEC>(a, stream);
+    case kTile16x64k4: return launch_cfg<BF16, 1, 2, 2, 4, 1, 2, XVEC>(a, stream);
+    case kTile32x16k8: return launch_cfg<BF16, 2, 1, 1, 8, 1, 2, XVEC>(a, stream);
+    case kTile32x64k4: return launch_cfg<BF16, 2, 2, 2, 4, 2, 1, XVEC>(a, stream);
+    case kTile64x32k4: return launch_cfg<BF16, 4, 1, 2, 4, 1, 2, XVEC>(a, stream);
+    case kTile64x64k4: return launch_cfg<BF16, 4, 2, 2, 4, 1, 2, XVEC>(a, stream);
   }
-  // column rules and sizes that the pipelined kernel does not serve: K over eight waves up to 16 tokens, else 32 tokens x
-  // 128 rows, K over two waves
-  if (a.M <= 16) return launch_cfg<BF16, 1, 1, 1, 8, 2, 1, XVEC>(a, stream);
-  return launch_cfg<BF16, 2, 2, 4, 2, 2, 1, XVEC>(a, stream);
+  return hipErrorInvalidValue;
 }
 
 // the staging mode of the activations, then the tile shape
@@ -453,6 +469,23 @@ static hipError_t launch_gemm_fmt(const LinearArgs& a, hipStream_t stream) {
   return xm == 1 ? launch_m<1, BF16>(a, stream) : xm == 2 ? launch_m<2, BF16>(a, stream) : launch_m<0, BF16>(a, stream);
 }
 
+// What launch_gemm_fmt (4 bits) and the pipelined kernel (every width) do with a linear of 2 tokens and more, as
+// uniql_w4_linear_kernel reports it: the kernel, the tile's tokens and rows and the waves that K is split over (0, 0, 0 for the
+// decode-batch kernel).
+static inline void gemm_choice_of(const LinearArgs& a, int out[4]) {
+  static const int tiles[][3] = {{0, 0, 0}, {0, 0, 0}, {256, 256, 1}, {128, 256, 1}, {64, 256, 1}, {64, 128, 2}, {32, 128, 2},
+                                 {16, 16, 8}, {16, 64, 4}, {32, 16, 8}, {32, 64, 4}, {64, 32, 4}, {64, 64, 4}};
+  const int xm = gemm_xm(a);
+  const GemmRoute r = a.bits == 4 ? gemm_route(a, xm) : kPipe;
+  out[0] = r == kSmallM ? 1 : r == kPipe ? 2 : r == kPrefill256 ? 3 : 4;
+  for (int i = 0; i < 3; ++i) out[1 + i] = tiles[r][i];
+  if (r != kPipe) return;
+  const PipeTile t = a.bits == 4 ? pipe_pick<4>(&a, 1) : a.bits == 8 ? pipe_pick<8>(&a, 1) : a.bits == 6 ? pipe_pick<6>(&a, 1) : pipe_pick<3>(&a, 1);
+  out[1] = 16 * t.af;
+  out[2] = 16 * t.bf * t.wn;
+  out[3] = kPipeConsumers / t.wn;
+}
+
 // n (2..4) linears of the same token count and format in one launch: a decode batch that the decode-batch kernel takes, or
 // linears that the pipelined kernel takes with the same split of K and kind of column rule.  *done = false: not such a
 // set, nothing was launched.
@@ -462,7 +495,7 @@ static hipError_t launch_gemm_batch_fmt(const LinearArgs* a, int n, hipStream_t 
   bool small = true, pipe = true;
   for (int i = 0; i < n; ++i) {
     const int xm = gemm_xm(a[i]);
-    const GemmRoute r = xm == 0 ? kTileSmall : gemm_route(a[i], xm);
+    const GemmRoute r = gemm_route(a[i], xm);
     small = small && r == kSmallM && xm == 1;
     pipe = pipe && r == kPipe && xm == gemm_xm(a[0]) && pipe_way(a[i]) == pipe_way(a[0]);
   }

@@ -1,0 +1,48 @@
+"""Host-side checks of which kernel a linear takes (no GPU): uniql_w4_linear_kernel reports the dispatch that uniql_w4_linear
+follows."""
+import pytest
+
+import paper_2512_03383_amd as uq
+from paper_2512_03383_amd import KeepDesc
+
+STREAM, BATCH, PIPE, BIG, TILED = range(5)
+
+
+def seg(stride, keep):
+    return KeepDesc(col_seg_stride=stride, col_seg_keep=keep)
+
+
+def test_reports_without_running():
+    assert uq.uniql_w4_linear_kernel(4096, 4096, None, 1) == (STREAM, 0, 0, 0)
+    assert uq.uniql_w4_linear_kernel(4096, 4096, None, 8, col_interleave=32)[0] == STREAM
+    assert uq.uniql_w4_linear_kernel(4096, 4096, None, 8) == (BATCH, 0, 0, 0)
+    assert uq.uniql_w4_linear_kernel(14336, 4096, None, 4096) == (BIG, 256, 256, 1)
+    with pytest.raises(uq.UniqlError):
+        uq.uniql_w4_linear_kernel(4096, 4100, None, 8)
+    with pytest.raises(uq.UniqlError):
+        uq.uniql_w4_linear_kernel(4096, 4096, KeepDesc(k_keep=4097), 8)
+    with pytest.raises(uq.UniqlError):
+        uq.uniql_w4_linear_kernel(4096, 4096, None, 65, col_interleave=32)
+    with pytest.raises(uq.UniqlError):
+        uq.uniql_w4_linear_kernel(128, 32896, None, 8, bits=8)
+
+
+# column rules and sizes that neither the decode-batch kernel nor the pipelined one takes keep K split over four or eight waves
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("N,K,keep", [(4096, 4096, seg(256, 216)), (3840, 3840, seg(96, 80)), (2560, 2560, seg(80, 68)),
+                                      (4096, 4096, seg(128, 107)), (4096, 896, None), (2560, 2560, KeepDesc(k_keep=5))])
+def test_unusual_rules_keep_their_split_of_k(N, K, keep, bf16):
+    for M in (33, 40, 48, 64):
+        assert uq.uniql_w4_linear_kernel(N, K, keep, M, bf16=bf16) == (TILED, 64, 32, 4)
+    if K < 1024:
+        for M in (2, 8, 16):
+            assert uq.uniql_w4_linear_kernel(N, K, keep, M, bf16=bf16) == (TILED, 16, 16, 8)
+        for M in (17, 32):
+            assert uq.uniql_w4_linear_kernel(N, K, keep, M, bf16=bf16) == (TILED, 32, 16, 8)
+
+
+@pytest.mark.parametrize("K,keep,first", [(896, None, 2), (4096, seg(256, 216), 9), (4096, seg(128, 107), 9)])
+def test_tall_matrices_of_unusual_rules(K, keep, first):
+    for M, want in ((first, (TILED, 16, 64, 4)), (16, (TILED, 16, 64, 4)), (17, (TILED, 32, 64, 4)), (32, (TILED, 32, 64, 4)),
+                    (33, (TILED, 64, 64, 4)), (64, (TILED, 64, 64, 4))):
+        assert uq.uniql_w4_linear_kernel(12288, K, keep, M) == want, M
