@@ -162,9 +162,9 @@ int uniql_w4_linear(const uniql_w4_t* W, const uniql_keep_t* keep, const void* x
  * projections of a layer (Eq. 2) or gate and up (Eq. 1), which read the same x.  W, keep (or NULL
  * = all unpruned), x_f16, ldx, y_f16, ldy are host arrays of n entries; each entry follows the
  * rules of uniql_w4_linear.  At M = 1 linears that stream rows of the same length are served by
- * ONE kernel launch (a decode step is launch-latency bound), and so are the linears of several
- * tokens when one kernel takes them all (the decode-batch kernel with column prefixes of at least
- * 8 columns, or the pipelined one); otherwise they are launched one after the other on the stream.
+ * ONE kernel launch (a decode step is launch-latency bound).  Of several tokens the members that one kernel takes
+ * share a launch (the decode-batch kernel: column prefixes of at least 8 columns; the pipelined one: the same split of
+ * K, see uniql_w4_linear_kernel, and prefixes or segments); the others are launched one after the other on the stream.
  * Results are identical to n separate uniql_w4_linear calls.
  * Errors: E_SHAPE also for n outside 1..4; otherwise as uniql_w4_linear (nothing is launched if
  * any entry is invalid).

@@ -218,18 +218,19 @@ extern "C" int uniql_w4_linear_multi(int32_t n, const uniql_w4_t* W, const uniql
     if (e == hipErrorInvalidValue) return UNIQL_E_SHAPE;
     return e == hipSuccess ? UNIQL_OK : hip_fail(e);
   }
+  unsigned left = (1u << n) - 1;
   if (n > 1) {
-    // one launch when one kernel takes every member (the same format: fill_linear's entries of one call may differ in
+    // the members that one kernel takes share a launch (the same format: fill_linear's entries of one call may differ in
     // it, then they go one by one)
-    bool same = true, done = false;
+    bool same = true;
     for (int i = 1; i < n; ++i) same = same && a[i].bf16 == a[0].bf16;
     if (same) {
-      hipError_t e = launch_w4_gemm_batch(a, n, s, &done);
+      hipError_t e = launch_w4_gemm_batch(a, n, s, &left);
       if (e != hipSuccess) return hip_fail(e);
-      if (done) return UNIQL_OK;
     }
   }
   for (int i = 0; i < n; ++i) {
+    if (!(left >> i & 1)) continue;
     rc = run_linear(a[i], s);
     if (rc) return rc;
   }

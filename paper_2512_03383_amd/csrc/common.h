@@ -296,9 +296,9 @@ hipError_t launch_w4_gemm(const LinearArgs& a, hipStream_t stream);
 hipError_t launch_w4_gemm_bf16(const LinearArgs& a, hipStream_t stream);
 // which kernel and tile a linear of 2 tokens and more takes (uniql_w4_linear_kernel)
 void gemm_choice(const LinearArgs& a, int out[4]);
-// n (2..4) linears of one token count in one launch where one kernel takes them all (*done says whether)
-hipError_t launch_w4_gemm_batch(const LinearArgs* a, int n, hipStream_t stream, bool* done);
-hipError_t launch_w4_gemm_batch_bf16(const LinearArgs* a, int n, hipStream_t stream, bool* done);
+// n (2..4) linears of one token count, one launch for those that one kernel takes (bit i of *left: linear i was not launched)
+hipError_t launch_w4_gemm_batch(const LinearArgs* a, int n, hipStream_t stream, unsigned* left);
+hipError_t launch_w4_gemm_batch_bf16(const LinearArgs* a, int n, hipStream_t stream, unsigned* left);
 // gate (p[0]) and up (p[1]) of a decode batch (2..16 tokens) with h = SiLU(g) * u in one launch (*done says whether)
 hipError_t launch_w4_gate_up_silu_batch(const LinearArgs* p, hipStream_t stream, bool* done);
 hipError_t launch_w4_gate_up_silu_batch_bf16(const LinearArgs* p, hipStream_t stream, bool* done);

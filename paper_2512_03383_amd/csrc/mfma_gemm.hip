@@ -11,11 +11,11 @@ hipError_t launch_w4_gemm(const LinearArgs& a, hipStream_t stream) {
   return launch_gemm_fmt<false>(a, stream);
 }
 
-// n linears of the same token count and format in one launch when one kernel takes them all; *done = false: nothing was
-// launched, run them one by one
-hipError_t launch_w4_gemm_batch(const LinearArgs* a, int n, hipStream_t stream, bool* done) {
-  if (a[0].bf16) return launch_w4_gemm_batch_bf16(a, n, stream, done);
-  return launch_gemm_batch_fmt<false>(a, n, stream, done);
+// n linears of the same token count and format, one launch for those that one kernel takes; bit i of *left: linear i was
+// not launched
+hipError_t launch_w4_gemm_batch(const LinearArgs* a, int n, hipStream_t stream, unsigned* left) {
+  if (a[0].bf16) return launch_w4_gemm_batch_bf16(a, n, stream, left);
+  return launch_gemm_batch_fmt<false>(a, n, stream, left);
 }
 
 // gate and up of a decode batch with h = SiLU(g) * u (Eq. 1) in one launch; *done = false: nothing was launched

@@ -4,8 +4,8 @@
 namespace uniql {
 
 hipError_t launch_w4_gemm_bf16(const LinearArgs& a, hipStream_t stream) { return launch_gemm_fmt<true>(a, stream); }
-hipError_t launch_w4_gemm_batch_bf16(const LinearArgs* a, int n, hipStream_t stream, bool* done) {
-  return launch_gemm_batch_fmt<true>(a, n, stream, done);
+hipError_t launch_w4_gemm_batch_bf16(const LinearArgs* a, int n, hipStream_t stream, unsigned* left) {
+  return launch_gemm_batch_fmt<true>(a, n, stream, left);
 }
 
 hipError_t launch_w4_gate_up_silu_batch_bf16(const LinearArgs* p, hipStream_t stream, bool* done) {

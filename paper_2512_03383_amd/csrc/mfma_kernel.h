@@ -396,10 +396,14 @@ static inline GemmRoute gemm_route(const LinearArgs& a, int xm) {
   const int row_tiles = (a.km.n_keep + 15) / 16;
   const bool pipe = xm != 0 && pipe_serves(a);
   // Decode batches (M <= 32) are bound by the weight stream and have a kernel of their own (smallm_kernel.h), except
-  // tall matrices whose activations it cannot stage once per block: a wave that stages its own 16 x 128 activations per
-  // group costs more than the pipelined kernel's slabs (9318 x 4096 at 8 / 16 / 24 tokens 12.7 / 16.6 / 23.2 us there,
-  // 11.0 / 11.0 / 12.4 us here; with 256 row tiles it is the other way round: 4096 x 9318 at 24 tokens 18.1 against 22.6).
-  const bool tall = row_tiles >= 400 && a.M >= 5 && !(xm == 1 && smallm_pre(a));
+  // tall matrices from 9 tokens on whose activations it cannot stage once per block: a wave that stages its own 16 x 128
+  // activations per group costs more than the pipelined kernel's slabs (9472 x 4096 at 12 / 24 tokens 16.9 / 23.2 us there,
+  // 11.4 / 12.4 here, 6400 x 4096 10.0 / 13.1 and 8.7 / 10.2; with 256 row tiles it is the other way round: 4096 x 9318 at 24
+  // tokens 18.1 there, 22.6 here).  Up to 8 tokens the two are closer (6400 x 4096 8.8 there, 8.6 here, 9472 x 4096 12.8 and
+  // 11.2), and a tall matrix in the other kernel would no longer share a launch with short ones: 8192 + 1024 + 1024 rows x 8192
+  // columns at 8 tokens 17.5 us in one launch, 28 in three.  From 9 tokens on such a set is two launches, 0.92..1.0 of the time
+  // of one at 17..32 tokens and 1.0..1.17 at 9..16 (8192 + 1024 + 1024 x 8192 22.3 -> 21.9, x 4096 15.4 -> 15.7).
+  const bool tall = row_tiles >= 400 && a.M >= 9 && !(xm == 1 && smallm_pre(a));
   if (smallm_takes(a, xm == 1) && !(pipe && tall)) return kSmallM;
   if (pipe && a.M <= 64) return kPipe;
   // What neither takes (rows of fewer than eight groups; above the decode batches, or on tall matrices from 9 tokens on,
@@ -486,23 +490,32 @@ static inline void gemm_choice_of(const LinearArgs& a, int out[4]) {
   out[3] = kPipeConsumers / t.wn;
 }
 
-// n (2..4) linears of the same token count and format in one launch: a decode batch that the decode-batch kernel takes, or
-// linears that the pipelined kernel takes with the same split of K and kind of column rule.  *done = false: not such a
-// set, nothing was launched.
+// n (2..4) linears of the same token count and format: those that the decode-batch kernel takes (column prefixes) share a
+// launch, and so do those that the pipelined kernel takes with the same split of K and kind of column rule.  Bit i of *left
+// stays set for a linear that shares with no other and was not launched.
 template <bool BF16>
-static hipError_t launch_gemm_batch_fmt(const LinearArgs* a, int n, hipStream_t stream, bool* done) {
-  *done = false;
-  bool small = true, pipe = true;
+static hipError_t launch_gemm_batch_fmt(const LinearArgs* a, int n, hipStream_t stream, unsigned* left) {
+  // what may share: 1 the decode-batch kernel, 2 and up the pipelined one, 0 none
+  int kind[kMaxBatch];
   for (int i = 0; i < n; ++i) {
     const int xm = gemm_xm(a[i]);
     const GemmRoute r = gemm_route(a[i], xm);
-    small = small && r == kSmallM && xm == 1;
-    pipe = pipe && r == kPipe && xm == gemm_xm(a[0]) && pipe_way(a[i]) == pipe_way(a[0]);
+    kind[i] = r == kSmallM ? (xm == 1 ? 1 : 0) : r == kPipe ? 2 + pipe_way(a[i]) * 2 + (xm == 2) : 0;
   }
-  if (small) return smallm_batch<BF16>(a, n, stream, done);
-  if (!pipe) return hipSuccess;
-  *done = true;
-  return launch_pipe4<BF16>(a, n, stream);
+  *left = (1u << n) - 1;
+  for (int i = 0; i < n; ++i) {
+    if (kind[i] == 0 || !(*left >> i & 1)) continue;
+    LinearArgs set[kMaxBatch];
+    unsigned taken = 0;
+    int m = 0;
+    for (int j = i; j < n; ++j)
+      if (kind[j] == kind[i]) set[m++] = a[j], taken |= 1u << j;
+    if (m < 2) continue;
+    const hipError_t e = kind[i] == 1 ? smallm_batch<BF16>(set, m, stream) : launch_pipe4<BF16>(set, m, stream);
+    if (e != hipSuccess) return e;
+    *left &= ~taken;
+  }
+  return hipSuccess;
 }
 
 }  // namespace uniql

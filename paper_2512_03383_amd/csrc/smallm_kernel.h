@@ -496,15 +496,9 @@ static hipError_t smallm_launch_batch(const LinearArgs* a, int n, hipStream_t st
 }
 
 // n (2..4) linears of one decode batch in one launch: column prefixes of at least 8 columns, the same token count and
-// format (the caller checks), each one a linear that smallm_dispatch<1> would take.  *done = false: not such a set,
-// nothing was launched.
+// format, each one a linear that smallm_dispatch<1> would take (the caller checks).
 template <bool BF16>
-static hipError_t smallm_batch(const LinearArgs* a, int n, hipStream_t stream, bool* done) {
-  *done = false;
-  for (int i = 0; i < n; ++i) {
-    if (a[i].km.cs_stride != 0 || a[i].km.k_keep < 8 || a[i].M != a[0].M || !smallm_takes(a[i], true)) return hipSuccess;
-  }
-  *done = true;
+static hipError_t smallm_batch(const LinearArgs* a, int n, hipStream_t stream) {
   const int M = a[0].M;
   bool pre = true;
   for (int i = 0; i < n; ++i) pre = pre && smallm_pre(a[i]);

@@ -46,3 +46,12 @@ def test_tall_matrices_of_unusual_rules(K, keep, first):
     for M, want in ((first, (TILED, 16, 64, 4)), (16, (TILED, 16, 64, 4)), (17, (TILED, 32, 64, 4)), (32, (TILED, 32, 64, 4)),
                     (33, (TILED, 64, 64, 4)), (64, (TILED, 64, 64, 4))):
         assert uq.uniql_w4_linear_kernel(12288, K, keep, M) == want, M
+
+
+# decode batches of 2..8 tokens stay with one kernel whatever the height, so that q, k and v or gate and up share a launch
+@pytest.mark.parametrize("N", [1024, 6400, 8192, 9472, 18944])
+@pytest.mark.parametrize("K,keep", [(4096, None), (8192, None), (4096, seg(128, 108))])
+def test_small_decode_batches_share_one_kernel(N, K, keep):
+    for M in (2, 5, 8):
+        assert uq.uniql_w4_linear_kernel(N, K, keep, M)[0] == BATCH
+    assert uq.uniql_w4_linear_kernel(N, 8192, keep and seg(128, 108), 12)[0] == (BATCH if N < 6400 else PIPE)
