@@ -18,7 +18,7 @@
 // rounding; the members are converted one by one, so any order costs the same and the cheaper pairs (j, j + 4) of common.h
 // serve 4 and 6 bits.  The constant (base + z) s overflows from scales of 2^128 / 1279 on where a weight need not, so a group
 // with such a scale takes the wide form (member - (base + z)) * s, exact up to the rounding as well and two instructions a
-// code; code_scale_wide tells.
+// code; kScaleWide tells.
 #pragma once
 #include "common.h"
 
@@ -101,8 +101,9 @@ template <int BITS> struct CodeGroup<BITS, true> {
   float s, nalo, nahi, nblo, nbhi;   // scale, -(base + z) s of the two classes and halves (wide: base + z)
 };
 
-// a bfloat16 scale of 2^117 or more in magnitude (infinities and NaN among them): (1024 + z) s may overflow (1279 * 2^117 < 2^128)
-__device__ __forceinline__ bool code_scale_wide(uint32_t sbits) { return (sbits & 0x7f80u) >= ((127u + 117u) << 7); }
+// bits of the smallest bfloat16 scale in magnitude, 2^117, from which on (1024 + z) s may overflow (1279 * 2^117 < 2^128);
+// infinities and NaN lie above it
+constexpr uint32_t kScaleWide = (127u + 117u) << 7;
 
 template <int BITS, bool BF16, bool WIDE = false>
 __device__ __forceinline__ CodeGroup<BITS, BF16> make_code_group(uint32_t sbits, uint32_t z) {

@@ -33,7 +33,6 @@ constexpr int kBeyond = (int)0x80000000u;   // as an unsigned offset: past the e
 constexpr int kPipeConsumers = 8, kPipeMovers = 2;
 constexpr int kPipeThreads = (kPipeConsumers + kPipeMovers + 2) * kWave;
 constexpr int kPipeDies = 8, kPipeTokTilesPerPass = 4;
-constexpr uint32_t kScaleWide = 0x80000000u;   // in a group's word of scale and zero point: the scale asks for the wide unpack (codes.h)
 
 // Up to four linears with the same token count and format; tiles are numbered through the whole batch.
 struct PipeBatch {
@@ -203,8 +202,8 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
       });
       return;
     }
-    // ---- scales and zero points: row lane (+ 64 p) of the block, windows of eight groups, scale | zero << 16
-    // (and kScaleWide).  The window
+    // ---- scales and zero points: row lane (+ 64 p) of the block, windows of eight groups, scale | zero << 16.
+    // The window
     // never leaves the row (a load whose last word lies partly past the array comes back with that word zeroed): at the
     // row's end it starts `back` groups earlier and is shifted.  Groups past the last one get a zero scale.
     constexpr int P = (BN + 63) / 64, SPW = 8 / G;      // rows per lane, slabs per window
@@ -239,10 +238,8 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
         const uint64_t zv = has_z ? (((uint64_t)z[p].y << 32) | z[p].x) >> (8 * back) : (uint64_t)(1u << (BITS - 1)) * 0x0101010101010101ull;
         uint32_t o[8];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const uint32_t sc = g + j < ngroups ? (uint32_t)(sv >> (16 * j)) & 0xffffu : 0u;
-          o[j] = sc | ((uint32_t)(zv >> (8 * j)) & 0xffu) << 16 | (BF16 && code_scale_wide(sc) ? kScaleWide : 0u);
-        }
+        for (int j = 0; j < 8; ++j)
+          o[j] = (g + j < ngroups ? (uint32_t)(sv >> (16 * j)) & 0xffffu : 0u) | ((uint32_t)(zv >> (8 * j)) & 0xffu) << 16;
         const int row = p * 64 + lane;
         uint4* dst = reinterpret_cast<uint4*>(szs + ((w & 1) * BN + row) * 8);
         if (BN % 64 == 0 || row < BN) {
@@ -314,7 +311,8 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
   // group after that are read from LDS.
   typedef RawCodes<BITS, T> Raw;
   struct Group { Raw raw[BF]; uint32_t sz[BF]; };
-  auto read_group = [&](const unsigned char* sl, int it, int g, Group& o) {   // sl: smem + offset of the slab's codes
+  auto sz_at = [&](int it) { return ((it / SPW) & 1) * (BN * 8) + (it % SPW) * G; };   // of slab `it`, in words
+  auto read_group = [&](const unsigned char* sl, int sz, int g, Group& o) {   // sl: smem + offset of the slab's codes; sz: sz_at of it
 #pragma unroll
     for (int b = 0; b < BF; ++b) {
       if constexpr (BITS == 8) {
@@ -332,7 +330,7 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
       } else {
         o.raw[b] = read_codes<BITS, T>(sl + wro[b][g], kq);
       }
-      o.sz[b] = szs[(((it / SPW) & 1) * BN + b * 16) * 8 + (it % SPW) * G + g * KG];
+      o.sz[b] = szs[sz + b * (16 * 8) + g * KG];
     }
   };
   auto read_a = [&](const unsigned char* sl, int g, int t, uint4 (&o)[AF]) {
@@ -342,18 +340,19 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
   auto constants = [&](auto wide_form, const Group& r, CodeGroup<BITS, BF16> (&o)[BF]) {
 #pragma unroll
     for (int b = 0; b < BF; ++b)
-      o[b] = make_code_group<BITS, BF16, decltype(wide_form)::value>(r.sz[b] & 0xffffu, BF16 ? (r.sz[b] >> 16) & 0xffu : r.sz[b] >> 16);
+      o[b] = make_code_group<BITS, BF16, decltype(wide_form)::value>(r.sz[b] & 0xffffu, r.sz[b] >> 16);
   };
   auto unpack = [&](auto wide_form, int t, const Group& r, const CodeGroup<BITS, BF16> (&c)[BF], uint4 (&o)[BF]) {
 #pragma unroll
     for (int b = 0; b < BF; ++b) o[b] = code_step<BITS, BF16, T, decltype(wide_form)::value>(r.raw[b], t, c[b], mg);
   };
-  // bfloat16: whether a row of the group has a scale that asks for the wide unpack, the same for the whole wave
+  // bfloat16: whether a row of the group has a scale that asks for the wide unpack (codes.h), the same for the whole wave.  (Here
+  // and not where the scales are staged: that wave is the last one at the barrier with small tiles, 8 bits at 8 tokens 10 %.)
   auto asks_wide = [&](const Group& r) {
-    uint32_t w = r.sz[0];
+    uint32_t largest = 0;
 #pragma unroll
-    for (int b = 1; b < BF; ++b) w |= r.sz[b];
-    return __builtin_amdgcn_ballot_w64((int)w < 0) != 0;
+    for (int b = 0; b < BF; ++b) largest = max(largest, r.sz[b] << 17);   // magnitude of the scale
+    return __builtin_amdgcn_ballot_w64(largest >= kScaleWide << 17) != 0;
   };
   // cur: the group whose operands are being unpacked; ahead: with T > 1 the next group, with T = 1 the two after the
   // current one take turns
@@ -365,7 +364,8 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
   read_group(wsl, 0, 0, cur);
   read_a(xsl, 0, 0, av[0]);
   if constexpr (T == 1) read_group(wsl, 0, 1, ahead[1]);
-  int xb = 1, wb = 1, it = 0;
+  int xb = 1, wb = 1, it = 0, sz = sz_at(1);
+  const unsigned char *xnext = smem + S::XBytes, *wnext = smem + S::WBytes;
   // Slabs from `it` on.  The usual form of the bfloat16 unpack leaves at the first slab of which a scale asks for the wide form,
   // and the wide form, which is exact for every scale, goes on from there: one test a slab (a branch around the unpack of a
   // step costs 3 % of the whole kernel).
@@ -374,19 +374,17 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
     unpack(wide_form, 0, cur, gq, wf[0]);
     int end = nslab;
     while (it < end) {
-      const unsigned char *xnext = smem + xb * S::XBytes, *wnext = smem + wb * S::WBytes;
-      xb = xb + 1 == NX ? 0 : xb + 1;
-      wb = wb + 1 == NW ? 0 : wb + 1;
 #pragma unroll
       for (int s = 0; s < GW * T; ++s) {
         const int g = s / T, t = s % T, s1 = (s + 1) % (GW * T), p = s & 1;
         read_a(s1 ? xsl : xnext, s1 / T, s1 % T, av[p ^ 1]);
+        __builtin_amdgcn_sched_barrier(0);   // (activations first: the products wait for them)
         if constexpr (T == 1) {
-          if (s + 2 < GW) read_group(wsl, it, s + 2, ahead[p]);
-          else read_group(wnext, it + 1, s + 2 - GW, ahead[p]);
+          if (s + 2 < GW) read_group(wsl, sz_at(it), s + 2, ahead[p]);
+          else read_group(wnext, sz, s + 2 - GW, ahead[p]);
         } else if (t == 0) {
-          if (g + 1 < GW) read_group(wsl, it, g + 1, ahead[0]);
-          else read_group(wnext, it + 1, 0, ahead[0]);
+          if (g + 1 < GW) read_group(wsl, sz_at(it), g + 1, ahead[0]);
+          else read_group(wnext, sz, 0, ahead[0]);
         }
         __builtin_amdgcn_sched_barrier(0);   // (or the compiler moves the reads behind the products to save registers)
         if constexpr (SEG) {
@@ -395,6 +393,16 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
             uint4& v = av[p][f];
             v.x &= mask[t].x; v.y &= mask[t].y; v.z &= mask[t].z; v.w &= mask[t].w;
           }
+        }
+        if (s == GW * T - 1) {
+          // where the next slab's reads go, here and not behind the barrier (3 % with 64 x 64 tiles)
+          xsl = xnext;
+          wsl = wnext;
+          xb = xb + 1 == NX ? 0 : xb + 1;
+          wb = wb + 1 == NW ? 0 : wb + 1;
+          xnext = smem + xb * S::XBytes;
+          wnext = smem + wb * S::WBytes;
+          sz = sz_at(++it + 1);
         }
         if (t == T - 1) {
           cur = ahead[T == 1 ? p ^ 1 : 0];
@@ -419,10 +427,8 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
         // (used here: or the compiler moves the unpack of the next slab's first step behind the barrier and the test)
 #pragma unroll
         for (int b = 0; b < BF; ++b) asm volatile("" : "+v"(wf[0][b].x), "+v"(wf[0][b].y), "+v"(wf[0][b].z), "+v"(wf[0][b].w));
+        asm volatile("" : "+s"(end));     // (and the selection: 64 tokens x 64 rows, 5 % of the kernel)
       }
-      xsl = xnext;
-      wsl = wnext;
-      ++it;
       pipe_barrier();                     // slab it + 1 is in LDS, and nobody reads slab it - 1 any more
     }
   };
