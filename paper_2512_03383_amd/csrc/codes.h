@@ -198,19 +198,4 @@ __device__ __forceinline__ uint4 code_step(const RawCodes<BITS, T>& r, int t, co
   return make_uint4(d[0], d[1], d[2], d[3]);
 }
 
-// the canonical weight of one element, for the few columns behind the last whole block of eight
-template <int BITS, bool BF16>
-__device__ __forceinline__ float code_weight(const LinearArgs& a, size_t row, int k) {
-  const size_t words = (size_t)a.K_total * BITS / 32;
-  const uint32_t* w = a.qweight + row * words;
-  const int pos = BITS * k, o = pos & 31;
-  uint32_t v = w[pos >> 5] >> o;
-  if (32 % BITS != 0 && o + BITS > 32) v |= w[(pos >> 5) + 1] << (32 - o);   // (the code runs into the row's next word)
-  const int q = (int)(v & ((1u << BITS) - 1u));
-  const size_t g = row * (size_t)(a.K_total / kGroup) + (k >> 7);
-  const int z = a.zeros ? a.zeros[g] : 1 << (BITS - 1);
-  const float s = in16<BF16>(__builtin_bit_cast(half_t, a.scales[g]));
-  return in16<BF16>(out16<BF16>((float)(q - z) * s));
-}
-
 }  // namespace uniql

@@ -100,7 +100,6 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
   const int row_bytes = a.K_total / 8 * BITS, gpr = a.K_total / kGroup;
   const int ngroups = (km.k_span + kGroup - 1) / kGroup;
   const int nslab = (ngroups + G - 1) / G;
-  const int kv = km.k_keep & ~7;
   // column segments: a power of two up to the group's 128 columns (the host checks), so every group has the same pattern
   const int seg_shift = SEG ? __builtin_ctz((unsigned)km.cs_stride) : 0;
 
@@ -110,16 +109,22 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
     typedef __attribute__((address_space(3))) void lds_void;
     lds_byte* const lds = (lds_byte*)smem;
     // A mover's walk: slabs 0 .. N - 2 to begin with, then, one barrier per slab, the slab that takes the buffer which
-    // everybody has left.  Before barrier `it` the slabs up to it + 1 have landed.
-    auto walk = [&](auto n, auto per, auto&& move) {
+    // everybody has left.  Before barrier `it` the slabs up to it + 1 have landed.  Before barrier `extra_at` (the one that
+    // publishes the last slab, or -1 for none) the mover does something more.
+    auto walk = [&](auto n, auto per, auto&& move, int extra_at, auto&& extra) {
       constexpr int N = decltype(n)::value, PER = decltype(per)::value;
 #pragma unroll
       for (int p = 0; p < N - 1; ++p)
         if (p < nslab) move(p, p);
       int buf = N - 1;
       for (int it = 0; it < nslab; ++it) {
-        if (it + N - 2 < nslab) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((N - 3) * PER) : "memory");
-        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (it + (N > 3 ? N - 2 : 2) < nslab) {
+          asm volatile("s_waitcnt vmcnt(%0)" ::"n"((N - 3) * PER) : "memory");
+        } else {
+          // (the last slabs; `extra` is asked for here only: on the way from the wait to the barrier it costs 3 % at NX = 3)
+          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+          if (it == extra_at) extra();
+        }
         pipe_barrier();
         if (it + N - 1 < nslab) move(it + N - 1, buf);
         buf = buf + 1 == N ? 0 : buf + 1;
@@ -147,7 +152,7 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
         const int c = (CH <= 64 ? lane % CH : v % CH + lane) ^ (tok & 15);
         const int g = slab * G + c / 16, k0 = (c % 16) * 8;   // group, column in it
         int col = g * kpg + k0;
-        bool there = g * kGroup + k0 + 8 <= kv;          // a prefix: whole blocks below kv, the rest in the epilogue
+        bool there = g * kGroup + k0 < km.k_keep;        // a prefix: its last block comes with what lies behind it
         if constexpr (SEG) {
           const int off = k0 & (km.cs_stride - 1);
           col = g * kpg + (k0 >> seg_shift) * km.cs_keep + off;
@@ -155,7 +160,19 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
         }
         return there ? tok * ldx2 + col * 2 : kBeyond;
       };
-      const int nwhole = SEG ? ngroups / G : kv / (G * kGroup);
+      const int nwhole = SEG ? ngroups / G : km.k_keep / (G * kGroup);
+      // The last block of a prefix whose columns are not whole blocks, in LDS: what lies behind the kept columns is cleared, and
+      // an odd last column, whose word may lie partly past the resource and then reads as zero, is put in place from a load of
+      // its own.  A lane per token, each mover the tokens that it has loaded itself.  (Added up in the epilogue, column after
+      // column, they cost a chain of loads per fragment: 4096 x 9318 at 48 / 777 tokens 22.9 / 106 us, so 18.6 / 70.)
+      const int tail = SEG ? 0 : km.k_keep & 7;
+      constexpr int TI = (BM + 63) / 64;
+      uint32_t odd[TI];
+#pragma unroll
+      for (int i = 0; i < TI; ++i) {
+        const int t = lane + 64 * i;
+        odd[i] = (tail & 1) && t < mt ? (uint32_t)__builtin_bit_cast(uint16_t, a.x[(size_t)(m0 + t) * a.ldx + km.k_keep - 1]) : 0u;
+      }
       int first[S::XPW];                                 // (of use when there is a whole slab: then slab 0 is one)
 #pragma unroll
       for (int k = 0; k < S::XPW; ++k) first[k] = unit(k, 0);
@@ -171,6 +188,21 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
           for (int k = 0; k < S::XPW; ++k)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void*)(d + kPipeMovers * k < S::XI ? to + k * (kPipeMovers * 1024) : to - d * 1024), 16,
                                                      unit(k, slab), 0, 0, 0);
+        }
+      }, tail == 0 ? -1 : nslab > 1 ? nslab - 2 : 0, [&]() {
+        const int c = km.k_keep / 8 - (nslab - 1) * (16 * G), keep = tail & ~1;   // chunk in the slab, columns that stay
+        auto m = [&](int i) { return keep > i ? ~0u : 0u; };
+#pragma unroll
+        for (int i = 0; i < TI; ++i) {
+          const int t = lane + 64 * i;
+          if (t >= BM || (t * G / 4) % kPipeMovers != d) continue;
+          uint4* p = reinterpret_cast<uint4*>(smem + (nslab - 1) % NX * S::XBytes) + t * (16 * G) + (c ^ (t & 15));
+          uint4 v = *p;
+          v.x = (v.x & m(0)) | (tail == 1 ? odd[i] : 0u);
+          v.y = (v.y & m(2)) | (tail == 3 ? odd[i] : 0u);
+          v.z = (v.z & m(4)) | (tail == 5 ? odd[i] : 0u);
+          v.w = tail == 7 ? odd[i] : 0u;
+          *p = v;
         }
       });
       return;
@@ -199,11 +231,10 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
           for (int k = 0; k < S::WI; ++k)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_void*)(lds + S::W0 + buf * S::WBytes + k * 1024), 16, woff[k] + slab * (U * 16), 0, 0, 0);
         }
-      });
+      }, -1, []() {});
       return;
     }
-    // ---- scales and zero points: row lane (+ 64 p) of the block, windows of eight groups, scale | zero << 16.
-    // The window
+    // ---- scales and zero points: row lane (+ 64 p) of the block, windows of eight groups, scale | zero << 16.  The window
     // never leaves the row (a load whose last word lies partly past the array comes back with that word zeroed): at the
     // row's end it starts `back` groups earlier and is shifted.  Groups past the last one get a zero scale.
     constexpr int P = (BN + 63) / 64, SPW = 8 / G;      // rows per lane, slabs per window
@@ -442,14 +473,6 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
   auto store = [&](int f, int b, float4_t s) {
     const int tok = m0 + f * 16 + n, rc = n0 + (wn * BF + b) * 16 + 4 * ks;
     if (tok >= a.M || rc >= km.n_keep) return;
-    if (!SEG && kv < km.k_keep) {
-      // the kept columns kv .. k_keep - 1 of a prefix, in fp32
-      for (int v = 0; v < 4; ++v) {
-        const size_t row = (size_t)stored_row(km, rc + v < km.n_keep ? rc + v : km.n_keep - 1);
-        for (int k = kv; k < km.k_keep; ++k)
-          s[v] = __builtin_fmaf(in16<BF16>(a.x[(size_t)tok * a.ldx + k]), code_weight<BITS, BF16>(a, row, k), s[v]);
-      }
-    }
     half_t* y = a.y + (size_t)tok * a.ldy + rc;
     uint16_t o[4];
 #pragma unroll

@@ -138,3 +138,33 @@ def test_shared_launch_gives_the_same_bits(env, M, fmt):
         torch.cuda.synchronize()
         for W, x, y in zip(ws, xs, ys):
             assert torch.equal(y, uq.uniql_w4_linear(W, None, x))
+
+
+# the last block of a prefix: every number of columns in it, in the first block and in later blocks of a group, groups 1, 2, 3 and 4
+# of a slab of four; 47 tokens (one and a half tiles of 32), 50 (64), 130 (two tiles, the second with two tokens).  NaN lies
+# between the rows of x, and the last row ends with the array.
+@pytest.mark.parametrize("bits", [4, 8, 6, 3])
+@pytest.mark.parametrize("fmt", ["f16", "bf16"])
+@pytest.mark.parametrize("N,M", [(70, 47), (6410, 50), (200, 130)])
+def test_ends_of_a_prefix(env, uref, N, M, fmt, bits):
+    uq, torch = env
+    rng = wl.rng_for(64, N + M + bits)
+    K = 1536
+    w = gen(rng, N, K, bits, fmt)
+    qw = uq.QuantLinear.from_numpy(w, bits=bits)
+    rows = np.arange(N) if N < 1000 else np.unique(np.concatenate([[0, 63, 64, N - 1], rng.integers(0, N, 40)]))
+    rows = rows.astype(np.int32)
+    tdt = torch.bfloat16 if fmt == "bf16" else torch.float16
+    for i, kk in enumerate([1025, 1042, 1123, 1252, 1285, 1390, 1415, 1527, 1535, 1032]):
+        assert uq.uniql_w4_linear_kernel(N, K, Keep(k_keep=kk), M, bits=bits, bf16=fmt == "bf16")[0] == 2
+        x = wl.gen_activations(rng, M, kk, fmt=fmt)
+        ref = oracle_linear(uref, bits, w, x, Keep(k_keep=kk), fmt, rows=rows)
+        ld = kk + (0, 1, 3, 8)[i % 4]
+        flat = torch.full(((M - 1) * ld + kk,), float("nan"), dtype=tdt, device="cuda")
+        xb = flat.as_strided((M, kk), (ld, 1))
+        xb.copy_(dev16(torch, x, fmt))
+        y = uq.uniql_w4_linear(qw, Keep(k_keep=kk), xb)
+        torch.cuda.synchronize()
+        y = y.float().cpu().numpy()[:, rows]
+        assert linear_err(y, ref) <= (TOL_BF16 if fmt == "bf16" else TOL), kk
+        assert normwise_err(y, ref) <= (NORM_TOL_BF16 if fmt == "bf16" else NORM_TOL), kk
