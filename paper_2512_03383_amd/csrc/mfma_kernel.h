@@ -413,22 +413,27 @@ static inline GemmRoute gemm_route(const LinearArgs& a, int xm) {
   if (a.M <= 16) return row_tiles >= 600 ? kTile16x64k4 : kTile16x16k8;
   if (a.M <= 32) return row_tiles >= 600 ? kTile32x64k4 : kTile32x16k8;
   if (a.M <= 64) return row_tiles >= 600 ? kTile64x64k4 : kTile64x32k4;
-  // More tokens: the cheapest of the tiles (launch_cost)
+  // More tokens: the cheapest of the tiles (launch_cost).  `tail`: what every kept column behind the last whole block of eight
+  // costs a round of these tiles, which add such columns up in the epilogue (the pipelined kernel does not: 2560 x 1999 at 2048
+  // tokens 65 us in 128 x 256 tiles, 39 there).
   const float ng = (float)((a.km.k_span + kGroup - 1) / kGroup);
-  auto cost = [&](int bm, int bn, float far, TileCost f16, TileCost b16, TileCost f16_seg, TileCost b16_seg) {
+  const int odd_columns = xm == 1 ? a.km.k_keep % 8 : 0;
+  auto cost = [&](int bm, int bn, float far, float tail, TileCost f16, TileCost b16, TileCost f16_seg, TileCost b16_seg) {
     const TileCost c = xm == 2 ? (a.bf16 ? b16_seg : f16_seg) : (a.bf16 ? b16 : f16);
-    return launch_cost((long long)((a.km.n_keep + bn - 1) / bn) * ((a.M + bm - 1) / bm), ng, c, a.km.k_span > 8192 ? far : 1.f);
+    const long long tiles = (long long)((a.km.n_keep + bn - 1) / bn) * ((a.M + bm - 1) / bm);
+    return launch_cost(tiles, ng, c, a.km.k_span > 8192 ? far : 1.f, tail * (float)odd_columns);
   };
   GemmRoute best = kTile32x128k2;
-  float best_us = cost(32, 128, 1.25f, {0.36f, 0.05f}, {0.47f, 0.05f}, {0.50f, 0.05f}, {0.56f, 0.05f});
+  float best_us = cost(32, 128, 1.25f, 0.4f, {0.36f, 0.05f}, {0.47f, 0.05f}, {0.50f, 0.05f}, {0.56f, 0.05f});
   auto take = [&](GemmRoute r, float us) {
     if (us < best_us) best = r, best_us = us;
   };
-  if (pipe) take(kPipe, pipe_pick<4>(&a, 1).us);
-  if (xm == 1 && prefill_serves(a)) take(kPrefill256, cost(256, 256, 1.05f, {2.75f, 0.8f}, {2.95f, 0.6f}, {}, {}));
-  take(kTile128x256, cost(128, 256, 1.05f, {1.65f, 0.5f}, {1.85f, 0.4f}, {1.95f, 0.45f}, {2.1f, 0.45f}));
-  take(kTile64x256, cost(64, 256, 1.05f, {1.03f, 0.22f}, {1.22f, 0.12f}, {1.2f, 0.18f}, {1.4f, 0.13f}));
-  take(kTile64x128k2, cost(64, 128, 1.1f, {0.57f, 0.16f}, {0.70f, 0.10f}, {0.78f, 0.14f}, {0.88f, 0.11f}));
+  // (the pipelined kernel's table is shared by formats and widths; of 4 bits fp16 takes 0.94 of it, bfloat16 0.97)
+  if (pipe) take(kPipe, pipe_pick<4>(&a, 1).us * (a.bf16 ? 0.97f : 0.94f));
+  if (xm == 1 && prefill_serves(a)) take(kPrefill256, cost(256, 256, 1.05f, 3.9f, {2.75f, 0.8f}, {2.95f, 0.6f}, {}, {}));
+  take(kTile128x256, cost(128, 256, 1.05f, 4.1f, {1.65f, 0.5f}, {1.85f, 0.4f}, {1.95f, 0.45f}, {2.1f, 0.45f}));
+  take(kTile64x256, cost(64, 256, 1.05f, 0.85f, {1.03f, 0.22f}, {1.22f, 0.12f}, {1.2f, 0.18f}, {1.4f, 0.13f}));
+  take(kTile64x128k2, cost(64, 128, 1.1f, 0.75f, {0.57f, 0.16f}, {0.70f, 0.10f}, {0.78f, 0.14f}, {0.88f, 0.11f}));
   return best;
 }
 

@@ -8,15 +8,18 @@
 namespace uniql {
 
 // What a launch costs, in microseconds: a group of 128 columns (or a slab of them) costs one tile `us` on an idle chip and
-// `slope` more with every compute unit busy (clock and L2), a round of tiles 4 besides, the launch 3.  Rows of more than
-// 8192 columns miss the L2 more often.  Fitted to 350 shapes of 2560..13260 columns, 80..4096 tokens, within 10 %.
+// `slope` more with every compute unit busy (clock and L2), a round of tiles 4 besides and `round` more, the launch 3.  Rows of
+// more than 8192 columns miss the L2 more often.  It ranks tiles; as a time it is rough: with every candidate timed on 20
+// matrices of 1024..32000 rows and 1024..14208 columns at 80..4096 tokens (480 sizes of 4 bits, both formats) a tile took 0.71..1.14
+// of its cost (5th to 95th percentile).  The tile picked took 0.1 % longer than the fastest one in the mean and 12 % at worst; with
+// codes of 8, 6 and 3 bits, which share the pipelined kernel's table (330 sizes), 3 % at worst.
 struct TileCost {
   float us, slope;
 };
-static inline float launch_cost(long long tiles, float steps, TileCost c, float far) {
+static inline float launch_cost(long long tiles, float steps, TileCost c, float far, float round = 0.f) {
   const int cus = prefill_grid_limit();
   const float rounds = (float)((tiles + cus - 1) / cus);
-  return 3.f + rounds * (4.f + steps * (c.us + c.slope * (float)tiles / (rounds * (float)cus)) * far);
+  return 3.f + rounds * (4.f + round + steps * (c.us + c.slope * (float)tiles / (rounds * (float)cus)) * far);
 }
 
 struct PipeTile {

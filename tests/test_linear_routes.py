@@ -55,3 +55,13 @@ def test_small_decode_batches_share_one_kernel(N, K, keep):
     for M in (2, 5, 8):
         assert uq.uniql_w4_linear_kernel(N, K, keep, M)[0] == BATCH
     assert uq.uniql_w4_linear_kernel(N, 8192, keep and seg(128, 108), 12)[0] == (BATCH if N < 6400 else PIPE)
+
+
+# columns behind the last whole block of eight cost the tiled kernels more than the pipelined one (65 against 39 us at 2560 x 1999
+# and 2048 tokens), whole blocks nothing
+def test_odd_columns_of_prompts():
+    assert uq.uniql_w4_linear_kernel(2560, 2560, KeepDesc(k_keep=1999), 2048, ldx=1999)[0] == PIPE
+    for bf16 in (False, True):
+        for M in (333, 777, 1000, 1500):
+            assert uq.uniql_w4_linear_kernel(4096, 14336, KeepDesc(k_keep=9318), M, bf16=bf16)[0] == PIPE, M
+    assert uq.uniql_w4_linear_kernel(14336, 4096, KeepDesc(n_keep=12185), 4096)[0] == BIG
