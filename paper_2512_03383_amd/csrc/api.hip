@@ -148,8 +148,7 @@ static hipError_t launch_pipe(const LinearArgs* p, int n, hipStream_t s) {
 static int run_linear(const LinearArgs& a, hipStream_t s) {
   if (a.bits != 4) {
     if (wide_codes_refused(a)) return UNIQL_E_SHAPE;
-    // several tokens: the matrix kernel; the streaming ones read the weights once per token
-    if (pipe_serves(a)) {
+    if (pipe_serves(a) && !wide_streams(a)) {
       hipError_t ep = launch_pipe(&a, 1, s);
       return ep == hipSuccess ? UNIQL_OK : hip_fail(ep);
     }
@@ -194,7 +193,7 @@ extern "C" int uniql_w4_linear_kernel(const uniql_w4_t* W, const uniql_keep_t* k
   if (a.bits != 4 && wide_codes_refused(a)) return UNIQL_E_SHAPE;
   if (a.il_heads > 0 && M > kInterleavedMaxTokens) return UNIQL_E_SHAPE;
   for (int i = 0; i < 4; ++i) choice[i] = 0;
-  if (M == 1 || a.il_heads > 0 || (a.bits != 4 && !pipe_serves(a))) return UNIQL_OK;
+  if (M == 1 || a.il_heads > 0 || (a.bits != 4 && (!pipe_serves(a) || wide_streams(a)))) return UNIQL_OK;
   gemm_choice(a, choice);
   return UNIQL_OK;
 }

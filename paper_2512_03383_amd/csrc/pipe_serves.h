@@ -29,4 +29,28 @@ static inline bool pipe_serves(const LinearArgs& a) {
   return (long long)a.N_total * (a.K_total / 8) * a.bits < lim && (long long)a.ldx * 2 * 128 + (long long)a.K_total * 2 < lim;
 }
 
+// Codes of 8, 6 and 3 bits: whether the streaming kernel with a token per grid row (w8.hip, wbits.hip) is faster than the pipelined
+// one.  It reads and unpacks the weights once per token, but spreads rows and tokens over the whole chip, where the other has a
+// block for 32 rows and all tokens: few rows or very few tokens (256 x 12185 at 6 bits and 8 tokens 9.0 against 26.0 us, 2048 x 4096
+// at 3 tokens 8.4 against 12.2; 4096 x 4096 at 4 tokens 14.2 against 12.2).  In microseconds, from 1584 timed sizes of 256..131072
+// rows, 1024..12185 columns, 2..16 tokens: streaming s0 + s1 kc + (s2 + s3 kc) (rows x tokens / 1000 - 1.5), kc thousands of
+// columns (+ s4 with column segments); pipelined p0 + p1 slabs of 512 columns (+ p4), and p2 slabs + p3 more for every further round
+// of 256 tiles of 32 rows (3 bits, which have 64-row tiles too: in proportion).  Ties go to the streaming kernel.  The kernel picked
+// takes 0.1 to 0.6 % longer than the faster one in the mean, 23 % at worst.
+static inline bool wide_streams(const LinearArgs& a) {
+  struct Line { float s0, s1, s2, s3, s4, p0, p1, p2, p3, p4; };
+  static const Line lines[3][2] = {   // 8, 6, 3 bits; fp16, bfloat16
+      {{4.30f, 0.335f, 0.307f, 0.091f, 0.78f, 4.24f, 0.483f, 0.49f, 3.25f, 0.77f}, {4.41f, 0.428f, 0.455f, 0.110f, 0.57f, 4.07f, 0.539f, 0.51f, 3.34f, 0.71f}},
+      {{4.00f, 0.417f, 0.157f, 0.114f, 1.81f, 4.65f, 0.936f, 0.91f, 3.20f, 0.66f}, {3.84f, 0.553f, 0.202f, 0.172f, 1.39f, 4.54f, 0.951f, 0.86f, 3.73f, 0.39f}},
+      {{4.15f, 0.305f, 0.270f, 0.066f, 0.96f, 3.87f, 0.641f, 0.68f, 1.10f, 0.51f}, {4.40f, 0.409f, 0.436f, 0.119f, 0.41f, 3.88f, 0.686f, 0.78f, 1.07f, 0.48f}}};
+  const Line& l = lines[a.bits == 8 ? 0 : a.bits == 6 ? 1 : 2][a.bf16 ? 1 : 0];
+  const float seg = a.km.cs_stride != 0 ? 1.f : 0.f, kc = (float)a.km.k_span * 1e-3f, work = (float)a.km.n_keep * (float)a.M * 1e-3f - 1.5f;
+  const float slabs = (float)((a.km.k_span + 4 * kGroup - 1) / (4 * kGroup));
+  const int tiles = (a.km.n_keep + 31) / 32;
+  const float more = a.bits == 3 ? (float)a.km.n_keep / (32.f * 256.f) - 1.f : (float)((tiles + 255) / 256 - 1);
+  const float stream = l.s0 + l.s1 * kc + l.s4 * seg + (l.s2 + l.s3 * kc) * (work > 0.f ? work : 0.f);
+  const float pipe = l.p0 + l.p1 * slabs + l.p4 * seg + (l.p2 * slabs + l.p3) * (more > 0.f ? more : 0.f);
+  return stream < 1.03f * pipe;
+}
+
 }  // namespace uniql

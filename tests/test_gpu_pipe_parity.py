@@ -145,7 +145,7 @@ def test_shared_launch_gives_the_same_bits(env, M, fmt):
 # between the rows of x, and the last row ends with the array.
 @pytest.mark.parametrize("bits", [4, 8, 6, 3])
 @pytest.mark.parametrize("fmt", ["f16", "bf16"])
-@pytest.mark.parametrize("N,M", [(70, 47), (6410, 50), (200, 130)])
+@pytest.mark.parametrize("N,M", [(420, 47), (6410, 50), (200, 130)])
 def test_ends_of_a_prefix(env, uref, N, M, fmt, bits):
     uq, torch = env
     rng = wl.rng_for(64, N + M + bits)

@@ -65,3 +65,23 @@ def test_odd_columns_of_prompts():
         for M in (333, 777, 1000, 1500):
             assert uq.uniql_w4_linear_kernel(4096, 14336, KeepDesc(k_keep=9318), M, bf16=bf16)[0] == PIPE, M
     assert uq.uniql_w4_linear_kernel(14336, 4096, KeepDesc(n_keep=12185), 4096)[0] == BIG
+
+
+# codes of 8, 6 and 3 bits: few rows or very few tokens stay with the streaming kernels (a token per grid row)
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("bits", [8, 6, 3])
+def test_wide_codes_stream_where_that_is_faster(bits, bf16):
+    def route(N, K, M, keep=None):
+        return uq.uniql_w4_linear_kernel(N, K, keep, M, bits=bits, bf16=bf16)[0]
+    for K in (1024, 4096, 14336):
+        for M in (2, 4, 8):
+            assert route(256, K, M) == STREAM
+    assert route(1024, 1024, 2) == STREAM and route(1024, 4096, 2) == STREAM
+    assert route(2048, 14336, 2) == STREAM
+    for N, K in ((4096, 4096), (12185, 4096), (4096, 14336)):
+        for M in (8, 16, 48, 512):
+            assert route(N, K, M) == PIPE
+    if bits == 6 and not bf16:
+        for N, K in ((4096, 4096), (4096, 14336), (14336, 2048)):
+            assert route(N, K, 2) == STREAM
+    assert route(128, 896, 8) == STREAM
