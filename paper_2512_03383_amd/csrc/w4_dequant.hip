@@ -8,56 +8,64 @@
 
 namespace uniql {
 
-// Bound by the output: 2 bytes written per half byte read.  A wave takes a row; its lanes take consecutive words, so a
-// store instruction writes 1 KB of consecutive output and a load reads 256 bytes of codes, eight words per lane in flight.
-// 10752 x 4096 kept: 24.4 us against 62 us (3072 x 4096: 8.3 against 21) of one thread per word of the whole matrix with
-// eight 2-byte stores and a 64-bit division each; four words in flight 24.9 (10.3), two 28.9 (12.4).  A word's eight
-// columns are written at once when all are kept; the word that holds the last kept columns of the row or of a segment, and
-// column rules whose segments are not whole words, go element by element.
-template <bool BF16>
-__global__ __launch_bounds__(256) void w4_dequant_kernel(LinearArgs a) {
-  constexpr int U = 8;                    // words per lane and turn
+// Bound by the output: 2 bytes written per half byte read.  A lane takes a word of a chunk, so a store instruction writes up to 1 KB
+// of consecutive output and a load reads 256 bytes of codes, U chunks in flight per wave: 1 << CL of each of U >> CL rows.  Rows
+// of at most 32 words (NARROW) share chunks: 1 << lanes_log2 lanes each.
+// 10752 x 4096 kept: 24.4 us with eight chunks in flight (four 24.9, two 28.9; a thread per word of the whole matrix with eight 2-byte
+// stores 62).  A wave to a row whatever its length left lanes idle on narrow rows and the chip on few long ones:
+// 343750 x 128 102 us, so 24.4, 13 x 18944 11.9, so 3.5.
+// A word's eight columns are written at once when all are kept; the word that holds the last kept columns of the row or of a
+// segment, and column rules whose segments are not whole words, go element by element.
+template <bool BF16, int U, int CL, bool NARROW>
+__global__ __launch_bounds__(256) void w4_dequant_kernel(LinearArgs a, int lanes_log2) {
+  constexpr int CH = 1 << CL;             // chunks of a row per turn
+  static_assert(CH <= U && (!NARROW || CL == 0), "whole rows per turn");
   const KeepMap& km = a.km;
-  const int lane = threadIdx.x & 63;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int words_span = (km.k_span + 7) >> 3;
   const int words_per_row = a.K_total >> 3;
   const int groups_per_row = a.K_total / kGroup;
   const int wph = a.il_heads > 0 ? words_per_row / a.il_heads : 1;
   const bool whole_words = km.cs_stride % 8 == 0;   // (a prefix: stride 0)
-  for (long long rc = (long long)blockIdx.x * 4 + (threadIdx.x >> 6); rc < km.n_keep; rc += (long long)gridDim.x * 4) {
-    const size_t row = (size_t)stored_row(km, (int)rc);
-    const uint32_t* codes = a.qweight + row * words_per_row;
-    const size_t g0 = row * groups_per_row;
-    half_t* out = a.y + (size_t)rc * km.k_keep;
-    for (int w0 = lane; w0 < words_span; w0 += 64 * U) {
+  const int ll = NARROW ? lanes_log2 : 6, lane_row = lane >> ll, lane_word = lane & ((1 << ll) - 1);
+  const int turn_rows = (U >> CL) << (6 - ll);
+  // the walk over rows, and over the turns of a long row
+  for (long long r0 = ((long long)blockIdx.x * 4 + wave) * turn_rows; r0 < km.n_keep; r0 += (long long)gridDim.x * 4 * turn_rows)
+    for (int part0 = (int)blockIdx.y * CH; part0 * 64 < words_span; part0 += (int)gridDim.y * CH) {
       uint32_t word[U], sb[U], zb[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int w = min(w0 + 64 * u, words_span - 1);
+        // (a row or word past the last one reads the last one)
+        const long long rc = r0 + ((u >> CL) << (6 - ll)) + (NARROW ? lane_row : 0);
+        const int w = min((part0 + u % CH) * 64 + lane_word, words_span - 1);
+        const size_t row = (size_t)stored_row(km, rc < km.n_keep ? (int)rc : km.n_keep - 1);
         // w counts words in column order; a head-interleaved row stores word (h, d / 8) at (d / 8) * H + h
         int ws = w;
         if (a.il_heads > 0) {
           const int h = w / wph;
           ws = (w - h * wph) * a.il_heads + h;
         }
-        word[u] = codes[ws];
-        sb[u] = a.scales[g0 + (w >> 4)];
-        zb[u] = a.zeros ? a.zeros[g0 + (w >> 4)] : 8;   // no zero points: the symmetric scheme
+        word[u] = (a.qweight + row * words_per_row)[ws];
+        sb[u] = (a.scales + row * groups_per_row)[w >> 4];
+        zb[u] = a.zeros ? (a.zeros + row * groups_per_row)[w >> 4] : 8;   // no zero points: the symmetric scheme
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int w = w0 + 64 * u;
-        if (w >= words_span) break;
+        const long long rc = r0 + ((u >> CL) << (6 - ll)) + (NARROW ? lane_row : 0);
+        const int w = (part0 + u % CH) * 64 + lane_word;
+        if (rc >= km.n_keep || w >= words_span) continue;
         const float s = in16<BF16>(__builtin_bit_cast(half_t, (uint16_t)sb[u]));
         const int z = (int)zb[u];
         uint16_t o[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) o[j] = __builtin_bit_cast(uint16_t, out16<BF16>((float)((int)((word[u] >> (4 * j)) & 15u) - z) * s));
-        int kc = 8 * w, nk = km.k_keep - kc;        // compact column of the first one, kept columns from there
-        if (km.cs_stride != 0 && whole_words) {
-          const int seg = kc / km.cs_stride, off = kc - seg * km.cs_stride;
+        half_t* out = a.y + (size_t)rc * km.k_keep;
+        int kc = 8 * w, nk = km.k_keep - kc, off = kc;   // compact column of the first one, kept columns from there, place in the segment
+        if (km.cs_stride != 0) {
+          const int seg = kc / km.cs_stride;
+          off = kc - seg * km.cs_stride;
           nk = km.cs_keep - off;
-          kc = seg * km.cs_keep + off;
+          kc = seg * km.cs_keep + min(off, km.cs_keep);
         }
         if (whole_words && nk >= 8) {
           typedef uint32_t u32x4_u2 __attribute__((ext_vector_type(4), aligned(2)));
@@ -65,25 +73,60 @@ __global__ __launch_bounds__(256) void w4_dequant_kernel(LinearArgs a) {
 #pragma unroll
           for (int j = 0; j < 4; ++j) v[j] = o[2 * j] | ((uint32_t)o[2 * j + 1] << 16);
           *reinterpret_cast<u32x4_u2*>(out + kc) = v;
+        } else if (whole_words) {
+#pragma unroll
+          for (int j = 0; j < 8; ++j)
+            if (j < nk) out[kc + j] = __builtin_bit_cast(half_t, o[j]);
         } else {
+          // (a word may hold the end of one segment and the beginning of the next)
+          half_t* to = out + kc;
 #pragma unroll
           for (int j = 0; j < 8; ++j) {
-            const int c = whole_words ? (j < nk ? kc + j : -1) : compact_col(km, 8 * w + j);
-            if (c >= 0) out[c] = __builtin_bit_cast(half_t, o[j]);
+            if (off < km.cs_keep) *to++ = __builtin_bit_cast(half_t, o[j]);
+            off = off + 1 == km.cs_stride ? 0 : off + 1;
           }
         }
       }
     }
+}
+
+template <bool BF16, int U, int CL, bool NARROW>
+static hipError_t launch_dequant_cfg(const LinearArgs& a, int lanes_log2, hipStream_t stream) {
+  const int chunks = (a.km.k_span + 511) / 512, turn_rows = (U >> CL) << (6 - (NARROW ? lanes_log2 : 6));
+  long long x = (((long long)a.km.n_keep + turn_rows - 1) / turn_rows + 3) / 4, y = (chunks + (1 << CL) - 1) >> CL;
+  if (x > 65536) x = 65536;
+  if (y > 65535) y = 65535;
+  hipLaunchKernelGGL((w4_dequant_kernel<BF16, U, CL, NARROW>), dim3((unsigned)x, (unsigned)y), dim3(256), 0, stream, a, lanes_log2);
+  return hipGetLastError();
+}
+
+template <bool BF16, int U>
+static hipError_t launch_dequant(const LinearArgs& a, hipStream_t stream) {
+  const int words = (a.km.k_span + 7) >> 3;
+  int lanes_log2 = 0;
+  while (lanes_log2 < 6 && (1 << lanes_log2) < words) ++lanes_log2;
+  if (lanes_log2 < 6) return launch_dequant_cfg<BF16, U, 0, true>(a, lanes_log2, stream);
+  if constexpr (U >= 8) {
+    if (words > 256) return launch_dequant_cfg<BF16, U, 3, false>(a, 6, stream);
+    if (words > 128) return launch_dequant_cfg<BF16, U, 2, false>(a, 6, stream);
   }
+  if constexpr (U >= 2) {
+    if (words > 64) return launch_dequant_cfg<BF16, U, 1, false>(a, 6, stream);
+  }
+  return launch_dequant_cfg<BF16, U, 0, false>(a, 6, stream);
+}
+
+template <bool BF16>
+static hipError_t launch_dequant_fmt(const LinearArgs& a, hipStream_t stream) {
+  const long long chunks = ((long long)a.km.n_keep * ((a.km.k_span + 7) >> 3) + 63) >> 6;
+  // chunks in flight: eight where that leaves every SIMD two waves and more, fewer on more waves otherwise (44 / 4.2 / 0.26 million
+  // codes of 4096 columns: eight 20.2 / 6.1 / 5.0 us, two 22.4 / 5.7 / 4.2, one 28.9 / 6.4 / 4.1)
+  if (chunks >= 16384) return launch_dequant<BF16, 8>(a, stream);
+  return chunks >= 4096 ? launch_dequant<BF16, 2>(a, stream) : launch_dequant<BF16, 1>(a, stream);
 }
 
 hipError_t launch_w4_dequant(const LinearArgs& a, hipStream_t stream) {
-  int blocks = (a.km.n_keep + 3) / 4;
-  if (blocks > 65536) blocks = 65536;
-  if (blocks < 1) blocks = 1;
-  if (a.bf16) hipLaunchKernelGGL(w4_dequant_kernel<true>, dim3((unsigned)blocks), dim3(256), 0, stream, a);
-  else hipLaunchKernelGGL(w4_dequant_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, stream, a);
-  return hipGetLastError();
+  return a.bf16 ? launch_dequant_fmt<true>(a, stream) : launch_dequant_fmt<false>(a, stream);
 }
 
 // Rows of a quantised table gathered by token id: out[i][:] = dequantised row ids[i].

@@ -31,6 +31,21 @@ pytestmark = pytest.mark.gpu
     (5, 2176, Keep(k_keep=64 * 33, col_seg_stride=34, col_seg_keep=33), 0),
     (5, 2176, Keep(k_keep=16 * 109, col_seg_stride=136, col_seg_keep=109), 0),
     (262147, 128, Keep(k_keep=3), 0),              # more rows than one turn of the grid
+    (5, 18944, Keep(k_keep=18931), 0),             # turns of a long row on several waves, one chunk each
+    (1300, 2048, Keep(k_keep=2041), 0),            # two chunks in flight: a row of 4, of 2, of 1 chunk, narrower rows
+    (2601, 1024, Keep(k_keep=1017), 0),
+    (5203, 512, Keep(k_keep=511), 0),
+    (9001, 384, Keep(k_keep=259), 0),
+    (5201, 8192, Keep(n_keep=2100, k_keep=4099), 0),   # eight: a row of nine chunks, of five, four, three, two, one, narrower ones
+    (5003, 2176, Keep(k_keep=2175), 0),
+    (5001, 2048, Keep(k_keep=2043), 0),
+    (6001, 1536, Keep(k_keep=1530), 0),
+    (9003, 1024, Keep(k_keep=1023), 0),
+    (17001, 512, Keep(k_keep=509), 0),
+    (35001, 384, Keep(row_seg_stride=7, row_seg_keep=5, row_seg_limit=34993, k_keep=257), 0),
+    (65539, 256, Keep(k_keep=250), 0),
+    (3300, 3072, Keep(k_keep=256 * 9, col_seg_stride=12, col_seg_keep=9), 0),
+    (5, 2040 * 64, Keep(k_keep=2040 * 55, col_seg_stride=64, col_seg_keep=55), 0),
     (5, 2048, Keep(k_keep=16 * 109, col_seg_stride=128, col_seg_keep=109), 16),
     (5, 2048, Keep(k_keep=32 * 40, col_seg_stride=64, col_seg_keep=40), 32),
 ])
