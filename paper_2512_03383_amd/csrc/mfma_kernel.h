@@ -421,19 +421,20 @@ static inline GemmRoute gemm_route(const LinearArgs& a, int xm) {
   auto cost = [&](int bm, int bn, float far, float tail, TileCost f16, TileCost b16, TileCost f16_seg, TileCost b16_seg) {
     const TileCost c = xm == 2 ? (a.bf16 ? b16_seg : f16_seg) : (a.bf16 ? b16 : f16);
     const long long tiles = (long long)((a.km.n_keep + bn - 1) / bn) * ((a.M + bm - 1) / bm);
+    if (bm < 256 && (a.M + bm - 1) / bm > 65535) return 1e30f;   // (a grid row per token tile)
     return launch_cost(tiles, ng, c, a.km.k_span > 8192 ? far : 1.f, tail * (float)odd_columns);
   };
-  GemmRoute best = kTile32x128k2;
-  float best_us = cost(32, 128, 1.25f, 0.4f, {0.36f, 0.05f}, {0.47f, 0.05f}, {0.50f, 0.05f}, {0.56f, 0.05f});
+  GemmRoute best = kTile128x256;
+  float best_us = cost(128, 256, 1.05f, 4.1f, {1.65f, 0.5f}, {1.85f, 0.4f}, {1.95f, 0.45f}, {2.1f, 0.45f});
   auto take = [&](GemmRoute r, float us) {
     if (us < best_us) best = r, best_us = us;
   };
   // (the pipelined kernel's table is shared by formats and widths; of 4 bits fp16 takes 0.94 of it, bfloat16 0.97)
   if (pipe) take(kPipe, pipe_pick<4>(&a, 1).us * (a.bf16 ? 0.97f : 0.94f));
   if (xm == 1 && prefill_serves(a)) take(kPrefill256, cost(256, 256, 1.05f, 3.9f, {2.75f, 0.8f}, {2.95f, 0.6f}, {}, {}));
-  take(kTile128x256, cost(128, 256, 1.05f, 4.1f, {1.65f, 0.5f}, {1.85f, 0.4f}, {1.95f, 0.45f}, {2.1f, 0.45f}));
   take(kTile64x256, cost(64, 256, 1.05f, 0.85f, {1.03f, 0.22f}, {1.22f, 0.12f}, {1.2f, 0.18f}, {1.4f, 0.13f}));
   take(kTile64x128k2, cost(64, 128, 1.1f, 0.75f, {0.57f, 0.16f}, {0.70f, 0.10f}, {0.78f, 0.14f}, {0.88f, 0.11f}));
+  take(kTile32x128k2, cost(32, 128, 1.25f, 0.4f, {0.36f, 0.05f}, {0.47f, 0.05f}, {0.50f, 0.05f}, {0.56f, 0.05f}));
   return best;
 }
 
@@ -513,8 +514,12 @@ static hipError_t launch_gemm_batch_fmt(const LinearArgs* a, int n, hipStream_t 
     LinearArgs set[kMaxBatch];
     unsigned taken = 0;
     int m = 0;
+    long long outputs = 0;
     for (int j = i; j < n; ++j)
-      if (kind[j] == kind[i]) set[m++] = a[j], taken |= 1u << j;
+      if (kind[j] == kind[i] && outputs + (long long)a[j].km.n_keep * a[j].M <= kPipeOutputs) {
+        set[m++] = a[j], taken |= 1u << j;
+        outputs += (long long)a[j].km.n_keep * a[j].M;
+      }
     if (m < 2) continue;
     const hipError_t e = kind[i] == 1 ? smallm_batch<BF16>(set, m, stream) : launch_pipe4<BF16>(set, m, stream);
     if (e != hipSuccess) return e;

@@ -58,7 +58,8 @@ static inline PipeTile pipe_pick(const LinearArgs* p, int n) {
     long long tiles = 0;
     for (int i = 0; i < n; ++i) tiles += (p[i].km.n_keep + t.wn * t.bf * 16 - 1) / (t.wn * t.bf * 16);
     tiles *= (M + 16 * t.af - 1) / (16 * t.af);
-    t.us = launch_cost(tiles, (float)((ngroups + t.g - 1) / t.g), seg ? t.seg : t.prefix, span > 8192 ? 1.18f : 1.f);
+    // (threads of a grid are counted in 32 bits; pipe_serves leaves the largest tiles below that)
+    t.us = tiles * kPipeThreads >= (1ll << 32) ? 1e30f : launch_cost(tiles, (float)((ngroups + t.g - 1) / t.g), seg ? t.seg : t.prefix, span > 8192 ? 1.18f : 1.f);
     if (best.af == 0 || t.us < best.us) best = t;
   }
   return best;

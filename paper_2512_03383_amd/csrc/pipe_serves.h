@@ -18,12 +18,17 @@ static inline PipeWay pipe_way(const LinearArgs& a) {
   return a.M > 32 && (a.km.n_keep + 15) / 16 >= 400 ? kPipeMixed : kPipeGroups;
 }
 
+// Outputs that a launch of the pipelined kernel reaches with its largest tiles (96 tokens x 128 rows and more, 768 threads each: the
+// threads of a grid are counted in 32 bits).
+constexpr long long kPipeOutputs = 60000000000ll;
+
 // At least two tokens, rows of eight groups and more (the window of scales), a column prefix of at least eight columns or
 // segments of a power of two up to a group that keep an even number of columns (the last kept pair of x is then a whole
 // 32-bit word of its row); 32-bit offsets reach the matrix and a token tile.
 static inline bool pipe_serves(const LinearArgs& a) {
   const KeepMap& km = a.km;
   const long long lim = (1ll << 31) - (1 << 17);
+  if ((long long)a.km.n_keep * a.M > kPipeOutputs) return false;
   if (a.M < 2 || a.il_heads > 0 || a.K_total < 8 * kGroup) return false;
   if (km.cs_stride == 0 ? km.k_keep < 8 : (km.cs_stride > kGroup || (km.cs_stride & (km.cs_stride - 1)) != 0 || km.cs_keep % 2 != 0)) return false;
   return (long long)a.N_total * (a.K_total / 8) * a.bits < lim && (long long)a.ldx * 2 * 128 + (long long)a.K_total * 2 < lim;

@@ -85,3 +85,16 @@ def test_wide_codes_stream_where_that_is_faster(bits, bf16):
         for N, K in ((4096, 4096), (4096, 14336), (14336, 2048)):
             assert route(N, K, 2) == STREAM
     assert route(128, 896, 8) == STREAM
+
+
+# what a grid holds: 65535 token tiles in y, fewer than 2^32 threads in all
+@pytest.mark.parametrize("N,K,keep,M,bits", [
+    (100, 4096, seg(256, 216), 5_000_000, 4), (16, 1024, KeepDesc(k_keep=5), 7_000_000, 4), (100, 896, None, 3_000_000, 4),
+    (1_000_000, 1024, None, 65535, 8), (2_000_000, 1024, None, 65535, 8), (500_000, 1024, seg(64, 54), 100_000, 4),
+    (4_000_000, 1024, None, 65_000, 4), (128256, 4096, None, 65535, 3)])
+def test_grids_hold_the_largest_calls(N, K, keep, M, bits):
+    kernel, bm, bn, _ = uq.uniql_w4_linear_kernel(N, K, keep, M, bits=bits)
+    if kernel == PIPE:
+        assert -(-N // bn) * -(-M // bm) * 768 < 2 ** 32
+    elif kernel == TILED:
+        assert -(-M // bm) <= 65535
