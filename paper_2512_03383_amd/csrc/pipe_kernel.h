@@ -43,20 +43,19 @@ struct PipeBatch {
 
 template <int AF, int BF, int WN, int KG, int KQ, int G, int NX, int NW, int BITS>
 struct PipeShape {
-  static_assert(WN * KG * KQ == kPipeConsumers && G % KG == 0 && 4 % KQ == 0, "eight waves multiply");
-  static constexpr int BM = 16 * AF, BN = WN * BF * 16, KS = KG * KQ, T = 4 / KQ, GW = G / KG;   // a wave: GW groups of a slab, T steps of each
-  static_assert(GW * T % 2 == 0, "two sets of activation fragments take turns");
+  static_assert(WN * KG * KQ == kPipeConsumers && G == KG && KQ <= 2 && KG * KQ > 1, "eight waves multiply, each one group of a slab, two or all four of its steps");
+  static constexpr int BM = 16 * AF, BN = WN * BF * 16, KS = KG * KQ, T = 4 / KQ;   // a wave: T steps of its group
   static constexpr int U = G * BITS;                           // 16-byte units of codes per row and slab
   static constexpr int XBytes = BM * G * 256, WBytes = BN * U * 16;
-  static constexpr int XI = XBytes / 1024, WI = (WBytes + 1023) / 1024; // loads of 64 x 16 bytes
-  static_assert(WBytes % 1024 == 0, "whole loads");
-  static constexpr int XPW = (XI + kPipeMovers - 1) / kPipeMovers;
+  static constexpr int XI = XBytes / 1024, WI = WBytes / 1024;   // loads of 64 x 16 bytes
+  static_assert(WBytes % 1024 == 0 && XI % kPipeMovers == 0, "whole loads, the same number for each mover");
+  static constexpr int XPW = XI / kPipeMovers;
   static constexpr int SZ = 2 * BN * 8 * 4;                    // two windows of eight groups
   static constexpr int W0 = NX * XBytes, SZ0 = W0 + NW * WBytes, Lds = SZ0 + SZ;
   static_assert((NX - 1) * XPW <= 63 && (NW - 1) * WI <= 63, "loads in flight are counted in six bits");
   static_assert(NX >= 3 && NW >= 3 && 8 % G == 0 && G <= 4, "a slab in use, one ready, one on its way; a window of scales is two slabs or more");
   static_assert(Lds <= 160 * 1024, "the slabs fit the LDS");
-  static_assert(KS == 1 || kPipeConsumers * AF * BF * 1024 <= Lds, "so do the partial sums");
+  static_assert(kPipeConsumers * AF * BF * 1024 <= Lds, "so do the partial sums");
 };
 
 __device__ __forceinline__ void pipe_barrier() {
@@ -145,9 +144,8 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
       // every 60 clocks otherwise).
       const int kpg = SEG ? (kGroup >> seg_shift) * km.cs_keep : kGroup;
       auto unit = [&](int k, int slab) {
-        const int q0 = d + kPipeMovers * k, q = q0 < S::XI ? q0 : 0;   // (uniform; a turn with nothing left repeats the first load)
         constexpr int CH = 16 * G;                       // chunks per token
-        const int v = q * 64;
+        const int v = (d + kPipeMovers * k) * 64;
         const int tok = v / CH + (CH < 64 ? lane / CH : 0);
         const int c = (CH <= 64 ? lane % CH : v % CH + lane) ^ (tok & 15);
         const int g = slab * G + c / 16, k0 = (c % 16) * 8;   // group, column in it
@@ -181,13 +179,11 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
         if (slab < nwhole) {
 #pragma unroll
           for (int k = 0; k < S::XPW; ++k)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void*)(d + kPipeMovers * k < S::XI ? to + k * (kPipeMovers * 1024) : to - d * 1024), 16,
-                                                     first[k], slab * (G * kpg * 2), 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void*)(to + k * (kPipeMovers * 1024)), 16, first[k], slab * (G * kpg * 2), 0, 0);
         } else {
 #pragma unroll
           for (int k = 0; k < S::XPW; ++k)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void*)(d + kPipeMovers * k < S::XI ? to + k * (kPipeMovers * 1024) : to - d * 1024), 16,
-                                                     unit(k, slab), 0, 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void*)(to + k * (kPipeMovers * 1024)), 16, unit(k, slab), 0, 0, 0);
         }
       }, tail == 0 ? -1 : nslab > 1 ? nslab - 2 : 0, [&]() {
         const int c = km.k_keep / 8 - (nslab - 1) * (16 * G), keep = tail & ~1;   // chunk in the slab, columns that stay
@@ -297,7 +293,7 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
   // ---- consumers
   const int wn = wave % WN, wk = wave / WN, kg = wk / KQ, kq = wk % KQ;
   const int n = lane & 15, ks = lane >> 4;
-  constexpr int SPW = 8 / G, T = S::T, GW = S::GW;
+  constexpr int SPW = 8 / G, T = S::T;
   float4_t acc[AF][BF];
 #pragma unroll
   for (int f = 0; f < AF; ++f)
@@ -305,23 +301,21 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
     for (int b = 0; b < BF; ++b) acc[f][b] = float4_t{0.f, 0.f, 0.f, 0.f};
   const CodeMagic mg = make_code_magic<BITS, BF16>();
   // LDS byte offsets inside a slab: activations of the wave's step t of its first group (token n), codes of its slots
-  int xoff[T], wro[BF][GW];
+  int xoff[T], wro[BF];
 #pragma unroll
   for (int t = 0; t < T; ++t) xoff[t] = (n * (16 * G) + kg * 16 + ((ks * 4 + kq * T + t) ^ n)) * 16;
 #pragma unroll
-  for (int b = 0; b < BF; ++b)
-#pragma unroll
-    for (int g = 0; g < GW; ++g) {
-      const int row = (wn * BF + b) * 16 + n, byte = (g * KG + kg) * (16 * BITS) + ks * (4 * BITS);   // of the row's codes in the slab
-      int o = byte;
-      if constexpr ((U & (U - 1)) == 0) {
-        // (8 bits: a slot is two units and the permutation may swap them, so the window's own unit is addressed)
-        const int by = byte + (BITS == 8 ? kq * (T * BITS) : 0);
-        const int sw = U >= 16 ? row & 15 : (row / (U < 16 ? 16 / U : 1)) & (U - 1);
-        o = (((by >> 4) ^ sw) << 4) | (by & 15);
-      }
-      wro[b][g] = S::W0 + row * U * 16 + o;
+  for (int b = 0; b < BF; ++b) {
+    const int row = (wn * BF + b) * 16 + n, byte = kg * (16 * BITS) + ks * (4 * BITS);   // of the row's codes in the slab
+    int o = byte;
+    if constexpr ((U & (U - 1)) == 0) {
+      // (8 bits: a slot is two units and the permutation may swap them, so the window's own unit is addressed)
+      const int by = byte + (BITS == 8 ? kq * (T * BITS) : 0);
+      const int sw = U >= 16 ? row & 15 : (row / (U < 16 ? 16 / U : 1)) & (U - 1);
+      o = (((by >> 4) ^ sw) << 4) | (by & 15);
     }
+    wro[b] = S::W0 + row * U * 16 + o;
+  }
   const uint32_t* szs = reinterpret_cast<const uint32_t*>(smem + S::SZ0) + (wn * BF * 16 + n) * 8 + kg;
 
   // segments: the block that holds a segment's last kept columns arrives with the next segment's first ones (or the next
@@ -343,30 +337,25 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
   typedef RawCodes<BITS, T> Raw;
   struct Group { Raw raw[BF]; uint32_t sz[BF]; };
   auto sz_at = [&](int it) { return ((it / SPW) & 1) * (BN * 8) + (it % SPW) * G; };   // of slab `it`, in words
-  auto read_group = [&](const unsigned char* sl, int sz, int g, Group& o) {   // sl: smem + offset of the slab's codes; sz: sz_at of it
+  auto read_group = [&](const unsigned char* sl, int sz, Group& o) {   // sl: smem + offset of the slab's codes; sz: sz_at of it
 #pragma unroll
     for (int b = 0; b < BF; ++b) {
       if constexpr (BITS == 8) {
-        // a slot is two units of 16 bytes: both, one or half of one
-        if constexpr (T == 1) {
-          const u32x2_t v = *reinterpret_cast<const u32x2_t*>(sl + wro[b][g]);
-          o.raw[b].w[0] = v.x; o.raw[b].w[1] = v.y;
-        } else {
+        // a slot is two units of 16 bytes: both or one
 #pragma unroll
-          for (int h = 0; h < T / 2; ++h) {
-            const uint4 v = *reinterpret_cast<const uint4*>(sl + (wro[b][g] ^ (16 * h)));
-            o.raw[b].w[4 * h] = v.x; o.raw[b].w[4 * h + 1] = v.y; o.raw[b].w[4 * h + 2] = v.z; o.raw[b].w[4 * h + 3] = v.w;
-          }
+        for (int h = 0; h < T / 2; ++h) {
+          const uint4 v = *reinterpret_cast<const uint4*>(sl + (wro[b] ^ (16 * h)));
+          o.raw[b].w[4 * h] = v.x; o.raw[b].w[4 * h + 1] = v.y; o.raw[b].w[4 * h + 2] = v.z; o.raw[b].w[4 * h + 3] = v.w;
         }
       } else {
-        o.raw[b] = read_codes<BITS, T>(sl + wro[b][g], kq);
+        o.raw[b] = read_codes<BITS, T>(sl + wro[b], kq);
       }
-      o.sz[b] = szs[sz + b * (16 * 8) + g * KG];
+      o.sz[b] = szs[sz + b * (16 * 8)];
     }
   };
-  auto read_a = [&](const unsigned char* sl, int g, int t, uint4 (&o)[AF]) {
+  auto read_a = [&](const unsigned char* sl, int t, uint4 (&o)[AF]) {
 #pragma unroll
-    for (int f = 0; f < AF; ++f) o[f] = *reinterpret_cast<const uint4*>(sl + xoff[t] + (f * (16 * 16 * G) + g * (KG * 16)) * 16);
+    for (int f = 0; f < AF; ++f) o[f] = *reinterpret_cast<const uint4*>(sl + xoff[t] + f * (16 * 16 * G) * 16);
   };
   auto constants = [&](auto wide_form, const Group& r, CodeGroup<BITS, BF16> (&o)[BF]) {
 #pragma unroll
@@ -385,16 +374,14 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
     for (int b = 0; b < BF; ++b) largest = max(largest, r.sz[b] << 17);   // magnitude of the scale
     return __builtin_amdgcn_ballot_w64(largest >= kScaleWide << 17) != 0;
   };
-  // cur: the group whose operands are being unpacked; ahead: with T > 1 the next group, with T = 1 the two after the
-  // current one take turns
-  Group cur, ahead[2];
+  // the group whose operands are being unpacked, and the next slab's
+  Group cur, ahead;
   CodeGroup<BITS, BF16> gq[BF];
   uint4 av[2][AF], wf[2][BF];
   pipe_barrier();                         // slabs 0 and 1 are in LDS
   const unsigned char *xsl = smem, *wsl = smem;
-  read_group(wsl, 0, 0, cur);
-  read_a(xsl, 0, 0, av[0]);
-  if constexpr (T == 1) read_group(wsl, 0, 1, ahead[1]);
+  read_group(wsl, 0, cur);
+  read_a(xsl, 0, av[0]);
   int xb = 1, wb = 1, it = 0, sz = sz_at(1);
   const unsigned char *xnext = smem + S::XBytes, *wnext = smem + S::WBytes;
   // Slabs from `it` on.  The usual form of the bfloat16 unpack leaves at the first slab of which a scale asks for the wide form,
@@ -406,17 +393,11 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
     int end = nslab;
     while (it < end) {
 #pragma unroll
-      for (int s = 0; s < GW * T; ++s) {
-        const int g = s / T, t = s % T, s1 = (s + 1) % (GW * T), p = s & 1;
-        read_a(s1 ? xsl : xnext, s1 / T, s1 % T, av[p ^ 1]);
+      for (int t = 0; t < T; ++t) {
+        const int p = t & 1;
+        read_a(t + 1 < T ? xsl : xnext, (t + 1) % T, av[p ^ 1]);
         __builtin_amdgcn_sched_barrier(0);   // (activations first: the products wait for them)
-        if constexpr (T == 1) {
-          if (s + 2 < GW) read_group(wsl, sz_at(it), s + 2, ahead[p]);
-          else read_group(wnext, sz, s + 2 - GW, ahead[p]);
-        } else if (t == 0) {
-          if (g + 1 < GW) read_group(wsl, sz_at(it), g + 1, ahead[0]);
-          else read_group(wnext, sz, 0, ahead[0]);
-        }
+        if (t == 0) read_group(wnext, sz, ahead);
         __builtin_amdgcn_sched_barrier(0);   // (or the compiler moves the reads behind the products to save registers)
         if constexpr (SEG) {
 #pragma unroll
@@ -425,7 +406,7 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
             v.x &= mask[t].x; v.y &= mask[t].y; v.z &= mask[t].z; v.w &= mask[t].w;
           }
         }
-        if (s == GW * T - 1) {
+        if (t == T - 1) {
           // where the next slab's reads go, here and not behind the barrier (3 % with 64 x 64 tiles)
           xsl = xnext;
           wsl = wnext;
@@ -434,9 +415,7 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
           xnext = smem + xb * S::XBytes;
           wnext = smem + wb * S::WBytes;
           sz = sz_at(++it + 1);
-        }
-        if (t == T - 1) {
-          cur = ahead[T == 1 ? p ^ 1 : 0];
+          cur = ahead;
           if constexpr (BF16 && !decltype(wide_form)::value) end = asks_wide(cur) ? 0 : nslab;
           constants(wide_form, cur, gq);
         }
@@ -446,7 +425,7 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
 #pragma unroll
           for (int f = 0; f < AF; ++f) acc[f][b] = mfma_16x16x32<BF16>(wf[p][b], av[p][f], acc[f][b]);
         // products and unpacking in turns
-        constexpr int kVec = (BF * (BITS == 6 ? 20 : 17) + (T == 1 ? 8 * BF : 0) + (SEG ? 4 * AF : 0) + AF * BF - 1) / (AF * BF);
+        constexpr int kVec = (BF * (BITS == 6 ? 20 : 17) + (SEG ? 4 * AF : 0) + AF * BF - 1) / (AF * BF);
 #pragma unroll
         for (int i = 0; i < AF * BF; ++i) {
           __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);      // matrix instruction
@@ -465,7 +444,6 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
   };
   if (!BF16 || !asks_wide(cur)) slabs(std::false_type());
   if constexpr (BF16) {
-    static_assert(GW == 1, "a wave leaves between two groups");
     if (__builtin_expect(it < nslab, 0)) slabs(std::true_type());
   }
 
@@ -489,26 +467,19 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
         if (rc + v < km.n_keep) y[v] = __builtin_bit_cast(half_t, o[v]);
     }
   };
-  if constexpr (KS == 1) {
+  // partial sums through LDS (nobody reads or moves slabs any more): fragment q = f BF + b of a row position is added up
+  // over the KS waves in order and stored by wave q % KS of them
+  float4_t* red = reinterpret_cast<float4_t*>(smem);
 #pragma unroll
-    for (int f = 0; f < AF; ++f)
+  for (int f = 0; f < AF; ++f)
 #pragma unroll
-      for (int b = 0; b < BF; ++b) store(f, b, acc[f][b]);
-  } else {
-    // partial sums through LDS (nobody reads or moves slabs any more): fragment q = f BF + b of a row position is added up
-    // over the KS waves in order and stored by wave q % KS of them
-    float4_t* red = reinterpret_cast<float4_t*>(smem);
+    for (int b = 0; b < BF; ++b) red[((wk * WN + wn) * AF * BF + f * BF + b) * 64 + lane] = acc[f][b];
+  pipe_barrier();
+  for (int q = wk; q < AF * BF; q += KS) {
+    float4_t s = red[(wn * AF * BF + q) * 64 + lane];
 #pragma unroll
-    for (int f = 0; f < AF; ++f)
-#pragma unroll
-      for (int b = 0; b < BF; ++b) red[((wk * WN + wn) * AF * BF + f * BF + b) * 64 + lane] = acc[f][b];
-    pipe_barrier();
-    for (int q = wk; q < AF * BF; q += KS) {
-      float4_t s = red[(wn * AF * BF + q) * 64 + lane];
-#pragma unroll
-      for (int k2 = 1; k2 < KS; ++k2) s += red[((k2 * WN + wn) * AF * BF + q) * 64 + lane];
-      store(q / BF, q % BF, s);
-    }
+    for (int k2 = 1; k2 < KS; ++k2) s += red[((k2 * WN + wn) * AF * BF + q) * 64 + lane];
+    store(q / BF, q % BF, s);
   }
 #endif
 }
