@@ -1,6 +1,7 @@
 """GPU parity of the matrix kernel whose loads run in waves of their own (csrc/pipe_kernel.h) through the C ABI: every code
-width, the edges of its token and row tiles and of its three ways to split K, ragged columns, column segments, against the
-CPU oracle; single weights bit for bit; the same bits alone and in a shared launch."""
+width, its three ways to split K at small sizes (tests/test_gpu_pipe_tiles.py has every tile), ragged columns, column segments,
+against the CPU oracle; single weights bit for bit; the same bits alone and in a shared launch.  Few rows of 8, 6 or 3 bits at few
+tokens run the streaming kernels."""
 import numpy as np
 import pytest
 
@@ -41,7 +42,7 @@ def oracle_linear(uref, bits, w, x, keep, fmt, rows=None):
     return uref.wq_linear(bits, w["qweight"], w["scales"], w["zeros"], x, keep, fmt=fmt, rows=rows)
 
 
-# (stored rows, stored columns, rule): rows around the tiles of 32..192 rows, 8..11 groups (whole and partial slabs of one,
+# (stored rows, stored columns, rule): rows around multiples of 32 and 64, 8..11 groups (whole and partial slabs of one,
 # two and four groups, windows of scales that end inside the row), columns that end inside a block of eight, segments
 SHAPES = [
     (129, 1024, Keep()),
@@ -53,7 +54,8 @@ SHAPES = [
 ]
 
 
-# tokens: both ends of every token tile (16, 32, 48, 64, 96, 112, 128) and one more
+# tokens around 16, 32, 48, 64, 96, 112 and 128.  So few rows take the smallest tiles: 16 or 32 tokens x 32 rows up to 64 tokens (or
+# what else serves them), 64 x 64 above
 @pytest.mark.parametrize("bits", [4, 8, 6, 3])
 @pytest.mark.parametrize("fmt", ["f16", "bf16"])
 @pytest.mark.parametrize("M", [2, 16, 17, 33, 48, 64, 65, 96, 113, 129])

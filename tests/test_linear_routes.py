@@ -98,3 +98,18 @@ def test_grids_hold_the_largest_calls(N, K, keep, M, bits):
         assert -(-N // bn) * -(-M // bm) * 768 < 2 ** 32
     elif kernel == TILED:
         assert -(-M // bm) <= 65535
+
+
+# the sizes of the GPU parity tests take every tile that the pipelined kernel is built with
+@pytest.mark.parametrize("segments", [False, True])
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("bits", [4, 8, 6, 3])
+def test_parity_sizes_take_every_tile(bits, bf16, segments):
+    import pipe_shapes as ps
+    seen = set()
+    for i, (N, K, M) in enumerate(ps.SIZES):
+        choice = uq.uniql_w4_linear_kernel(N, K, ps.keep_rule(N, K, segments), M, bits=bits, bf16=bf16,
+                                           ldx=ps.kept_columns(K, segments) + i % 3)
+        if choice[0] == PIPE:
+            seen.add(choice[1:])
+    assert seen == ps.tiles(bits, segments)
