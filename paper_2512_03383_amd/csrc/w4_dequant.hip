@@ -17,8 +17,9 @@ namespace uniql {
 // A word's eight columns are written at once when all are kept; the word that holds the last kept columns of the row or of a
 // segment, and column rules whose segments are not whole words, go element by element.
 template <bool BF16, int U, int CL, bool NARROW>
-__global__ __launch_bounds__(256) void w4_dequant_kernel(LinearArgs a, int lanes_log2) {
+__global__ __launch_bounds__(256) void w4_dequant_kernel(LinearArgs a, int lanes_log2, int row_step, int part_step) {
   constexpr int CH = 1 << CL;             // chunks of a row per turn
+  constexpr bool one_row = CH == U && !NARROW;
   static_assert(CH <= U && (!NARROW || CL == 0), "whole rows per turn");
   const KeepMap& km = a.km;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -29,16 +30,17 @@ __global__ __launch_bounds__(256) void w4_dequant_kernel(LinearArgs a, int lanes
   const bool whole_words = km.cs_stride % 8 == 0;   // (a prefix: stride 0)
   const int ll = NARROW ? lanes_log2 : 6, lane_row = lane >> ll, lane_word = lane & ((1 << ll) - 1);
   const int turn_rows = (U >> CL) << (6 - ll);
-  // the walk over rows, and over the turns of a long row
-  for (long long r0 = ((long long)blockIdx.x * 4 + wave) * turn_rows; r0 < km.n_keep; r0 += (long long)gridDim.x * 4 * turn_rows)
-    for (int part0 = (int)blockIdx.y * CH; part0 * 64 < words_span; part0 += (int)gridDim.y * CH) {
+  // the walk over rows, and over the turns of a long row (by steps that come with the other arguments: the grid's size would be a
+  // load of its own on the way to the first word)
+  for (long long r0 = ((long long)blockIdx.x * 4 + wave) * turn_rows; r0 < km.n_keep; r0 += row_step)
+    for (int part0 = (int)blockIdx.y * CH; part0 * 64 < words_span; part0 += part_step) {
       uint32_t word[U], sb[U], zb[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         // (a row or word past the last one reads the last one)
         const long long rc = r0 + ((u >> CL) << (6 - ll)) + (NARROW ? lane_row : 0);
         const int w = min((part0 + u % CH) * 64 + lane_word, words_span - 1);
-        const size_t row = (size_t)stored_row(km, rc < km.n_keep ? (int)rc : km.n_keep - 1);
+        const size_t row = (size_t)stored_row(km, one_row || rc < km.n_keep ? (int)rc : km.n_keep - 1);
         // w counts words in column order; a head-interleaved row stores word (h, d / 8) at (d / 8) * H + h
         int ws = w;
         if (a.il_heads > 0) {
@@ -53,7 +55,11 @@ __global__ __launch_bounds__(256) void w4_dequant_kernel(LinearArgs a, int lanes
       for (int u = 0; u < U; ++u) {
         const long long rc = r0 + ((u >> CL) << (6 - ll)) + (NARROW ? lane_row : 0);
         const int w = (part0 + u % CH) * 64 + lane_word;
-        if (rc >= km.n_keep || w >= words_span) continue;
+        if (one_row) {
+          if (w >= words_span) break;
+        } else if (rc >= km.n_keep || w >= words_span) {
+          continue;
+        }
         const float s = in16<BF16>(__builtin_bit_cast(half_t, (uint16_t)sb[u]));
         const int z = (int)zb[u];
         uint16_t o[8];
@@ -96,7 +102,8 @@ static hipError_t launch_dequant_cfg(const LinearArgs& a, int lanes_log2, hipStr
   long long x = (((long long)a.km.n_keep + turn_rows - 1) / turn_rows + 3) / 4, y = (chunks + (1 << CL) - 1) >> CL;
   if (x > 65536) x = 65536;
   if (y > 65535) y = 65535;
-  hipLaunchKernelGGL((w4_dequant_kernel<BF16, U, CL, NARROW>), dim3((unsigned)x, (unsigned)y), dim3(256), 0, stream, a, lanes_log2);
+  hipLaunchKernelGGL((w4_dequant_kernel<BF16, U, CL, NARROW>), dim3((unsigned)x, (unsigned)y), dim3(256), 0, stream, a, lanes_log2,
+                     (int)x * 4 * turn_rows, (int)y << CL);
   return hipGetLastError();
 }
 
