@@ -6,16 +6,21 @@ namespace uniql {
 
 // Ways to split K over the waves of a block.  The way decides the order of the sums, so it follows from the linear alone,
 // never from what it shares a launch with: a linear gives the same bits in a batch and by itself.
-//  kPipeGroups : four groups of a slab at a time (KG = 4): up to 32 tokens, and 33..64 on matrices of fewer than 400 row
-//                tiles (32 x 32 tiles give those the most blocks: 656 x 4096 at 48 tokens 8.7 us, 13.6 us in the next way)
+//  kPipeGroups : four groups of a slab at a time (KG = 4): up to 32 tokens, and 33..64 on matrices that one round of its tiles of 32
+//                tokens takes: 512 row tiles with codes of 3 bits (64-row tiles), 256 with 8 and 6 (32-row ones)
 //  kPipeMixed  : two groups, two halves of their steps (KG = KQ = 2): 33..64 tokens, taller matrices (64 or 96 rows x all
-//                tokens: 9318 x 4096 at 48 tokens 15.0 us, 22.4 us in the way before)
+//                tokens)
 //  kPipeHalves : two halves of a group's steps (KQ = 2): more tokens, 128 x 128 tiles and smaller ones
+// 4096 columns at 40 tokens, groups / mixed, with 256, 300, 512, 592 row tiles: 3 bits 11.2 / 16.2, 14.7 / 16.4, 14.9 / 16.5,
+// 26.4 / 16.7 us; 8 bits 10.8 / 15.2, 18.4 / 15.3, 18.4 / 15.7, 26.0 / 16.1; 4 bits 10.3 / 14.3, 12.8 / 14.5, 12.9 / 14.5,
+// 22.8 / 14.8.  4 bits change over at 400: such matrices share launches (gate and up, q with k and v), and two of 400..512 row tiles
+// are two rounds of the one and one round of the other.
 enum PipeWay { kPipeGroups, kPipeMixed, kPipeHalves };
 
 static inline PipeWay pipe_way(const LinearArgs& a) {
   if (a.M > 64) return kPipeHalves;
-  return a.M > 32 && (a.km.n_keep + 15) / 16 >= 400 ? kPipeMixed : kPipeGroups;
+  const int tall = a.bits == 4 ? 400 : a.bits == 3 ? 513 : 257;   // row tiles
+  return a.M > 32 && (a.km.n_keep + 15) / 16 >= tall ? kPipeMixed : kPipeGroups;
 }
 
 // Outputs that a launch of the pipelined kernel reaches with its largest tiles (96 tokens x 128 rows and more, 768 threads each: the

@@ -4,7 +4,7 @@ from paper_2512_03383_amd import KeepDesc
 # (rows, stored columns, tokens): ragged in each; enough groups that every ring of slabs goes round (9 slabs of four groups, 17 of two,
 # 17 of one)
 SIZES = [(6410, 4224, 11), (8300, 4224, 11), (6410, 4224, 19), (8300, 4224, 19), (3000, 4224, 13), (3000, 4224, 27),
-         (6410, 4224, 37), (16500, 4224, 37), (6410, 4224, 51), (16500, 4224, 51),
+         (6410, 4224, 37), (8300, 4224, 37), (16500, 4224, 37), (6410, 4224, 51), (8300, 4224, 51), (16500, 4224, 51),
          (300, 2176, 67), (8300, 2176, 67), (11000, 2176, 67), (16500, 2176, 67), (16500, 2176, 101), (16500, 2176, 127), (5101, 2176, 333)]
 
 

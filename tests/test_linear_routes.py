@@ -113,3 +113,12 @@ def test_parity_sizes_take_every_tile(bits, bf16, segments):
         if choice[0] == PIPE:
             seen.add(choice[1:])
     assert seen == ps.tiles(bits, segments)
+
+
+# 33..64 tokens of 8, 6 and 3 bits: K over four groups while one round of those tiles takes the matrix, then 64 or 96 rows x all tokens
+@pytest.mark.parametrize("bits,last", [(8, 256), (6, 256), (3, 512)])
+def test_height_at_which_wide_codes_change_their_split(bits, last):
+    for K in (2560, 4096):
+        for M in (40, 64):
+            assert uq.uniql_w4_linear_kernel(16 * last, K, None, M, bits=bits)[1] == 32
+            assert uq.uniql_w4_linear_kernel(16 * last + 1, K, None, M, bits=bits)[1] in (48, 64)
