@@ -13,7 +13,7 @@ namespace uniql {
 // of at most 32 words (NARROW) share chunks: 1 << lanes_log2 lanes each.
 // 10752 x 4096 kept: 24.4 us with eight chunks in flight (four 24.9, two 28.9; a thread per word of the whole matrix with eight 2-byte
 // stores 62).  A wave to a row whatever its length left lanes idle on narrow rows and the chip on few long ones:
-// 343750 x 128 102 us, so 24.4, 13 x 18944 11.9, so 3.5.
+// 343750 x 128 102 us, so 24.4, 13 x 18944 11.9, so 3.5 (from graphs over six copies of the matrix; 10752 x 4096 in that way 20).
 // A word's eight columns are written at once when all are kept; the word that holds the last kept columns of the row or of a
 // segment, and column rules whose segments are not whole words, go element by element.
 template <bool BF16, int U, int CL, bool NARROW>

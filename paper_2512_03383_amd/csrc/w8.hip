@@ -9,8 +9,8 @@
 // subtraction of 1024 + z is exact and the fp16 multiply by s rounds once; the pair meets (x0, x2) in one
 // two-element dot product with fp32 accumulation (the activations are staged in that order).  bfloat16: the weight is
 // formed in fp32 (q s - z s, exact) and rounded by the packed conversion.  One launch serves one token per block row
-// (grid.y = tokens).  Several tokens come here only where pipe_serves.h says no (short rows, unusual segments): they
-// re-read the weights through L2.
+// (grid.y = tokens).  Several tokens come here only where pipe_serves.h says so (short rows, unusual segments, few rows, two or
+// three tokens): they re-read the weights through L2.
 #include "common.h"
 
 namespace uniql {

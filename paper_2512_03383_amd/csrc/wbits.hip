@@ -15,7 +15,7 @@
 // (x_p, x_{p + C/2}) in one two-element dot product with fp32 accumulation (the activations are staged in that order,
 // 16 bytes = four pairs per piece, piece-major so that the 64 lanes of a wave read consecutive pieces).  bfloat16: the
 // weight is formed in fp32 (q s - z s, exact) and rounded by the packed conversion.  One launch serves one token per
-// block row (grid.y = tokens); several tokens come here only where pipe_serves.h says no and re-read the weights through L2.
+// block row (grid.y = tokens); several tokens come here only where pipe_serves.h says so and re-read the weights through L2.
 #include "common.h"
 
 namespace uniql {
