@@ -33,6 +33,8 @@ static inline PipeTile pipe_pick(const LinearArgs* p, int n) {
   // groups: 32- and 64-row tiles; mixed: 64- and 96-row tiles (96 rows x 64 tokens do not fit with 8-bit codes);
   // halves: rows x tokens from 128 x 128 down to 64 x 64 (segments: no 128 tokens, the masks cost it its registers;
   // 8-bit codes: no 112, its buffers)
+  // (128 x 128 takes all of a wave's 168 registers: in bfloat16 one to four words go to scratch around the loop, none in it,
+  // and up to 18 in the loop of the wide unpack)
   static const PipeTile groups[] = {{1, 1, 2, 4, {0.50f, 0.05f}, {0.55f, 0.05f}, 0.f}, {1, 2, 2, 4, {0.90f, 0.05f}, {0.95f, 0.05f}, 0.f},
                                     {2, 1, 2, 4, {0.55f, 0.05f}, {0.65f, 0.05f}, 0.f}, {2, 2, 2, 4, {1.0f, 0.05f}, {1.05f, 0.05f}, 0.f}};
   static const PipeTile mixed[] = {{3, 2, 2, 2, {0.62f, 0.07f}, {0.70f, 0.05f}, 0.f}, {3, 3, 2, 2, {0.80f, 0.07f}, {0.90f, 0.05f}, 0.f},
