@@ -22,7 +22,9 @@ __global__ __launch_bounds__(256) void w4_dequant_kernel(LinearArgs a, int lanes
   constexpr bool one_row = CH == U && !NARROW;
   static_assert(CH <= U && (!NARROW || CL == 0), "whole rows per turn");
   const KeepMap& km = a.km;
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // a scalar wave number makes the addresses of several rows scalar (114583 x 384: 24.8 us, 27.8 from vectors); one row has a
+  // single base, and with that formed once per turn a vector is no slower (10752 x 4096, 25 % rate: 61.9 us with the whole step, so 61.7)
+  const int lane = threadIdx.x & 63, wave = one_row ? (int)(threadIdx.x >> 6) : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int words_span = (km.k_span + 7) >> 3;
   const int words_per_row = a.K_total >> 3;
   const int groups_per_row = a.K_total / kGroup;
@@ -35,12 +37,13 @@ __global__ __launch_bounds__(256) void w4_dequant_kernel(LinearArgs a, int lanes
   for (long long r0 = ((long long)blockIdx.x * 4 + wave) * turn_rows; r0 < km.n_keep; r0 += row_step)
     for (int part0 = (int)blockIdx.y * CH; part0 * 64 < words_span; part0 += part_step) {
       uint32_t word[U], sb[U], zb[U];
+      const size_t row1 = one_row ? (size_t)stored_row(km, (int)r0) : 0;   // of the whole turn
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         // (a row or word past the last one reads the last one)
         const long long rc = r0 + ((u >> CL) << (6 - ll)) + (NARROW ? lane_row : 0);
         const int w = min((part0 + u % CH) * 64 + lane_word, words_span - 1);
-        const size_t row = (size_t)stored_row(km, one_row || rc < km.n_keep ? (int)rc : km.n_keep - 1);
+        const size_t row = one_row ? row1 : (size_t)stored_row(km, rc < km.n_keep ? (int)rc : km.n_keep - 1);
         // w counts words in column order; a head-interleaved row stores word (h, d / 8) at (d / 8) * H + h
         int ws = w;
         if (a.il_heads > 0) {
