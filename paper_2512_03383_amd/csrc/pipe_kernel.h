@@ -58,6 +58,14 @@ struct PipeShape {
   static_assert(kPipeConsumers * AF * BF * 1024 <= Lds, "so do the partial sums");
 };
 
+// What the place of a 16-byte unit in LDS is permuted by, from its token or row.  A 128-bit LDS read serves 16 lanes a clock, and
+// these are not 16 consecutive ones: 0-3, 12-15 and 20-27 go together, then 4-11, 16-19 and 28-31 (likewise from lane 32 on).  Lane
+// l of a fragment reads row l % 16, chunk 4 (l / 16) + t, so rows 0-3 and 12-15 of one chunk share a clock with rows 4-11 of the
+// chunk four further on: under r % 16 alone each of these meets one of the former in its bank group (SQ_LDS_BANK_CONFLICT was
+// half of the LDS's busy clocks, which were half of all: 8-bit gate at 512 tokens).  With bit 2 of the row added to bit 3 the
+// rows that share a clock differ in that bit.
+__device__ __forceinline__ int bank_key(int row) { return (row ^ (row << 1 & 8)) & 15; }
+
 __device__ __forceinline__ void pipe_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
@@ -147,7 +155,7 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
         constexpr int CH = 16 * G;                       // chunks per token
         const int v = (d + kPipeMovers * k) * 64;
         const int tok = v / CH + (CH < 64 ? lane / CH : 0);
-        const int c = (CH <= 64 ? lane % CH : v % CH + lane) ^ (tok & 15);
+        const int c = (CH <= 64 ? lane % CH : v % CH + lane) ^ bank_key(tok);
         const int g = slab * G + c / 16, k0 = (c % 16) * 8;   // group, column in it
         int col = g * kpg + k0;
         bool there = g * kGroup + k0 < km.k_keep;        // a prefix: its last block comes with what lies behind it
@@ -192,7 +200,7 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
         for (int i = 0; i < TI; ++i) {
           const int t = lane + 64 * i;
           if (t >= BM || (t * G / 4) % kPipeMovers != d) continue;
-          uint4* p = reinterpret_cast<uint4*>(smem + (nslab - 1) % NX * S::XBytes) + t * (16 * G) + (c ^ (t & 15));
+          uint4* p = reinterpret_cast<uint4*>(smem + (nslab - 1) % NX * S::XBytes) + t * (16 * G) + (c ^ bank_key(t));
           uint4 v = *p;
           v.x = (v.x & m(0)) | (tail == 1 ? odd[i] : 0u);
           v.y = (v.y & m(2)) | (tail == 3 ? odd[i] : 0u);
@@ -211,7 +219,7 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
       for (int k = 0; k < S::WI; ++k) {
         const int v = k * 64 + lane, row = v / U, j = v - row * U;
         int js = j;
-        if constexpr ((U & (U - 1)) == 0) js = U >= 16 ? j ^ (row & 15) : j ^ ((row / (U < 16 ? 16 / U : 1)) & (U - 1));
+        if constexpr ((U & (U - 1)) == 0) js = j ^ (bank_key(row) / (U < 16 ? 16 / U : 1));
         int rc = n0 + row;
         rc = rc < km.n_keep ? rc : km.n_keep - 1;       // (rows past the last one: a valid, unused load)
         woff[k] = stored_row(km, rc) * row_bytes + js * 16;
@@ -303,7 +311,7 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
   // LDS byte offsets inside a slab: activations of the wave's step t of its first group (token n), codes of its slots
   int xoff[T], wro[BF];
 #pragma unroll
-  for (int t = 0; t < T; ++t) xoff[t] = (n * (16 * G) + kg * 16 + ((ks * 4 + kq * T + t) ^ n)) * 16;
+  for (int t = 0; t < T; ++t) xoff[t] = (n * (16 * G) + kg * 16 + ((ks * 4 + kq * T + t) ^ bank_key(n))) * 16;
 #pragma unroll
   for (int b = 0; b < BF; ++b) {
     const int row = (wn * BF + b) * 16 + n, byte = kg * (16 * BITS) + ks * (4 * BITS);   // of the row's codes in the slab
@@ -311,7 +319,7 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
     if constexpr ((U & (U - 1)) == 0) {
       // (8 bits: a slot is two units and the permutation may swap them, so the window's own unit is addressed)
       const int by = byte + (BITS == 8 ? kq * (T * BITS) : 0);
-      const int sw = U >= 16 ? row & 15 : (row / (U < 16 ? 16 / U : 1)) & (U - 1);
+      const int sw = bank_key(row) / (U < 16 ? 16 / U : 1);
       o = (((by >> 4) ^ sw) << 4) | (by & 15);
     }
     wro[b] = S::W0 + row * U * 16 + o;
