@@ -31,17 +31,16 @@ struct PipeTile {
 template <int BITS>
 static inline PipeTile pipe_pick(const LinearArgs* p, int n) {
   // groups: 32- and 64-row tiles; mixed: 64- and 96-row tiles (96 rows x 64 tokens do not fit with 8-bit codes);
-  // halves: rows x tokens from 128 x 128 down to 64 x 64 (segments: no 128 tokens, the masks cost it its registers;
-  // 8-bit codes: no 112, its buffers)
+  // halves: rows x tokens from 128 x 128 down to 64 x 64 (8-bit codes: no 112, its buffers)
   // (128 x 128 takes all of a wave's 168 registers: in bfloat16 one to four words go to scratch around the loop, none in it,
   // and up to 18 in the loop of the wide unpack)
   static const PipeTile groups[] = {{1, 1, 2, 4, {0.50f, 0.05f}, {0.55f, 0.05f}, 0.f}, {1, 2, 2, 4, {0.90f, 0.05f}, {0.95f, 0.05f}, 0.f},
                                     {2, 1, 2, 4, {0.55f, 0.05f}, {0.65f, 0.05f}, 0.f}, {2, 2, 2, 4, {1.0f, 0.05f}, {1.05f, 0.05f}, 0.f}};
   static const PipeTile mixed[] = {{3, 2, 2, 2, {0.62f, 0.07f}, {0.70f, 0.05f}, 0.f}, {3, 3, 2, 2, {0.80f, 0.07f}, {0.90f, 0.05f}, 0.f},
                                    {4, 2, 2, 2, {0.73f, 0.07f}, {0.85f, 0.05f}, 0.f}, {4, 3, 2, 2, {0.93f, 0.07f}, {1.05f, 0.05f}, 0.f}};
-  static const PipeTile halves[] = {{8, 2, 4, 1, {1.0f, 0.15f}, {0.f, 0.f}, 0.f}, {7, 2, 4, 1, {0.93f, 0.12f}, {1.0f, 0.13f}, 0.f},
-                                    {6, 2, 4, 1, {0.85f, 0.07f}, {0.95f, 0.12f}, 0.f}, {4, 2, 4, 1, {0.56f, 0.15f}, {0.62f, 0.22f}, 0.f},
-                                    {4, 1, 4, 1, {0.33f, 0.09f}, {0.39f, 0.08f}, 0.f}};
+  static const PipeTile halves[] = {{8, 2, 4, 1, {1.0f, 0.15f}, {0.82f, 0.22f}, 0.f}, {7, 2, 4, 1, {0.93f, 0.12f}, {0.76f, 0.12f}, 0.f},
+                                    {6, 2, 4, 1, {0.85f, 0.07f}, {0.71f, 0.09f}, 0.f}, {4, 2, 4, 1, {0.56f, 0.15f}, {0.58f, 0.07f}, 0.f},
+                                    {4, 1, 4, 1, {0.33f, 0.09f}, {0.33f, 0.04f}, 0.f}};
   const PipeWay way = pipe_way(p[0]);
   const bool seg = p[0].km.cs_stride != 0;
   const PipeTile* set = way == kPipeGroups ? groups : way == kPipeMixed ? mixed : halves;
@@ -56,7 +55,7 @@ static inline PipeTile pipe_pick(const LinearArgs* p, int n) {
     if (way == kPipeMixed && t.af != (M <= 48 ? 3 : 4)) continue;
     if (BITS > 4 && way != kPipeGroups && ((t.af == 4 && t.bf == 3) || t.af == 7)) continue;
     if (BITS > 4 && way == kPipeGroups && t.bf == 2) continue;
-    if (seg && t.seg.us == 0.f) continue;
+    if (seg && t.af == 8 && M <= 384) continue;   // (up to three token tiles the smaller ones leave less of the last one empty)
     long long tiles = 0;
     for (int i = 0; i < n; ++i) tiles += (p[i].km.n_keep + t.wn * t.bf * 16 - 1) / (t.wn * t.bf * 16);
     tiles *= (M + 16 * t.af - 1) / (16 * t.af);
@@ -97,9 +96,7 @@ static hipError_t pipe_run(const LinearArgs* p, int n, hipStream_t s) {
       }
       return pipe_tile<4, 2, 2, 2, 2, 2, 3, BITS, BF16, SEG>(p, n, s);
     default:
-      if constexpr (!SEG) {
-        if (t.af == 8) return pipe_tile<8, 2, 4, 1, 2, 1, 3, BITS, BF16, SEG>(p, n, s);
-      }
+      if (t.af == 8) return pipe_tile<8, 2, 4, 1, 2, 1, 3, BITS, BF16, SEG>(p, n, s);
       if constexpr (BITS <= 4) {
         if (t.af == 7) return pipe_tile<7, 2, 4, 1, 2, 1, 4, BITS, BF16, SEG>(p, n, s);
       }

@@ -117,8 +117,9 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
     lds_byte* const lds = (lds_byte*)smem;
     // A mover's walk: slabs 0 .. N - 2 to begin with, then, one barrier per slab, the slab that takes the buffer which
     // everybody has left.  Before barrier `it` the slabs up to it + 1 have landed.  Before barrier `extra_at` (the one that
-    // publishes the last slab, or -1 for none) the mover does something more.
-    auto walk = [&](auto n, auto per, auto&& move, int extra_at, auto&& extra) {
+    // publishes the last slab, or -1 for none) the mover does something more; with column segments it does `landed` for every slab
+    // before the barrier that publishes it.
+    auto walk = [&](auto n, auto per, auto&& move, int extra_at, auto&& extra, auto&& landed) {
       constexpr int N = decltype(n)::value, PER = decltype(per)::value;
 #pragma unroll
       for (int p = 0; p < N - 1; ++p)
@@ -131,6 +132,10 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
           // (the last slabs; `extra` is asked for here only: on the way from the wait to the barrier it costs 3 % at NX = 3)
           asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
           if (it == extra_at) extra();
+        }
+        if constexpr (SEG) {
+          if (it == 0) landed(0);
+          landed(it + 1);
         }
         pipe_barrier();
         if (it + N - 1 < nslab) move(it + N - 1, buf);
@@ -151,6 +156,7 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
       // wholly in the row takes slab 0's offsets and a scalar (a load is then two instructions; a mover issues one
       // every 60 clocks otherwise).
       const int kpg = SEG ? (kGroup >> seg_shift) * km.cs_keep : kGroup;
+      const int partial = SEG ? km.cs_keep & 7 : 0, seg_log = 7 - seg_shift;   // columns in a segment's last block (even), segments of a group
       auto unit = [&](int k, int slab) {
         constexpr int CH = 16 * G;                       // chunks per token
         const int v = (d + kPipeMovers * k) * 64;
@@ -208,6 +214,24 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
           v.w = tail == 7 ? odd[i] : 0u;
           *p = v;
         }
+      }, [&](int slab) {
+        // Segments: the block that holds a segment's last kept columns arrives with the next segment's first ones (or the next
+        // token's) behind them, which are cleared here, in the mover's own tokens (masked in the registers of the eight waves
+        // that multiply, they were four vector instructions per activation fragment and step: 1000 x 4096 x 4096 in bfloat16, 108
+        // of 128 columns, 62 -> 41 us, and 128 tokens a tile did not fit the registers).
+        if constexpr (SEG) {
+          if (!partial || slab >= nslab) return;
+          unsigned char* const to = smem + slab % NX * S::XBytes;
+          constexpr int TU = 4 / G;                      // tokens per load
+          for (int i = lane; i < BM / 2 * G << seg_log; i += 64) {
+            const int sg = i & ((1 << seg_log) - 1), g = (i >> seg_log) % G, j = (i >> seg_log) / G;
+            const int t = (j / TU * kPipeMovers + d) * TU + j % TU, c = g * 16 + (sg << (seg_shift - 3)) + km.cs_keep / 8;
+            uint32_t* p = reinterpret_cast<uint32_t*>(to + (t * (16 * G) + (c ^ bank_key(t))) * 16);
+            if (partial == 2) p[1] = 0u;
+            if (partial <= 4) *reinterpret_cast<u32x2_t*>(p + 2) = u32x2_t{0u, 0u};
+            else p[3] = 0u;
+          }
+        }
       });
       return;
     }
@@ -235,7 +259,7 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
           for (int k = 0; k < S::WI; ++k)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_void*)(lds + S::W0 + buf * S::WBytes + k * 1024), 16, woff[k] + slab * (U * 16), 0, 0, 0);
         }
-      }, -1, []() {});
+      }, -1, []() {}, [](int) {});
       return;
     }
     // ---- scales and zero points: row lane (+ 64 p) of the block, windows of eight groups, scale | zero << 16.  The window
@@ -326,18 +350,6 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
   }
   const uint32_t* szs = reinterpret_cast<const uint32_t*>(smem + S::SZ0) + (wn * BF * 16 + n) * 8 + kg;
 
-  // segments: the block that holds a segment's last kept columns arrives with the next segment's first ones (or the next
-  // token's) behind them; the masks of the lane's blocks of a group
-  uint4 mask[SEG ? T : 1];
-  if constexpr (SEG) {
-#pragma unroll
-    for (int t = 0; t < T; ++t) {
-      const int k = km.cs_keep - (((ks * 4 + kq * T + t) * 8) & (km.cs_stride - 1));   // kept columns from the block's first one on
-      auto m = [&](int i) { return (k > i ? 0xffffu : 0u) | (k > i + 1 ? 0xffff0000u : 0u); };
-      mask[t] = make_uint4(m(0), m(2), m(4), m(6));
-    }
-  }
-
   // A step multiplies one unpacked operand per row fragment with AF activation fragments.  Meanwhile the operands of the next
   // step are unpacked between the products -- two waves share a SIMD and run in phase, so a wave that unpacks, then
   // multiplies, leaves the matrix pipe idle while it unpacks -- and the fragments of the next step and the codes of the
@@ -407,13 +419,6 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
         __builtin_amdgcn_sched_barrier(0);   // (activations first: the products wait for them)
         if (t == 0) read_group(wnext, sz, ahead);
         __builtin_amdgcn_sched_barrier(0);   // (or the compiler moves the reads behind the products to save registers)
-        if constexpr (SEG) {
-#pragma unroll
-          for (int f = 0; f < AF; ++f) {
-            uint4& v = av[p][f];
-            v.x &= mask[t].x; v.y &= mask[t].y; v.z &= mask[t].z; v.w &= mask[t].w;
-          }
-        }
         if (t == T - 1) {
           // where the next slab's reads go, here and not behind the barrier (3 % with 64 x 64 tiles)
           xsl = xnext;
@@ -433,7 +438,7 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
 #pragma unroll
           for (int f = 0; f < AF; ++f) acc[f][b] = mfma_16x16x32<BF16>(wf[p][b], av[p][f], acc[f][b]);
         // products and unpacking in turns
-        constexpr int kVec = (BF * (BITS == 6 ? 20 : 17) + (SEG ? 4 * AF : 0) + AF * BF - 1) / (AF * BF);
+        constexpr int kVec = (BF * (BITS == 6 ? 20 : 17) + AF * BF - 1) / (AF * BF);
 #pragma unroll
         for (int i = 0; i < AF * BF; ++i) {
           __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);      // matrix instruction
