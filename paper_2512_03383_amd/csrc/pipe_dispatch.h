@@ -60,7 +60,7 @@ static inline PipeTile pipe_pick(const LinearArgs* p, int n) {
     for (int i = 0; i < n; ++i) tiles += (p[i].km.n_keep + t.wn * t.bf * 16 - 1) / (t.wn * t.bf * 16);
     tiles *= (M + 16 * t.af - 1) / (16 * t.af);
     // (threads of a grid are counted in 32 bits; pipe_serves leaves the largest tiles below that)
-    t.us = tiles * kPipeThreads >= (1ll << 32) ? 1e30f : launch_cost(tiles, (float)((ngroups + t.g - 1) / t.g), seg ? t.seg : t.prefix, span > 8192 ? 1.18f : 1.f);
+    t.us = tiles * kPipeMostThreads >= (1ll << 32) ? 1e30f : launch_cost(tiles, (float)((ngroups + t.g - 1) / t.g), seg ? t.seg : t.prefix, span > 8192 ? 1.18f : 1.f);
     if (best.af == 0 || t.us < best.us) best = t;
   }
   return best;
@@ -101,7 +101,7 @@ static hipError_t pipe_run(const LinearArgs* p, int n, hipStream_t s) {
         if (t.af == 7) return pipe_tile<7, 2, 4, 1, 2, 1, 4, BITS, BF16, SEG>(p, n, s);
       }
       if (t.af == 6) return pipe_tile<6, 2, 4, 1, 2, 1, BITS <= 4 ? 4 : 3, BITS, BF16, SEG>(p, n, s);
-      return t.bf == 2 ? pipe_tile<4, 2, 4, 1, 2, 1, 6, BITS, BF16, SEG>(p, n, s) : pipe_tile<4, 1, 4, 1, 2, 1, 6, BITS, BF16, SEG>(p, n, s);
+      return t.bf == 2 ? pipe_tile<4, 2, 4, 1, 2, 1, BITS == 8 ? 4 : 6, BITS, BF16, SEG>(p, n, s) : pipe_tile<4, 1, 4, 1, 2, 1, 6, BITS, BF16, SEG>(p, n, s);
   }
 }
 

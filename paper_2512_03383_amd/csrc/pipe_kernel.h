@@ -1,11 +1,13 @@
 // Linears of more than a few tokens on MFMA for codes of 8, 6, 4 and 3 bits: y[M][n_keep] = x[M][k_keep] * W'^T, with the
 // loads in waves of their own.
 //
-// A block of twelve waves owns BN = WN * BF * 16 rows and BM = 16 AF tokens.  The columns go by in slabs of G groups; a slab
+// A block of twelve waves (fifteen, small tiles) owns BN = WN * BF * 16 rows and BM = 16 AF tokens.  The columns go by in slabs of G groups; a slab
 // is the block's activations and packed codes of those groups.
-//  - Two waves do nothing but move activations into LDS (128-bit loads that write LDS directly: no registers, no LDS
-//    instructions), up to NX - 1 slabs ahead, and a third one codes, NW - 1 slabs ahead: loads return in order, and codes
-//    come from memory where activations come from the L2.  The next slab is there one barrier early.
+//  - Two waves (four where the block's registers allow) do nothing but move activations into LDS (128-bit loads that write LDS
+//    directly: no registers, no LDS instructions), up to NX - 1 slabs ahead, and one more (two) codes, NW - 1 slabs ahead: loads
+//    return in order, and codes come from memory where activations come from the L2.  A mover issues a load every 60 clocks and a
+//    CU takes one every 17, so in tiles with little to multiply the moving is what a slab takes: 48 tokens, 35 % of the channels,
+//    148 us a pass of two decoder layers with three movers, 140 with six.  The next slab is there one barrier early (but see XLate).
 //  - One wave does the same for scales and zero points, eight groups of a row at a time, through registers.
 //  - Eight waves, WN along the rows times KG along the groups of a slab times KQ along the four steps of a group, read codes
 //    and activations from LDS, unpack in registers (codes.h) and multiply.  They never wait for memory, and the first
@@ -15,9 +17,9 @@
 // same time.  And a block's share of a packed row is fetched as contiguous runs (17 clocks of the address unit per KB)
 // instead of 16 rows per load (65 clocks).
 //
-// LDS layout: activations [token][16 G chunks of 8 columns], chunk c of token t at c ^ (t % 16); codes [row][units of 16
-// bytes], the units of a row permuted likewise where their number is a power of two: the 16 lanes of a fragment read 16
-// different bank groups.  Activations stay in memory order (codes.h gives the weights in that order).
+// LDS layout: activations [token][16 G chunks of 8 columns], chunk c of token t at c ^ bank_key(t); codes [row][units of 16
+// bytes], the units of a row permuted likewise where their number is a power of two: the 16 lanes that a 128-bit read serves in
+// one clock read 16 different bank groups.  Activations stay in memory order (codes.h gives the weights in that order).
 //
 // The partial sums of the KG x KQ waves meet in LDS and are added in order; within a wave sums run in order of the columns.  The
 // result depends on KG and KQ, not on AF, BF, WN, G, NX or NW.
@@ -30,8 +32,7 @@ namespace uniql {
 constexpr uint32_t kBufferWord3 = 0x00020000u;
 constexpr int kBeyond = (int)0x80000000u;   // as an unsigned offset: past the end of every resource below 2 GiB; reads zeros
 
-constexpr int kPipeConsumers = 8, kPipeMovers = 2;
-constexpr int kPipeThreads = (kPipeConsumers + kPipeMovers + 2) * kWave;
+constexpr int kPipeConsumers = 8;
 constexpr int kPipeDies = 8, kPipeTokTilesPerPass = 4;
 
 // Up to four linears with the same token count and format; tiles are numbered through the whole batch.
@@ -48,11 +49,14 @@ struct PipeShape {
   static constexpr int U = G * BITS;                           // 16-byte units of codes per row and slab
   static constexpr int XBytes = BM * G * 256, WBytes = BN * U * 16;
   static constexpr int XI = XBytes / 1024, WI = WBytes / 1024;   // loads of 64 x 16 bytes
-  static_assert(WBytes % 1024 == 0 && XI % kPipeMovers == 0, "whole loads, the same number for each mover");
-  static constexpr int XPW = XI / kPipeMovers;
+  static constexpr bool Small = AF * BF <= 9;
+  static constexpr int XM = Small ? 4 : 2, WM = Small && WI % 2 == 0 ? 2 : 1;   // waves that move activations, codes
+  static constexpr int Threads = (kPipeConsumers + XM + WM + 1) * kWave;
+  static_assert(WBytes % 1024 == 0 && XI % XM == 0, "whole loads, the same number for each mover");
+  static constexpr int XPW = XI / XM, WPW = WI / WM;
   static constexpr int SZ = 2 * BN * 8 * 4;                    // two windows of eight groups
   static constexpr int W0 = NX * XBytes, SZ0 = W0 + NW * WBytes, Lds = SZ0 + SZ;
-  static_assert((NX - 1) * XPW <= 63 && (NW - 1) * WI <= 63, "loads in flight are counted in six bits");
+  static_assert((NX - 1) * XPW <= 63 && (NW - 1) * WPW <= 63, "loads in flight are counted in six bits");
   static_assert(NX >= 3 && NW >= 3 && 8 % G == 0 && G <= 4, "a slab in use, one ready, one on its way; a window of scales is two slabs or more");
   static_assert(Lds <= 160 * 1024, "the slabs fit the LDS");
   static_assert(kPipeConsumers * AF * BF * 1024 <= Lds, "so do the partial sums");
@@ -71,10 +75,15 @@ __device__ __forceinline__ void pipe_barrier() {
 }
 
 template <int AF, int BF, int WN, int KG, int KQ, int G, int NX, int NW, int BITS, bool BF16, bool SEG>
-__global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
+__global__ __launch_bounds__((PipeShape<AF, BF, WN, KG, KQ, G, NX, NW, BITS>::Threads), (PipeShape<AF, BF, WN, KG, KQ, G, NX, NW, BITS>::Small ? 4 : 3)) void w_pipe_kernel(PipeBatch bt) {
 #ifdef __HIP_DEVICE_COMPILE__   // (the loads into LDS have no form in the host's pass)
   typedef PipeShape<AF, BF, WN, KG, KQ, G, NX, NW, BITS> S;
-  constexpr int BM = S::BM, BN = S::BN, U = S::U, KS = S::KS;
+  constexpr int BM = S::BM, BN = S::BN, U = S::U, KS = S::KS, XM = S::XM, WM = S::WM;
+  // A slab's activations land by the barrier before its use and not one earlier: its first fragments are then read behind that
+  // barrier (some 5 % of a slab), but with three or four buffers the loads have twice the time.  Small tiles wait for them
+  // otherwise, and so do segments, whose movers still clear columns (48 tokens x 4096 x 9318 18.1 -> 15 us, the attention block at 1000
+  // tokens 106 -> 103; prefixes in 96..128-token tiles 4 % the other way).
+  constexpr bool XLate = S::Small ? NX <= 4 : SEG && NX == 3;
   extern __shared__ __align__(16) unsigned char smem[];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -119,23 +128,23 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
     // everybody has left.  Before barrier `it` the slabs up to it + 1 have landed.  Before barrier `extra_at` (the one that
     // publishes the last slab, or -1 for none) the mover does something more; with column segments it does `landed` for every slab
     // before the barrier that publishes it.
-    auto walk = [&](auto n, auto per, auto&& move, int extra_at, auto&& extra, auto&& landed) {
-      constexpr int N = decltype(n)::value, PER = decltype(per)::value;
+    auto walk = [&](auto n, auto per, auto late, auto&& move, int extra_at, auto&& extra, auto&& landed) {
+      constexpr int N = decltype(n)::value, PER = decltype(per)::value, AHEAD = decltype(late)::value ? 0 : 1;
 #pragma unroll
       for (int p = 0; p < N - 1; ++p)
         if (p < nslab) move(p, p);
       int buf = N - 1;
       for (int it = 0; it < nslab; ++it) {
-        if (it + (N > 3 ? N - 2 : 2) < nslab) {
-          asm volatile("s_waitcnt vmcnt(%0)" ::"n"((N - 3) * PER) : "memory");
+        if (it + (N > 3 || !AHEAD ? N - 2 : 2) < nslab) {
+          asm volatile("s_waitcnt vmcnt(%0)" ::"n"((N - 2 - AHEAD) * PER) : "memory");
         } else {
           // (the last slabs; `extra` is asked for here only: on the way from the wait to the barrier it costs 3 % at NX = 3)
           asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
           if (it == extra_at) extra();
         }
         if constexpr (SEG) {
-          if (it == 0) landed(0);
-          landed(it + 1);
+          if (AHEAD && it == 0) landed(0);
+          landed(it + AHEAD);
         }
         pipe_barrier();
         if (it + N - 1 < nslab) move(it + N - 1, buf);
@@ -143,7 +152,7 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
       }
       pipe_barrier();
     };
-    if (wave < kPipeConsumers + kPipeMovers) {
+    if (wave < kPipeConsumers + XM) {
       // ---- activations
       const int d = wave - kPipeConsumers;
       const int mt = a.M - m0 < BM ? a.M - m0 : BM;
@@ -159,7 +168,7 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
       const int partial = SEG ? km.cs_keep & 7 : 0, seg_log = 7 - seg_shift;   // columns in a segment's last block (even), segments of a group
       auto unit = [&](int k, int slab) {
         constexpr int CH = 16 * G;                       // chunks per token
-        const int v = (d + kPipeMovers * k) * 64;
+        const int v = (d + XM * k) * 64;
         const int tok = v / CH + (CH < 64 ? lane / CH : 0);
         const int c = (CH <= 64 ? lane % CH : v % CH + lane) ^ bank_key(tok);
         const int g = slab * G + c / 16, k0 = (c % 16) * 8;   // group, column in it
@@ -188,24 +197,24 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
       int first[S::XPW];                                 // (of use when there is a whole slab: then slab 0 is one)
 #pragma unroll
       for (int k = 0; k < S::XPW; ++k) first[k] = unit(k, 0);
-      walk(std::integral_constant<int, NX>(), std::integral_constant<int, S::XPW>(), [&](int slab, int buf) {
+      walk(std::integral_constant<int, NX>(), std::integral_constant<int, S::XPW>(), std::integral_constant<bool, XLate>(), [&](int slab, int buf) {
         lds_byte* const to = lds + buf * S::XBytes + d * 1024;
         if (slab < nwhole) {
 #pragma unroll
           for (int k = 0; k < S::XPW; ++k)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void*)(to + k * (kPipeMovers * 1024)), 16, first[k], slab * (G * kpg * 2), 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void*)(to + k * (XM * 1024)), 16, first[k], slab * (G * kpg * 2), 0, 0);
         } else {
 #pragma unroll
           for (int k = 0; k < S::XPW; ++k)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void*)(to + k * (kPipeMovers * 1024)), 16, unit(k, slab), 0, 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void*)(to + k * (XM * 1024)), 16, unit(k, slab), 0, 0, 0);
         }
-      }, tail == 0 ? -1 : nslab > 1 ? nslab - 2 : 0, [&]() {
+      }, tail == 0 ? -1 : nslab > 1 ? nslab - (XLate ? 1 : 2) : 0, [&]() {
         const int c = km.k_keep / 8 - (nslab - 1) * (16 * G), keep = tail & ~1;   // chunk in the slab, columns that stay
         auto m = [&](int i) { return keep > i ? ~0u : 0u; };
 #pragma unroll
         for (int i = 0; i < TI; ++i) {
           const int t = lane + 64 * i;
-          if (t >= BM || (t * G / 4) % kPipeMovers != d) continue;
+          if (t >= BM || (t * G / 4) % XM != d) continue;
           uint4* p = reinterpret_cast<uint4*>(smem + (nslab - 1) % NX * S::XBytes) + t * (16 * G) + (c ^ bank_key(t));
           uint4 v = *p;
           v.x = (v.x & m(0)) | (tail == 1 ? odd[i] : 0u);
@@ -223,9 +232,9 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
           if (!partial || slab >= nslab) return;
           unsigned char* const to = smem + slab % NX * S::XBytes;
           constexpr int TU = 4 / G;                      // tokens per load
-          for (int i = lane; i < BM / 2 * G << seg_log; i += 64) {
+          for (int i = lane; i < BM / XM * G << seg_log; i += 64) {
             const int sg = i & ((1 << seg_log) - 1), g = (i >> seg_log) % G, j = (i >> seg_log) / G;
-            const int t = (j / TU * kPipeMovers + d) * TU + j % TU, c = g * 16 + (sg << (seg_shift - 3)) + km.cs_keep / 8;
+            const int t = (j / TU * XM + d) * TU + j % TU, c = g * 16 + (sg << (seg_shift - 3)) + km.cs_keep / 8;
             uint32_t* p = reinterpret_cast<uint32_t*>(to + (t * (16 * G) + (c ^ bank_key(t))) * 16);
             if (partial == 2) p[1] = 0u;
             if (partial <= 4) *reinterpret_cast<u32x2_t*>(p + 2) = u32x2_t{0u, 0u};
@@ -235,29 +244,31 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
       });
       return;
     }
-    if (wave == kPipeConsumers + kPipeMovers) {
+    if (wave < kPipeConsumers + XM + WM) {
       // ---- codes
       const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(a.qweight), 0, a.N_total * row_bytes, kBufferWord3);
-      int woff[S::WI];                                   // byte offset of the lane's unit in slab 0
+      const int d = wave - kPipeConsumers - XM;
+      int woff[S::WPW];                                  // byte offset of the lane's unit in slab 0
 #pragma unroll
-      for (int k = 0; k < S::WI; ++k) {
-        const int v = k * 64 + lane, row = v / U, j = v - row * U;
+      for (int k = 0; k < S::WPW; ++k) {
+        const int v = (d + WM * k) * 64 + lane, row = v / U, j = v - row * U;
         int js = j;
         if constexpr ((U & (U - 1)) == 0) js = j ^ (bank_key(row) / (U < 16 ? 16 / U : 1));
         int rc = n0 + row;
         rc = rc < km.n_keep ? rc : km.n_keep - 1;       // (rows past the last one: a valid, unused load)
         woff[k] = stored_row(km, rc) * row_bytes + js * 16;
       }
-      walk(std::integral_constant<int, NW>(), std::integral_constant<int, S::WI>(), [&](int slab, int buf) {
+      walk(std::integral_constant<int, NW>(), std::integral_constant<int, S::WPW>(), std::false_type(), [&](int slab, int buf) {
+        lds_byte* const to = lds + S::W0 + buf * S::WBytes + d * 1024;
         if ((slab + 1) * G <= gpr) {
 #pragma unroll
-          for (int k = 0; k < S::WI; ++k)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_void*)(lds + S::W0 + buf * S::WBytes + k * 1024), 16, woff[k], slab * (U * 16), 0, 0);
+          for (int k = 0; k < S::WPW; ++k)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_void*)(to + k * (WM * 1024)), 16, woff[k], slab * (U * 16), 0, 0);
         } else {
           // (a slab's groups past the row's end: the next row's codes, or nothing behind the matrix; their scale is zero)
 #pragma unroll
-          for (int k = 0; k < S::WI; ++k)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_void*)(lds + S::W0 + buf * S::WBytes + k * 1024), 16, woff[k] + slab * (U * 16), 0, 0, 0);
+          for (int k = 0; k < S::WPW; ++k)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_void*)(to + k * (WM * 1024)), 16, woff[k] + slab * (U * 16), 0, 0, 0);
         }
       }, -1, []() {}, [](int) {});
       return;
@@ -401,7 +412,7 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
   pipe_barrier();                         // slabs 0 and 1 are in LDS
   const unsigned char *xsl = smem, *wsl = smem;
   read_group(wsl, 0, cur);
-  read_a(xsl, 0, av[0]);
+  if (!XLate) read_a(xsl, 0, av[0]);
   int xb = 1, wb = 1, it = 0, sz = sz_at(1);
   const unsigned char *xnext = smem + S::XBytes, *wnext = smem + S::WBytes;
   // Slabs from `it` on.  The usual form of the bfloat16 unpack leaves at the first slab of which a scale asks for the wide form,
@@ -415,7 +426,8 @@ __global__ __launch_bounds__(kPipeThreads, 3) void w_pipe_kernel(PipeBatch bt) {
 #pragma unroll
       for (int t = 0; t < T; ++t) {
         const int p = t & 1;
-        read_a(t + 1 < T ? xsl : xnext, (t + 1) % T, av[p ^ 1]);
+        if (XLate && t == 0) read_a(xsl, 0, av[0]);
+        if (t + 1 < T || !XLate) read_a(t + 1 < T ? xsl : xnext, (t + 1) % T, av[p ^ 1]);
         __builtin_amdgcn_sched_barrier(0);   // (activations first: the products wait for them)
         if (t == 0) read_group(wnext, sz, ahead);
         __builtin_amdgcn_sched_barrier(0);   // (or the compiler moves the reads behind the products to save registers)
@@ -515,7 +527,7 @@ static hipError_t pipe_launch(const LinearArgs* p, int n, hipStream_t stream) {
     if (i < n) tiles += (p[i].km.n_keep + S::BN - 1) / S::BN * b.ntt;
   }
   b.tiles = tiles;
-  hipLaunchKernelGGL(kern, dim3(tiles), dim3(kPipeThreads), S::Lds, stream, b);
+  hipLaunchKernelGGL(kern, dim3(tiles), dim3(S::Threads), S::Lds, stream, b);
   return hipGetLastError();
 }
 

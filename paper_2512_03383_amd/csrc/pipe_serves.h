@@ -26,6 +26,7 @@ static inline PipeWay pipe_way(const LinearArgs& a) {
 // Outputs that a launch of the pipelined kernel reaches with its largest tiles (96 tokens x 128 rows and more, 768 threads each: the
 // threads of a grid are counted in 32 bits).
 constexpr long long kPipeOutputs = 60000000000ll;
+constexpr long long kPipeMostThreads = 960;   // of a block, any tile
 
 // At least two tokens, rows of eight groups and more (the window of scales), a column prefix of at least eight columns or
 // segments of a power of two up to a group that keep an even number of columns (the last kept pair of x is then a whole
