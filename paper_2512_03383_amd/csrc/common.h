@@ -280,6 +280,10 @@ hipError_t launch_w4_gate_up_silu_bf16_sym(const LinearArgs* probs, hipStream_t 
 // persistent streaming GEMV for tall row-prefix x column-prefix matrices; *done = false (nothing launched)
 // when the shape is not one it serves
 hipError_t launch_w4_gemv_stream(const LinearArgs& a, hipStream_t stream, bool* done);
+// the same walk over codes of 8, 6 and 3 bits, both formats
+hipError_t launch_w8_gemv_stream(const LinearArgs& a, hipStream_t stream, bool* done);
+hipError_t launch_w6_gemv_stream(const LinearArgs& a, hipStream_t stream, bool* done);
+hipError_t launch_w3_gemv_stream(const LinearArgs& a, hipStream_t stream, bool* done);
 hipError_t launch_w4_gate_up_stream(const LinearArgs* probs, hipStream_t stream, bool* done);
 hipError_t launch_w4_gate_up_stream_probe(const LinearArgs* probs, hipStream_t stream, bool* done);
 hipError_t launch_w4_gemv_stream_bf16(const LinearArgs& a, hipStream_t stream, bool* done);

@@ -28,6 +28,7 @@
 // h[r] = SiLU(gate) * up itself, so gate and up never meet through memory or LDS.
 #pragma once
 #include "gemv_kernel.h"
+#include "codes.h"
 #include <atomic>
 #include <type_traits>
 
@@ -106,13 +107,26 @@ struct StreamArgs {
 // puts into LDS once ([table row][pair], then one identity entry for v), and writes both outputs.  The loads of a
 // body go through the resources of that body's matrix; they are switched when a wave's next body lies in another
 // matrix (bodies are handed out in rising order, so at most twice per wave).
+//
+// BITS = 8, 6, 3: the same walk over codes of those widths.  A lane's 32 columns of a tile are BITS words, unpacked by codes.h
+// into matrix operands in column order, so the activations are staged in memory order.  Whether there are zero points is a
+// run-time matter there (the resource of none is empty), and the scales of columns past the last kept one count as zero.
+// rows per loop body: four tiles and more in flight
+constexpr int stream_rows(int tiles_per_row, bool qkv) { return qkv ? 2 : (tiles_per_row >= 4 ? 1 : 4 / tiles_per_row); }
+// a lane's words of a tile: BITS of them, in two registers tuples where there are more than four
+template <int BITS> struct TileCodes { typedef u32x4_t A; typedef u32x4_t B; };
+template <> struct TileCodes<3> { typedef u32x3_t A; typedef u32x2_t B; };
+template <> struct TileCodes<6> { typedef u32x4_t A; typedef u32x2_t B; };
+
 template <int NCH, int NM, bool ZP, bool BF16, bool SEG, bool PROBE, bool XWAIT = false, bool YTHROUGH = false, bool HI = false, bool QKV = false,
-          bool CS = false>
+          bool CS = false, int BITS = 4>
 __device__ __forceinline__ bool stream_phase(const StreamArgs& a, uint4* xs /* LDS, [NCH][4][64] units of 8 halves */,
                                              int* next_body_p /* LDS */, uint32_t tag = 0) {
   constexpr int TPR = NM * NCH;                                  // tiles per row (pair)
-  constexpr int RB = QKV ? 2 : (TPR >= 4 ? 1 : 4 / TPR);         // rows per loop body
+  constexpr int RB = stream_rows(TPR, QKV);                // rows per loop body
   static_assert(!QKV || (NM == 1 && !SEG && !PROBE && !XWAIT && !YTHROUGH && !HI && !CS), "the fused q / k / v walk is a mode of its own");
+  constexpr bool WIDE = BITS != 4, TWO = BITS > 4;               // TWO: a tile's codes take two loads
+  static_assert(!WIDE || (NM == 1 && ZP && !PROBE && !XWAIT && !HI && !QKV), "codes of other widths: one matrix, plain words");
   static_assert(!CS || (NM == 1 && !PROBE && !XWAIT && !HI), "column segments: one matrix, plain words");
   constexpr int D = RB * TPR;                                    // tiles per body = tiles in flight
   constexpr bool XREG = NCH <= 2;                                // activations live in registers
@@ -120,7 +134,7 @@ __device__ __forceinline__ bool stream_phase(const StreamArgs& a, uint4* xs /* L
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int total_waves = (int)gridDim.x * kStreamWaves;
-  const int words_per_row = a.K_total >> 3, groups_per_row = a.K_total / kGroup;
+  const int words_per_row = WIDE ? a.K_total / 32 * BITS : a.K_total >> 3, groups_per_row = a.K_total / kGroup;
   const int k_span32 = ((CS ? a.k_span : a.k_keep) + 31) & ~31;
 
   // ---- x loads first (memory returns in issue order; x is an L2 hit).  Unit u = stored columns [8u, 8u + 8).
@@ -218,7 +232,7 @@ __device__ __forceinline__ bool stream_phase(const StreamArgs& a, uint4* xs /* L
       woff[c] = w0 < ((a.d_keep + 7) >> 3) * a.il_heads ? (uint32_t)w0 * 4u : 0u;
     } else {
       const int kb = tile_k0(lane, c, NCH);
-      woff[c] = kb < k_span32 ? (uint32_t)kb >> 1 : 0u;
+      woff[c] = kb < k_span32 ? (WIDE ? (uint32_t)(kb >> 3) * BITS : (uint32_t)kb >> 1) : 0u;
     }
   }
   // first group of the lane (a quad past the row's groups reads the row start).  A quad may own groups past the row's
@@ -234,7 +248,16 @@ __device__ __forceinline__ bool stream_phase(const StreamArgs& a, uint4* xs /* L
     rq[m] = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(a.qweight[m]), 0, rows * words_per_row * 4, kRsrcWord3);
     rs[m] = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(a.scales[m]), 0, rows * groups_per_row * 2, kRsrcWord3);
     if constexpr (ZP)
-      rz[m] = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(a.zeros[m]), 0, rows * groups_per_row, kRsrcWord3);
+      rz[m] = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(a.zeros[m]), 0, WIDE && !a.zeros[m] ? 0 : rows * groups_per_row, kRsrcWord3);
+  }
+  // WIDE: without zero points every one is the middle of the range; a lane's scales of columns past the last kept one are zero
+  const uint32_t zmask = WIDE && !a.zeros[0] ? 0u : ~0u, zdef = WIDE && !a.zeros[0] ? 0x01010101u << (BITS - 1) : 0u;
+  uint32_t smask[WIDE ? (NCH + 1) / 2 : 1];
+  if constexpr (WIDE) {
+#pragma unroll
+    for (int i = 0; i < (NCH + 1) / 2; ++i)
+      smask[i] = (tile_k0(lane, 2 * i, NCH) < k_span32 ? 0xffffu : 0u) |
+                 (2 * i + 1 < NCH && tile_k0(lane, 2 * i + 1, NCH) < k_span32 ? 0xffff0000u : 0u);
   }
   // QKV: loads are issued through the resources of the matrix of the body being fetched, rebuilt from that matrix's
   // pointers when the matrix changes (a select between ready-made resources ends up in vector registers, and every
@@ -279,8 +302,12 @@ __device__ __forceinline__ bool stream_phase(const StreamArgs& a, uint4* xs /* L
     load_bytes<2 * NGQ>(rs[m], 2 * goff, 2 * ro.g, r.s);
     if constexpr (ZP) load_bytes<NGQ>(rz[m], goff, ro.g, r.z);
   };
-  auto load_codes = [&](const RowOff& ro, int m, int c) {
-    return __builtin_amdgcn_raw_buffer_load_b128(rq[m], (int)woff[c], ro.q, 0);
+  typedef TileCodes<BITS> Codes;
+  auto load_codes = [&](const RowOff& ro, int m, int c, typename Codes::A& wa, typename Codes::B& wb) {
+    if constexpr (BITS == 3) wa = __builtin_amdgcn_raw_buffer_load_b96(rq[m], (int)woff[c], ro.q, 0);
+    else wa = __builtin_amdgcn_raw_buffer_load_b128(rq[m], (int)woff[c], ro.q, 0);
+    if constexpr (BITS == 6) wb = __builtin_amdgcn_raw_buffer_load_b64(rq[m], (int)woff[c] + 16, ro.q, 0);
+    if constexpr (BITS == 8) wb = __builtin_amdgcn_raw_buffer_load_b128(rq[m], (int)woff[c] + 16, ro.q, 0);
   };
   // slot s of a body: row s / TPR of the body, then tile-major with the matrices of a tile adjacent
   auto slot_tile = [](int s) { return (s % TPR) / NM; };
@@ -295,7 +322,8 @@ __device__ __forceinline__ bool stream_phase(const StreamArgs& a, uint4* xs /* L
   auto row_of = [&](int j, int rr) { return (blk8 + (j & 7)) * RB + rr + (j >> 3) * RB * total_waves; };
   int& next_body = *next_body_p;
 
-  u32x4_t ring[D];
+  typename Codes::A ring[D];
+  typename Codes::B ring2[TWO ? D : 1];
   RowQn cur[RB][NM], nxt[RB][NM];
   PairLoc cur_loc = {0, 0, 0}, nxt_loc = {0, 0, 0};   // QKV: where the body in hand and the next one lie
   // the RB rows of body j as offsets into the arrays (QKV: through the resources of the body's matrix, which become current)
@@ -325,7 +353,7 @@ __device__ __forceinline__ bool stream_phase(const StreamArgs& a, uint4* xs /* L
 #pragma unroll
       for (int m = 0; m < NM; ++m) load_rowq(ro0[rr], m, cur[rr][m]);
 #pragma unroll
-      for (int t = 0; t < TPR; ++t) ring[rr * TPR + t] = load_codes(ro0[rr], slot_mat(t), slot_tile(t));
+      for (int t = 0; t < TPR; ++t) load_codes(ro0[rr], slot_mat(t), slot_tile(t), ring[rr * TPR + t], ring2[TWO ? rr * TPR + t : 0]);
     }
   }
   __builtin_amdgcn_sched_barrier(0);
@@ -356,7 +384,8 @@ __device__ __forceinline__ bool stream_phase(const StreamArgs& a, uint4* xs /* L
     }
     if (u < NCH * 256)
       xs[HI ? ((u >> 8) * 4 + (u & 3)) * 64 + ((u >> 2) & 63) : unit_slot(u, NCH)] =
-          make_uint4(e[0] | (e[4] << 16), e[1] | (e[5] << 16), e[2] | (e[6] << 16), e[3] | (e[7] << 16));
+          WIDE ? make_uint4(e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16))
+               : make_uint4(e[0] | (e[4] << 16), e[1] | (e[5] << 16), e[2] | (e[6] << 16), e[3] | (e[7] << 16));
   }
   // QKV: sin / cos of pos * theta^(-2j/D) for every (table row, kept pair), then the identity for v.  The angle is
   // formed in fp64, in revolutions (theta^(-2j/D) = base^j by binary powering), and its fraction goes to the hardware
@@ -414,6 +443,30 @@ __device__ __forceinline__ bool stream_phase(const StreamArgs& a, uint4* xs /* L
     for (int q = 0; q < 4; ++q) acc = mfma_16x16x32<BF16>(xf[q], dequant_word4<BF16>(wv[q], gq[HI ? q : 0], mg), acc);
   };
 
+  const CodeMagic cm = make_code_magic<BITS, BF16>();
+  bool wide_row = false;   // bfloat16: a scale of the row asks for the wide unpack (codes.h)
+  auto needs_wide = [&](const uint32_t (&sc)[(2 * NGQ + 3) / 4]) {
+    uint32_t largest = 0;
+#pragma unroll
+    for (int i = 0; i < (NCH + 1) / 2; ++i) {
+      const uint32_t v = sc[i] & (WIDE ? smask[i] : ~0u);
+      largest = max(largest, max(v << 17, (v & 0x7fff0000u) << 1));
+    }
+    return __builtin_amdgcn_ballot_w64(largest >= kScaleWide << 17) != 0;
+  };
+  auto consume_wide = [&](auto wide_form, const typename Codes::A& wa, const typename Codes::B& wb, uint32_t sbits, uint32_t zero, int c, float4_t& ac) {
+    if constexpr (WIDE) {
+      constexpr bool W = decltype(wide_form)::value;
+      RawCodes<BITS, 4> raw;
+#pragma unroll
+      for (int i = 0; i < BITS; ++i) raw.w[i] = i < 4 ? wa[i & 3] : wb[BITS == 6 ? i & 1 : i & 3];
+      const CodeGroup<BITS, BF16> g = make_code_group<BITS, BF16, W>(sbits, zero);
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        ac = mfma_16x16x32<BF16>(XREG ? xr[XREG ? c : 0][q] : xs[(c * 4 + q) * 64 + lane], code_step<BITS, BF16, 4, W>(raw, q, g, cm), ac);
+    }
+  };
+
   float4_t acc[RB][NM];
 #pragma unroll
   for (int rr = 0; rr < RB; ++rr)
@@ -446,22 +499,31 @@ __device__ __forceinline__ bool stream_phase(const StreamArgs& a, uint4* xs /* L
         // loaded registers there would wait for every load in flight).
         const int ps = (s + D - 1) % D;   // the tile consumed just before this one (compile-time after unrolling)
         asm volatile("" : "+v"(ring[s]), "+v"(acc[ps / TPR][ps % NM]));
-        Group g[HI ? 4 : 1];
-        if constexpr (HI) {
-#pragma unroll
-          for (int q = 0; q < 4; ++q) g[q] = group_of<ZP, BF16, 4>(cur[rr][m], q);   // (the same for every tile of the row)
+        if constexpr (WIDE) {
+          if constexpr (TWO) asm volatile("" : "+v"(ring2[s]));
+          const uint32_t sw = cur[rr][m].s[c >> 1] & smask[c >> 1], zw = (cur[rr][m].z[c >> 2] & zmask) | zdef;
+          const uint32_t sbits = c & 1 ? sw >> 16 : sw & 0xffffu, zero = (zw >> (8 * (c & 3))) & 0xffu;
+          if (t == 0) wide_row = BF16 && needs_wide(cur[rr][m].s);
+          if (BF16 && wide_row) consume_wide(std::true_type{}, ring[s], ring2[TWO ? s : 0], sbits, zero, c, acc[rr][m]);
+          else consume_wide(std::false_type{}, ring[s], ring2[TWO ? s : 0], sbits, zero, c, acc[rr][m]);
         } else {
-          g[0] = group_of<ZP, BF16, NCH>(cur[rr][m], c);
-        }
-        if constexpr (XREG) {
-          consume(ring[s], g, xr[c], acc[rr][m]);
-        } else {
-          uint4 xf[4];
+          Group g[HI ? 4 : 1];
+          if constexpr (HI) {
 #pragma unroll
-          for (int q = 0; q < 4; ++q) xf[q] = xs[(c * 4 + q) * 64 + lane];
-          consume(ring[s], g, xf, acc[rr][m]);
+            for (int q = 0; q < 4; ++q) g[q] = group_of<ZP, BF16, 4>(cur[rr][m], q);   // (the same for every tile of the row)
+          } else {
+            g[0] = group_of<ZP, BF16, NCH>(cur[rr][m], c);
+          }
+          if constexpr (XREG) {
+            consume(ring[s], g, xr[c], acc[rr][m]);
+          } else {
+            uint4 xf[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) xf[q] = xs[(c * 4 + q) * 64 + lane];
+            consume(ring[s], g, xf, acc[rr][m]);
+          }
         }
-        if constexpr (RELOAD) ring[s] = load_codes(nro[rr], m, c);
+        if constexpr (RELOAD) load_codes(nro[rr], m, c, ring[s], ring2[TWO ? s : 0]);
       }
       const int rc = row_of(body, rr);
       if constexpr (QKV) {
@@ -519,16 +581,16 @@ __device__ __forceinline__ bool stream_phase(const StreamArgs& a, uint4* xs /* L
 }
 
 
-template <int NCH, int NM, bool ZP, bool BF16, bool SEG, bool PROBE = false, bool HI = false, bool QKV = false, bool CS = false>
+template <int NCH, int NM, bool ZP, bool BF16, bool SEG, bool PROBE = false, bool HI = false, bool QKV = false, bool CS = false, int BITS = 4>
 __global__ __launch_bounds__(kStreamThreads) void w4_gemv_stream_kernel(StreamArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ int next_body;
-  stream_phase<NCH, NM, ZP, BF16, SEG, PROBE, false, false, HI, QKV, CS>(a, reinterpret_cast<uint4*>(smem), &next_body);
+  stream_phase<NCH, NM, ZP, BF16, SEG, PROBE, false, false, HI, QKV, CS, BITS>(a, reinterpret_cast<uint4*>(smem), &next_body);
 }
 
-template <int NCH, int NM, bool ZP, bool BF16, bool SEG, bool PROBE, bool HI = false, bool QKV = false, bool CS = false>
+template <int NCH, int NM, bool ZP, bool BF16, bool SEG, bool PROBE, bool HI = false, bool QKV = false, bool CS = false, int BITS = 4>
 static hipError_t stream_launch(const StreamArgs& a, hipStream_t stream) {
-  auto kern = w4_gemv_stream_kernel<NCH, NM, ZP, BF16, SEG, PROBE, HI, QKV, CS>;
+  auto kern = w4_gemv_stream_kernel<NCH, NM, ZP, BF16, SEG, PROBE, HI, QKV, CS, BITS>;
   // the image of x, then (QKV) the sin / cos table and its identity entry
   const size_t smem = (size_t)NCH * 4096 + (QKV ? ((size_t)a.H_tab * a.hk + 1) * sizeof(float2_t) : 0);
   // CU count per device ordinal, read once (host threads that race on the first call all store the same value)
@@ -546,7 +608,7 @@ static hipError_t stream_launch(const StreamArgs& a, hipStream_t stream) {
   }
   // One block (8 waves, one body of tiles in flight each) per CU: more waves or deeper rings measured slower at every
   // size tried (the kernel is bound by instruction issue, and more loads in flight only queue).
-  constexpr int TPR = NM * NCH, RB = QKV ? 2 : (TPR >= 4 ? 1 : 4 / TPR);
+  constexpr int RB = stream_rows(NM * NCH, QKV);
   int blocks = (a.n_keep + kStreamWaves * RB - 1) / (kStreamWaves * RB);
   // (QKV, a few thousand pairs in all: one, two or three blocks per compute unit measured the same, 6.7 us for 11.1 MB)
   // (down_proj, two rows per wave: two blocks per compute unit 8.6 against 8.2 us)
@@ -592,7 +654,7 @@ static inline bool stream_shape(const LinearArgs& a, int max_tiles) {
   const KeepMap& km = a.km;
   const int nch = row_tiles(km.k_keep);
   // row offsets inside the buffer resources are signed 32-bit byte counts
-  const bool fits = (long long)a.N_total * (a.K_total / 2) < (1ll << 31);
+  const bool fits = (long long)a.N_total * (a.K_total / 8) * a.bits < (1ll << 31);
   return a.M == 1 && a.il_heads == 0 && km.cs_stride == 0 && km.k_keep >= 8 && nch <= max_tiles && fits && whole_quads(a.K_total, nch);
 }
 
@@ -601,9 +663,9 @@ static inline bool stream_shape(const LinearArgs& a, int max_tiles) {
 static inline bool stream_shape_cs(const LinearArgs& a, int max_tiles) {
   const KeepMap& km = a.km;
   const int nch = row_tiles(km.k_span);
-  const bool fits = (long long)a.N_total * (a.K_total / 2) < (1ll << 31);
+  const bool fits = (long long)a.N_total * (a.K_total / 8) * a.bits < (1ll << 31);
   return a.M == 1 && a.il_heads == 0 && km.cs_stride >= 8 && km.cs_stride % 8 == 0 && km.cs_keep >= 1 && km.k_keep >= 8 &&
-         km.rs_stride == 0 && nch <= max_tiles && fits && whole_quads(a.K_total, nch);
+         (km.rs_stride == 0 || a.bits != 4) && nch <= max_tiles && fits && whole_quads(a.K_total, nch);
 }
 
 static inline StreamArgs stream_args(const LinearArgs& a) {
@@ -684,6 +746,43 @@ static hipError_t stream_one(const LinearArgs& a, hipStream_t stream, bool* done
   if (a.km.rs_stride != 0)
     return a.zeros ? stream_nch<1, true, BF16, true, false>(s, nch, stream) : stream_nch<1, false, BF16, true, false>(s, nch, stream);
   return a.zeros ? stream_nch<1, true, BF16, false, false>(s, nch, stream) : stream_nch<1, false, BF16, false, false>(s, nch, stream);
+}
+
+// One linear of one token with codes of 8, 6 or 3 bits: *done = false (nothing launched) for shapes that the kernels of w8.hip and
+// wbits.hip keep.
+template <int BITS, bool BF16, bool CS>
+static hipError_t stream_wide_nch(const StreamArgs& s, int nch, hipStream_t stream) {
+  switch (nch) {
+    case 1: return stream_launch<1, 1, true, BF16, true, false, false, false, CS, BITS>(s, stream);
+    case 2: return stream_launch<2, 1, true, BF16, true, false, false, false, CS, BITS>(s, stream);
+    case 3: return stream_launch<3, 1, true, BF16, true, false, false, false, CS, BITS>(s, stream);
+    case 4: return stream_launch<4, 1, true, BF16, true, false, false, false, CS, BITS>(s, stream);
+    case 5: return stream_launch<5, 1, true, BF16, true, false, false, false, CS, BITS>(s, stream);
+    case 6: return stream_launch<6, 1, true, BF16, true, false, false, false, CS, BITS>(s, stream);
+    case 7: return stream_launch<7, 1, true, BF16, true, false, false, false, CS, BITS>(s, stream);
+    case 8: return stream_launch<8, 1, true, BF16, true, false, false, false, CS, BITS>(s, stream);
+    default: return hipErrorInvalidValue;
+  }
+}
+// The other kernels put a row on a wave and start more of them; the walk wins once its waves have rows enough, and sooner the longer
+// those are.  3 / 6 / 8 bits, fp16, one token, weights from memory, this kernel against the others: 12185 x 4096 7.7 / 9.4 / 10.5 against
+// 10.2 / 12.7 / 11.8 us (bfloat16 9.3 / 10.0 / 10.9 against 14.9 / 17.1 / 15.5), 4096 x 12185 7.7 / 9.9 / 10.2 against 10.2 / 12.9 / 12.4,
+// 512 x 14336 5.5 / 6.3 / 6.5 against 7.0 / 7.6 / 8.0, 2048 x 7168 4.2 / 5.1 / 5.4 against 5.4 / 6.6 / 7.0, 3000 x 4096 4.4 / 5.3 / 5.1
+// against 5.3 / 6.4 / 6.4, 4096 x 1024 4.5 / 4.9 / 4.4 against 5.0 / 4.4 / 5.2; below the line 2048 x 2048 4.5 / 4.9 / 4.5 against 3.9 / 3.6 / 4.2.
+static inline int stream_min_rows_wide(int nch, int bits) {
+  if (nch >= 5) return 512;
+  if (nch >= 3) return 2048;
+  return nch == 2 ? 2560 : bits == 6 ? INT32_MAX : 4096;
+}
+template <int BITS>
+static hipError_t stream_wide(const LinearArgs& a, hipStream_t stream, bool* done) {
+  const bool cs = a.km.cs_stride != 0;
+  const int nch = row_tiles(cs ? a.km.k_span : a.km.k_keep);
+  *done = (cs ? stream_shape_cs(a, 8) : stream_shape(a, 8)) && a.km.n_keep >= stream_min_rows_wide(nch, BITS);
+  if (!*done) return hipSuccess;
+  const StreamArgs s = stream_args(a);
+  if (a.bf16) return cs ? stream_wide_nch<BITS, true, true>(s, nch, stream) : stream_wide_nch<BITS, true, false>(s, nch, stream);
+  return cs ? stream_wide_nch<BITS, false, true>(s, nch, stream) : stream_wide_nch<BITS, false, false>(s, nch, stream);
 }
 
 // The loads of stream_one's launch without its arithmetic (y receives one folded word per row): the read-stream

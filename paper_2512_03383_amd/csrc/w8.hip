@@ -10,7 +10,8 @@
 // two-element dot product with fp32 accumulation (the activations are staged in that order).  bfloat16: the weight is
 // formed in fp32 (q s - z s, exact) and rounded by the packed conversion.  One launch serves one token per block row
 // (grid.y = tokens).  Several tokens come here only where pipe_serves.h says so (short rows, unusual segments, few rows, two or
-// three tokens): they re-read the weights through L2.
+// three tokens): they re-read the weights through L2.  One token comes here with few rows or a column rule that the walk of
+// gemv_stream_kernel.h does not take.
 #include "common.h"
 
 namespace uniql {
@@ -214,13 +215,17 @@ hipError_t launch_w8_dequant(const LinearArgs& a, hipStream_t stream) {
 
 // hipErrorInvalidValue: rows whose kept span does not fit the LDS image of the activations (more than 32768 columns)
 hipError_t launch_w8_linear(const LinearArgs& a, hipStream_t stream) {
+  bool done = false;
+  const hipError_t e = launch_w8_gemv_stream(a, stream, &done);
+  if (done) return e;
   const int nchunks = (a.km.k_span + 15) >> 4;
   const size_t smem = (size_t)nchunks * 32;
   if (smem > 64 * 1024 || a.M > 65535) return hipErrorInvalidValue;
   const int waves = kW8Threads / 64;
   int bx = (a.km.n_keep + waves - 1) / waves;
   if (bx > 256) bx = 256;   // a block of eight waves per compute unit, each stages the activations once; waves walk the rows
-                            // (gate / down shapes: 13.7 / 13.9 us; 512 blocks of four waves 13.5 / 14.5, 384 blocks of eight 15.1 / 16.9)
+                            // (gate / down shapes: 13.7 / 13.9 us; 512 blocks of four waves 13.5 / 14.5, 384 blocks of eight 15.1 / 16.9;
+                            // the walk takes these shapes now)
   if (a.bf16) hipLaunchKernelGGL(w8_gemv_kernel<true>, dim3(bx, a.M), dim3(kW8Threads), smem, stream, a);
   else hipLaunchKernelGGL(w8_gemv_kernel<false>, dim3(bx, a.M), dim3(kW8Threads), smem, stream, a);
   return hipGetLastError();

@@ -15,7 +15,8 @@
 // (x_p, x_{p + C/2}) in one two-element dot product with fp32 accumulation (the activations are staged in that order,
 // 16 bytes = four pairs per piece, piece-major so that the 64 lanes of a wave read consecutive pieces).  bfloat16: the
 // weight is formed in fp32 (q s - z s, exact) and rounded by the packed conversion.  One launch serves one token per
-// block row (grid.y = tokens); several tokens come here only where pipe_serves.h says so and re-read the weights through L2.
+// block row (grid.y = tokens); several tokens come here only where pipe_serves.h says so and re-read the weights through L2, one
+// token only with few rows or a column rule that the walk of gemv_stream_kernel.h does not take.
 #include "common.h"
 
 namespace uniql {
@@ -272,7 +273,8 @@ static hipError_t linear_bits(const LinearArgs& a, hipStream_t stream) {
   const int waves = kWbThreads / 64;
   int bx = (a.km.n_keep + waves - 1) / waves;
   if (bx > 256) bx = 256;   // a block of eight waves per compute unit, each stages the activations once; waves walk the rows
-                            // (3-bit gate / down shapes 10.7 / 11.1 us; 512 blocks 10.9 / 12.2, 384 blocks 12.1 / 13.9)
+                            // (3-bit gate / down shapes 10.7 / 11.1 us; 512 blocks 10.9 / 12.2, 384 blocks 12.1 / 13.9; the walk
+                            // takes these shapes now)
   if (a.bf16) hipLaunchKernelGGL((wb_gemv_kernel<BITS, true>), dim3(bx, a.M), dim3(kWbThreads), smem, stream, a);
   else hipLaunchKernelGGL((wb_gemv_kernel<BITS, false>), dim3(bx, a.M), dim3(kWbThreads), smem, stream, a);
   return hipGetLastError();
@@ -280,6 +282,9 @@ static hipError_t linear_bits(const LinearArgs& a, hipStream_t stream) {
 
 // hipErrorInvalidValue: rows whose kept span does not fit the LDS image of the activations (more than 32768 columns)
 hipError_t launch_wb_linear(const LinearArgs& a, hipStream_t stream) {
+  bool done = false;
+  const hipError_t e = a.bits == 3 ? launch_w3_gemv_stream(a, stream, &done) : launch_w6_gemv_stream(a, stream, &done);
+  if (done) return e;
   return a.bits == 3 ? linear_bits<3>(a, stream) : linear_bits<6>(a, stream);
 }
 
