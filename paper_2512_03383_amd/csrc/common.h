@@ -351,6 +351,7 @@ struct RopeArgs {
   int T, Hq, Hkv, H_tab, D_full, D_keep;
   double theta;
   int bf16;   // q and k are bfloat16
+  double log2_theta;   // (the launcher fills it in)
 };
 hipError_t launch_pruned_rope(const RopeArgs& a, hipStream_t stream);
 hipError_t launch_stream_read(const void* src, long long bytes, uint32_t* out, hipStream_t stream);

@@ -44,7 +44,7 @@ constexpr int kHeadChunk = 4;
 
 // BF16: q and k are bfloat16 (half_t / half2_t then only carry the bits).
 template <bool V2, int kBatch, bool BF16>
-__global__ __launch_bounds__(kRopeThreads) void pruned_rope_kernel(RopeArgs a, int tokens_per_block) {
+__global__ __launch_bounds__(kRopeThreads) void pruned_rope_kernel(RopeArgs a, int tokens_per_block, int heads_per_block) {
   extern __shared__ __align__(8) unsigned char rope_smem[];
   double* invf = reinterpret_cast<double*>(rope_smem);   // [D_keep / 2]
   typedef typename std::conditional<V2, half2_t, half_t>::type elem_t;   // one or two adjacent channels
@@ -54,7 +54,8 @@ __global__ __launch_bounds__(kRopeThreads) void pruned_rope_kernel(RopeArgs a, i
   const int g = blockIdx.y;
   const int t0 = blockIdx.x * tokens_per_block;
   const int qper = a.Hq / a.H_tab, kper = a.Hkv / a.H_tab;
-  const int nheads = qper + kper;                 // heads that share this table row: Q heads, then K heads
+  // heads that share this table row: Q heads, then K heads; this block's are [hbeg, nheads)
+  const int hbeg = blockIdx.z * heads_per_block, nheads = min(qper + kper, hbeg + heads_per_block);
   const int per_tok = hk / W;
   const int tb = min(tokens_per_block, a.T - t0);
   const int n_items = tb * per_tok;               // one batch (kBatch * kRopeThreads) unless a single token has more
@@ -100,13 +101,12 @@ __global__ __launch_bounds__(kRopeThreads) void pruned_rope_kernel(RopeArgs a, i
     for (int b = 0; b < kBatch; ++b) pos[b] = (double)a.positions[tok[b]];
   };
   load_pos();
-  load_chunk(0);
+  load_chunk(hbeg);
 
   // theta^(-2j/D) of the block's kept pairs, once, in fp64
-  const double l2t = log2(a.theta);
   for (int i = threadIdx.x; i < hk; i += kRopeThreads) {
     const int j = a.kept_idx[(size_t)g * hk + i];
-    invf[i] = exp2(-(2.0 * (double)j / (double)a.D_full) * l2t);
+    invf[i] = exp2(-(2.0 * (double)j / (double)a.D_full) * a.log2_theta);
   }
   __syncthreads();
 
@@ -117,7 +117,7 @@ __global__ __launch_bounds__(kRopeThreads) void pruned_rope_kernel(RopeArgs a, i
 #pragma unroll
       for (int w = 0; w < W; ++w) angle_sincos(pos[b], invf[ch[b] + w], &sn[b][w], &cs[b][w]);
 
-    for (int h0 = 0; h0 < nheads; h0 += kHeadChunk) {
+    for (int h0 = hbeg; h0 < nheads; h0 += kHeadChunk) {
       // rotate into registers, fetch the next chunk, then store: the next chunk's loads are in
       // flight while this one is written back
       elem_t y1[kBatch][kHeadChunk], y2[kBatch][kHeadChunk];
@@ -154,7 +154,7 @@ __global__ __launch_bounds__(kRopeThreads) void pruned_rope_kernel(RopeArgs a, i
     if (base >= n_items) break;
     take_items(base);
     load_pos();
-    load_chunk(0);
+    load_chunk(hbeg);
   }
 }
 
@@ -304,7 +304,7 @@ __global__ __launch_bounds__(kRopeThreads) void pruned_rope_rows_kernel(RopeArgs
   const int j = (int)threadIdx.x < hk ? a.kept_idx[(size_t)g * hk + threadIdx.x] : 0;
   Set cur, nxt;
   take(cur, tp);
-  if ((int)threadIdx.x < hk) invf[threadIdx.x] = exp2(-(2.0 * (double)j / (double)a.D_full) * log2(a.theta));
+  if ((int)threadIdx.x < hk) invf[threadIdx.x] = exp2(-(2.0 * (double)j / (double)a.D_full) * a.log2_theta);
   __syncthreads();
 #pragma unroll
   for (int e = 0; e < 2; ++e) {
@@ -326,9 +326,9 @@ __global__ __launch_bounds__(kRopeThreads) void pruned_rope_rows_kernel(RopeArgs
 }
 
 template <bool BF16>
-static hipError_t launch_rope_fmt(const RopeArgs& a, bool v2, dim3 grid, size_t smem, int tpb, hipStream_t stream) {
-  if (v2) hipLaunchKernelGGL((pruned_rope_kernel<true, 1, BF16>), grid, dim3(kRopeThreads), smem, stream, a, tpb);
-  else hipLaunchKernelGGL((pruned_rope_kernel<false, 1, BF16>), grid, dim3(kRopeThreads), smem, stream, a, tpb);
+static hipError_t launch_rope_fmt(const RopeArgs& a, bool v2, dim3 grid, size_t smem, int tpb, int hpb, hipStream_t stream) {
+  if (v2) hipLaunchKernelGGL((pruned_rope_kernel<true, 1, BF16>), grid, dim3(kRopeThreads), smem, stream, a, tpb, hpb);
+  else hipLaunchKernelGGL((pruned_rope_kernel<false, 1, BF16>), grid, dim3(kRopeThreads), smem, stream, a, tpb, hpb);
   return hipGetLastError();
 }
 
@@ -354,7 +354,9 @@ static hipError_t launch_rope_rows(const RopeArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
-hipError_t launch_pruned_rope(const RopeArgs& a, hipStream_t stream) {
+hipError_t launch_pruned_rope(const RopeArgs& args, hipStream_t stream) {
+  RopeArgs a = args;
+  a.log2_theta = log2(a.theta);   // (a block took a third of a microsecond over it)
   const int hk = a.D_keep >> 1;
   // half2 accesses need an even pair count (then every head row and both halves start on a
   // 4-byte boundary, since D_keep is a multiple of 4) and 4-byte aligned tensors
@@ -370,8 +372,17 @@ hipError_t launch_pruned_rope(const RopeArgs& a, hipStream_t stream) {
   if (tpb > a.T) tpb = a.T;
   if (tpb < 1) tpb = 1;
   dim3 grid((a.T + tpb - 1) / tpb, a.H_tab);
+  // A call of few blocks is one chain of latencies: its blocks take the heads of a table row four at a time, one load and one store
+  // each, and build the frequencies again, instead of one round of loads after the other.
+  const int heads = (a.Hq + a.Hkv) / a.H_tab;
+  const int chunks = (heads + kHeadChunk - 1) / kHeadChunk;
+  int hpb = heads;
+  if (chunks > 1 && (long long)grid.x * grid.y * chunks <= kRopeRowsBlocks && chunks <= 65535) {
+    hpb = kHeadChunk;
+    grid.z = chunks;
+  }
   const size_t smem = (size_t)hk * sizeof(double);
-  return a.bf16 ? launch_rope_fmt<true>(a, v2, grid, smem, tpb, stream) : launch_rope_fmt<false>(a, v2, grid, smem, tpb, stream);
+  return a.bf16 ? launch_rope_fmt<true>(a, v2, grid, smem, tpb, hpb, stream) : launch_rope_fmt<false>(a, v2, grid, smem, tpb, hpb, stream);
 }
 
 }  // namespace uniql
