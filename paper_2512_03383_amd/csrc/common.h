@@ -47,7 +47,7 @@ struct LinearArgs {
   int N_total, K_total, M;
   int bf16;           // scales, x and y are bfloat16 (the weights are then rounded to bfloat16 as well)
   int il_heads;       // > 0: the row's words are stored head-interleaved over this many heads (uniql_w4_t.col_interleave)
-  int bits;           // width of a code: 4, or 8 (one token: w8.hip), or 3 / 6 (wbits.hip); several tokens of any width: pipe_kernel.h
+  int bits;           // width of a code: 4, or 8, 6 or 3 (one token: the walk of gemv_stream_kernel.h, few rows w8.hip and wbits.hip; more: pipe_kernel.h)
   KeepMap km;
 };
 

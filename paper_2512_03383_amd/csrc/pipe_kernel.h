@@ -80,9 +80,9 @@ __global__ __launch_bounds__((PipeShape<AF, BF, WN, KG, KQ, G, NX, NW, BITS>::Th
   typedef PipeShape<AF, BF, WN, KG, KQ, G, NX, NW, BITS> S;
   constexpr int BM = S::BM, BN = S::BN, U = S::U, KS = S::KS, XM = S::XM, WM = S::WM;
   // A slab's activations land by the barrier before its use and not one earlier: its first fragments are then read behind that
-  // barrier (some 5 % of a slab), but with three or four buffers the loads have twice the time.  Small tiles wait for them
-  // otherwise, and so do segments, whose movers still clear columns (48 tokens x 4096 x 9318 18.1 -> 15 us, the attention block at 1000
-  // tokens 106 -> 103; prefixes in 96..128-token tiles 4 % the other way).
+  // barrier, but with three or four buffers the loads have a slab more of time.  Small tiles wait for them otherwise, and so do
+  // segments, whose movers still clear columns (two decoder layers at 48 tokens 140 -> 125 us a pass, the attention block at 1000
+  // tokens 106 -> 103; prefixes in 96..128-token tiles 4 % the other way: 5120 x 4096 at 512 tokens 31.2 -> 33.2 us).
   constexpr bool XLate = S::Small ? NX <= 4 : SEG && NX == 3;
   extern __shared__ __align__(16) unsigned char smem[];
   const int lane = threadIdx.x & 63;
