@@ -229,13 +229,13 @@ def uniql_w4_linear_kernel(N: int, K: int, keep, M: int, bits: int = 4, bf16: bo
 
 def uniql_w4_linear(W: QuantLinear, keep, x, y=None, stream=None):
     """y[M][n_keep] = x[M][k_keep] @ W'^T on the current device; returns y."""
-    import torch
-    n_keep, k_keep = kept_dims(W, keep)
     ftype = W.ftype
     assert x.dtype == ftype and x.is_cuda and x.dim() == 2 and x.stride(1) == 1
     M = x.shape[0]
     if y is None:
-        y = torch.empty((M, n_keep), dtype=ftype, device=x.device)
+        # (kept_dims, half a microsecond of a small linear's seven, only where an output is made: the C call has the same rule)
+        import torch
+        y = torch.empty((M, kept_dims(W, keep)[0]), dtype=ftype, device=x.device)
     assert y.dtype == ftype and y.is_cuda and y.stride(1) == 1
     d, kd = W.desc(), _keep_desc(keep)
     rc = lib().uniql_w4_linear(C.byref(d), C.byref(kd) if kd is not None else None,
