@@ -125,6 +125,17 @@ __device__ __forceinline__ CodeGroup<BITS, BF16> make_code_group(uint32_t sbits,
   return g;
 }
 
+// a group's constants where `kept` is all ones, those of a scale of zero where it is zero
+template <int BITS>
+__device__ __forceinline__ CodeGroup<BITS, false> mask_code_group(const CodeGroup<BITS, false>& g, uint32_t kept) {
+  return {g.za, g.zb, as_half2(as_u32(g.s2) & kept)};
+}
+template <int BITS>
+__device__ __forceinline__ CodeGroup<BITS, true> mask_code_group(const CodeGroup<BITS, true>& g, uint32_t kept) {
+  auto m = [&](float f) { return __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, f) & kept); };
+  return {m(g.s), m(g.nalo), m(g.nahi), m(g.nblo), m(g.nbhi)};
+}
+
 // the four pairs base + q of step t of the window
 template <int BITS, bool BF16, int T>
 __device__ __forceinline__ void code_pairs(const RawCodes<BITS, T>& r, int t, const CodeMagic& m, uint32_t (&p)[4]) {

@@ -259,6 +259,14 @@ __device__ __forceinline__ bool stream_phase(const StreamArgs& a, uint4* xs /* L
       smask[i] = (tile_k0(lane, 2 * i, NCH) < k_span32 ? 0xffffu : 0u) |
                  (2 * i + 1 < NCH && tile_k0(lane, 2 * i + 1, NCH) < k_span32 ? 0xffff0000u : 0u);
   }
+  // TWO: where the kept columns end in the lower half of a lane's 32, the scale of the upper half is zero as well: the weights there,
+  // whatever is stored, must not reach the sum as zero times infinity (w8.hip and wbits.hip, whose units are 16 columns for these widths,
+  // do not read them).  It costs 1 % of a launch: 14.8 -> 14.8 us at 18944 x 3584 in 8 bits, 15.2 -> 15.4 in 6 (bfloat16).
+  uint32_t upper[TWO ? NCH : 1];
+  if constexpr (TWO) {
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) upper[c] = tile_k0(lane, c, NCH) + 16 < (CS ? a.k_span : a.k_keep) ? ~0u : 0u;
+  }
   // QKV: loads are issued through the resources of the matrix of the body being fetched, rebuilt from that matrix's
   // pointers when the matrix changes (a select between ready-made resources ends up in vector registers, and every
   // load through such a resource becomes a loop over its distinct values)
@@ -460,10 +468,10 @@ __device__ __forceinline__ bool stream_phase(const StreamArgs& a, uint4* xs /* L
       RawCodes<BITS, 4> raw;
 #pragma unroll
       for (int i = 0; i < BITS; ++i) raw.w[i] = i < 4 ? wa[i & 3] : wb[BITS == 6 ? i & 1 : i & 3];
-      const CodeGroup<BITS, BF16> g = make_code_group<BITS, BF16, W>(sbits, zero);
+      const CodeGroup<BITS, BF16> g = make_code_group<BITS, BF16, W>(sbits, zero), gu = TWO ? mask_code_group<BITS>(g, upper[TWO ? c : 0]) : g;
 #pragma unroll
       for (int q = 0; q < 4; ++q)
-        ac = mfma_16x16x32<BF16>(XREG ? xr[XREG ? c : 0][q] : xs[(c * 4 + q) * 64 + lane], code_step<BITS, BF16, 4, W>(raw, q, g, cm), ac);
+        ac = mfma_16x16x32<BF16>(XREG ? xr[XREG ? c : 0][q] : xs[(c * 4 + q) * 64 + lane], code_step<BITS, BF16, 4, W>(raw, q, q < 2 ? g : gu, cm), ac);
     }
   };
 
