@@ -403,11 +403,12 @@ static inline GemmRoute gemm_route(const LinearArgs& a, int xm) {
   // 11.2), and a tall matrix in the other kernel would no longer share a launch with short ones: 8192 + 1024 + 1024 rows x 8192
   // columns at 8 tokens 17.5 us in one launch, 28 in three.  From 9 tokens on such a set is two launches, 0.92..1.0 of the time
   // of one at 17..32 tokens and 1.0..1.17 at 9..16 (8192 + 1024 + 1024 x 8192 22.3 -> 21.9, x 4096 15.4 -> 15.7).
-  // (From 375 row tiles: 6000 x 4096 at 9 / 16 / 32 tokens 9.6 / 9.8 / 13.0 there, 8.8 / 9.0 / 9.9 here, x 9472 17.0 / 18.8 / 26.6 and
-  // 14.2 / 15.1 / 17.9; with 256 level at 17..32 tokens, 14 % the other way at 9.)  Column segments, whose activations a wave
+  // (Below 400 row tiles a tall matrix by itself is still faster here, 6000 x 4096 at 9 / 16 / 32 tokens 9.6 / 9.8 / 13.0 there, 8.8 / 9.0 /
+  // 9.9 here, but in a set with short ones it costs a launch of its own: 6000 + 1536 rows x 2560 columns at 9 / 32 tokens 8.1 / 10.3 in
+  // one launch, 13.6 / 16.5 in two, x 4096 12.2 / 16.9 and 14.8 / 17.9, x 8192 18.7 / 26.0 and 22.0 / 28.1.)  Column segments, whose activations a wave
   // of the other kernel gathers for itself, come here from 17 tokens on at any height: 4096 x 4096, 108 of 128, at 24 / 32
   // tokens 10.6 / 11.1 there, 9.4 / 9.7 here, 2560 x 5120, 54 of 64, 11.8 and 10.9; at 16 tokens 8.5 and 8.3, at 9 8.1 and 8.2.
-  const bool tall = row_tiles >= 375 && a.M >= 9 && !(xm == 1 && smallm_pre(a));
+  const bool tall = row_tiles >= 400 && a.M >= 9 && !(xm == 1 && smallm_pre(a));
   if (smallm_takes(a, xm == 1) && !(pipe && (tall || (xm == 2 && a.M >= 17)))) return kSmallM;
   if (pipe && a.M <= 64) return kPipe;
   // What neither takes (rows of fewer than eight groups; above the decode batches, or on tall matrices from 9 tokens on,
