@@ -81,9 +81,11 @@ __global__ __launch_bounds__((PipeShape<AF, BF, WN, KG, KQ, G, NX, NW, BITS>::Th
   constexpr int BM = S::BM, BN = S::BN, U = S::U, KS = S::KS, XM = S::XM, WM = S::WM;
   // A slab's activations land by the barrier before its use and not one earlier: its first fragments are then read behind that
   // barrier, but with three or four buffers the loads have a slab more of time.  Small tiles wait for them otherwise, and so do
-  // segments, whose movers still clear columns (two decoder layers at 48 tokens 140 -> 125 us a pass, the attention block at 1000
-  // tokens 106 -> 103; prefixes in 96..128-token tiles 4 % the other way: 5120 x 4096 at 512 tokens 31.2 -> 33.2 us).
-  constexpr bool XLate = S::Small ? NX <= 4 : SEG && NX == 3;
+  // segments in tiles of three buffers, whose movers still clear columns (two decoder layers at 48 tokens 140 -> 125 us a pass, the
+  // attention block at 1000 tokens 106 -> 103), and 96 tokens with three buffers, i.e. codes of 8 and 6 bits (12185 x 4096 at 333 tokens
+  // 67.5 -> 56.4 and 75.8 -> 65.3 us; 73.2 with 6 bits before units were placed by bank_key).  Prefixes in 96..112-token tiles of four
+  // buffers and in 128-token ones go the other way (4 bits, 5120 x 4096 at 512 tokens 31.2 -> 33.2 us).
+  constexpr bool XLate = S::Small ? NX <= 4 : NX == 3 && (SEG || AF == 6);
   extern __shared__ __align__(16) unsigned char smem[];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
