@@ -51,9 +51,15 @@ struct PipeShape {
   static constexpr int XI = XBytes / 1024, WI = WBytes / 1024;   // loads of 64 x 16 bytes
   static constexpr bool Small = AF * BF <= 9;
   static constexpr int XM = Small ? 4 : 2, WM = Small && WI % 2 == 0 ? 2 : 1;   // waves that move activations, codes
+  // In 32 x 32 tiles of 8-bit codes (a slab is 32 loads of activations and 16 of codes) the codes, which come from memory, must not wait:
+  // the two movers of activations that share a SIMD with the movers of codes stand by, and the other two take their loads.
+  // 4096 x 12185 at 40 tokens 33.5 -> 26.8 us, x 4096 12.0 -> 10.8 (with the other pair standing by 31.3 and 11.7).  Rows of up to three
+  // slabs are mostly the start, which four movers make shorter (4096 x 1024 at 40 tokens 5.4 us, with two 5.7).
+  static constexpr bool TwoStandBy = BITS == 8 && AF == 2 && BF == 1;
+  static constexpr int MostSlabsOfFour = 3;
   static constexpr int Threads = (kPipeConsumers + XM + WM + 1) * kWave;
   static_assert(WBytes % 1024 == 0 && XI % XM == 0, "whole loads, the same number for each mover");
-  static constexpr int XPW = XI / XM, WPW = WI / WM;
+  static constexpr int XPW = XI / (TwoStandBy ? XM / 2 : XM), WPW = WI / WM;   // (the most that a wave moves of a slab)
   static constexpr int SZ = 2 * BN * 8 * 4;                    // two windows of eight groups
   static constexpr int W0 = NX * XBytes, SZ0 = W0 + NW * WBytes, Lds = SZ0 + SZ;
   static_assert((NX - 1) * XPW <= 63 && (NW - 1) * WPW <= 63, "loads in flight are counted in six bits");
@@ -156,94 +162,99 @@ __global__ __launch_bounds__((PipeShape<AF, BF, WN, KG, KQ, G, NX, NW, BITS>::Th
     };
     if (wave < kPipeConsumers + XM) {
       // ---- activations
-      const int d = wave - kPipeConsumers;
-      const int mt = a.M - m0 < BM ? a.M - m0 : BM;
-      const int ldx2 = (int)a.ldx * 2;
-      // rows past the last token lie beyond the resource and read as zero
-      const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<half_t*>(a.x + (size_t)m0 * a.ldx), 0,
-                                                                          (mt - 1) * ldx2 + km.k_keep * 2, kBufferWord3);
-      // Byte offset of this lane's unit of load k in slab `slab`.  Segments divide the groups, so every group is alike: its
-      // kept columns are `kpg` consecutive ones of x, a block's kept columns its first ones, contiguous.  A slab that lies
-      // wholly in the row takes slab 0's offsets and a scalar (a load is then two instructions; a mover issues one
-      // every 60 clocks otherwise).
-      const int kpg = SEG ? (kGroup >> seg_shift) * km.cs_keep : kGroup;
-      const int partial = SEG ? km.cs_keep & 7 : 0, seg_log = 7 - seg_shift;   // columns in a segment's last block (even), segments of a group
-      auto unit = [&](int k, int slab) {
-        constexpr int CH = 16 * G;                       // chunks per token
-        const int v = (d + XM * k) * 64;
-        const int tok = v / CH + (CH < 64 ? lane / CH : 0);
-        const int c = (CH <= 64 ? lane % CH : v % CH + lane) ^ bank_key(tok);
-        const int g = slab * G + c / 16, k0 = (c % 16) * 8;   // group, column in it
-        int col = g * kpg + k0;
-        bool there = g * kGroup + k0 < km.k_keep;        // a prefix: its last block comes with what lies behind it
-        if constexpr (SEG) {
-          const int off = k0 & (km.cs_stride - 1);
-          col = g * kpg + (k0 >> seg_shift) * km.cs_keep + off;
-          there = off < km.cs_keep && g < ngroups;
-        }
-        return there ? tok * ldx2 + col * 2 : kBeyond;
-      };
-      const int nwhole = SEG ? ngroups / G : km.k_keep / (G * kGroup);
-      // The last block of a prefix whose columns are not whole blocks, in LDS: what lies behind the kept columns is cleared, and
-      // an odd last column, whose word may lie partly past the resource and then reads as zero, is put in place from a load of
-      // its own.  A lane per token, each mover the tokens that it has loaded itself.  (Added up in the epilogue, column after
-      // column, they cost a chain of loads per fragment: 4096 x 9318 at 48 / 777 tokens 22.9 / 106 us, so 18.6 / 70.)
-      const int tail = SEG ? 0 : km.k_keep & 7;
-      constexpr int TI = (BM + 63) / 64;
-      uint32_t odd[TI];
-#pragma unroll
-      for (int i = 0; i < TI; ++i) {
-        const int t = lane + 64 * i;
-        odd[i] = (tail & 1) && t < mt ? (uint32_t)__builtin_bit_cast(uint16_t, a.x[(size_t)(m0 + t) * a.ldx + km.k_keep - 1]) : 0u;
-      }
-      int first[S::XPW];                                 // (of use when there is a whole slab: then slab 0 is one)
-#pragma unroll
-      for (int k = 0; k < S::XPW; ++k) first[k] = unit(k, 0);
-      walk(std::integral_constant<int, NX>(), std::integral_constant<int, S::XPW>(), std::integral_constant<bool, XLate>(), [&](int slab, int buf) {
-        lds_byte* const to = lds + buf * S::XBytes + d * 1024;
-        if (slab < nwhole) {
-#pragma unroll
-          for (int k = 0; k < S::XPW; ++k)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void*)(to + k * (XM * 1024)), 16, first[k], slab * (G * kpg * 2), 0, 0);
-        } else {
-#pragma unroll
-          for (int k = 0; k < S::XPW; ++k)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void*)(to + k * (XM * 1024)), 16, unit(k, slab), 0, 0, 0);
-        }
-      }, tail == 0 ? -1 : nslab > 1 ? nslab - (XLate ? 1 : 2) : 0, [&]() {
-        const int c = km.k_keep / 8 - (nslab - 1) * (16 * G), keep = tail & ~1;   // chunk in the slab, columns that stay
-        auto m = [&](int i) { return keep > i ? ~0u : 0u; };
+      auto move_activations = [&](auto movers, const int d) {   // (d: which of the movers)
+        constexpr int XM = decltype(movers)::value, XPW = S::XI / XM;
+        const int mt = a.M - m0 < BM ? a.M - m0 : BM;
+        const int ldx2 = (int)a.ldx * 2;
+        // rows past the last token lie beyond the resource and read as zero
+        const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<half_t*>(a.x + (size_t)m0 * a.ldx), 0,
+                                                                            (mt - 1) * ldx2 + km.k_keep * 2, kBufferWord3);
+        // Byte offset of this lane's unit of load k in slab `slab`.  Segments divide the groups, so every group is alike: its
+        // kept columns are `kpg` consecutive ones of x, a block's kept columns its first ones, contiguous.  A slab that lies
+        // wholly in the row takes slab 0's offsets and a scalar (a load is then two instructions; a mover issues one
+        // every 60 clocks otherwise).
+        const int kpg = SEG ? (kGroup >> seg_shift) * km.cs_keep : kGroup;
+        const int partial = SEG ? km.cs_keep & 7 : 0, seg_log = 7 - seg_shift;   // columns in a segment's last block (even), segments of a group
+        auto unit = [&](int k, int slab) {
+          constexpr int CH = 16 * G;                       // chunks per token
+          const int v = (d + XM * k) * 64;
+          const int tok = v / CH + (CH < 64 ? lane / CH : 0);
+          const int c = (CH <= 64 ? lane % CH : v % CH + lane) ^ bank_key(tok);
+          const int g = slab * G + c / 16, k0 = (c % 16) * 8;   // group, column in it
+          int col = g * kpg + k0;
+          bool there = g * kGroup + k0 < km.k_keep;        // a prefix: its last block comes with what lies behind it
+          if constexpr (SEG) {
+            const int off = k0 & (km.cs_stride - 1);
+            col = g * kpg + (k0 >> seg_shift) * km.cs_keep + off;
+            there = off < km.cs_keep && g < ngroups;
+          }
+          return there ? tok * ldx2 + col * 2 : kBeyond;
+        };
+        const int nwhole = SEG ? ngroups / G : km.k_keep / (G * kGroup);
+        // The last block of a prefix whose columns are not whole blocks, in LDS: what lies behind the kept columns is cleared, and
+        // an odd last column, whose word may lie partly past the resource and then reads as zero, is put in place from a load of
+        // its own.  A lane per token, each mover the tokens that it has loaded itself.  (Added up in the epilogue, column after
+        // column, they cost a chain of loads per fragment: 4096 x 9318 at 48 / 777 tokens 22.9 / 106 us, so 18.6 / 70.)
+        const int tail = SEG ? 0 : km.k_keep & 7;
+        constexpr int TI = (BM + 63) / 64;
+        uint32_t odd[TI];
 #pragma unroll
         for (int i = 0; i < TI; ++i) {
           const int t = lane + 64 * i;
-          if (t >= BM || (t * G / 4) % XM != d) continue;
-          uint4* p = reinterpret_cast<uint4*>(smem + (nslab - 1) % NX * S::XBytes) + t * (16 * G) + (c ^ bank_key(t));
-          uint4 v = *p;
-          v.x = (v.x & m(0)) | (tail == 1 ? odd[i] : 0u);
-          v.y = (v.y & m(2)) | (tail == 3 ? odd[i] : 0u);
-          v.z = (v.z & m(4)) | (tail == 5 ? odd[i] : 0u);
-          v.w = tail == 7 ? odd[i] : 0u;
-          *p = v;
+          odd[i] = (tail & 1) && t < mt ? (uint32_t)__builtin_bit_cast(uint16_t, a.x[(size_t)(m0 + t) * a.ldx + km.k_keep - 1]) : 0u;
         }
-      }, [&](int slab) {
-        // Segments: the block that holds a segment's last kept columns arrives with the next segment's first ones (or the next
-        // token's) behind them, which are cleared here, in the mover's own tokens (masked in the registers of the eight waves
-        // that multiply, they were four vector instructions per activation fragment and step: 1000 x 4096 x 4096 in bfloat16, 108
-        // of 128 columns, 62 -> 41 us, and 128 tokens a tile did not fit the registers).
-        if constexpr (SEG) {
-          if (!partial || slab >= nslab) return;
-          unsigned char* const to = smem + slab % NX * S::XBytes;
-          constexpr int TU = 4 / G;                      // tokens per load
-          for (int i = lane; i < BM / XM * G << seg_log; i += 64) {
-            const int sg = i & ((1 << seg_log) - 1), g = (i >> seg_log) % G, j = (i >> seg_log) / G;
-            const int t = (j / TU * XM + d) * TU + j % TU, c = g * 16 + (sg << (seg_shift - 3)) + km.cs_keep / 8;
-            uint32_t* p = reinterpret_cast<uint32_t*>(to + (t * (16 * G) + (c ^ bank_key(t))) * 16);
-            if (partial == 2) p[1] = 0u;
-            if (partial <= 4) *reinterpret_cast<u32x2_t*>(p + 2) = u32x2_t{0u, 0u};
-            else p[3] = 0u;
+        int first[XPW];                                 // (of use when there is a whole slab: then slab 0 is one)
+#pragma unroll
+        for (int k = 0; k < XPW; ++k) first[k] = unit(k, 0);
+        walk(std::integral_constant<int, NX>(), std::integral_constant<int, XPW>(), std::integral_constant<bool, XLate>(), [&](int slab, int buf) {
+          lds_byte* const to = lds + buf * S::XBytes + d * 1024;
+          if (slab < nwhole) {
+#pragma unroll
+            for (int k = 0; k < XPW; ++k)
+              __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void*)(to + k * (XM * 1024)), 16, first[k], slab * (G * kpg * 2), 0, 0);
+          } else {
+#pragma unroll
+            for (int k = 0; k < XPW; ++k)
+              __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void*)(to + k * (XM * 1024)), 16, unit(k, slab), 0, 0, 0);
           }
-        }
-      });
+        }, tail == 0 ? -1 : nslab > 1 ? nslab - (XLate ? 1 : 2) : 0, [&]() {
+          const int c = km.k_keep / 8 - (nslab - 1) * (16 * G), keep = tail & ~1;   // chunk in the slab, columns that stay
+          auto m = [&](int i) { return keep > i ? ~0u : 0u; };
+#pragma unroll
+          for (int i = 0; i < TI; ++i) {
+            const int t = lane + 64 * i;
+            if (t >= BM || (t * G / 4) % XM != d) continue;
+            uint4* p = reinterpret_cast<uint4*>(smem + (nslab - 1) % NX * S::XBytes) + t * (16 * G) + (c ^ bank_key(t));
+            uint4 v = *p;
+            v.x = (v.x & m(0)) | (tail == 1 ? odd[i] : 0u);
+            v.y = (v.y & m(2)) | (tail == 3 ? odd[i] : 0u);
+            v.z = (v.z & m(4)) | (tail == 5 ? odd[i] : 0u);
+            v.w = tail == 7 ? odd[i] : 0u;
+            *p = v;
+          }
+        }, [&](int slab) {
+          // Segments: the block that holds a segment's last kept columns arrives with the next segment's first ones (or the next
+          // token's) behind them, which are cleared here, in the mover's own tokens (masked in the registers of the eight waves
+          // that multiply, they were four vector instructions per activation fragment and step: 1000 x 4096 x 4096 in bfloat16, 108
+          // of 128 columns, 62 -> 41 us, and 128 tokens a tile did not fit the registers).
+          if constexpr (SEG) {
+            if (!partial || slab >= nslab) return;
+            unsigned char* const to = smem + slab % NX * S::XBytes;
+            constexpr int TU = 4 / G;                      // tokens per load
+            for (int i = lane; i < BM / XM * G << seg_log; i += 64) {
+              const int sg = i & ((1 << seg_log) - 1), g = (i >> seg_log) % G, j = (i >> seg_log) / G;
+              const int t = (j / TU * XM + d) * TU + j % TU, c = g * 16 + (sg << (seg_shift - 3)) + km.cs_keep / 8;
+              uint32_t* p = reinterpret_cast<uint32_t*>(to + (t * (16 * G) + (c ^ bank_key(t))) * 16);
+              if (partial == 2) p[1] = 0u;
+              if (partial <= 4) *reinterpret_cast<u32x2_t*>(p + 2) = u32x2_t{0u, 0u};
+              else p[3] = 0u;
+            }
+          }
+        });
+      };
+      if (!S::TwoStandBy || nslab <= S::MostSlabsOfFour) move_activations(std::integral_constant<int, XM>(), wave - kPipeConsumers);
+      else if (wave >= kPipeConsumers + XM / 2) move_activations(std::integral_constant<int, XM / 2>(), wave - kPipeConsumers - XM / 2);
+      else for (int it = 0; it <= nslab; ++it) pipe_barrier();
       return;
     }
     if (wave < kPipeConsumers + XM + WM) {
