@@ -451,7 +451,7 @@ __device__ __forceinline__ bool stream_phase(const StreamArgs& a, uint4* xs /* L
     for (int q = 0; q < 4; ++q) acc = mfma_16x16x32<BF16>(xf[q], dequant_word4<BF16>(wv[q], gq[HI ? q : 0], mg), acc);
   };
 
-  const CodeMagic cm = make_code_magic<BITS, BF16>();
+  const CodeMagic cm = WIDE ? make_code_magic<BITS, BF16>() : CodeMagic{};   // (its registers are pinned: only where they are read)
   bool wide_row = false;   // bfloat16: a scale of the row asks for the wide unpack (codes.h)
   auto needs_wide = [&](const uint32_t (&sc)[(2 * NGQ + 3) / 4]) {
     uint32_t largest = 0;
