@@ -111,9 +111,9 @@ struct StreamArgs {
 // BITS = 8, 6, 3: the same walk over codes of those widths.  A lane's 32 columns of a tile are BITS words, unpacked by codes.h
 // into matrix operands in column order, so the activations are staged in memory order.  Whether there are zero points is a
 // run-time matter there (the resource of none is empty), and the scales of columns past the last kept one count as zero.
-// rows per loop body: four tiles and more in flight
+// rows per loop body: four tiles and more in flight (rows of three tiles: three)
 constexpr int stream_rows(int tiles_per_row, bool qkv) { return qkv ? 2 : (tiles_per_row >= 4 ? 1 : 4 / tiles_per_row); }
-// a lane's words of a tile: BITS of them, in two registers tuples where there are more than four
+// a lane's words of a tile: BITS of them, in two register tuples where there are more than four
 template <int BITS> struct TileCodes { typedef u32x4_t A; typedef u32x4_t B; };
 template <> struct TileCodes<3> { typedef u32x3_t A; typedef u32x2_t B; };
 template <> struct TileCodes<6> { typedef u32x4_t A; typedef u32x2_t B; };
@@ -761,7 +761,9 @@ static hipError_t stream_one(const LinearArgs& a, hipStream_t stream, bool* done
 template <int BITS, bool BF16, bool CS>
 static hipError_t stream_wide_nch(const StreamArgs& s, int nch, hipStream_t stream) {
   switch (nch) {
-    case 1: return stream_launch<1, 1, true, BF16, true, false, false, false, CS, BITS>(s, stream);
+    case 1:
+      if constexpr (BITS != 6) return stream_launch<1, 1, true, BF16, true, false, false, false, CS, BITS>(s, stream);   // (stream_wide_takes)
+      else return hipErrorInvalidValue;
     case 2: return stream_launch<2, 1, true, BF16, true, false, false, false, CS, BITS>(s, stream);
     case 3: return stream_launch<3, 1, true, BF16, true, false, false, false, CS, BITS>(s, stream);
     case 4: return stream_launch<4, 1, true, BF16, true, false, false, false, CS, BITS>(s, stream);
@@ -777,16 +779,18 @@ static hipError_t stream_wide_nch(const StreamArgs& s, int nch, hipStream_t stre
 // 10.2 / 12.7 / 11.8 us (bfloat16 9.3 / 10.0 / 10.9 against 14.9 / 17.1 / 15.5), 4096 x 12185 7.7 / 9.9 / 10.2 against 10.2 / 12.9 / 12.4,
 // 512 x 14336 5.5 / 6.3 / 6.5 against 7.0 / 7.6 / 8.0, 2048 x 7168 4.2 / 5.1 / 5.4 against 5.4 / 6.6 / 7.0, 3000 x 4096 4.4 / 5.3 / 5.1
 // against 5.3 / 6.4 / 6.4, 4096 x 1024 4.5 / 4.9 / 4.4 against 5.0 / 4.4 / 5.2; below the line 2048 x 2048 4.5 / 4.9 / 4.5 against 3.9 / 3.6 / 4.2.
-static inline int stream_min_rows_wide(int nch, int bits) {
-  if (nch >= 5) return 512;
-  if (nch >= 3) return 2048;
-  return nch == 2 ? 2560 : bits == 6 ? INT32_MAX : 4096;
+// Rows of one tile of 6-bit codes stay with wbits.hip at any height.
+static inline bool stream_wide_takes(const LinearArgs& a) {
+  if (!(a.km.cs_stride != 0 ? stream_shape_cs(a, 8) : stream_shape(a, 8))) return false;
+  const int nch = row_tiles(a.km.k_span);
+  if (nch == 1 && a.bits == 6) return false;
+  return a.km.n_keep >= (nch >= 5 ? 512 : nch >= 3 ? 2048 : nch == 2 ? 2560 : 4096);
 }
 template <int BITS>
 static hipError_t stream_wide(const LinearArgs& a, hipStream_t stream, bool* done) {
   const bool cs = a.km.cs_stride != 0;
-  const int nch = row_tiles(cs ? a.km.k_span : a.km.k_keep);
-  *done = (cs ? stream_shape_cs(a, 8) : stream_shape(a, 8)) && a.km.n_keep >= stream_min_rows_wide(nch, BITS);
+  const int nch = row_tiles(a.km.k_span);
+  *done = stream_wide_takes(a);
   if (!*done) return hipSuccess;
   const StreamArgs s = stream_args(a);
   if (a.bf16) return cs ? stream_wide_nch<BITS, true, true>(s, nch, stream) : stream_wide_nch<BITS, true, false>(s, nch, stream);
