@@ -284,6 +284,7 @@ hipError_t launch_w4_gemv_stream(const LinearArgs& a, hipStream_t stream, bool* 
 hipError_t launch_w8_gemv_stream(const LinearArgs& a, hipStream_t stream, bool* done);
 hipError_t launch_w6_gemv_stream(const LinearArgs& a, hipStream_t stream, bool* done);
 hipError_t launch_w3_gemv_stream(const LinearArgs& a, hipStream_t stream, bool* done);
+int wide_walk_rows(const LinearArgs& a);   // rows of a body of that walk for one token, 0 where it does not serve
 hipError_t launch_w4_gate_up_stream(const LinearArgs* probs, hipStream_t stream, bool* done);
 hipError_t launch_w4_gate_up_stream_probe(const LinearArgs* probs, hipStream_t stream, bool* done);
 hipError_t launch_w4_gemv_stream_bf16(const LinearArgs& a, hipStream_t stream, bool* done);

@@ -135,3 +135,21 @@ def test_decode_batches_that_the_pipelined_kernel_takes(bf16):
         for M in (9, 17, 32):
             assert uq.uniql_w4_linear_kernel(N, 8192, None, M, bf16=bf16)[0] == want
         assert uq.uniql_w4_linear_kernel(N, 8192, None, 8, bf16=bf16)[0] == BATCH
+
+
+# one token of 8-, 6- and 3-bit codes: the walk's rows at a time, and what it leaves to the other kernels
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("bits", [8, 6, 3])
+def test_one_token_of_wide_codes(bits, bf16):
+    def rows(N, K, keep=None):
+        c = uq.uniql_w4_linear_kernel(N, K, keep, 1, bits=bits, bf16=bf16)
+        assert c[0] == STREAM and c[1] == c[3] == int(c[2] > 0)
+        return c[2]
+    for N, K, want in ((4096, 1024, 0 if bits == 6 else 4), (4095, 1024, 0), (2560, 4096, 2), (2559, 4096, 0), (2048, 6144, 1), (2047, 6144, 0), (2048, 8192, 1),
+                       (512, 10240, 1), (511, 10240, 0), (512, 16384, 1), (4096, 5120, 0), (4096, 8448, 0), (4096, 16512, 0)):
+        assert rows(N, K) == want, (N, K)
+    assert rows(4096, 8192, KeepDesc(k_keep=4096)) == 2 and rows(4096, 5120, KeepDesc(k_keep=4096)) == 2
+    assert rows(4096, 4096, KeepDesc(k_keep=7)) == 0
+    assert rows(4096, 6144, seg(8, 5)) == 1 and rows(4096, 6144, seg(24, 5)) == 1 and rows(4096, 6144, seg(12, 5)) == 0
+    assert rows(4096, 4096, KeepDesc(row_seg_stride=64, row_seg_keep=40, row_seg_limit=4096)) == 2
+    assert rows(4096, 4096, KeepDesc(row_seg_stride=64, row_seg_keep=39, row_seg_limit=4096)) == 0
