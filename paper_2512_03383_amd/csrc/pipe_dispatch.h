@@ -55,7 +55,6 @@ static inline PipeTile pipe_pick(const LinearArgs* p, int n) {
     if (way == kPipeMixed && t.af != (M <= 48 ? 3 : 4)) continue;
     if (BITS > 4 && way != kPipeGroups && ((t.af == 4 && t.bf == 3) || t.af == 7)) continue;
     if (BITS > 4 && way == kPipeGroups && t.bf == 2) continue;
-    if (seg && t.af == 8 && M <= 384) continue;   // (up to three token tiles the smaller ones leave less of the last one empty)
     long long tiles = 0;
     for (int i = 0; i < n; ++i) tiles += (p[i].km.n_keep + t.wn * t.bf * 16 - 1) / (t.wn * t.bf * 16);
     tiles *= (M + 16 * t.af - 1) / (16 * t.af);

@@ -22,9 +22,7 @@ def kept_columns(K, segments):
 def tiles(bits, segments):
     """(tokens, rows, waves along K) of every tile that the kernel is built with for a width and a kind of column rule."""
     narrow = bits <= 4
-    t = {(16, 32, 4), (32, 32, 4), (48, 64, 4), (48, 96, 4), (64, 64, 4), (96, 128, 2), (64, 128, 2), (64, 64, 2)}
+    t = {(16, 32, 4), (32, 32, 4), (48, 64, 4), (48, 96, 4), (64, 64, 4), (96, 128, 2), (64, 128, 2), (64, 64, 2), (128, 128, 2)}
     if narrow:
         t |= {(16, 64, 4), (32, 64, 4), (64, 96, 4), (112, 128, 2)}
-    if not segments:
-        t |= {(128, 128, 2)}
     return t

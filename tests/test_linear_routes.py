@@ -153,3 +153,12 @@ def test_one_token_of_wide_codes(bits, bf16):
     assert rows(4096, 6144, seg(8, 5)) == 1 and rows(4096, 6144, seg(24, 5)) == 1 and rows(4096, 6144, seg(12, 5)) == 0
     assert rows(4096, 4096, KeepDesc(row_seg_stride=64, row_seg_keep=40, row_seg_limit=4096)) == 2
     assert rows(4096, 4096, KeepDesc(row_seg_stride=64, row_seg_keep=39, row_seg_limit=4096)) == 0
+
+
+# column segments: tiles of 128 tokens wherever the cost of a launch says so, from one token tile on (16384 x 4096, 108 of 128 columns,
+# 256 tokens: 52 -> 41 us)
+@pytest.mark.parametrize("bits", [4, 8, 6, 3])
+def test_tall_segments_take_128_tokens(bits):
+    assert uq.uniql_w4_linear_kernel(16384, 4096, seg(128, 108), 256, bits=bits)[:3] == (PIPE, 128, 128)
+    assert uq.uniql_w4_linear_kernel(24576, 4096, seg(128, 108), 128, bits=bits)[:3] == (PIPE, 128, 128)
+    assert uq.uniql_w4_linear_kernel(4096, 4096, seg(128, 108), 256, bits=bits)[:3] == (PIPE, 64, 64)
