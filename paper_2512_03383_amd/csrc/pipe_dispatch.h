@@ -24,7 +24,7 @@ static inline float launch_cost(long long tiles, float steps, TileCost c, float 
 
 struct PipeTile {
   int af, bf, wn, g;
-  TileCost prefix, seg;   // per slab of g groups; segments take the masks on top
+  TileCost prefix, seg;   // per slab of g groups
   float us;               // of the launch
 };
 
@@ -32,8 +32,8 @@ template <int BITS>
 static inline PipeTile pipe_pick(const LinearArgs* p, int n) {
   // groups: 32- and 64-row tiles; mixed: 64- and 96-row tiles (96 rows x 64 tokens do not fit with 8-bit codes);
   // halves: rows x tokens from 128 x 128 down to 64 x 64 (8-bit codes: no 112, its buffers)
-  // (128 x 128 takes all of a wave's 168 registers: in bfloat16 one to four words go to scratch around the loop, none in it,
-  // and up to 18 in the loop of the wide unpack)
+  // (128 x 128 takes all of a wave's 168 registers: with 8 and 6 bits a word (fp16) or up to five (bfloat16) goes to scratch around
+  // the loop, and 2 to 17 words in the loop of the bfloat16 unpack's wide form)
   static const PipeTile groups[] = {{1, 1, 2, 4, {0.50f, 0.05f}, {0.55f, 0.05f}, 0.f}, {1, 2, 2, 4, {0.90f, 0.05f}, {0.95f, 0.05f}, 0.f},
                                     {2, 1, 2, 4, {0.55f, 0.05f}, {0.65f, 0.05f}, 0.f}, {2, 2, 2, 4, {1.0f, 0.05f}, {1.05f, 0.05f}, 0.f}};
   static const PipeTile mixed[] = {{3, 2, 2, 2, {0.62f, 0.07f}, {0.70f, 0.05f}, 0.f}, {3, 3, 2, 2, {0.80f, 0.07f}, {0.90f, 0.05f}, 0.f},
@@ -76,6 +76,7 @@ template <int AF, int BF, int WN, int KG, int KQ, int G, int NX, int BITS, bool 
 static hipError_t pipe_tile(const LinearArgs* p, int n, hipStream_t s) {
   constexpr int BN = WN * BF * 16;
   constexpr int NW = pipe_nw(NX * 16 * AF * G * 256, BN * 64, BN * G * BITS * 16, 8);
+  static_assert(PipeShape<AF, BF, WN, KG, KQ, G, NX, NW, BITS>::Threads <= kPipeMostThreads, "pipe_pick counts the threads of a grid with the largest block");
   return pipe_launch<AF, BF, WN, KG, KQ, G, NX, NW, BITS, BF16, SEG>(p, n, s);
 }
 

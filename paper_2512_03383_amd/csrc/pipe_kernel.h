@@ -1,13 +1,13 @@
 // Linears of more than a few tokens on MFMA for codes of 8, 6, 4 and 3 bits: y[M][n_keep] = x[M][k_keep] * W'^T, with the
 // loads in waves of their own.
 //
-// A block of twelve waves (fifteen, small tiles) owns BN = WN * BF * 16 rows and BM = 16 AF tokens.  The columns go by in slabs of G groups; a slab
-// is the block's activations and packed codes of those groups.
+// A block of twelve waves (small tiles: fourteen or fifteen) owns BN = WN * BF * 16 rows and BM = 16 AF tokens.  The columns go by in
+// slabs of G groups; a slab is the block's activations and packed codes of those groups.
 //  - Two waves (four where the block's registers allow) do nothing but move activations into LDS (128-bit loads that write LDS
 //    directly: no registers, no LDS instructions), up to NX - 1 slabs ahead, and one more (two) codes, NW - 1 slabs ahead: loads
 //    return in order, and codes come from memory where activations come from the L2.  A mover issues a load every 60 clocks and a
-//    CU takes one every 17, so in tiles with little to multiply the moving is what a slab takes: 48 tokens, 35 % of the channels,
-//    148 us a pass of two decoder layers with three movers, 140 with six.  The next slab is there one barrier early (but see XLate).
+//    CU takes one every 17, so in tiles with little to multiply the moving is what a slab takes: 48 tokens, 35 % of the channels
+//    pruned, 148 us a pass of two decoder layers with three movers, 140 with six.  The next slab is there one barrier early (but see XLate).
 //  - One wave does the same for scales and zero points, eight groups of a row at a time, through registers.
 //  - Eight waves, WN along the rows times KG along the groups of a slab times KQ along the four steps of a group, read codes
 //    and activations from LDS, unpack in registers (codes.h) and multiply.  They never wait for memory, and the first
@@ -69,7 +69,8 @@ struct PipeShape {
 };
 
 // What the place of a 16-byte unit in LDS is permuted by, from its token or row.  A 128-bit LDS read serves 16 lanes a clock, and
-// these are not 16 consecutive ones: 0-3, 12-15 and 20-27 go together, then 4-11, 16-19 and 28-31 (likewise from lane 32 on).  Lane
+// these are not 16 consecutive ones: 0-3, 12-15 and 20-27 go together, then 4-11, 16-19 and 28-31 (likewise from lane 32 on; measured
+// pair by pair, two lanes of each of eight waves reading one bank at two addresses: 28.2 clocks a read within a set, 24.1 across).  Lane
 // l of a fragment reads row l % 16, chunk 4 (l / 16) + t, so rows 0-3 and 12-15 of one chunk share a clock with rows 4-11 of the
 // chunk four further on: under r % 16 alone each of these meets one of the former in its bank group (SQ_LDS_BANK_CONFLICT was
 // half of the LDS's busy clocks, which were half of all: 8-bit gate at 512 tokens).  With bit 2 of the row added to bit 3 the
@@ -133,9 +134,9 @@ __global__ __launch_bounds__((PipeShape<AF, BF, WN, KG, KQ, G, NX, NW, BITS>::Th
     typedef __attribute__((address_space(3))) void lds_void;
     lds_byte* const lds = (lds_byte*)smem;
     // A mover's walk: slabs 0 .. N - 2 to begin with, then, one barrier per slab, the slab that takes the buffer which
-    // everybody has left.  Before barrier `it` the slabs up to it + 1 have landed.  Before barrier `extra_at` (the one that
-    // publishes the last slab, or -1 for none) the mover does something more; with column segments it does `landed` for every slab
-    // before the barrier that publishes it.
+    // everybody has left.  Before barrier `it` the slabs up to it + 1 have landed (codes, and activations unless XLate), or up to `it`
+    // (`late`: activations with XLate).  Before barrier `extra_at` (the one that publishes the last slab, or -1 for none) the mover does
+    // something more; with column segments it does `landed` for every slab before the barrier that publishes it.
     auto walk = [&](auto n, auto per, auto late, auto&& move, int extra_at, auto&& extra, auto&& landed) {
       constexpr int N = decltype(n)::value, PER = decltype(per)::value, AHEAD = decltype(late)::value ? 0 : 1;
 #pragma unroll
@@ -422,7 +423,7 @@ __global__ __launch_bounds__((PipeShape<AF, BF, WN, KG, KQ, G, NX, NW, BITS>::Th
   Group cur, ahead;
   CodeGroup<BITS, BF16> gq[BF];
   uint4 av[2][AF], wf[2][BF];
-  pipe_barrier();                         // slabs 0 and 1 are in LDS
+  pipe_barrier();                         // slab 0 is in LDS, and slab 1 (with XLate only its codes)
   const unsigned char *xsl = smem, *wsl = smem;
   read_group(wsl, 0, cur);
   if (!XLate) read_a(xsl, 0, av[0]);
@@ -477,7 +478,7 @@ __global__ __launch_bounds__((PipeShape<AF, BF, WN, KG, KQ, G, NX, NW, BITS>::Th
         for (int b = 0; b < BF; ++b) asm volatile("" : "+v"(wf[0][b].x), "+v"(wf[0][b].y), "+v"(wf[0][b].z), "+v"(wf[0][b].w));
         asm volatile("" : "+s"(end));     // (and the selection: 64 tokens x 64 rows, 5 % of the kernel)
       }
-      pipe_barrier();                     // slab it + 1 is in LDS, and nobody reads slab it - 1 any more
+      pipe_barrier();                     // slab it + 1 is in LDS (with XLate only its codes, slab it whole), nobody reads slab it - 1 any more
     }
   };
   if (!BF16 || !asks_wide(cur)) slabs(std::false_type());
