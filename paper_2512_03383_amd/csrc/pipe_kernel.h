@@ -136,13 +136,13 @@ __global__ __launch_bounds__((PipeShape<AF, BF, WN, KG, KQ, G, NX, NW, BITS>::Th
     // A mover's walk: slabs 0 .. N - 2 to begin with, then, one barrier per slab, the slab that takes the buffer which
     // everybody has left.  Before barrier `it` the slabs up to it + 1 have landed (codes, and activations unless XLate), or up to `it`
     // (`late`: activations with XLate).  Before barrier `extra_at` (the one that publishes the last slab, or -1 for none) the mover does
-    // something more; with column segments it does `landed` for every slab before the barrier that publishes it.
+    // something more; with column segments it does `landed` for every slab's buffer before the barrier that publishes it.
     auto walk = [&](auto n, auto per, auto late, auto&& move, int extra_at, auto&& extra, auto&& landed) {
       constexpr int N = decltype(n)::value, PER = decltype(per)::value, AHEAD = decltype(late)::value ? 0 : 1;
 #pragma unroll
       for (int p = 0; p < N - 1; ++p)
         if (p < nslab) move(p, p);
-      int buf = N - 1;
+      int buf = N - 1, lbuf = AHEAD;                     // the buffers of slabs it + N - 1 and it + AHEAD
       for (int it = 0; it < nslab; ++it) {
         if (it + (N > 3 || !AHEAD ? N - 2 : 2) < nslab) {
           asm volatile("s_waitcnt vmcnt(%0)" ::"n"((N - 2 - AHEAD) * PER) : "memory");
@@ -153,7 +153,8 @@ __global__ __launch_bounds__((PipeShape<AF, BF, WN, KG, KQ, G, NX, NW, BITS>::Th
         }
         if constexpr (SEG) {
           if (AHEAD && it == 0) landed(0);
-          landed(it + AHEAD);
+          if (it + AHEAD < nslab) landed(lbuf);
+          lbuf = lbuf + 1 == N ? 0 : lbuf + 1;
         }
         pipe_barrier();
         if (it + N - 1 < nslab) move(it + N - 1, buf);
@@ -204,6 +205,25 @@ __global__ __launch_bounds__((PipeShape<AF, BF, WN, KG, KQ, G, NX, NW, BITS>::Th
           const int t = lane + 64 * i;
           odd[i] = (tail & 1) && t < mt ? (uint32_t)__builtin_bit_cast(uint16_t, a.x[(size_t)(m0 + t) * a.ldx + km.k_keep - 1]) : 0u;
         }
+        // Segments: the block that holds a segment's last kept columns arrives with the next segment's first ones (or the next
+        // token's) behind them, which are cleared here, in the mover's own tokens (masked in the registers of the eight waves
+        // that multiply, they were four vector instructions per activation fragment and step: 1000 x 4096 x 4096 in bfloat16, 108
+        // of 128 columns, 62 -> 41 us, and 128 tokens a tile did not fit the registers).  Slabs are alike, so where those blocks lie is
+        // worked out once, a lane's block of each turn: for every slab anew it was what a slab of short segments took (6 of 8
+        // columns: 4096 x 8192 at 777 tokens in 112 x 128 tiles, 3 bits, 1.5 times as long, 32 x 32 tiles of 8 bits up to twice).  Lanes
+        // without a block clear the last one again (a test of each costs 5 % with 32 x 32 tiles).
+        const int blocks = (BM / XM * G) << seg_log, turns = partial ? (blocks + 63) / 64 : 0;
+        int clear[SEG ? XPW : 1];                        // (segments of eight columns: as many turns as loads)
+        if constexpr (SEG) {
+          constexpr int TU = 4 / G;                      // tokens per load
+#pragma unroll
+          for (int k = 0; k < XPW; ++k) {
+            const int i = lane + 64 * k < blocks ? lane + 64 * k : blocks - 1;
+            const int sg = i & ((1 << seg_log) - 1), g = (i >> seg_log) % G, j = (i >> seg_log) / G;
+            const int t = (j / TU * XM + d) * TU + j % TU, c = g * 16 + (sg << (seg_shift - 3)) + km.cs_keep / 8;
+            clear[k] = (t * (16 * G) + (c ^ bank_key(t))) * 16;
+          }
+        }
         int first[XPW];                                 // (of use when there is a whole slab: then slab 0 is one)
 #pragma unroll
         for (int k = 0; k < XPW; ++k) first[k] = unit(k, 0);
@@ -233,23 +253,19 @@ __global__ __launch_bounds__((PipeShape<AF, BF, WN, KG, KQ, G, NX, NW, BITS>::Th
             v.w = tail == 7 ? odd[i] : 0u;
             *p = v;
           }
-        }, [&](int slab) {
-          // Segments: the block that holds a segment's last kept columns arrives with the next segment's first ones (or the next
-          // token's) behind them, which are cleared here, in the mover's own tokens (masked in the registers of the eight waves
-          // that multiply, they were four vector instructions per activation fragment and step: 1000 x 4096 x 4096 in bfloat16, 108
-          // of 128 columns, 62 -> 41 us, and 128 tokens a tile did not fit the registers).
+        }, [&](int buf) {
           if constexpr (SEG) {
-            if (!partial || slab >= nslab) return;
-            unsigned char* const to = smem + slab % NX * S::XBytes;
-            constexpr int TU = 4 / G;                      // tokens per load
-            for (int i = lane; i < BM / XM * G << seg_log; i += 64) {
-              const int sg = i & ((1 << seg_log) - 1), g = (i >> seg_log) % G, j = (i >> seg_log) / G;
-              const int t = (j / TU * XM + d) * TU + j % TU, c = g * 16 + (sg << (seg_shift - 3)) + km.cs_keep / 8;
-              uint32_t* p = reinterpret_cast<uint32_t*>(to + (t * (16 * G) + (c ^ bank_key(t))) * 16);
-              if (partial == 2) p[1] = 0u;
-              if (partial <= 4) *reinterpret_cast<u32x2_t*>(p + 2) = u32x2_t{0u, 0u};
-              else p[3] = 0u;
-            }
+            unsigned char* const to = smem + buf * S::XBytes;
+            auto each = [&](auto&& put) {
+#pragma unroll
+              for (int k = 0; k < XPW; ++k) {
+                if (k >= turns) return;
+                put(reinterpret_cast<uint32_t*>(to + clear[k]));
+              }
+            };
+            if (partial == 6) each([](uint32_t* p) { p[3] = 0u; });
+            else if (partial == 4) each([](uint32_t* p) { *reinterpret_cast<u32x2_t*>(p + 2) = u32x2_t{0u, 0u}; });
+            else each([](uint32_t* p) { p[1] = 0u; *reinterpret_cast<u32x2_t*>(p + 2) = u32x2_t{0u, 0u}; });
           }
         });
       };
