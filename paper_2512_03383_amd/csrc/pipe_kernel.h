@@ -50,7 +50,9 @@ struct PipeShape {
   static constexpr int XBytes = BM * G * 256, WBytes = BN * U * 16;
   static constexpr int XI = XBytes / 1024, WI = WBytes / 1024;   // loads of 64 x 16 bytes
   static constexpr bool Small = AF * BF <= 9;
-  static constexpr int XM = Small ? 4 : 2, WM = Small && WI % 2 == 0 ? 2 : 1;   // waves that move activations, codes
+  // (tiles of 16 tokens x 64 rows, 3 and 4 bits, are bound by their codes and lose 1..5 % with more movers)
+  static constexpr bool MoreMovers = Small && !(AF == 1 && BF == 2);
+  static constexpr int XM = MoreMovers ? 4 : 2, WM = MoreMovers && WI % 2 == 0 ? 2 : 1;   // waves that move activations, codes
   // In 32 x 32 tiles of 8-bit codes (a slab is 32 loads of activations and 16 of codes) the codes, which come from memory, must not wait:
   // the two movers of activations that share a SIMD with the movers of codes stand by, and the other two take their loads.
   // 4096 x 12185 at 40 tokens 33.5 -> 26.8 us, x 4096 12.0 -> 10.8 (with the other pair standing by 31.3 and 11.7).  Rows of up to three
@@ -92,7 +94,8 @@ __global__ __launch_bounds__((PipeShape<AF, BF, WN, KG, KQ, G, NX, NW, BITS>::Th
   // attention block at 1000 tokens 106 -> 103), and 96 tokens with three buffers, i.e. codes of 8 and 6 bits (12185 x 4096 at 333 tokens
   // 67.5 -> 56.4 and 75.8 -> 65.3 us; 73.2 with 6 bits before units were placed by bank_key).  Prefixes in 96..112-token tiles of four
   // buffers and in 128-token ones go the other way (4 bits, 5120 x 4096 at 512 tokens 31.2 -> 33.2 us).
-  constexpr bool XLate = S::Small ? NX <= 4 : NX == 3 && (SEG || AF == 6);
+  // (16 x 32 tiles of up to 6 bits: early is up to 8 % better, rows of 14208 columns on segments above all; 8 bits: level)
+  constexpr bool XLate = S::Small ? NX <= 4 && !(AF == 1 && BF == 1 && BITS != 8) : NX == 3 && (SEG || AF == 6);
   extern __shared__ __align__(16) unsigned char smem[];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
