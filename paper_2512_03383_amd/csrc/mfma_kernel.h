@@ -391,6 +391,18 @@ enum GemmRoute {
   kTile16x16k8, kTile16x64k4, kTile32x16k8, kTile32x64k4, kTile64x32k4, kTile64x64k4
 };
 
+// Column segments of 17..32 tokens that the decode-batch kernel keeps: those whose kept columns are not whole blocks of eight, which the
+// pipelined kernel's movers clear slab after slab, in long rows of up to 256 row tiles (more are two rounds of the other kernel's waves:
+// 5120 x 8192 23.3 us there, 16.6 here).  24 tokens, there against here, fp16: 98..108 of 128 or 54 of 64 columns 1024 x 4096 9.3 / 9.5,
+// 1024 x 14208 20.6 / 23.6, 3584 x 8192 16.6 / 16.6, 3584 x 14208 23.2 / 25.2; 26 of 32 columns 1024 x 8192 14.1 / 17.9.  bfloat16, whose
+// unpack is longer there, 54 of 64 1024 x 8192 14.8 / 13.6, 1024 x 14208 21.5 / 20.6; 26 of 32 1024 x 8192 14.8 / 16.8.
+static inline bool segments_stay(const LinearArgs& a) {
+  const KeepMap& km = a.km;
+  if (km.cs_keep % 8 == 0 || km.n_keep > 4096) return false;
+  if (km.cs_stride < 64) return km.k_span > 3400 + km.n_keep / 10;
+  return !a.bf16 && km.k_span > 4096 + (km.n_keep > 1024 ? (km.n_keep - 1024) * 3 / 2 : 0);
+}
+
 // xm: staging mode of the activations (0 element by element, 1 column prefix, 2 column segments of whole 8-column units)
 static inline GemmRoute gemm_route(const LinearArgs& a, int xm) {
   const int row_tiles = (a.km.n_keep + 15) / 16;
@@ -409,7 +421,7 @@ static inline GemmRoute gemm_route(const LinearArgs& a, int xm) {
   // of the other kernel gathers for itself, come here from 17 tokens on at any height: 4096 x 4096, 108 of 128, at 24 / 32
   // tokens 10.6 / 11.1 there, 9.4 / 9.7 here, 2560 x 5120, 54 of 64, 11.8 and 10.9; at 16 tokens 8.5 and 8.3, at 9 8.1 and 8.2.
   const bool tall = row_tiles >= 400 && a.M >= 9 && !(xm == 1 && smallm_pre(a));
-  if (smallm_takes(a, xm == 1) && !(pipe && (tall || (xm == 2 && a.M >= 17)))) return kSmallM;
+  if (smallm_takes(a, xm == 1) && !(pipe && (tall || (xm == 2 && a.M >= 17 && !segments_stay(a))))) return kSmallM;
   if (pipe && a.M <= 64) return kPipe;
   // What neither takes (rows of fewer than eight groups; above the decode batches, or on tall matrices from 9 tokens on,
   // segments that are not a power of two up to a group with an even number kept): K over four or eight waves of a block, or

@@ -137,6 +137,17 @@ def test_decode_batches_that_the_pipelined_kernel_takes(bf16):
         assert uq.uniql_w4_linear_kernel(N, 8192, None, 8, bf16=bf16)[0] == BATCH
 
 
+# column segments of 17..32 tokens whose kept columns are not whole blocks of eight: long rows of up to 4096 stay with the decode batches
+# (512 x 14208, 98 of 128 columns, 17 tokens: 0.82 of the other kernel's time); fp16, or segments of fewer than 64 columns
+@pytest.mark.parametrize("M", [17, 32])
+def test_segments_that_decode_batches_keep(M):
+    for N, K, keep, f16, bf in ((512, 14208, seg(128, 98), BATCH, PIPE), (512, 14208, seg(128, 96), PIPE, PIPE), (1024, 4096, seg(64, 54), PIPE, PIPE),
+                                (1024, 4224, seg(64, 54), BATCH, PIPE), (3584, 7936, seg(64, 54), PIPE, PIPE), (3584, 8192, seg(64, 54), BATCH, PIPE),
+                                (4097, 14208, seg(64, 54), PIPE, PIPE), (1000, 3456, seg(32, 26), PIPE, PIPE), (1000, 3584, seg(32, 26), BATCH, BATCH)):
+        for bf16, want in ((False, f16), (True, bf)):
+            assert uq.uniql_w4_linear_kernel(N, K, keep, M, bf16=bf16)[0] == want, (N, K, bf16)
+
+
 # one token of 8-, 6- and 3-bit codes: the walk's rows at a time, and what it leaves to the other kernels
 @pytest.mark.parametrize("bf16", [False, True])
 @pytest.mark.parametrize("bits", [8, 6, 3])
