@@ -76,7 +76,7 @@ template <int AF, int BF, int WN, int KG, int KQ, int G, int NX, int BITS, bool 
 static hipError_t pipe_tile(const LinearArgs* p, int n, hipStream_t s) {
   constexpr int BN = WN * BF * 16;
   constexpr int NW = pipe_nw(NX * 16 * AF * G * 256, BN * 64, BN * G * BITS * 16, 8);
-  static_assert(PipeShape<AF, BF, WN, KG, KQ, G, NX, NW, BITS>::Threads <= kPipeMostThreads, "pipe_pick counts the threads of a grid with the largest block");
+  static_assert(PipeShape<AF, BF, WN, KG, KQ, G, NX, NW, BITS, SEG>::Threads <= kPipeMostThreads, "pipe_pick counts the threads of a grid with the largest block");
   return pipe_launch<AF, BF, WN, KG, KQ, G, NX, NW, BITS, BF16, SEG>(p, n, s);
 }
 

@@ -42,7 +42,7 @@ struct PipeBatch {
   int n, tiles, ntt;      // problems, all tiles, token tiles (the same for every problem)
 };
 
-template <int AF, int BF, int WN, int KG, int KQ, int G, int NX, int NW, int BITS>
+template <int AF, int BF, int WN, int KG, int KQ, int G, int NX, int NW, int BITS, bool SEG>
 struct PipeShape {
   static_assert(WN * KG * KQ == kPipeConsumers && G == KG && KQ <= 2 && KG * KQ > 1, "eight waves multiply, each one group of a slab, two or all four of its steps");
   static constexpr int BM = 16 * AF, BN = WN * BF * 16, KS = KG * KQ, T = 4 / KQ;   // a wave: T steps of its group
@@ -50,8 +50,9 @@ struct PipeShape {
   static constexpr int XBytes = BM * G * 256, WBytes = BN * U * 16;
   static constexpr int XI = XBytes / 1024, WI = WBytes / 1024;   // loads of 64 x 16 bytes
   static constexpr bool Small = AF * BF <= 9;
-  // (tiles of 16 tokens x 64 rows, 3 and 4 bits, are bound by their codes and lose 1..5 % with more movers)
-  static constexpr bool MoreMovers = Small && !(AF == 1 && BF == 2);
+  // (tiles of 16 tokens x 64 rows, 3 and 4 bits, are bound by their codes and lose 1..5 % with more movers, so do 32 x 64 ones of 4 bits on
+  // a prefix: 35 sizes of 17..32 tokens, fp16, 1.3 %)
+  static constexpr bool MoreMovers = Small && !(BF == 2 && (AF == 1 || (AF == 2 && BITS == 4 && !SEG)));
   static constexpr int XM = MoreMovers ? 4 : 2, WM = MoreMovers && WI % 2 == 0 ? 2 : 1;   // waves that move activations, codes
   // In 32 x 32 tiles of 8-bit codes (a slab is 32 loads of activations and 16 of codes) the codes, which come from memory, must not wait:
   // the two movers of activations that share a SIMD with the movers of codes stand by, and the other two take their loads.
@@ -84,9 +85,9 @@ __device__ __forceinline__ void pipe_barrier() {
 }
 
 template <int AF, int BF, int WN, int KG, int KQ, int G, int NX, int NW, int BITS, bool BF16, bool SEG>
-__global__ __launch_bounds__((PipeShape<AF, BF, WN, KG, KQ, G, NX, NW, BITS>::Threads), (PipeShape<AF, BF, WN, KG, KQ, G, NX, NW, BITS>::Small ? 4 : 3)) void w_pipe_kernel(PipeBatch bt) {
+__global__ __launch_bounds__((PipeShape<AF, BF, WN, KG, KQ, G, NX, NW, BITS, SEG>::Threads), (PipeShape<AF, BF, WN, KG, KQ, G, NX, NW, BITS, SEG>::Small ? 4 : 3)) void w_pipe_kernel(PipeBatch bt) {
 #ifdef __HIP_DEVICE_COMPILE__   // (the loads into LDS have no form in the host's pass)
-  typedef PipeShape<AF, BF, WN, KG, KQ, G, NX, NW, BITS> S;
+  typedef PipeShape<AF, BF, WN, KG, KQ, G, NX, NW, BITS, SEG> S;
   constexpr int BM = S::BM, BN = S::BN, U = S::U, KS = S::KS, XM = S::XM, WM = S::WM;
   // A slab's activations land by the barrier before its use and not one earlier: its first fragments are then read behind that
   // barrier, but with three or four buffers the loads have a slab more of time.  Small tiles wait for them otherwise, and so do
@@ -544,7 +545,7 @@ __global__ __launch_bounds__((PipeShape<AF, BF, WN, KG, KQ, G, NX, NW, BITS>::Th
 
 template <int AF, int BF, int WN, int KG, int KQ, int G, int NX, int NW, int BITS, bool BF16, bool SEG>
 static hipError_t pipe_launch(const LinearArgs* p, int n, hipStream_t stream) {
-  typedef PipeShape<AF, BF, WN, KG, KQ, G, NX, NW, BITS> S;
+  typedef PipeShape<AF, BF, WN, KG, KQ, G, NX, NW, BITS, SEG> S;
   auto kern = w_pipe_kernel<AF, BF, WN, KG, KQ, G, NX, NW, BITS, BF16, SEG>;
   if (S::Lds > 64 * 1024) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, S::Lds);
