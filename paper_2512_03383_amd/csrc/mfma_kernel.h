@@ -409,17 +409,19 @@ static inline GemmRoute gemm_route(const LinearArgs& a, int xm) {
   const bool pipe = xm != 0 && pipe_serves(a);
   // Decode batches (M <= 32) are bound by the weight stream and have a kernel of their own (smallm_kernel.h), except
   // tall matrices from 9 tokens on whose activations it cannot stage once per block: a wave that stages its own 16 x 128
-  // activations per group costs more than the pipelined kernel's slabs (9472 x 4096 at 12 / 24 tokens 16.9 / 23.2 us there,
-  // 11.4 / 12.4 here, 6400 x 4096 10.0 / 13.1 and 8.7 / 10.2; with 256 row tiles it is the other way round: 4096 x 9318 at 24
-  // tokens 18.1 there, 22.6 here).  Up to 8 tokens the two are closer (6400 x 4096 8.8 there, 8.6 here, 9472 x 4096 12.8 and
-  // 11.2), and a tall matrix in the other kernel would no longer share a launch with short ones: 8192 + 1024 + 1024 rows x 8192
-  // columns at 8 tokens 17.5 us in one launch, 28 in three.  From 9 tokens on such a set is two launches, 0.92..1.0 of the time
-  // of one at 17..32 tokens and 1.0..1.17 at 9..16 (8192 + 1024 + 1024 x 8192 22.3 -> 21.9, x 4096 15.4 -> 15.7).
-  // (Below 400 row tiles a tall matrix by itself is still faster here, 6000 x 4096 at 9 / 16 / 32 tokens 9.6 / 9.8 / 13.0 there, 8.8 / 9.0 /
-  // 9.9 here, but in a set with short ones it costs a launch of its own: 6000 + 1536 rows x 2560 columns at 9 / 32 tokens 8.1 / 10.3 in
+  // activations per group costs more than the pipelined kernel's slabs (9472 x 4096 at 12 / 24 tokens 16.9 / 23.3 us there,
+  // 11.4 / 14.1 here, 6400 x 4096 9.6 / 12.7 and 8.7 / 9.4; with 256 row tiles it is the other way round at 9..16 tokens and level
+  // beyond: 4096 x 9344 at 12 / 24 tokens 12.3 / 16.7 there, 13.9 / 16.6 here).  Up to 8 tokens the two are closer (6400 x 4096 8.6 in
+  // both, 9472 x 4096 13.4 there, 11.4 here), and a tall matrix in the other kernel would no longer share a launch with short ones: 8192 +
+  // 1024 + 1024 rows x 8192 columns at 8 tokens 21.4 us in one launch, 28 in three.  From 9 tokens on such a set is two launches, 0.85..1.1 of
+  // the time of one at 17..32 tokens and 0.94..1.2 at 9..16 (8192 + 1024 + 1024 at 9 / 24 tokens, one -> two: x 8192 25.4 / 35.3 -> 25.4 / 30.7,
+  // x 4096 15.9 / 21.8 -> 16.8 / 20.2, x 2560 14.0 / 19.3 -> 15.9 / 19.2); a set of 6400 + 1536 x 2560, which stages its activations once
+  // a block where it is one launch, takes 1.6..1.75 times as long in two (9 / 32 tokens 8.3 / 10.9 -> 14.3 / 17.7).
+  // (Below 400 row tiles a tall matrix by itself is still faster here, 6000 x 4096 at 9 / 16 / 32 tokens 9.5 / 9.6 / 12.8 there, 8.5 / 8.8 /
+  // 9.6 here, but in a set with short ones it costs a launch of its own: 6000 + 1536 rows x 2560 columns at 9 / 32 tokens 8.1 / 10.3 in
   // one launch, 13.6 / 16.5 in two, x 4096 12.2 / 16.9 and 14.8 / 17.9, x 8192 18.7 / 26.0 and 22.0 / 28.1.)  Column segments, whose activations a wave
-  // of the other kernel gathers for itself, come here from 17 tokens on at any height: 4096 x 4096, 108 of 128, at 24 / 32
-  // tokens 10.6 / 11.1 there, 9.4 / 9.7 here, 2560 x 5120, 54 of 64, 11.8 and 10.9; at 16 tokens 8.5 and 8.3, at 9 8.1 and 8.2.
+  // of the other kernel gathers for itself, come here from 17 tokens on (but see segments_stay): 4096 x 4096, 108 of 128, at 24 / 32
+  // tokens 10.3 / 10.7 there, 9.2 / 9.3 here, 2560 x 5120, 54 of 64, 11.2 / 11.6 and 10.8 / 10.8; at 9..16 tokens level.
   const bool tall = row_tiles >= 400 && a.M >= 9 && !(xm == 1 && smallm_pre(a));
   if (smallm_takes(a, xm == 1) && !(pipe && (tall || (xm == 2 && a.M >= 17 && !segments_stay(a))))) return kSmallM;
   if (pipe && a.M <= 64) return kPipe;

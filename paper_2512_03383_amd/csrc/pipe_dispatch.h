@@ -9,10 +9,13 @@ namespace uniql {
 
 // What a launch costs, in microseconds: a group of 128 columns (or a slab of them) costs one tile `us` on an idle chip and
 // `slope` more with every compute unit busy (clock and L2), a round of tiles 4 besides and `round` more, the launch 3.  Rows of
-// more than 8192 columns miss the L2 more often.  It ranks tiles; as a time it is rough: with every candidate timed on 20
-// matrices of 1024..32000 rows and 1024..14208 columns at 80..4096 tokens (480 sizes of 4 bits, both formats) a tile took 0.71..1.14
-// of its cost (5th to 95th percentile).  The tile picked took 0.1 % longer than the fastest one in the mean and 12 % at worst; with
-// codes of 8, 6 and 3 bits, which share the pipelined kernel's table (330 sizes), 3 % at worst.
+// more than 8192 columns miss the L2 more often.  It ranks tiles; as a time it is rough.  The costs of a prefix, and all of up to 64 tokens, are of an
+// earlier form of the pipelined kernel and lie above its times now, those of segments at more tokens are of the present one: with every
+// tile timed at 1591 sizes (1024..28672 rows, 1024..14208 columns, 72..2048 tokens, all widths and formats, prefixes and 108 of 128
+// columns) a tile took 0.74..1.12 of its cost (5th to 95th percentile; median 0.84 for a prefix in 4 and 8 bits, 0.94 for segments).  The
+// tile picked takes 0.1 % longer than the fastest one in the mean and 6 % at worst; with 8 bits 0.2 %, and 13 % (6000 x 14208 at 1000
+// tokens 230 us in 64 x 128 tiles, 203 in 128 x 128) to 17 % at worst (12185 x 14208, segments, 512 tokens: 296 in 128 x 128, 253 in 64 x 128).
+// Up to 64 tokens (809 sizes) 0.0 % in the mean, 5 % at worst.
 struct TileCost {
   float us, slope;
 };

@@ -11,9 +11,9 @@ namespace uniql {
 //  kPipeMixed  : two groups, two halves of their steps (KG = KQ = 2): 33..64 tokens, taller matrices (64 or 96 rows x all
 //                tokens)
 //  kPipeHalves : two halves of a group's steps (KQ = 2): more tokens, 128 x 128 tiles and smaller ones
-// 4096 columns at 40 tokens, groups / mixed, with 256, 300, 512, 592 row tiles: 3 bits 11.2 / 16.2, 14.7 / 16.4, 14.9 / 16.5,
-// 26.4 / 16.7 us; 8 bits 10.8 / 15.2, 18.4 / 15.3, 18.4 / 15.7, 26.0 / 16.1; 4 bits 10.3 / 14.3, 12.8 / 14.5, 12.9 / 14.5,
-// 22.8 / 14.8.  4 bits change over at 400: such matrices share launches (gate and up, q with k and v), and two of 400..512 row tiles
+// 4096 columns at 40 tokens, groups / mixed, with 256, 300, 512, 592 row tiles: 3 bits 10.0 / 15.6, 13.6 / 15.6, 14.7 / 16.4,
+// 26.1 / 17.0 us; 8 bits 11.0 / 15.0, 19.3 / 15.3, 20.8 / 16.8, 29.2 / 17.6; 6 bits 13.5 / 17.3, 23.8 / 17.6, 25.1 / 18.5, 35.9 / 19.1;
+// 4 bits 9.3 / 13.6, 12.6 / 14.0, 13.5 / 14.6, 24.2 / 15.1.  4 bits change over at 400: such matrices share launches (gate and up, q with k and v), and two of 400..512 row tiles
 // are two rounds of the one and one round of the other.
 enum PipeWay { kPipeGroups, kPipeMixed, kPipeHalves };
 
@@ -42,12 +42,14 @@ static inline bool pipe_serves(const LinearArgs& a) {
 
 // Codes of 8, 6 and 3 bits: whether the streaming kernel with a token per grid row (w8.hip, wbits.hip) is faster than the pipelined
 // one.  It reads and unpacks the weights once per token, but spreads rows and tokens over the whole chip, where the other has a
-// block for 32 rows and all tokens: few rows or very few tokens (256 x 12185 at 6 bits and 8 tokens 9.0 against 26.0 us, 2048 x 4096
-// at 3 tokens 8.4 against 12.2; 4096 x 4096 at 4 tokens 14.2 against 12.2).  In microseconds, from 1584 timed sizes of 256..131072
+// block for 32 rows and all tokens: few rows or very few tokens (6 bits, 256 x 12160 at 8 tokens 7.7 against 24.5 us, 2048 x 4096
+// at 3 tokens 8.0 against 11.2; 4096 x 4096 at 4 tokens 15.1 against 12.0).  In microseconds, from 1584 timed sizes of 256..131072
 // rows, 1024..12185 columns, 2..16 tokens: streaming s0 + s1 kc + (s2 + s3 kc) (rows x tokens / 1000 - 1.5), kc thousands of
 // columns (+ s4 with column segments); pipelined p0 + p1 slabs of 512 columns (+ p4), and p2 slabs + p3 more for every further round
-// of 256 tiles of 32 rows (3 bits, which have 64-row tiles too: in proportion).  Ties go to the streaming kernel.  The kernel picked
-// takes 0.1 to 0.6 % longer than the faster one in the mean, 23 % at worst.
+// of 256 tiles of 32 rows (3 bits, which have 64-row tiles too: in proportion).  Ties go to the streaming kernel.  The p are
+// of an earlier form of the pipelined kernel, which has become faster.  Over 2500 sizes the kernel picked takes 0.2 to 0.9 % longer than
+// the faster one in the mean on prefixes and 1.1 to 2.0 % on segments; the worst are matrices of 1000..2000 rows and long segmented
+// rows, which stay with the streaming kernel (3 bits, 1024 x 12160, 108 of 128 columns, 11 tokens 35.5 us for 18.9).
 static inline bool wide_streams(const LinearArgs& a) {
   struct Line { float s0, s1, s2, s3, s4, p0, p1, p2, p3, p4; };
   static const Line lines[3][2] = {   // 8, 6, 3 bits; fp16, bfloat16
