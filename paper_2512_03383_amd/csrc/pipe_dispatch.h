@@ -29,7 +29,13 @@ struct PipeTile {
   int af, bf, wn, g;
   TileCost prefix, seg;   // per slab of g groups
   float us;               // of the launch
+  int whole;              // tiles that are taken whole, -1: all (the others as two halves of the tokens)
 };
+
+// Tiles of this many fragments of 16 tokens have halves (of 64 and 48 tokens; their blocks have the same waves and the same LDS).  8-bit
+// codes: not those of 96 tokens, which the shared costs rate too well against 128 (12185 x 4096, 108 of 128 columns, 200 tokens
+// 41.5 us in 128-token tiles, 44.6 in 96 with halves).
+constexpr bool pipe_halves(int bits, int af) { return af == 8 || (af == 6 && bits != 8); }
 
 template <int BITS>
 static inline PipeTile pipe_pick(const LinearArgs* p, int n) {
@@ -37,13 +43,13 @@ static inline PipeTile pipe_pick(const LinearArgs* p, int n) {
   // halves: rows x tokens from 128 x 128 down to 64 x 64 (8-bit codes: no 112, its buffers)
   // (128 x 128 takes all of a wave's 168 registers: with 8 and 6 bits a word (fp16) or up to five (bfloat16) goes to scratch around
   // the loop, and 2 to 17 words in the loop of the bfloat16 unpack's wide form)
-  static const PipeTile groups[] = {{1, 1, 2, 4, {0.50f, 0.05f}, {0.55f, 0.05f}, 0.f}, {1, 2, 2, 4, {0.90f, 0.05f}, {0.95f, 0.05f}, 0.f},
-                                    {2, 1, 2, 4, {0.55f, 0.05f}, {0.65f, 0.05f}, 0.f}, {2, 2, 2, 4, {1.0f, 0.05f}, {1.05f, 0.05f}, 0.f}};
-  static const PipeTile mixed[] = {{3, 2, 2, 2, {0.62f, 0.07f}, {0.70f, 0.05f}, 0.f}, {3, 3, 2, 2, {0.80f, 0.07f}, {0.90f, 0.05f}, 0.f},
-                                   {4, 2, 2, 2, {0.73f, 0.07f}, {0.85f, 0.05f}, 0.f}, {4, 3, 2, 2, {0.93f, 0.07f}, {1.05f, 0.05f}, 0.f}};
-  static const PipeTile halves[] = {{8, 2, 4, 1, {1.0f, 0.15f}, {0.82f, 0.22f}, 0.f}, {7, 2, 4, 1, {0.93f, 0.12f}, {0.76f, 0.12f}, 0.f},
-                                    {6, 2, 4, 1, {0.85f, 0.07f}, {0.71f, 0.09f}, 0.f}, {4, 2, 4, 1, {0.56f, 0.15f}, {0.58f, 0.07f}, 0.f},
-                                    {4, 1, 4, 1, {0.33f, 0.09f}, {0.33f, 0.04f}, 0.f}};
+  static const PipeTile groups[] = {{1, 1, 2, 4, {0.50f, 0.05f}, {0.55f, 0.05f}, 0.f, -1}, {1, 2, 2, 4, {0.90f, 0.05f}, {0.95f, 0.05f}, 0.f, -1},
+                                    {2, 1, 2, 4, {0.55f, 0.05f}, {0.65f, 0.05f}, 0.f, -1}, {2, 2, 2, 4, {1.0f, 0.05f}, {1.05f, 0.05f}, 0.f, -1}};
+  static const PipeTile mixed[] = {{3, 2, 2, 2, {0.62f, 0.07f}, {0.70f, 0.05f}, 0.f, -1}, {3, 3, 2, 2, {0.80f, 0.07f}, {0.90f, 0.05f}, 0.f, -1},
+                                   {4, 2, 2, 2, {0.73f, 0.07f}, {0.85f, 0.05f}, 0.f, -1}, {4, 3, 2, 2, {0.93f, 0.07f}, {1.05f, 0.05f}, 0.f, -1}};
+  static const PipeTile halves[] = {{8, 2, 4, 1, {1.0f, 0.15f}, {0.82f, 0.22f}, 0.f, -1}, {7, 2, 4, 1, {0.93f, 0.12f}, {0.76f, 0.12f}, 0.f, -1},
+                                    {6, 2, 4, 1, {0.85f, 0.07f}, {0.71f, 0.09f}, 0.f, -1}, {4, 2, 4, 1, {0.56f, 0.15f}, {0.58f, 0.07f}, 0.f, -1},
+                                    {4, 1, 4, 1, {0.33f, 0.09f}, {0.33f, 0.04f}, 0.f, -1}};
   const PipeWay way = pipe_way(p[0]);
   const bool seg = p[0].km.cs_stride != 0;
   const PipeTile* set = way == kPipeGroups ? groups : way == kPipeMixed ? mixed : halves;
@@ -63,6 +69,18 @@ static inline PipeTile pipe_pick(const LinearArgs* p, int n) {
     tiles *= (M + 16 * t.af - 1) / (16 * t.af);
     // (threads of a grid are counted in 32 bits; pipe_serves leaves the largest tiles below that)
     t.us = tiles * kPipeMostThreads >= (1ll << 32) ? 1e30f : launch_cost(tiles, (float)((ngroups + t.g - 1) / t.g), seg ? t.seg : t.prefix, span > 8192 ? 1.18f : 1.f);
+    // A last round of at most half as many tiles as there are compute units goes out as halves of the tokens, two blocks a tile.  Such a
+    // round takes 0.78 (128 tokens) or 0.82 (96) of a whole one, with 500 sizes timed both ways (1.1 .. 8 rounds, all widths): the launch
+    // 0.85 to 0.997 of the time.  The costs here are a little above, so that another tile is not left for too small a gain.
+    if (way == kPipeHalves && pipe_halves(BITS, t.af) && tiles < (1 << 20)) {
+      const int cus = prefill_grid_limit(), rest = (int)(tiles % cus);
+      if (tiles > cus && rest > 0 && 2 * rest <= cus) {
+        const TileCost& c = seg ? t.seg : t.prefix;
+        const float steps = (float)((ngroups + t.g - 1) / t.g), far = span > 8192 ? 1.18f : 1.f;
+        const float us = launch_cost(tiles - rest, steps, c, far) + (t.af == 8 ? 0.8f : 0.88f) * (4.f + steps * (c.us + c.slope) * far);
+        if (us < t.us) t.us = us, t.whole = (int)tiles - rest;
+      }
+    }
     if (best.af == 0 || t.us < best.us) best = t;
   }
   return best;
@@ -76,11 +94,12 @@ constexpr int pipe_nw(int lds, int sz, int wbytes, int most) {
   return n < counted ? n : counted;
 }
 template <int AF, int BF, int WN, int KG, int KQ, int G, int NX, int BITS, bool BF16, bool SEG>
-static hipError_t pipe_tile(const LinearArgs* p, int n, hipStream_t s) {
+static hipError_t pipe_tile(const LinearArgs* p, int n, hipStream_t s, int whole = -1) {
   constexpr int BN = WN * BF * 16;
   constexpr int NW = pipe_nw(NX * 16 * AF * G * 256, BN * 64, BN * G * BITS * 16, 8);
   static_assert(PipeShape<AF, BF, WN, KG, KQ, G, NX, NW, BITS, SEG>::Threads <= kPipeMostThreads, "pipe_pick counts the threads of a grid with the largest block");
-  return pipe_launch<AF, BF, WN, KG, KQ, G, NX, NW, BITS, BF16, SEG>(p, n, s);
+  // (a slab of half the tokens is half as long: the same LDS)
+  return pipe_launch<AF, BF, WN, KG, KQ, G, NX, NW, BITS, BF16, SEG, pipe_halves(BITS, AF) ? 2 * NX : 0>(p, n, s, whole);
 }
 
 template <int BITS, bool BF16, bool SEG>
@@ -99,11 +118,11 @@ static hipError_t pipe_run(const LinearArgs* p, int n, hipStream_t s) {
       }
       return pipe_tile<4, 2, 2, 2, 2, 2, 3, BITS, BF16, SEG>(p, n, s);
     default:
-      if (t.af == 8) return pipe_tile<8, 2, 4, 1, 2, 1, 3, BITS, BF16, SEG>(p, n, s);
+      if (t.af == 8) return pipe_tile<8, 2, 4, 1, 2, 1, 3, BITS, BF16, SEG>(p, n, s, t.whole);
       if constexpr (BITS <= 4) {
         if (t.af == 7) return pipe_tile<7, 2, 4, 1, 2, 1, 4, BITS, BF16, SEG>(p, n, s);
       }
-      if (t.af == 6) return pipe_tile<6, 2, 4, 1, 2, 1, BITS <= 4 ? 4 : 3, BITS, BF16, SEG>(p, n, s);
+      if (t.af == 6) return pipe_tile<6, 2, 4, 1, 2, 1, BITS <= 4 ? 4 : 3, BITS, BF16, SEG>(p, n, s, t.whole);
       return t.bf == 2 ? pipe_tile<4, 2, 4, 1, 2, 1, BITS == 8 ? 4 : 6, BITS, BF16, SEG>(p, n, s) : pipe_tile<4, 1, 4, 1, 2, 1, 6, BITS, BF16, SEG>(p, n, s);
   }
 }

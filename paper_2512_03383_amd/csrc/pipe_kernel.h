@@ -17,6 +17,10 @@
 // same time.  And a block's share of a packed row is fetched as contiguous runs (17 clocks of the address unit per KB)
 // instead of 16 rows per load (65 clocks).
 //
+// The last round of a grid, where it has at most half as many tiles as there are compute units, goes out as halves: a block takes half the
+// tokens of a tile (pipe_block with HALF), twice as many compute units have work and it takes 0.8 of the time.  8 bits, 12185 x
+// 4096 at 512 tokens, 384 tiles on 256 compute units: 89 -> 83 us, 6 bits 93 -> 80.  The order of the sums is that of any tile.
+//
 // LDS layout: activations [token][16 G chunks of 8 columns], chunk c of token t at c ^ bank_key(t); codes [row][units of 16
 // bytes], the units of a row permuted likewise where their number is a power of two: the 16 lanes that a 128-bit read serves in
 // one clock read 16 different bank groups.  Activations stay in memory order (codes.h gives the weights in that order).
@@ -40,16 +44,18 @@ struct PipeBatch {
   LinearArgs p[kMaxBatch];
   int first[kMaxBatch];   // first tile of problem i
   int n, tiles, ntt;      // problems, all tiles, token tiles (the same for every problem)
+  int whole;              // tiles that a block takes whole; the rest go out as two halves of the tokens each
 };
 
-template <int AF, int BF, int WN, int KG, int KQ, int G, int NX, int NW, int BITS, bool SEG>
+// HALF: half a tile of a kernel whose blocks have twelve waves
+template <int AF, int BF, int WN, int KG, int KQ, int G, int NX, int NW, int BITS, bool SEG, bool HALF = false>
 struct PipeShape {
   static_assert(WN * KG * KQ == kPipeConsumers && G == KG && KQ <= 2 && KG * KQ > 1, "eight waves multiply, each one group of a slab, two or all four of its steps");
   static constexpr int BM = 16 * AF, BN = WN * BF * 16, KS = KG * KQ, T = 4 / KQ;   // a wave: T steps of its group
   static constexpr int U = G * BITS;                           // 16-byte units of codes per row and slab
   static constexpr int XBytes = BM * G * 256, WBytes = BN * U * 16;
   static constexpr int XI = XBytes / 1024, WI = WBytes / 1024;   // loads of 64 x 16 bytes
-  static constexpr bool Small = AF * BF <= 9;
+  static constexpr bool Small = !HALF && AF * BF <= 9;
   // (tiles of 16 tokens x 64 rows, 3 and 4 bits, are bound by their codes and lose 1..5 % with more movers, so do 32 x 64 ones of 4 bits on
   // a prefix: 35 sizes of 17..32 tokens, fp16, 1.3 %)
   static constexpr bool MoreMovers = Small && !(BF == 2 && (AF == 1 || (AF == 2 && BITS == 4 && !SEG)));
@@ -84,10 +90,11 @@ __device__ __forceinline__ void pipe_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-template <int AF, int BF, int WN, int KG, int KQ, int G, int NX, int NW, int BITS, bool BF16, bool SEG>
-__global__ __launch_bounds__((PipeShape<AF, BF, WN, KG, KQ, G, NX, NW, BITS, SEG>::Threads), (PipeShape<AF, BF, WN, KG, KQ, G, NX, NW, BITS, SEG>::Small ? 4 : 3)) void w_pipe_kernel(PipeBatch bt) {
+// The tile of tokens m0 .. m0 + 16 AF - 1 and the BN rows of row tile rt of a linear.
+template <int AF, int BF, int WN, int KG, int KQ, int G, int NX, int NW, int BITS, bool BF16, bool SEG, bool HALF>
+__device__ __forceinline__ void pipe_block(const LinearArgs& a, int rt, int m0) {
 #ifdef __HIP_DEVICE_COMPILE__   // (the loads into LDS have no form in the host's pass)
-  typedef PipeShape<AF, BF, WN, KG, KQ, G, NX, NW, BITS, SEG> S;
+  typedef PipeShape<AF, BF, WN, KG, KQ, G, NX, NW, BITS, SEG, HALF> S;
   constexpr int BM = S::BM, BN = S::BN, U = S::U, KS = S::KS, XM = S::XM, WM = S::WM;
   // A slab's activations land by the barrier before its use and not one earlier: its first fragments are then read behind that
   // barrier, but with three or four buffers the loads have a slab more of time.  Small tiles wait for them otherwise, and so do
@@ -101,31 +108,8 @@ __global__ __launch_bounds__((PipeShape<AF, BF, WN, KG, KQ, G, NX, NW, BITS, SEG
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 
-  // Tile of this block.  Consecutive blocks go to the eight dies in turn, each with an L2 of its own: a die takes a
-  // contiguous stretch of the tiles, and inside a problem the tiles run row tile by row tile over a few token tiles at
-  // a time, so that the blocks a die runs at once share codes and activations through its L2.
-  int rt, tt, pi = 0;
-  {
-    const int b = (int)blockIdx.x, die = b % kPipeDies, nb = bt.tiles;
-    int L = die * (nb / kPipeDies) + (die < nb % kPipeDies ? die : nb % kPipeDies) + b / kPipeDies;
-#pragma unroll
-    for (int i = 1; i < kMaxBatch; ++i) pi += (i < bt.n && L >= bt.first[i]) ? 1 : 0;
-    L -= bt.first[pi];
-    const int nrt = (bt.p[pi].km.n_keep + BN - 1) / BN, ntt = bt.ntt;
-    const int full = ntt / kPipeTokTilesPerPass * kPipeTokTilesPerPass;
-    if (L < nrt * full) {
-      const int pass = L / (nrt * kPipeTokTilesPerPass), r = L - pass * (nrt * kPipeTokTilesPerPass);
-      rt = r / kPipeTokTilesPerPass;
-      tt = pass * kPipeTokTilesPerPass + (r - rt * kPipeTokTilesPerPass);
-    } else {
-      const int w = ntt - full, r = L - nrt * full;
-      rt = r / w;
-      tt = full + (r - rt * w);
-    }
-  }
-  const LinearArgs a = bt.p[pi];
   const KeepMap& km = a.km;
-  const int n0 = rt * BN, m0 = tt * BM;
+  const int n0 = rt * BN;
   const int row_bytes = a.K_total / 8 * BITS, gpr = a.K_total / kGroup;
   const int ngroups = (km.k_span + kGroup - 1) / kGroup;
   const int nslab = (ngroups + G - 1) / G;
@@ -543,12 +527,67 @@ __global__ __launch_bounds__((PipeShape<AF, BF, WN, KG, KQ, G, NX, NW, BITS, SEG
 #endif
 }
 
-template <int AF, int BF, int WN, int KG, int KQ, int G, int NX, int NW, int BITS, bool BF16, bool SEG>
-static hipError_t pipe_launch(const LinearArgs* p, int n, hipStream_t stream) {
+template <int AF, int BF, int WN, int KG, int KQ, int G, int NX, int NW, int BITS, bool BF16, bool SEG, int HNX>
+__global__ __launch_bounds__((PipeShape<AF, BF, WN, KG, KQ, G, NX, NW, BITS, SEG>::Threads), (PipeShape<AF, BF, WN, KG, KQ, G, NX, NW, BITS, SEG>::Small ? 4 : 3)) void w_pipe_kernel(PipeBatch bt) {
+#ifdef __HIP_DEVICE_COMPILE__
   typedef PipeShape<AF, BF, WN, KG, KQ, G, NX, NW, BITS, SEG> S;
-  auto kern = w_pipe_kernel<AF, BF, WN, KG, KQ, G, NX, NW, BITS, BF16, SEG>;
-  if (S::Lds > 64 * 1024) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, S::Lds);
+  constexpr int BM = S::BM, BN = S::BN;
+  // Tile of this block.  Consecutive blocks go to the eight dies in turn, each with an L2 of its own: a die takes a
+  // contiguous stretch of the tiles, and inside a problem the tiles run row tile by row tile over a few token tiles at
+  // a time, so that the blocks a die runs at once share codes and activations through its L2.
+  int rt, tt, pi = 0, half = 0;
+  {
+    int b = (int)blockIdx.x, nb = HNX ? bt.whole : bt.tiles, from = 0;
+    if (HNX && b >= bt.whole) b -= bt.whole, nb = 2 * (bt.tiles - bt.whole), from = bt.whole, half = 1;
+    const int die = b % kPipeDies;
+    int L = die * (nb / kPipeDies) + (die < nb % kPipeDies ? die : nb % kPipeDies) + b / kPipeDies;
+    if (HNX && half != 0) half += L & 1, L = from + (L >> 1);
+#pragma unroll
+    for (int i = 1; i < kMaxBatch; ++i) pi += (i < bt.n && L >= bt.first[i]) ? 1 : 0;
+    L -= bt.first[pi];
+    const int nrt = (bt.p[pi].km.n_keep + BN - 1) / BN, ntt = bt.ntt;
+    const int full = ntt / kPipeTokTilesPerPass * kPipeTokTilesPerPass;
+    if (L < nrt * full) {
+      const int pass = L / (nrt * kPipeTokTilesPerPass), r = L - pass * (nrt * kPipeTokTilesPerPass);
+      rt = r / kPipeTokTilesPerPass;
+      tt = pass * kPipeTokTilesPerPass + (r - rt * kPipeTokTilesPerPass);
+    } else {
+      const int w = ntt - full, r = L - nrt * full;
+      rt = r / w;
+      tt = full + (r - rt * w);
+    }
+  }
+  const LinearArgs a = bt.p[pi];
+  if constexpr (HNX != 0) {
+    if (half != 0) {
+      const int m0 = tt * BM + (half - 1) * (BM / 2);
+      if (m0 < a.M) pipe_block<AF / 2, BF, WN, KG, KQ, G, HNX, NW, BITS, BF16, SEG, true>(a, rt, m0);
+      return;
+    }
+  }
+  pipe_block<AF, BF, WN, KG, KQ, G, NX, NW, BITS, BF16, SEG, false>(a, rt, tt * BM);
+#endif
+}
+
+template <int AF, int BF, int WN, int KG, int KQ, int G, int NX, int NW, int BITS, bool SEG, int HNX>
+constexpr int pipe_lds() {
+  constexpr int whole = PipeShape<AF, BF, WN, KG, KQ, G, NX, NW, BITS, SEG>::Lds;
+  if constexpr (HNX != 0) {
+    typedef PipeShape<AF / 2, BF, WN, KG, KQ, G, HNX, NW, BITS, SEG, true> Half;
+    static_assert(Half::Threads == PipeShape<AF, BF, WN, KG, KQ, G, NX, NW, BITS, SEG>::Threads && AF % 2 == 0, "halves run in the same blocks");
+    return Half::Lds > whole ? Half::Lds : whole;
+  }
+  return whole;
+}
+
+// HNX: slabs of activations of half a tile in flight, 0 where there are no halves; whole: tiles that are taken whole (-1: all)
+template <int AF, int BF, int WN, int KG, int KQ, int G, int NX, int NW, int BITS, bool BF16, bool SEG, int HNX = 0>
+static hipError_t pipe_launch(const LinearArgs* p, int n, hipStream_t stream, int whole = -1) {
+  typedef PipeShape<AF, BF, WN, KG, KQ, G, NX, NW, BITS, SEG> S;
+  constexpr int lds = pipe_lds<AF, BF, WN, KG, KQ, G, NX, NW, BITS, SEG, HNX>();
+  auto kern = w_pipe_kernel<AF, BF, WN, KG, KQ, G, NX, NW, BITS, BF16, SEG, HNX>;
+  if (lds > 64 * 1024) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
   }
   PipeBatch b;
@@ -561,7 +600,8 @@ static hipError_t pipe_launch(const LinearArgs* p, int n, hipStream_t stream) {
     if (i < n) tiles += (p[i].km.n_keep + S::BN - 1) / S::BN * b.ntt;
   }
   b.tiles = tiles;
-  hipLaunchKernelGGL(kern, dim3(tiles), dim3(S::Threads), S::Lds, stream, b);
+  b.whole = whole < 0 ? tiles : whole;
+  hipLaunchKernelGGL(kern, dim3(b.whole + 2 * (tiles - b.whole)), dim3(S::Threads), lds, stream, b);
   return hipGetLastError();
 }
 
