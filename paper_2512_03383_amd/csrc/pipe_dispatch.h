@@ -96,7 +96,7 @@ constexpr int pipe_nw(int lds, int sz, int wbytes, int most) {
 template <int AF, int BF, int WN, int KG, int KQ, int G, int NX, int BITS, bool BF16, bool SEG>
 static hipError_t pipe_tile(const LinearArgs* p, int n, hipStream_t s, int whole = -1) {
   constexpr int BN = WN * BF * 16;
-  constexpr int NW = pipe_nw(NX * 16 * AF * G * 256, BN * 64, BN * G * BITS * 16, 8);
+  constexpr int NW = pipe_nw(NX * 16 * AF * G * 256, BN * 64 + (pipe_touches(BITS, AF) ? kPipeTouch : 0), BN * G * BITS * 16, 8);
   static_assert(PipeShape<AF, BF, WN, KG, KQ, G, NX, NW, BITS, SEG>::Threads <= kPipeMostThreads, "pipe_pick counts the threads of a grid with the largest block");
   // (a slab of half the tokens is half as long: the same LDS)
   return pipe_launch<AF, BF, WN, KG, KQ, G, NX, NW, BITS, BF16, SEG, pipe_halves(BITS, AF) ? 2 * NX : 0>(p, n, s, whole);

@@ -21,6 +21,12 @@
 // tokens of a tile (pipe_block with HALF), twice as many compute units have work and it takes 0.8 of the time.  8 bits, 12185 x
 // 4096 at 512 tokens, 384 tiles on 256 compute units: 89 -> 83 us, 6 bits 93 -> 80.  The order of the sums is that of any tile.
 //
+// Codes of 8 bits in 128-token tiles have two slabs on their way, less than the memory's latency: 12185 x 4096 at 512 tokens took 69 us with the
+// weights in the 256 MB cache and 83 without.  There the blocks that a die runs side by side on one row tile bring its codes into the L2 a
+// window of eight groups ahead (touch), each a quarter of the lines, a dword of each: 83 -> 75 us.  A line costs a compute unit as much as
+// its data (29 bytes a clock come in from the L2, whoever asks), so it pays only where four blocks share the work and there is more than
+// a round of tiles: 2560 x 2560 at 777 tokens (140 tiles) 21.6 -> 23.2, two or three token tiles 2..9 % slower, 6 and 4 bits level.
+//
 // LDS layout: activations [token][16 G chunks of 8 columns], chunk c of token t at c ^ bank_key(t); codes [row][units of 16
 // bytes], the units of a row permuted likewise where their number is a power of two: the 16 lanes that a 128-bit read serves in
 // one clock read 16 different bank groups.  Activations stay in memory order (codes.h gives the weights in that order).
@@ -37,6 +43,9 @@ constexpr uint32_t kBufferWord3 = 0x00020000u;
 constexpr int kBeyond = (int)0x80000000u;   // as an unsigned offset: past the end of every resource below 2 GiB; reads zeros
 
 constexpr int kPipeConsumers = 8;
+constexpr int kPipeTouch = 256;   // bytes of LDS that loads write which only bring lines into the L2
+constexpr bool pipe_touches(int bits, int af) { return bits == 8 && af == 8; }
+constexpr int kPipeRound = 256;   // tiles of a round
 constexpr int kPipeDies = 8, kPipeTokTilesPerPass = 4;
 
 // Up to four linears with the same token count and format; tiles are numbered through the whole batch.
@@ -69,8 +78,10 @@ struct PipeShape {
   static constexpr int Threads = (kPipeConsumers + XM + WM + 1) * kWave;
   static_assert(WBytes % 1024 == 0 && XI % XM == 0, "whole loads, the same number for each mover");
   static constexpr int XPW = XI / (TwoStandBy ? XM / 2 : XM), WPW = WI / WM;   // (the most that a wave moves of a slab)
+  // 8-bit codes in the largest tiles, two slabs in flight: the wave of the scales brings them into the L2 ahead of the movers
+  static constexpr bool Touches = pipe_touches(BITS, HALF ? 2 * AF : AF);
   static constexpr int SZ = 2 * BN * 8 * 4;                    // two windows of eight groups
-  static constexpr int W0 = NX * XBytes, SZ0 = W0 + NW * WBytes, Lds = SZ0 + SZ;
+  static constexpr int W0 = NX * XBytes, SZ0 = W0 + NW * WBytes, Lds = SZ0 + SZ + (Touches ? kPipeTouch : 0);
   static_assert((NX - 1) * XPW <= 63 && (NW - 1) * WPW <= 63, "loads in flight are counted in six bits");
   static_assert(NX >= 3 && NW >= 3 && 8 % G == 0 && G <= 4, "a slab in use, one ready, one on its way; a window of scales is two slabs or more");
   static_assert(Lds <= 160 * 1024, "the slabs fit the LDS");
@@ -90,9 +101,10 @@ __device__ __forceinline__ void pipe_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-// The tile of tokens m0 .. m0 + 16 AF - 1 and the BN rows of row tile rt of a linear.
+// The tile of tokens m0 .. m0 + 16 AF - 1 and the BN rows of row tile rt of a linear; `share` token tiles of the row tile run side by side, this
+// one is the `mine`th.
 template <int AF, int BF, int WN, int KG, int KQ, int G, int NX, int NW, int BITS, bool BF16, bool SEG, bool HALF>
-__device__ __forceinline__ void pipe_block(const LinearArgs& a, int rt, int m0) {
+__device__ __forceinline__ void pipe_block(const LinearArgs& a, int rt, int m0, int share, int mine) {
 #ifdef __HIP_DEVICE_COMPILE__   // (the loads into LDS have no form in the host's pass)
   typedef PipeShape<AF, BF, WN, KG, KQ, G, NX, NW, BITS, SEG, HALF> S;
   constexpr int BM = S::BM, BN = S::BN, U = S::U, KS = S::KS, XM = S::XM, WM = S::WM;
@@ -336,15 +348,42 @@ __device__ __forceinline__ void pipe_block(const LinearArgs& a, int rt, int m0) 
         }
       }
     };
+    // codes of window w, this block's share of the lines (asm: the compiler would have the stores of the scales wait for them; what they write
+    // is not read)
+    const bool touches = S::Touches && share == kPipeTokTilesPerPass;
+    [[maybe_unused]] u32x4_t rt4 = {};
+    [[maybe_unused]] const uint32_t spare = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem + S::Lds - kPipeTouch;
+    if constexpr (S::Touches) {
+      const uint64_t at = (uint64_t)a.qweight;
+      rt4 = u32x4_t{(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)at), (uint32_t)__builtin_amdgcn_readfirstlane((int)((at >> 32) & 0xffffu)),
+                    (uint32_t)__builtin_amdgcn_readfirstlane(a.N_total * row_bytes), kBufferWord3};
+    }
+    auto touch = [&](int w) {
+      if constexpr (S::Touches) {
+        const int end = (w + 1) * 8 < ngroups ? (w + 1) * (128 * BITS) : ngroups * (16 * BITS);
+        for (int b = w * (128 * BITS) + mine * 128; b < end; b += kPipeTokTilesPerPass * 128)
+#pragma unroll
+          for (int p = 0; p < P; ++p)
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds" ::"s"(spare), "v"(e0[p] * (16 * BITS)), "s"(rt4), "s"(b) : "memory");
+      }
+    };
     fetch(0);
     put(0);
     fetch(1);
+    if (touches) {
+      // (both windows before the first touches: the stores of a window wait for every load before them)
+      put(1);
+      fetch(2);
+      touch(0);
+      touch(1);
+    }
     for (int it = 0; it < nslab; ++it) {
       pipe_barrier();
-      if (it % SPW == 0) {
+      if (it % SPW == 0 && (!touches || it > 0)) {
         const int w = it / SPW;
         put(w + 1);                       // into the window before the current one
         fetch(w + 2);
+        if (touches) touch(w + 1);
       }
     }
     pipe_barrier();
@@ -535,7 +574,7 @@ __global__ __launch_bounds__((PipeShape<AF, BF, WN, KG, KQ, G, NX, NW, BITS, SEG
   // Tile of this block.  Consecutive blocks go to the eight dies in turn, each with an L2 of its own: a die takes a
   // contiguous stretch of the tiles, and inside a problem the tiles run row tile by row tile over a few token tiles at
   // a time, so that the blocks a die runs at once share codes and activations through its L2.
-  int rt, tt, pi = 0, half = 0;
+  int rt, tt, share, mine, pi = 0, half = 0;
   {
     int b = (int)blockIdx.x, nb = HNX ? bt.whole : bt.tiles, from = 0;
     if (HNX && b >= bt.whole) b -= bt.whole, nb = 2 * (bt.tiles - bt.whole), from = bt.whole, half = 1;
@@ -550,22 +589,26 @@ __global__ __launch_bounds__((PipeShape<AF, BF, WN, KG, KQ, G, NX, NW, BITS, SEG
     if (L < nrt * full) {
       const int pass = L / (nrt * kPipeTokTilesPerPass), r = L - pass * (nrt * kPipeTokTilesPerPass);
       rt = r / kPipeTokTilesPerPass;
-      tt = pass * kPipeTokTilesPerPass + (r - rt * kPipeTokTilesPerPass);
+      mine = r - rt * kPipeTokTilesPerPass;
+      share = bt.tiles > kPipeRound ? kPipeTokTilesPerPass : 0;   // (as far as touches go)
+      tt = pass * kPipeTokTilesPerPass + mine;
     } else {
       const int w = ntt - full, r = L - nrt * full;
       rt = r / w;
-      tt = full + (r - rt * w);
+      mine = r - rt * w;
+      share = 0;
+      tt = full + mine;
     }
   }
   const LinearArgs a = bt.p[pi];
   if constexpr (HNX != 0) {
     if (half != 0) {
       const int m0 = tt * BM + (half - 1) * (BM / 2);
-      if (m0 < a.M) pipe_block<AF / 2, BF, WN, KG, KQ, G, HNX, NW, BITS, BF16, SEG, true>(a, rt, m0);
+      if (m0 < a.M) pipe_block<AF / 2, BF, WN, KG, KQ, G, HNX, NW, BITS, BF16, SEG, true>(a, rt, m0, share, mine);
       return;
     }
   }
-  pipe_block<AF, BF, WN, KG, KQ, G, NX, NW, BITS, BF16, SEG, false>(a, rt, tt * BM);
+  pipe_block<AF, BF, WN, KG, KQ, G, NX, NW, BITS, BF16, SEG, false>(a, rt, tt * BM, share, mine);
 #endif
 }
 
