@@ -462,6 +462,9 @@ __device__ __forceinline__ void pipe_block(const LinearArgs& a, int rt, int m0, 
     for (int b = 0; b < BF; ++b) largest = max(largest, r.sz[b] << 17);   // magnitude of the scale
     return __builtin_amdgcn_ballot_w64(largest >= kScaleWide << 17) != 0;
   };
+  // With many products a step its reads from LDS stand between them as well: eight waves that all read first wait in line for the LDS
+  constexpr bool Spread = AF * BF >= 12;
+  constexpr int kReads = 1 + (BITS == 8 ? T / 2 : BITS == 6 ? (T * BITS / 4 + 1) / 2 : BITS == 4 ? 1 : 2);   // of a row fragment's codes, scale and zero point
   // the group whose operands are being unpacked, and the next slab's
   Group cur, ahead;
   CodeGroup<BITS, BF16> gq[BF];
@@ -484,10 +487,11 @@ __device__ __forceinline__ void pipe_block(const LinearArgs& a, int rt, int m0, 
       for (int t = 0; t < T; ++t) {
         const int p = t & 1;
         if (XLate && t == 0) read_a(xsl, 0, av[0]);
+        if (Spread && XLate && t == 0) __builtin_amdgcn_sched_barrier(0);   // (what the products of this step wait for)
         if (t + 1 < T || !XLate) read_a(t + 1 < T ? xsl : xnext, (t + 1) % T, av[p ^ 1]);
-        __builtin_amdgcn_sched_barrier(0);   // (activations first: the products wait for them)
+        if (!Spread) __builtin_amdgcn_sched_barrier(0);   // (activations first: the products wait for them)
         if (t == 0) read_group(wnext, sz, ahead);
-        __builtin_amdgcn_sched_barrier(0);   // (or the compiler moves the reads behind the products to save registers)
+        if (!Spread) __builtin_amdgcn_sched_barrier(0);   // (or the compiler moves the reads behind the products to save registers)
         if (t == T - 1) {
           // where the next slab's reads go, here and not behind the barrier (3 % with 64 x 64 tiles)
           xsl = xnext;
@@ -512,6 +516,11 @@ __device__ __forceinline__ void pipe_block(const LinearArgs& a, int rt, int m0, 
         for (int i = 0; i < AF * BF; ++i) {
           __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);      // matrix instruction
           __builtin_amdgcn_sched_group_barrier(0x002, kVec, 0);   // vector instructions
+          if constexpr (Spread) {
+            const int reads = (t + 1 < T || !XLate ? AF : 0) + (t == 0 ? BF * kReads : 0), n = (i + 1) * reads / (AF * BF) - i * reads / (AF * BF);
+            if (n == 1) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // LDS reads
+            if (n >= 2) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+          }
         }
         __builtin_amdgcn_sched_barrier(0);
       }
