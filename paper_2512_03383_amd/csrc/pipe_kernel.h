@@ -463,7 +463,7 @@ __device__ __forceinline__ void pipe_block(const LinearArgs& a, int rt, int m0, 
     return __builtin_amdgcn_ballot_w64(largest >= kScaleWide << 17) != 0;
   };
   // With many products a step its reads from LDS stand between them as well: eight waves that all read first wait in line for the LDS
-  constexpr bool Spread = AF * BF >= 12;
+  constexpr bool Spread = AF >= 6 && AF * BF >= 12;   // (64 tokens x 96 rows, 12 products a step of two groups a slab: 2 % slower with it)
   constexpr int kReads = 1 + (BITS == 8 ? T / 2 : BITS == 6 ? (T * BITS / 4 + 1) / 2 : BITS == 4 ? 1 : 2);   // of a row fragment's codes, scale and zero point
   // the group whose operands are being unpacked, and the next slab's
   Group cur, ahead;
