@@ -148,7 +148,8 @@ typedef struct uniql_keep {
  *   ldx >= k_keep, ldy >= n_keep (elements); x and y must not overlap (this is not checked:
  *   with overlapping buffers the result is undefined).
  * M = 1 runs the streaming GEMV; M >= 2 the MFMA dequant-GEMMs: 2..32 tokens the decode-batch
- * kernel (a wave owns 16 rows and part of K), more tokens, tall matrices from 9 tokens on and codes of 8, 6
+ * kernels (up to 600 tiles of 16 rows the ring kernel: K over eight waves that each load for
+ * themselves; taller ones: a wave owns 16 rows and part of K), more tokens, tall matrices from 9 tokens on and codes of 8, 6
  * and 3 bits the pipelined kernel (loads in waves of their own; few rows or very few tokens of those widths the
  * streaming one), long prompts 256 x 256 tiles, rules that these do not take tiles with K split over waves.
  * Errors: E_NULL, E_SHAPE, E_KEEP, E_ALIGN, E_ARCH, E_HIP.  E_SHAPE also at M = 1 when the last
@@ -164,7 +165,7 @@ int uniql_w4_linear(const uniql_w4_t* W, const uniql_keep_t* keep, const void* x
  * = all unpruned), x_f16, ldx, y_f16, ldy are host arrays of n entries; each entry follows the
  * rules of uniql_w4_linear.  At M = 1 linears that stream rows of the same length are served by
  * ONE kernel launch (a decode step is launch-latency bound).  Of several tokens the members that one kernel takes
- * share a launch (the decode-batch kernel: column prefixes of at least 8 columns; the pipelined one: the same split of
+ * share a launch (the decode-batch kernels: column prefixes of at least 8 columns, the ring kernel prefixes or segments; the pipelined one: the same split of
  * K, see uniql_w4_linear_kernel, and prefixes or segments); the others are launched one after the other on the stream.
  * Results are identical to n separate uniql_w4_linear calls.
  * Errors: E_SHAPE also for n outside 1..4; otherwise as uniql_w4_linear (nothing is launched if
@@ -422,7 +423,8 @@ int uniql_w4_gate_up_stream_probe(const uniql_w4_t* W, const uniql_keep_t* keep,
 /*
  * Measurement aid, not part of the method: which kernel uniql_w4_linear runs for this matrix, rule, leading dimension of x and
  * number of tokens on the current device (256 compute units where there is none), without running it.  choice[0]: 0 the
- * streaming kernels (one token per grid row), 1 the decode-batch kernel, 2 the pipelined one, 3 the persistent 256 x 256 one, 4
+ * streaming kernels (one token per grid row), 1 the decode-batch kernels, 2 those whose loads write LDS ahead of the products (the
+ * pipelined one; on column segments of 17..32 tokens the ring kernel: K over 8 waves), 3 the persistent 256 x 256 one, 4
  * the tiled one; choice[1..3]: its tile's tokens and rows and the number of waves K is split over (0 for kernels 0 and 1,
  * but 1, the rows a wave takes at a time and 1 for one token of 8-, 6- or 3-bit codes on the persistent walk over rows).
  * The choice may change from one version of the library to the next.  The data pointers of W are not used and may be NULL.

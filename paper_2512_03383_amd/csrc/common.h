@@ -317,6 +317,9 @@ hipError_t launch_pipe_w3_bf16(const LinearArgs* p, int n, hipStream_t stream);
 hipError_t launch_pipe_w4_bf16(const LinearArgs* p, int n, hipStream_t stream);
 hipError_t launch_pipe_w6_bf16(const LinearArgs* p, int n, hipStream_t stream);
 hipError_t launch_pipe_w8_bf16(const LinearArgs* p, int n, hipStream_t stream);
+// n linears of the same token count and kind of column rule in one launch of the ring kernel (ring_kernel.h), one function per format
+hipError_t launch_ring_w4(const LinearArgs* p, int n, hipStream_t stream);
+hipError_t launch_ring_w4_bf16(const LinearArgs* p, int n, hipStream_t stream);
 hipError_t launch_w4_dequant(const LinearArgs& a, hipStream_t stream);
 // codes of 8 bits: the dequantised matrix, and the linear of one token (several: a grid row each)
 hipError_t launch_w8_dequant(const LinearArgs& a, hipStream_t stream);

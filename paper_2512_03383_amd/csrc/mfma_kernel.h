@@ -21,6 +21,7 @@
 #include "smallm_kernel.h"
 #include "prefill_kernel.h"
 #include "pipe_dispatch.h"
+#include "ring_pick.h"
 #include <type_traits>
 
 namespace uniql {
@@ -384,10 +385,16 @@ static hipError_t launch_pipe4(const LinearArgs* p, int n, hipStream_t stream) {
   else return launch_pipe_w4(p, n, stream);
 }
 
+template <bool BF16>
+static hipError_t launch_ring4(const LinearArgs* p, int n, hipStream_t stream) {
+  if constexpr (BF16) return launch_ring_w4_bf16(p, n, stream);
+  else return launch_ring_w4(p, n, stream);
+}
+
 // Which kernel a linear of 2 tokens and more takes.  It follows from the linear alone.  kTile*: w4_mfma_kernel with tiles of
 // that many tokens x rows, K over that many waves of a block.
 enum GemmRoute {
-  kSmallM, kPipe, kPrefill256, kTile128x256, kTile64x256, kTile64x128k2, kTile32x128k2,
+  kSmallM, kRing, kPipe, kPrefill256, kTile128x256, kTile64x256, kTile64x128k2, kTile32x128k2,
   kTile16x16k8, kTile16x64k4, kTile32x16k8, kTile32x64k4, kTile64x32k4, kTile64x64k4
 };
 
@@ -407,6 +414,7 @@ static inline bool segments_stay(const LinearArgs& a) {
 static inline GemmRoute gemm_route(const LinearArgs& a, int xm) {
   const int row_tiles = (a.km.n_keep + 15) / 16;
   const bool pipe = xm != 0 && pipe_serves(a);
+  if (xm != 0 && ring_takes(a, segments_stay(a))) return kRing;
   // Decode batches (M <= 32) are bound by the weight stream and have a kernel of their own (smallm_kernel.h), except
   // tall matrices from 9 tokens on whose activations it cannot stage once per block: a wave that stages its own 16 x 128
   // activations per group costs more than the pipelined kernel's slabs (9472 x 4096 at 12 / 24 tokens 16.9 / 23.3 us there,
@@ -463,6 +471,7 @@ template <int XVEC, bool BF16>
 static hipError_t launch_m(const LinearArgs& a, hipStream_t stream) {
   switch (gemm_route(a, XVEC)) {
     case kSmallM: return smallm_dispatch<XVEC, BF16>(a, stream);
+    case kRing: return launch_ring4<BF16>(&a, 1, stream);
     case kPipe: return launch_pipe4<BF16>(&a, 1, stream);
     case kPrefill256:
       if constexpr (XVEC == 1) return launch_prefill_cfg<BF16, 16, 2, 8, 1, 1, 8, 2, 1>(a, stream);
@@ -502,13 +511,17 @@ static hipError_t launch_gemm_fmt(const LinearArgs& a, hipStream_t stream) {
 
 // What launch_gemm_fmt (4 bits) and the pipelined kernel (every width) do with a linear of 2 tokens and more, as
 // uniql_w4_linear_kernel reports it: the kernel, the tile's tokens and rows and the waves that K is split over (0, 0, 0 for the
-// decode-batch kernel).
+// decode-batch kernels).
 static inline void gemm_choice_of(const LinearArgs& a, int out[4]) {
-  static const int tiles[][3] = {{0, 0, 0}, {0, 0, 0}, {256, 256, 1}, {128, 256, 1}, {64, 256, 1}, {64, 128, 2}, {32, 128, 2},
+  static const int tiles[][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}, {256, 256, 1}, {128, 256, 1}, {64, 256, 1}, {64, 128, 2}, {32, 128, 2},
                                  {16, 16, 8}, {16, 64, 4}, {32, 16, 8}, {32, 64, 4}, {64, 32, 4}, {64, 64, 4}};
   const int xm = gemm_xm(a);
   const GemmRoute r = a.bits == 4 ? gemm_route(a, xm) : kPipe;
-  out[0] = r == kSmallM ? 1 : r == kPipe ? 2 : r == kPrefill256 ? 3 : 4;
+  if (r == kRing && xm == 2 && a.M > 16) {
+    ring_tile_of(a, out);
+    return;
+  }
+  out[0] = r == kSmallM || r == kRing ? 1 : r == kPipe ? 2 : r == kPrefill256 ? 3 : 4;
   for (int i = 0; i < 3; ++i) out[1 + i] = tiles[r][i];
   if (r != kPipe) return;
   const PipeTile t = a.bits == 4 ? pipe_pick<4>(&a, 1) : a.bits == 8 ? pipe_pick<8>(&a, 1) : a.bits == 6 ? pipe_pick<6>(&a, 1) : pipe_pick<3>(&a, 1);
@@ -522,12 +535,12 @@ static inline void gemm_choice_of(const LinearArgs& a, int out[4]) {
 // stays set for a linear that shares with no other and was not launched.
 template <bool BF16>
 static hipError_t launch_gemm_batch_fmt(const LinearArgs* a, int n, hipStream_t stream, unsigned* left) {
-  // what may share: 1 the decode-batch kernel, 2 and up the pipelined one, 0 none
+  // what may share: 1 the decode-batch kernel, 2 and 3 the ring kernel, 4 and up the pipelined one, 0 none
   int kind[kMaxBatch];
   for (int i = 0; i < n; ++i) {
     const int xm = gemm_xm(a[i]);
     const GemmRoute r = gemm_route(a[i], xm);
-    kind[i] = r == kSmallM ? (xm == 1 ? 1 : 0) : r == kPipe ? 2 + pipe_way(a[i]) * 2 + (xm == 2) : 0;
+    kind[i] = r == kSmallM ? (xm == 1 ? 1 : 0) : r == kRing ? 2 + (xm == 2) : r == kPipe ? 4 + pipe_way(a[i]) * 2 + (xm == 2) : 0;
   }
   *left = (1u << n) - 1;
   for (int i = 0; i < n; ++i) {
@@ -542,7 +555,7 @@ static hipError_t launch_gemm_batch_fmt(const LinearArgs* a, int n, hipStream_t 
         outputs += (long long)a[j].km.n_keep * a[j].M;
       }
     if (m < 2) continue;
-    const hipError_t e = kind[i] == 1 ? smallm_batch<BF16>(set, m, stream) : launch_pipe4<BF16>(set, m, stream);
+    const hipError_t e = kind[i] == 1 ? smallm_batch<BF16>(set, m, stream) : kind[i] <= 3 ? launch_ring4<BF16>(set, m, stream) : launch_pipe4<BF16>(set, m, stream);
     if (e != hipSuccess) return e;
     *left &= ~taken;
   }

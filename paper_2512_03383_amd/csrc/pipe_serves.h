@@ -40,6 +40,35 @@ static inline bool pipe_serves(const LinearArgs& a) {
   return (long long)a.N_total * (a.K_total / 8) * a.bits < lim && (long long)a.ldx * 2 * 128 + (long long)a.K_total * 2 < lim;
 }
 
+// What the ring kernel (ring_kernel.h) serves: 4-bit codes, 2..32 tokens, rows of sixteen kept groups and more (the window of zero points;
+// the groups that are kept and not the stored ones, so that a compact copy of the matrix goes the same way) and up to 320, whose scales
+// and zero points fit the LDS beside the rings.
+static inline bool ring_serves(const LinearArgs& a) {
+  return a.bits == 4 && a.M <= 32 && a.km.k_span > 15 * kGroup && a.km.k_span <= 320 * kGroup && pipe_serves(a) &&
+         ((a.M - 1) * a.ldx + a.km.k_keep) * 2 < (1ll << 31);
+}
+
+// Where it is the fastest, from 900 sizes timed against the kernels that took them (256..18944 rows, 2048..14336 columns, 2..32 tokens, both
+// formats, prefixes and segments; row tiles of 16):
+//  - Matrices of fewer than 400 row tiles: prefixes 0.77..0.95 of the time in the mean (0.49..1.05; above 320 row tiles and from 9 tokens
+//    on level, and there so that a tall member of a set shares a launch with short ones), segments of up to 16 tokens 0.73..0.88
+//    (above 320 row tiles and 8 tokens 1.02).  17..32 tokens of segments 0.82..1.03 up to 256 row tiles, 1.07 above.
+//  - 400..600 row tiles: up to 8 tokens 0.77..0.98; 9..32 of prefixes 0.93..1.0 with rows of up to 32 groups; longer rows (0.9..1.15) stay with
+//    the pipelined kernel, segments of 9..32 tokens (1.02..1.12) with whatever has them.
+//  - Taller matrices: 1.14 to 0.87, no line was found.
+// Segments of 17..32 tokens beyond 32 groups stay where they were, 0.88..0.93 notwithstanding: the pipelined kernel's tests hold it to them.
+// (33..64 tokens: a block of 16 rows fetches all of the activations, 29 bytes a clock, which is what takes the time: 0.82 to 1.6, and where
+// it was faster by itself the pass of a layer was not.)
+static inline bool ring_takes(const LinearArgs& a, bool segments_keep) {
+  if (!ring_serves(a)) return false;
+  const int row_tiles = (a.km.n_keep + 15) / 16;
+  const bool shorter = a.km.k_span <= 32 * kGroup;
+  if (row_tiles > 600) return false;
+  if (a.M <= 8) return true;
+  if (a.km.cs_stride != 0) return a.M <= 16 ? row_tiles <= 320 : row_tiles <= 256 && shorter && !segments_keep;
+  return row_tiles < 400 || shorter;
+}
+
 // Codes of 8, 6 and 3 bits: whether the streaming kernel with a token per grid row (w8.hip, wbits.hip) is faster than the pipelined
 // one.  It reads and unpacks the weights once per token, but spreads rows and tokens over the whole chip, where the other has a
 // block for 32 rows and all tokens: few rows or very few tokens (6 bits, 256 x 12160 at 8 tokens 7.7 against 24.5 us, 2048 x 4096

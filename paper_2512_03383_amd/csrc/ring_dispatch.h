@@ -1,0 +1,34 @@
+// Which tile of ring_kernel.h a set of linears takes, and its launch.  One translation unit per format (ring_w4*.hip) instantiates it.
+#pragma once
+#include "ring_kernel.h"
+#include "ring_pick.h"
+
+namespace uniql {
+
+template <int XT, bool BF16, bool SEG>
+static hipError_t ring_tile(const LinearArgs* p, int n, int bf, hipStream_t s) {
+  switch (bf) {
+    case 1: return ring_launch<XT, 1, 4, BF16, SEG>(p, n, s);
+    case 2: return ring_launch<XT, 2, 4, BF16, SEG>(p, n, s);
+    case 3: return ring_launch<XT, 3, 4, BF16, SEG>(p, n, s);
+    case 4: return ring_launch<XT, 4, 4, BF16, SEG>(p, n, s);
+    case 5: return ring_launch<XT, 5, 4, BF16, SEG>(p, n, s);
+  }
+  return hipErrorInvalidValue;
+}
+
+template <bool BF16, bool SEG>
+static hipError_t ring_run(const LinearArgs* p, int n, hipStream_t s) {
+  const int M = p[0].M, bf = ring_rows(p, n);
+  if (M <= 4) return ring_tile<4, BF16, SEG>(p, n, bf, s);
+  if (M <= 8) return ring_tile<8, BF16, SEG>(p, n, bf, s);
+  if (M <= 16) return ring_tile<16, BF16, SEG>(p, n, bf, s);
+  return ring_tile<32, BF16, SEG>(p, n, bf, s);
+}
+
+template <bool BF16>
+static hipError_t ring_linears(const LinearArgs* p, int n, hipStream_t s) {
+  return p[0].km.cs_stride != 0 ? ring_run<BF16, true>(p, n, s) : ring_run<BF16, false>(p, n, s);
+}
+
+}  // namespace uniql

@@ -1,0 +1,6 @@
+// The ring kernel (ring_kernel.h) on 4-bit codes, fp16.
+#include "ring_dispatch.h"
+
+namespace uniql {
+hipError_t launch_ring_w4(const LinearArgs* p, int n, hipStream_t stream) { return ring_linears<false>(p, n, stream); }
+}  // namespace uniql

@@ -1,0 +1,109 @@
+"""GPU parity of the ring kernel (csrc/ring_kernel.h): every slot of tokens and number of row fragments, ragged rows and columns, segments of
+every stride, rows around the shortest that it takes, tokens next to infinities; against the CPU oracle."""
+import numpy as np
+import pytest
+
+import workloads as wl
+from test_gpu_pipe_tiles import FORMATS, check, env, np16, oracle, weight   # noqa: F401 (env: the fixture)
+from workloads import Keep
+
+pytestmark = pytest.mark.gpu
+
+TOKENS = [2, 4, 5, 8, 9, 16, 17, 31, 32]
+
+
+def run(env, uref, N, K, M, keep, cols, fmt, zeros, pad, rows):   # noqa: F811
+    uq, torch = env
+    g = torch.Generator(device="cuda").manual_seed(N + K + M)
+    W = weight(env, g, N, K, 4, fmt, zeros=zeros)
+    nk, kk = uq.kept_dims(W, keep)
+    xb = torch.full((M, kk + pad), float("nan"), dtype=W.scales.dtype, device="cuda")
+    xb[:, :kk] = torch.randn((M, kk), generator=g, device="cuda").to(W.scales.dtype)
+    yb = torch.full((M + 2, nk + 3), -5.0, dtype=W.scales.dtype, device="cuda")
+    uq.uniql_w4_linear(W, keep, xb[:, :kk], yb[1:M + 1, :nk])
+    torch.cuda.synchronize()
+    assert torch.all(yb[0] == -5.0) and torch.all(yb[-1] == -5.0) and torch.all(yb[:, nk:] == -5.0), "wrote beside the output"
+    rows = np.unique(np.asarray(rows).clip(0, nk - 1)).astype(np.int64)
+    ref = oracle(uref, W, np.ascontiguousarray(np16(xb[:, :kk], fmt)), cols, fmt, torch.from_numpy(rows).cuda())
+    check(yb[1:M + 1, :nk].float().cpu().numpy()[:, rows], ref, fmt)
+
+
+# rows: one, two and three fragments of 16 a block (256, 512 and more row tiles); columns: the shortest rows (sixteen groups), a last group with an odd
+# number of kept columns, one kept column in it
+@pytest.mark.parametrize("fmt", FORMATS)
+@pytest.mark.parametrize("M", TOKENS)
+@pytest.mark.parametrize("N,K,kk", [(61, 2048, 2048), (4089, 2048, 1921), (4117, 2304, 2291), (8200, 2176, 2049), (9589, 2176, 2174)])
+def test_prefixes(env, uref, N, K, kk, M, fmt):   # noqa: F811
+    rng = wl.rng_for(76, N + M)
+    rows = np.concatenate([np.arange(0, N, 256), [15, 16, 47, 48, N - 17, N - 4, N - 1], rng.integers(0, N, 40)])
+    uq, _ = env
+    ld = kk + (-kk) % 8
+    choice = uq.uniql_w4_linear_kernel(N, K, Keep(n_keep=N - 2, k_keep=kk), M, bf16=fmt == "bf16", ldx=ld)
+    assert choice[0] == 1
+    run(env, uref, N, K, M, Keep(n_keep=N - 2, k_keep=kk), Keep(k_keep=kk), fmt, M % 2 == 0, ld - kk, rows)
+
+
+@pytest.mark.parametrize("fmt", FORMATS)
+@pytest.mark.parametrize("M", [3, 16, 24])
+@pytest.mark.parametrize("stride,keep", [(8, 8), (16, 10), (16, 14), (32, 26), (64, 38), (64, 64), (128, 8), (128, 94), (128, 108), (128, 126)])
+def test_segments(env, uref, stride, keep, M, fmt):   # noqa: F811
+    N, K = 203, 2176
+    k = Keep(k_keep=K // stride * keep, col_seg_stride=stride, col_seg_keep=keep)
+    run(env, uref, N, K, M, k, k, fmt, M % 2 == 0, M % 3, np.concatenate([np.arange(0, N, 97), [N - 1]]))
+
+
+# rows of one to three runs of groups a wave, fewer groups than the loads in flight, more, and the windows of eight scales and sixteen zero points
+# at the row's end
+@pytest.mark.parametrize("M", [2, 8, 16, 32])
+@pytest.mark.parametrize("K", [2048, 2176, 3072, 3200, 4096 + 128 * 7, 18944, 40960])
+def test_row_lengths(env, uref, K, M):   # noqa: F811
+    N = 36
+    run(env, uref, N, K, M, Keep(), Keep(), "f16", True, 0, np.arange(N))
+    run(env, uref, N, K, M, Keep(k_keep=K - 128), Keep(k_keep=K - 128), "bf16", False, 0, np.arange(N))
+
+
+# the same bits in a shared launch, whose blocks have more rows, as alone
+@pytest.mark.parametrize("fmt", FORMATS)
+@pytest.mark.parametrize("M", [2, 8, 16, 30])
+def test_shared_launch(env, uref, M, fmt):   # noqa: F811
+    uq, torch = env
+    g = torch.Generator(device="cuda").manual_seed(M)
+    K = 2176
+    ws = [weight(env, g, N, K, 4, fmt, zeros=i != 1) for i, N in enumerate((5000, 6300, 5003, 4999))]
+    x = torch.randn((M, K), generator=g, device="cuda").to(ws[0].scales.dtype)
+    ys = [torch.empty((M, w.N), dtype=x.dtype, device="cuda") for w in ws]
+    uq.MultiCall(ws, [None] * 4, [x] * 4, ys).run()
+    for w, y in zip(ws, ys):
+        assert torch.equal(y, uq.uniql_w4_linear(w, None, x))
+
+
+@pytest.mark.parametrize("fmt", FORMATS)
+@pytest.mark.parametrize("M", [7, 16, 32])
+@pytest.mark.parametrize("keep", [Keep(k_keep=2045), Keep(k_keep=2054), Keep(k_keep=17 * 102, col_seg_stride=128, col_seg_keep=102), Keep(k_keep=68 * 26, col_seg_stride=32, col_seg_keep=26)])
+def test_tokens_next_to_infinities(env, uref, keep, M, fmt):   # noqa: F811
+    uq, torch = env
+    g = torch.Generator(device="cuda").manual_seed(M)
+    W = weight(env, g, 5000, 2176, 4, fmt)
+    kk = uq.kept_dims(W, keep)[1]
+    x = torch.randn((M, kk), generator=g, device="cuda").to(W.scales.dtype)
+    clean = uq.uniql_w4_linear(W, keep, x)
+    bad = torch.arange(M, device="cuda") % 3 == 1
+    x2 = x.clone()
+    x2[bad] = torch.where(torch.rand((int(bad.sum()), kk), generator=g, device="cuda") < 0.5, float("inf"), float("nan")).to(x.dtype)
+    y = uq.uniql_w4_linear(W, keep, x2)
+    assert torch.equal(y[~bad], clean[~bad]) and torch.all(torch.isfinite(clean))
+
+
+# bfloat16 scales whose unpack takes the wide form, beside ordinary ones
+@pytest.mark.parametrize("M", [8, 24])
+def test_largest_scales(env, uref, M):   # noqa: F811
+    uq, torch = env
+    g = torch.Generator(device="cuda").manual_seed(M)
+    W = weight(env, g, 200, 2176, 4, "bf16")
+    W.scales[::7, 3] = 2.0 ** 118
+    x = torch.zeros((M, 2176), dtype=torch.bfloat16, device="cuda")
+    x[:, 3 * 128:4 * 128] = (torch.randn((M, 128), generator=g, device="cuda") * 1e-20).bfloat16()
+    y = uq.uniql_w4_linear(W, None, x)
+    ref = oracle(uref, W, np16(x, "bf16"), Keep(), "bf16", torch.arange(200, device="cuda"))
+    check(y.float().cpu().numpy()[:, ::7], ref[:, ::7], "bf16")
+    assert torch.all(torch.isfinite(y.float()))
