@@ -55,18 +55,22 @@ static inline bool ring_serves(const LinearArgs& a) {
 //    (above 320 row tiles and 8 tokens 1.02).  17..32 tokens of segments 0.82..1.03 up to 256 row tiles, 1.07 above.
 //  - 400..600 row tiles: up to 8 tokens 0.77..0.98; 9..32 of prefixes 0.93..1.0 with rows of up to 32 groups; longer rows (0.9..1.15) stay with
 //    the pipelined kernel, segments of 9..32 tokens (1.02..1.12) with whatever has them.
-//  - Taller matrices: 1.14 to 0.87, no line was found.
+//  - Taller prefixes with rows of up to 32 groups, by themselves and two of one height in a launch (gate and up).  9..16 tokens: 0.65..0.96
+//    and 0.68..0.91 up to 24000 rows, but 0.95..1.06 (0.75..0.81) from 14000 to 16500; at 32000 rows 1.01..1.09 (1.05..1.08).  17..32
+//    tokens: 0.97..1.08 (0.75..0.82) up to 12200 rows, 0.75..0.82 (0.85..0.99) at 19000 and 24000; between them, where the tiles of the
+//    pipelined kernel fill their rounds, 1.10..1.17 (0.86..0.89): left there; 1.04 (1.02..1.04) at 32000.  Up to 8 tokens 0.9..1.26.
 // Segments of 17..32 tokens beyond 32 groups stay where they were, 0.88..0.93 notwithstanding: the pipelined kernel's tests hold it to them.
 // (33..64 tokens: a block of 16 rows fetches all of the activations, 29 bytes a clock, which is what takes the time: 0.82 to 1.6, and where
 // it was faster by itself the pass of a layer was not.)
+constexpr int kRingTallest = 1536;   // row tiles
 static inline bool ring_takes(const LinearArgs& a, bool segments_keep) {
   if (!ring_serves(a)) return false;
   const int row_tiles = (a.km.n_keep + 15) / 16;
   const bool shorter = a.km.k_span <= 32 * kGroup;
-  if (row_tiles > 600) return false;
-  if (a.M <= 8) return true;
+  if (a.M <= 8) return row_tiles <= 600;
   if (a.km.cs_stride != 0) return a.M <= 16 ? row_tiles <= 320 : row_tiles <= 256 && shorter && !segments_keep;
-  return row_tiles < 400 || shorter;
+  if (row_tiles < 400) return true;
+  return shorter && row_tiles <= kRingTallest && (a.M <= 16 || row_tiles <= 820 || row_tiles > 1040);
 }
 
 // Codes of 8, 6 and 3 bits: whether the streaming kernel with a token per grid row (w8.hip, wbits.hip) is faster than the pipelined

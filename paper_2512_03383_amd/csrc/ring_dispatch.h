@@ -14,6 +14,13 @@ static hipError_t ring_tile(const LinearArgs* p, int n, int bf, hipStream_t s) {
     case 4: return ring_launch<XT, 4, 4, BF16, SEG>(p, n, s);
     case 5: return ring_launch<XT, 5, 4, BF16, SEG>(p, n, s);
   }
+  if constexpr (!SEG) {
+    if (bf == 6) return ring_launch<XT, 6, 4, BF16, SEG>(p, n, s);
+    if (bf == 7) return ring_launch<XT, 7, 4, BF16, SEG>(p, n, s);
+    if constexpr (XT <= 16) {
+      if (bf == 8) return ring_launch<XT, 8, 4, BF16, SEG>(p, n, s);
+    }
+  }
   return hipErrorInvalidValue;
 }
 

@@ -14,9 +14,10 @@ constexpr int kRingLds = 160 * 1024;
 
 // Fragments of 16 rows per block: the fewest rounds of the chip's compute units (a block fills one), then the fewest rows: a round costs
 // its fragments and one more (14208 x 3584 at 8 tokens, 888 row tiles, 1 .. 5 fragments 19.6, 16.0, 18.5, 13.3, 13.7 us; 14336 x 4096 at 32
-// tokens 28.4, 19.5, 23.2, 15.8, 17.4).  The order of the sums does not depend on it.
+// tokens 28.4, 19.5, 23.2, 15.8, 17.4; two of 14336 x 4096 at 16 tokens, 3 .. 8 fragments 30.1, 27.4, 31.2, 30.0, 21.4, 22.3).  Beyond five
+// a launch of column segments has not been found faster; eight of 32 tokens do not fit the LDS.  The order of the sums does not depend on it.
 static inline int ring_rows(const LinearArgs* p, int n) {
-  const int cus = prefill_grid_limit(), most = 5;
+  const int cus = prefill_grid_limit(), most = p[0].km.cs_stride != 0 ? 5 : p[0].M <= 16 ? 8 : 7;
   int groups = 0;
   for (int i = 0; i < n; ++i) groups = (p[i].km.k_span + kGroup - 1) / kGroup > groups ? (p[i].km.k_span + kGroup - 1) / kGroup : groups;
   int best = 1;

@@ -43,6 +43,16 @@ def test_prefixes(env, uref, N, K, kk, M, fmt):   # noqa: F811
     run(env, uref, N, K, M, Keep(n_keep=N - 2, k_keep=kk), Keep(k_keep=kk), fmt, M % 2 == 0, ld - kk, rows)
 
 
+# taller matrices: four to six fragments of 16 a block
+@pytest.mark.parametrize("fmt", FORMATS)
+@pytest.mark.parametrize("M", [9, 16, 19, 32])
+@pytest.mark.parametrize("N,kk", [(12801, 2048), (16260, 2048), (19203, 2175), (21001, 2173), (24570, 2050)])
+def test_tall_prefixes(env, uref, N, kk, M, fmt):   # noqa: F811
+    rng = wl.rng_for(77, N + M)
+    rows = np.concatenate([np.arange(0, N, 512), [15, 16, 63, 64, 79, 80, 111, 112, 127, 128, N - 17, N - 4, N - 1], rng.integers(0, N, 40)])
+    run(env, uref, N, 2176, M, Keep(n_keep=N - 2, k_keep=kk), Keep(k_keep=kk), fmt, M % 2 == 0, (-kk) % 8, rows)
+
+
 @pytest.mark.parametrize("fmt", FORMATS)
 @pytest.mark.parametrize("M", [3, 16, 24])
 @pytest.mark.parametrize("stride,keep", [(8, 8), (16, 10), (16, 14), (32, 26), (64, 38), (64, 64), (128, 8), (128, 94), (128, 108), (128, 126)])
@@ -62,17 +72,18 @@ def test_row_lengths(env, uref, K, M):   # noqa: F811
     run(env, uref, N, K, M, Keep(k_keep=K - 128), Keep(k_keep=K - 128), "bf16", False, 0, np.arange(N))
 
 
-# the same bits in a shared launch, whose blocks have more rows, as alone
+# the same bits in a shared launch, whose blocks have more rows (five fragments, seven and eight), as alone
 @pytest.mark.parametrize("fmt", FORMATS)
 @pytest.mark.parametrize("M", [2, 8, 16, 30])
-def test_shared_launch(env, uref, M, fmt):   # noqa: F811
+@pytest.mark.parametrize("sizes", [(5000, 6300, 5003, 4999), (12801, 12799), (16380, 16361), (9001, 16401)])
+def test_shared_launch(env, uref, sizes, M, fmt):   # noqa: F811
     uq, torch = env
     g = torch.Generator(device="cuda").manual_seed(M)
     K = 2176
-    ws = [weight(env, g, N, K, 4, fmt, zeros=i != 1) for i, N in enumerate((5000, 6300, 5003, 4999))]
+    ws = [weight(env, g, N, K, 4, fmt, zeros=i != 1) for i, N in enumerate(sizes)]
     x = torch.randn((M, K), generator=g, device="cuda").to(ws[0].scales.dtype)
     ys = [torch.empty((M, w.N), dtype=x.dtype, device="cuda") for w in ws]
-    uq.MultiCall(ws, [None] * 4, [x] * 4, ys).run()
+    uq.MultiCall(ws, [None] * len(ws), [x] * len(ws), ys).run()
     for w, y in zip(ws, ys):
         assert torch.equal(y, uq.uniql_w4_linear(w, None, x))
 
