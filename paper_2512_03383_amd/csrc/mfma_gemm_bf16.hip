@@ -9,7 +9,7 @@ hipError_t launch_w4_gemm_batch_bf16(const LinearArgs* a, int n, hipStream_t str
 }
 
 hipError_t launch_w4_gate_up_silu_batch_bf16(const LinearArgs* p, hipStream_t stream, bool* done) {
-  return smallm_glu<true>(p, stream, done);
+  return glu_batch<true>(p, stream, done);
 }
 
 }  // namespace uniql

@@ -391,6 +391,24 @@ static hipError_t launch_ring4(const LinearArgs* p, int n, hipStream_t stream) {
   else return launch_ring_w4(p, n, stream);
 }
 
+// gate and up of a decode batch in one launch: what smallm_glu serves.  From 9 tokens on, with rows of sixteen groups and more, the ring
+// kernel's form of it: a block stages its activations once for both matrices and every wave loads for itself (12185 x 4096 at 9 and 16 tokens 25.0 -> 18.4 and 28.4 -> 19.8 us, 14208 x 3584 25.7 -> 20.5 and 24.2 -> 21.5,
+// 18944 x 3584 36.6 -> 29.8 and 35.2 -> 30.3, 24000 x 4096 41.2 -> 35.2 and 38.5 -> 35.9; 32000 x 4096 43.2 for 48.4).  Up to 8 tokens as the pair
+// of linears: not faster.
+template <bool BF16>
+static hipError_t glu_batch(const LinearArgs* p, hipStream_t stream, bool* done) {
+  if (!smallm_glu_serves(p)) {
+    *done = false;
+    return hipSuccess;
+  }
+  if (p[0].M >= 9 && (p[0].km.n_keep + 15) / 16 <= kRingTallest && ring_serves(p[0]) && ring_serves(p[1])) {
+    *done = true;
+    if constexpr (BF16) return launch_ring_glu_bf16(p, stream);
+    else return launch_ring_glu(p, stream);
+  }
+  return smallm_glu<BF16>(p, stream, done);
+}
+
 // Which kernel a linear of 2 tokens and more takes.  It follows from the linear alone.  kTile*: w4_mfma_kernel with tiles of
 // that many tokens x rows, K over that many waves of a block.
 enum GemmRoute {

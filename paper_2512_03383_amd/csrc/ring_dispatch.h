@@ -33,6 +33,12 @@ static hipError_t ring_run(const LinearArgs* p, int n, hipStream_t s) {
   return ring_tile<32, BF16, SEG>(p, n, bf, s);
 }
 
+// gate (p[0]) and up (p[1]) of 9..16 tokens with h = SiLU(g) * u in one launch (the caller checks that both are served)
+template <bool BF16>
+static hipError_t ring_glu(const LinearArgs* p, hipStream_t s) {
+  return ring_glu_rows(p) == 6 ? ring_launch<16, 6, 4, BF16, false, true>(p, 2, s) : ring_launch<16, 8, 4, BF16, false, true>(p, 2, s);
+}
+
 template <bool BF16>
 static hipError_t ring_linears(const LinearArgs* p, int n, hipStream_t s) {
   return p[0].km.cs_stride != 0 ? ring_run<BF16, true>(p, n, s) : ring_run<BF16, false>(p, n, s);

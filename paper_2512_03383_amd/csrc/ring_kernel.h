@@ -96,12 +96,16 @@ __device__ __forceinline__ void ring_wait(int rem) {
   else ring_wait_last<S, P, MOST - 1>(rem);
 }
 
-template <int XT, int BF, int BITS, bool BF16, bool SEG>
+// GLU: the gate and the up matrix of a gated MLP (Eq. 1; problems 0 and 1: the same activations, sizes and number of kept rows).  Fragments of a block
+// are gate rows and up rows of one row tile in turn, and the wave that adds the partial sums of both stores h = SiLU(g) * u, rounded once.
+template <int XT, int BF, int BITS, bool BF16, bool SEG, bool GLU>
 __global__ __launch_bounds__(kRingWaves * kWave, 2) void w_ring_kernel(RingBatch bt) {
 #ifdef __HIP_DEVICE_COMPILE__
   typedef RingShape<XT, BF, BITS> S;
   constexpr int AF = S::AF, H = S::H, T = S::T, CH = S::CH, XL = S::XL, WL = S::WL, U = S::U, L = S::L, R = S::R;
   static_assert(BITS == 4, "other widths read their windows differently");
+  static_assert(!GLU || (BF % 2 == 0 && S::AF == 1 && !SEG), "pairs of fragments");
+  constexpr int NM = GLU ? 2 : 1;                          // matrices of a block: fragment b is of matrix b % NM
   extern __shared__ __align__(16) unsigned char smem[];
   typedef __attribute__((address_space(3))) unsigned char lds_byte;
   const int lane = threadIdx.x & 63;
@@ -118,7 +122,11 @@ __global__ __launch_bounds__(kRingWaves * kWave, 2) void w_ring_kernel(RingBatch
   }
   const LinearArgs a = bt.p[pi];
   const KeepMap& km = a.km;
-  const int n0 = tile * R;
+  const int n0 = tile * (R / NM);
+  auto stored = [&](int m, int rc) {                       // compact row of matrix m -> stored row (past the last one: a valid, unused row)
+    rc = rc < km.n_keep ? rc : km.n_keep - 1;
+    return stored_row(GLU && m == 1 ? bt.p[1].km : km, rc);
+  };
   const int row_bytes = a.K_total / 8 * BITS, gpr = a.K_total / kGroup;
   const int ngroups = (km.k_span + kGroup - 1) / kGroup;
   // this wave's groups; the first waves, which lie on different SIMDs, take one more
@@ -129,11 +137,16 @@ __global__ __launch_bounds__(kRingWaves * kWave, 2) void w_ring_kernel(RingBatch
   const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_byte*)smem;
   const int ring0 = wave * S::WaveLds, wring0 = ring0 + L * S::XPart;
   const int sz0 = kRingWaves * S::WaveLds, nws = (ngroups + 7) / 8, nwz = (ngroups + 15) / 16, zz0 = sz0 + nws * R * 16;
-  const bool has_z = a.zeros != nullptr;
-  const uint32_t zmask = has_z ? 0xffu : 0u, zdef = has_z ? 0u : 1u << (BITS - 1);   // (without zero points every one is the middle of the range)
+  uint32_t zmask[NM], zdef[NM];                            // (without zero points every one is the middle of the range)
 
   const u32x4_t rx = ring_rsrc(a.x, (int)(((long long)(a.M - 1) * a.ldx + km.k_keep) * 2));
-  const u32x4_t rw = ring_rsrc(a.qweight, a.N_total * row_bytes);
+  u32x4_t rw[NM];
+#pragma unroll
+  for (int m = 0; m < NM; ++m) {
+    const LinearArgs& w = bt.p[GLU ? m : pi];
+    rw[m] = ring_rsrc(w.qweight, w.N_total * row_bytes);
+    zmask[m] = w.zeros ? 0xffu : 0u, zdef[m] = w.zeros ? 0u : 1u << (BITS - 1);
+  }
 
   // ---- an odd last column of a prefix, whose word may lie partly past the resource and then reads as zero (see clear, below): from the
   // word that ends with it, a lane per token
@@ -144,19 +157,21 @@ __global__ __launch_bounds__(kRingWaves * kWave, 2) void w_ring_kernel(RingBatch
   // ---- scales and zero points: window w of eight (sixteen) groups of every row of the tile, windows dealt to the waves.  A window never
   // leaves the row (at the row's end it starts earlier).
   {
-    const u32x4_t rs = ring_rsrc(a.scales, a.N_total * gpr * 2);
-    const u32x4_t rz = ring_rsrc(a.zeros, has_z ? a.N_total * gpr : 0);
 #pragma unroll
-    for (int p = 0; p < (R + 63) / 64; ++p) {
-      int rc = n0 + p * 64 + lane;
-      rc = rc < km.n_keep ? rc : km.n_keep - 1;
-      const int e0 = stored_row(km, rc) * gpr;
-      if (p * 64 + lane < R) {
-        for (int w = wave; w < nws; w += kRingWaves)
-          ring_load(rs, lds0 + sz0 + (w * R + p * 64) * 16, 2 * e0, 2 * (8 * w < gpr - 8 ? 8 * w : gpr - 8));
-        if (has_z)
-          for (int w = kRingWaves - 1 - wave; w < nwz; w += kRingWaves)
-            ring_load(rz, lds0 + zz0 + (w * R + p * 64) * 16, e0, 16 * w < gpr - 16 ? 16 * w : gpr - 16);
+    for (int m = 0; m < NM; ++m) {
+      const LinearArgs& w = bt.p[GLU ? m : pi];
+      const u32x4_t rs = ring_rsrc(w.scales, w.N_total * gpr * 2);
+      const u32x4_t rz = ring_rsrc(w.zeros, w.zeros ? w.N_total * gpr : 0);
+#pragma unroll
+      for (int p = 0; p < (R + 63) / 64; ++p) {
+        const int r = p * 64 + lane, e0 = stored(m, GLU ? n0 + (r >> 5) * 16 + (r & 15) : n0 + r) * gpr;
+        if (r < R && (!GLU || (r >> 4 & 1) == m)) {
+          for (int i = wave; i < nws; i += kRingWaves)
+            ring_load(rs, lds0 + sz0 + (i * R + p * 64) * 16, 2 * e0, 2 * (8 * i < gpr - 8 ? 8 * i : gpr - 8));
+          if (w.zeros)
+            for (int i = kRingWaves - 1 - wave; i < nwz; i += kRingWaves)
+              ring_load(rz, lds0 + zz0 + (i * R + p * 64) * 16, e0, 16 * i < gpr - 16 ? 16 * i : gpr - 16);
+        }
       }
     }
   }
@@ -185,9 +200,7 @@ __global__ __launch_bounds__(kRingWaves * kWave, 2) void w_ring_kernel(RingBatch
 #pragma unroll
   for (int k = 0; k < WL; ++k) {
     const int v = k * 64 + lane, row = v / U, j = v - row * U, js = j ^ (bank_key(row) >> 2);
-    int rc = n0 + row;
-    rc = rc < km.n_keep ? rc : km.n_keep - 1;
-    woff[k] = stored_row(km, rc) * row_bytes + js * 16;
+    woff[k] = stored(k % NM, GLU ? n0 + (row >> 5) * 16 + (row & 15) : n0 + row) * row_bytes + js * 16;   // (GLU: a load is a fragment)
   }
   const int whole = SEG ? ngroups : km.k_keep / kGroup;    // groups that are kept as a whole
   // part p of the wave's group i, into slots xs and ws
@@ -195,7 +208,7 @@ __global__ __launch_bounds__(kRingWaves * kWave, 2) void w_ring_kernel(RingBatch
     const int g = g0 + i;
     if (p == 0) {
 #pragma unroll
-      for (int k = 0; k < WL; ++k) ring_load(rw, lds0 + wring0 + ws * S::WSlot + k * 1024, woff[k], g * (U * 16));
+      for (int k = 0; k < WL; ++k) ring_load(rw[k % NM], lds0 + wring0 + ws * S::WSlot + k * 1024, woff[k], g * (U * 16));
     }
     const uint32_t to = lds0 + ring0 + xs * S::XPart;
     if (g < whole) {
@@ -303,7 +316,7 @@ __global__ __launch_bounds__(kRingWaves * kWave, 2) void w_ring_kernel(RingBatch
 #pragma unroll
         for (int b = 0; b < BF; ++b) sb[b] = *reinterpret_cast<const uint16_t*>(sp + b * 256);
 #pragma unroll
-        for (int b = 0; b < BF; ++b) zb[b] = (zp[b * 256] & zmask) | zdef;
+        for (int b = 0; b < BF; ++b) zb[b] = (zp[b * 256] & zmask[b % NM]) | zdef[b % NM];
         ws = ws + 1 == S::WS ? 0 : ws + 1;
       }
       xs = xs + 1 == L ? 0 : xs + 1;
@@ -346,12 +359,19 @@ __global__ __launch_bounds__(kRingWaves * kWave, 2) void w_ring_kernel(RingBatch
 #pragma unroll
     for (int b = 0; b < BF; ++b) red[(wave * AF * BF + f * BF + b) * 64 + lane] = acc[f][b];
   pipe_barrier();
-  for (int q = wave; q < AF * BF; q += kRingWaves) {
-    float4_t s = red[q * 64 + lane];
+  for (int q = wave; q < AF * BF / NM; q += kRingWaves) {
+    float4_t s = red[q * NM * 64 + lane];
 #pragma unroll
-    for (int k = 1; k < kRingWaves; ++k) s += red[(k * AF * BF + q) * 64 + lane];
+    for (int k = 1; k < kRingWaves; ++k) s += red[(k * AF * BF + q * NM) * 64 + lane];
+    if constexpr (GLU) {
+      float4_t u = red[(q * 2 + 1) * 64 + lane];
+#pragma unroll
+      for (int k = 1; k < kRingWaves; ++k) u += red[(k * AF * BF + q * 2 + 1) * 64 + lane];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) s[v] = s[v] * u[v] * __builtin_amdgcn_rcpf(1.0f + __expf(-s[v]));
+    }
     // lane l holds token l % 16 of the fragment, rows 4 (l / 16) + v
-    const int f = q / BF, b = q - f * BF, to = f * 16 + n, rc = n0 + b * 16 + 4 * ks;
+    const int f = q / (BF / NM), b = q - f * (BF / NM), to = f * 16 + n, rc = n0 + b * 16 + 4 * ks;
     if (to >= a.M || rc >= km.n_keep) continue;
     half_t* y = a.y + (size_t)to * a.ldy + rc;
     uint16_t o[4];
@@ -372,13 +392,13 @@ __global__ __launch_bounds__(kRingWaves * kWave, 2) void w_ring_kernel(RingBatch
 #endif
 }
 
-template <int XT, int BF, int BITS, bool BF16, bool SEG>
+template <int XT, int BF, int BITS, bool BF16, bool SEG, bool GLU = false>
 static hipError_t ring_launch(const LinearArgs* p, int n, hipStream_t stream) {
   typedef RingShape<XT, BF, BITS> S;
   if constexpr (!S::Valid) {
     return hipErrorInvalidValue;
   } else {
-    auto kern = w_ring_kernel<XT, BF, BITS, BF16, SEG>;
+    auto kern = w_ring_kernel<XT, BF, BITS, BF16, SEG, GLU>;
     RingBatch b;
     b.n = n;
     int tiles = 0, most = 0;
@@ -386,10 +406,12 @@ static hipError_t ring_launch(const LinearArgs* p, int n, hipStream_t stream) {
       b.p[i] = p[i < n ? i : 0];
       b.first[i] = tiles;
       if (i >= n) continue;
-      tiles += (p[i].km.n_keep + S::R - 1) / S::R;
+      if (!GLU) tiles += (p[i].km.n_keep + S::R - 1) / S::R;
+      else tiles = (p[i].km.n_keep + S::R / 2 - 1) / (S::R / 2);
       const int ng = (p[i].km.k_span + kGroup - 1) / kGroup;
       most = ng > most ? ng : most;
     }
+    if (GLU) b.n = 1;                                      // (tiles are those of the pair)
     b.tiles = tiles;
     const int lds = S::lds(most);
     if (lds > kRingLds) return hipErrorInvalidValue;

@@ -33,6 +33,13 @@ static inline int ring_rows(const LinearArgs* p, int n) {
   return best;
 }
 
+// the same for a gated pair: three or four fragments of each matrix (the pairs that are served have 640 .. 1536 row tiles: fewer never are the best)
+static inline int ring_glu_rows(const LinearArgs* p) {
+  const int cus = prefill_grid_limit(), row_tiles = (p[0].km.n_keep + 15) / 16;
+  auto rounds = [&](int rows) { return ((row_tiles + rows - 1) / rows + cus - 1) / cus; };
+  return rounds(3) * 7 <= rounds(4) * 9 ? 6 : 8;
+}
+
 // as uniql_w4_linear_kernel reports it: among the kernels whose loads write LDS directly, tokens and rows of a tile, K over eight waves
 static inline void ring_tile_of(const LinearArgs& a, int out[4]) {
   out[0] = 2, out[1] = ring_tokens(a.M), out[2] = 16 * ring_rows(&a, 1), out[3] = 8;

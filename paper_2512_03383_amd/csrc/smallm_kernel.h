@@ -531,12 +531,15 @@ static hipError_t smallm_launch_glu(const LinearArgs* p, hipStream_t stream) {
 // gate (p[0]) and up (p[1]) of a decode batch with h = SiLU(g) * u in one launch: 2..16 tokens, the same kept rows in
 // number and the same column prefix (the caller checks), tall matrices whose activations fit the block's image.
 // *done = false: not such a pair, nothing was launched.
+static inline bool smallm_glu_serves(const LinearArgs* p) {
+  for (int i = 0; i < 2; ++i)
+    if (p[i].km.cs_stride != 0 || p[i].km.k_keep < 8 || !smallm_serves(p[i]) || !smallm_pre(p[i])) return false;
+  return true;
+}
 template <bool BF16>
 static hipError_t smallm_glu(const LinearArgs* p, hipStream_t stream, bool* done) {
-  *done = false;
-  for (int i = 0; i < 2; ++i)
-    if (p[i].km.cs_stride != 0 || p[i].km.k_keep < 8 || !smallm_serves(p[i]) || !smallm_pre(p[i])) return hipSuccess;
-  *done = true;
+  *done = smallm_glu_serves(p);
+  if (!*done) return hipSuccess;
   if (p[0].M <= 4) return smallm_launch_glu<4, BF16>(p, stream);
   if (p[0].M <= 8) return smallm_launch_glu<8, BF16>(p, stream);
   return smallm_launch_glu<16, BF16>(p, stream);

@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 
 import workloads as wl
+from parity_util import TOL, TOL_BF16, linear_err
 from test_gpu_pipe_tiles import FORMATS, check, env, np16, oracle, weight   # noqa: F401 (env: the fixture)
 from workloads import Keep
 
@@ -51,6 +52,31 @@ def test_tall_prefixes(env, uref, N, kk, M, fmt):   # noqa: F811
     rng = wl.rng_for(77, N + M)
     rows = np.concatenate([np.arange(0, N, 512), [15, 16, 63, 64, 79, 80, 111, 112, 127, 128, N - 17, N - 4, N - 1], rng.integers(0, N, 40)])
     run(env, uref, N, 2176, M, Keep(n_keep=N - 2, k_keep=kk), Keep(k_keep=kk), fmt, M % 2 == 0, (-kk) % 8, rows)
+
+
+# gate and up with h = SiLU(g) * u: two to four pairs of fragments a block, one round and more; rows kept apart; one matrix without zero points.
+@pytest.mark.parametrize("fmt", FORMATS)
+@pytest.mark.parametrize("M", [9, 15, 16])
+@pytest.mark.parametrize("N,K,keep", [(10233, 2048, Keep(k_keep=1921)), (12185, 4096, Keep(k_keep=3968)), (16300, 2176, Keep(n_keep=16299)), (20011, 2304, Keep(k_keep=2302)),
+                                      (24573, 2048, Keep()), (14400, 2176, Keep(n_keep=12000, row_seg_stride=96, row_seg_keep=80, row_seg_limit=14400))])
+def test_gated_pair(env, uref, N, K, keep, M, fmt):   # noqa: F811
+    uq, torch = env
+    g = torch.Generator(device="cuda").manual_seed(N + K + M)
+    ws = [weight(env, g, N, K, 4, fmt, zeros=i == 0) for i in range(2)]
+    nk, kk = uq.kept_dims(ws[0], keep)
+    xb = torch.full((M, kk + (-kk) % 8), float("nan"), dtype=ws[0].scales.dtype, device="cuda")
+    x = xb[:, :kk]
+    x.copy_(torch.randn((M, kk), generator=g, device="cuda"))
+    hb = torch.full((M + 2, nk + 3), -5.0, dtype=x.dtype, device="cuda")
+    uq.uniql_w4_gate_up_silu_batch(ws, [keep] * 2, x, hb[1:M + 1, :nk])
+    torch.cuda.synchronize()
+    assert torch.all(hb[0] == -5.0) and torch.all(hb[-1] == -5.0) and torch.all(hb[:, nk:] == -5.0), "wrote beside the output"
+    rows = np.unique(np.concatenate([np.arange(0, nk, 512), [15, 16, 31, 32, 47, 48, 63, 64, nk - 17, nk - 4, nk - 1]]).clip(0, nk - 1)).astype(np.int64)
+    stored = rows // keep.row_seg_keep * keep.row_seg_stride + rows % keep.row_seg_keep if keep.row_seg_stride else rows
+    go, up = (oracle(uref, w, np.ascontiguousarray(np16(x, fmt)), Keep(k_keep=kk), fmt, torch.from_numpy(stored).cuda()).astype(np.float64) for w in ws)
+    ref = go * up / (1.0 + np.exp(-go))
+    # (element by element alone: a few products carry a token's norm, and the rounding of one is up to 2^-8 of it in bfloat16)
+    assert linear_err(hb[1:M + 1, :nk].float().cpu().numpy()[:, rows], ref) <= (TOL_BF16 if fmt == "bf16" else TOL)
 
 
 @pytest.mark.parametrize("fmt", FORMATS)
