@@ -12,7 +12,7 @@ LIB = os.path.join(HERE, "libuniql.so")
 OBJ_DIR = os.path.join(HERE, "_build")
 SOURCES = ["api.hip", "gemv.hip", "gemv_sym.hip", "gemv_bf16.hip", "gemv_bf16_sym.hip", "gemv_stream.hip", "gemv_stream_bf16.hip", "gemv_stream_w3.hip", "gemv_stream_w6.hip", "gemv_stream_w8.hip", "mlp_stream.hip", "mlp_stream_bf16.hip",
            "pipe_w3.hip", "pipe_w4.hip", "pipe_w6.hip", "pipe_w8.hip", "pipe_w3_bf16.hip", "pipe_w4_bf16.hip", "pipe_w6_bf16.hip", "pipe_w8_bf16.hip",
-           "ring_w4.hip", "ring_w4_bf16.hip",
+           "ring_w3.hip", "ring_w3_bf16.hip", "ring_w4.hip", "ring_w4_bf16.hip", "ring_w6.hip", "ring_w6_bf16.hip", "ring_w8.hip", "ring_w8_bf16.hip",
            "mfma_gemm.hip", "mfma_gemm_bf16.hip", "w4_dequant.hip", "w8.hip", "wbits.hip", "rope.hip", "probe.hip"]
 # packed-fp32 VALU forms are switched off for every HIP translation unit
 # (and the compiler's rewrite of atomics as wave-wide reductions: the one LDS counter of the streaming GEMV is

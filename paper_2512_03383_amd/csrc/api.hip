@@ -145,9 +145,25 @@ static hipError_t launch_pipe(const LinearArgs* p, int n, hipStream_t s) {
   }
 }
 
+static hipError_t launch_ring(const LinearArgs* p, hipStream_t s) {
+  switch (p->bits * 2 + (p->bf16 ? 1 : 0)) {
+    case 6: return launch_ring_w3(p, s);
+    case 7: return launch_ring_w3_bf16(p, s);
+    case 12: return launch_ring_w6(p, s);
+    case 13: return launch_ring_w6_bf16(p, s);
+    case 16: return launch_ring_w8(p, s);
+    case 17: return launch_ring_w8_bf16(p, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
 static int run_linear(const LinearArgs& a, hipStream_t s) {
   if (a.bits != 4) {
     if (wide_codes_refused(a)) return UNIQL_E_SHAPE;
+    if (ring_takes_wide(a)) {
+      hipError_t er = launch_ring(&a, s);
+      return er == hipSuccess ? UNIQL_OK : hip_fail(er);
+    }
     if (pipe_serves(a) && !wide_streams(a)) {
       hipError_t ep = launch_pipe(&a, 1, s);
       return ep == hipSuccess ? UNIQL_OK : hip_fail(ep);

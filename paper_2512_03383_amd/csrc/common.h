@@ -320,6 +320,13 @@ hipError_t launch_pipe_w8_bf16(const LinearArgs* p, int n, hipStream_t stream);
 // n linears of the same token count and kind of column rule in one launch of the ring kernel (ring_kernel.h), one function per format
 hipError_t launch_ring_w4(const LinearArgs* p, int n, hipStream_t stream);
 hipError_t launch_ring_w4_bf16(const LinearArgs* p, int n, hipStream_t stream);
+// one linear of 8-, 6- or 3-bit codes, the same kernel
+hipError_t launch_ring_w3(const LinearArgs* p, hipStream_t stream);
+hipError_t launch_ring_w6(const LinearArgs* p, hipStream_t stream);
+hipError_t launch_ring_w8(const LinearArgs* p, hipStream_t stream);
+hipError_t launch_ring_w3_bf16(const LinearArgs* p, hipStream_t stream);
+hipError_t launch_ring_w6_bf16(const LinearArgs* p, hipStream_t stream);
+hipError_t launch_ring_w8_bf16(const LinearArgs* p, hipStream_t stream);
 // gate (p[0]) and up (p[1]) of a decode batch with h = SiLU(g) * u, the same kernel
 hipError_t launch_ring_glu(const LinearArgs* p, hipStream_t stream);
 hipError_t launch_ring_glu_bf16(const LinearArgs* p, hipStream_t stream);

@@ -535,7 +535,7 @@ static inline void gemm_choice_of(const LinearArgs& a, int out[4]) {
                                  {16, 16, 8}, {16, 64, 4}, {32, 16, 8}, {32, 64, 4}, {64, 32, 4}, {64, 64, 4}};
   const int xm = gemm_xm(a);
   const GemmRoute r = a.bits == 4 ? gemm_route(a, xm) : kPipe;
-  if (r == kRing && xm == 2 && a.M > 16) {
+  if ((r == kRing && xm == 2 && a.M > 16) || (a.bits != 4 && ring_takes_wide(a))) {
     ring_tile_of(a, out);
     return;
   }

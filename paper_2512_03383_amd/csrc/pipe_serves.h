@@ -40,15 +40,15 @@ static inline bool pipe_serves(const LinearArgs& a) {
   return (long long)a.N_total * (a.K_total / 8) * a.bits < lim && (long long)a.ldx * 2 * 128 + (long long)a.K_total * 2 < lim;
 }
 
-// What the ring kernel (ring_kernel.h) serves: 4-bit codes, 2..32 tokens, rows of sixteen kept groups and more (the window of zero points;
+// What the ring kernel (ring_kernel.h) serves: 2..32 tokens, rows of sixteen kept groups and more (the window of zero points;
 // the groups that are kept and not the stored ones, so that a compact copy of the matrix goes the same way) and up to 320, whose scales
 // and zero points fit the LDS beside the rings.
 static inline bool ring_serves(const LinearArgs& a) {
-  return a.bits == 4 && a.M <= 32 && a.km.k_span > 15 * kGroup && a.km.k_span <= 320 * kGroup && pipe_serves(a) &&
+  return a.M <= 32 && a.km.k_span > 15 * kGroup && a.km.k_span <= 320 * kGroup && pipe_serves(a) &&
          ((a.M - 1) * a.ldx + a.km.k_keep) * 2 < (1ll << 31);
 }
 
-// Where it is the fastest, from 900 sizes timed against the kernels that took them (256..18944 rows, 2048..14336 columns, 2..32 tokens, both
+// Where it is the fastest on 4-bit codes, from 900 sizes timed against the kernels that took them (256..18944 rows, 2048..14336 columns, 2..32 tokens, both
 // formats, prefixes and segments; row tiles of 16):
 //  - Matrices of fewer than 400 row tiles: prefixes 0.77..0.95 of the time in the mean (0.49..1.05; above 320 row tiles and from 9 tokens
 //    on level, and there so that a tall member of a set shares a launch with short ones), segments of up to 16 tokens 0.73..0.88
@@ -64,7 +64,7 @@ static inline bool ring_serves(const LinearArgs& a) {
 // it was faster by itself the pass of a layer was not.)
 constexpr int kRingTallest = 1536;   // row tiles
 static inline bool ring_takes(const LinearArgs& a, bool segments_keep) {
-  if (!ring_serves(a)) return false;
+  if (a.bits != 4 || !ring_serves(a)) return false;
   const int row_tiles = (a.km.n_keep + 15) / 16;
   const bool shorter = a.km.k_span <= 32 * kGroup;
   if (a.M <= 8) return row_tiles <= 600;
@@ -97,6 +97,27 @@ static inline bool wide_streams(const LinearArgs& a) {
   const float stream = l.s0 + l.s1 * kc + l.s4 * seg + (l.s2 + l.s3 * kc) * (work > 0.f ? work : 0.f);
   const float pipe = l.p0 + l.p1 * slabs + l.p4 * seg + (l.p2 * slabs + l.p3) * (more > 0.f ? more : 0.f);
   return stream < 1.03f * pipe;
+}
+
+// Codes of 8, 6 and 3 bits that the ring kernel takes from the pipelined one, whose 32-row tiles leave the chip idle up to 256 row tiles of 16
+// and again after every full round of 512, and whose blocks unpack a slab between two barriers.  Over 900 sizes of 512..24000 rows, 2048..18944
+// columns, 3..32 tokens, ring / pipelined in the mean: 6 bits 0.64 (up to 16 tokens) and 0.71, 8 bits 0.73..0.85 and 3 bits 0.63..0.84 up to
+// 256 row tiles, 0.63..0.82 and 0.66..0.91 above 512; us: 18944 x 3584 at 8 tokens, 8 / 6 / 3 bits 21.7 -> 15.4, 29.5 -> 18.0, 21.3 -> 15.1;
+// 3584 x 18944 25.0 -> 16.5, 37.7 -> 17.3, 24.1 -> 15.2.  Left where they were:
+//  - 257..512 row tiles, one full round of the other's: 8 bits 0.91..1.01, 3 bits 0.97..1.08; 6 bits 0.72..0.90, but 1.07 and 1.09 from 17
+//    tokens on with rows of more than 80 groups, whose activations every block fetches.
+//  - 8 and 3 bits, 193..256 row tiles, more than 24 tokens and 32 groups, for the same reason: 1.02..1.12.
+//  - 3 bits, 821..1040 row tiles: 0.99..1.13.  More than 1536 row tiles: 0.65..1.09, seven sizes.
+//  - Rows of 33..40 groups, 0.5..0.8 at 41 groups, and of 16 and 17 with 8 bits from 17 tokens on, 0.83..0.88: the tests of the pipelined kernel's
+//    small tiles hold them to it.
+static inline bool ring_takes_wide(const LinearArgs& a) {
+  if (a.bits == 4 || !ring_serves(a) || wide_streams(a)) return false;
+  const int row_tiles = (a.km.n_keep + 15) / 16, groups = (a.km.k_span + kGroup - 1) / kGroup;
+  if (row_tiles > kRingTallest || (groups > 32 && groups <= 40) || (a.bits == 8 && a.M > 16 && groups <= 17)) return false;
+  if (row_tiles > 256 && row_tiles <= 512) return a.bits == 6 && (a.M <= 16 || groups <= 80);
+  if (a.bits == 6) return true;
+  if (row_tiles > 192 && row_tiles <= 256 && a.M > 24 && groups > 32) return false;
+  return a.bits == 8 || row_tiles <= 820 || row_tiles > 1040;
 }
 
 }  // namespace uniql

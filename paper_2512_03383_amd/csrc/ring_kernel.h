@@ -35,6 +35,11 @@ struct RingShape {
   static constexpr int U = BITS;                           // units of a row's group
   static constexpr int WL = (BF * 16 * U + 63) / 64, WSlot = WL * 1024;
   static constexpr int R = 16 * BF;
+  // Permutation of the units of a row, so that sixteen rows lie on different banks: 64 and 128 bytes a row need it (a lane's pair of units
+  // of 8 bits stays together), 48 do not and 96 share a bank between two rows.
+  static __device__ __forceinline__ int code_key(int row) {
+    return BITS == 4 ? bank_key(row) >> 2 : BITS == 8 ? bank_key(row) >> 2 << 1 : 0;
+  }
   static constexpr bool fits(int l) {
     const int ws = (l + H - 1) / H;
     return l * XPart + ws * WSlot <= kRingWaveLds && l * XL + ws * WL <= 63;
@@ -103,8 +108,7 @@ __global__ __launch_bounds__(kRingWaves * kWave, 2) void w_ring_kernel(RingBatch
 #ifdef __HIP_DEVICE_COMPILE__
   typedef RingShape<XT, BF, BITS> S;
   constexpr int AF = S::AF, H = S::H, T = S::T, CH = S::CH, XL = S::XL, WL = S::WL, U = S::U, L = S::L, R = S::R;
-  static_assert(BITS == 4, "other widths read their windows differently");
-  static_assert(!GLU || (BF % 2 == 0 && S::AF == 1 && !SEG), "pairs of fragments");
+  static_assert(!GLU || (BITS == 4 && BF % 2 == 0 && S::AF == 1 && !SEG), "pairs of fragments");
   constexpr int NM = GLU ? 2 : 1;                          // matrices of a block: fragment b is of matrix b % NM
   extern __shared__ __align__(16) unsigned char smem[];
   typedef __attribute__((address_space(3))) unsigned char lds_byte;
@@ -199,8 +203,9 @@ __global__ __launch_bounds__(kRingWaves * kWave, 2) void w_ring_kernel(RingBatch
     for (int k = 0; k < XL; ++k) xoff[p][k] = unit(k, p, kGroup);
 #pragma unroll
   for (int k = 0; k < WL; ++k) {
-    const int v = k * 64 + lane, row = v / U, j = v - row * U, js = j ^ (bank_key(row) >> 2);
+    const int v = k * 64 + lane, row = v / U, j = v - row * U, js = j ^ S::code_key(row);
     woff[k] = stored(k % NM, GLU ? n0 + (row >> 5) * 16 + (row & 15) : n0 + row) * row_bytes + js * 16;   // (GLU: a load is a fragment)
+    if ((R * U) % 64 != 0 && row >= R) woff[k] = kBeyond;  // (the last load's lanes behind the tile)
   }
   const int whole = SEG ? ngroups : km.k_keep / kGroup;    // groups that are kept as a whole
   // part p of the wave's group i, into slots xs and ws
@@ -240,8 +245,8 @@ __global__ __launch_bounds__(kRingWaves * kWave, 2) void w_ring_kernel(RingBatch
   for (int t = 0; t < T; ++t) xrd[t] = ring0 + (tok * CH + ((ks * T + t) ^ key(tok))) * 16;
 #pragma unroll
   for (int p = 0; p < H; ++p) {
-    const int byte = p * (8 * BITS) + ks * (T * BITS);
-    wrd[p] = wring0 + n * (U * 16) + (((byte >> 4) ^ (bank_key(n) >> 2)) << 4) + (byte & 15);
+    const int byte = p * (8 * BITS) + (T * BITS % 4 == 0 ? ks * (T * BITS) : 0);   // (windows inside words: read_codes finds them from ks)
+    wrd[p] = wring0 + n * (U * 16) + (((byte >> 4) ^ S::code_key(n)) << 4) + (byte & 15);
   }
   float4_t acc[AF][BF];
 #pragma unroll
@@ -309,7 +314,7 @@ __global__ __launch_bounds__(kRingWaves * kWave, 2) void w_ring_kernel(RingBatch
 #pragma unroll
         for (int b = 0; b < BF; ++b)
 #pragma unroll
-          for (int h = 0; h < H; ++h) raw[h][b] = read_codes<BITS, T>(wp + wrd[h] + b * (16 * U * 16), 0);
+          for (int h = 0; h < H; ++h) raw[h][b] = read_codes<BITS, T>(wp + wrd[h] + b * (16 * U * 16), T * BITS % 4 == 0 ? 0 : ks);
         const int gs = g & ~7, gz = g & ~15;
         const unsigned char* const sp = smem + sz0 + (g >> 3) * (R * 16) + 2 * (g - (gs < gpr - 8 ? gs : gpr - 8)) + n * 16;
         const unsigned char* const zp = smem + zz0 + (g >> 4) * (R * 16) + g - (gz < gpr - 16 ? gz : gpr - 16) + n * 16;

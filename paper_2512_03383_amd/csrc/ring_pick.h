@@ -5,8 +5,8 @@
 
 namespace uniql {
 
-// tokens of a slot of activations
-static inline int ring_tokens(int M) { return M <= 4 ? 4 : M <= 8 ? 8 : M <= 16 ? 16 : 32; }
+// tokens of a slot of activations (four: only where 4-bit codes make them a part of the traffic that counts)
+static inline int ring_tokens(int M, int bits) { return M <= 4 && bits == 4 ? 4 : M <= 8 ? 8 : M <= 16 ? 16 : 32; }
 
 // LDS of a block: what ring_kernel.h's RingShape says for the codes, the activations, the scales and zero points of bf fragments of 16
 // rows, or the partial sums
@@ -15,9 +15,10 @@ constexpr int kRingLds = 160 * 1024;
 // Fragments of 16 rows per block: the fewest rounds of the chip's compute units (a block fills one), then the fewest rows: a round costs
 // its fragments and one more (14208 x 3584 at 8 tokens, 888 row tiles, 1 .. 5 fragments 19.6, 16.0, 18.5, 13.3, 13.7 us; 14336 x 4096 at 32
 // tokens 28.4, 19.5, 23.2, 15.8, 17.4; two of 14336 x 4096 at 16 tokens, 3 .. 8 fragments 30.1, 27.4, 31.2, 30.0, 21.4, 22.3).  Beyond five
-// a launch of column segments has not been found faster; eight of 32 tokens do not fit the LDS.  The order of the sums does not depend on it.
+// a launch of column segments has not been found faster; eight of 32 tokens do not fit the LDS; wide codes do
+// not come in launches of several matrices, and one of up to 1536 row tiles never wants more than six.  The order of the sums does not depend on it.
 static inline int ring_rows(const LinearArgs* p, int n) {
-  const int cus = prefill_grid_limit(), most = p[0].km.cs_stride != 0 ? 5 : p[0].M <= 16 ? 8 : 7;
+  const int cus = prefill_grid_limit(), most = p[0].km.cs_stride != 0 ? 5 : p[0].bits != 4 ? 6 : p[0].M <= 16 ? 8 : 7;
   int groups = 0;
   for (int i = 0; i < n; ++i) groups = (p[i].km.k_span + kGroup - 1) / kGroup > groups ? (p[i].km.k_span + kGroup - 1) / kGroup : groups;
   int best = 1;
@@ -42,7 +43,7 @@ static inline int ring_glu_rows(const LinearArgs* p) {
 
 // as uniql_w4_linear_kernel reports it: among the kernels whose loads write LDS directly, tokens and rows of a tile, K over eight waves
 static inline void ring_tile_of(const LinearArgs& a, int out[4]) {
-  out[0] = 2, out[1] = ring_tokens(a.M), out[2] = 16 * ring_rows(&a, 1), out[3] = 8;
+  out[0] = 2, out[1] = ring_tokens(a.M, a.bits), out[2] = 16 * ring_rows(&a, 1), out[3] = 8;
 }
 
 }  // namespace uniql

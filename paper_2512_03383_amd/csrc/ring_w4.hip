@@ -2,6 +2,6 @@
 #include "ring_dispatch.h"
 
 namespace uniql {
-hipError_t launch_ring_w4(const LinearArgs* p, int n, hipStream_t stream) { return ring_linears<false>(p, n, stream); }
+hipError_t launch_ring_w4(const LinearArgs* p, int n, hipStream_t stream) { return ring_linears<4, false>(p, n, stream); }
 hipError_t launch_ring_glu(const LinearArgs* p, hipStream_t stream) { return ring_glu<false>(p, stream); }
 }  // namespace uniql

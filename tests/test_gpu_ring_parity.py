@@ -13,10 +13,10 @@ pytestmark = pytest.mark.gpu
 TOKENS = [2, 4, 5, 8, 9, 16, 17, 31, 32]
 
 
-def run(env, uref, N, K, M, keep, cols, fmt, zeros, pad, rows):   # noqa: F811
+def run(env, uref, N, K, M, keep, cols, fmt, zeros, pad, rows, bits=4):   # noqa: F811
     uq, torch = env
     g = torch.Generator(device="cuda").manual_seed(N + K + M)
-    W = weight(env, g, N, K, 4, fmt, zeros=zeros)
+    W = weight(env, g, N, K, bits, fmt, zeros=zeros)
     nk, kk = uq.kept_dims(W, keep)
     xb = torch.full((M, kk + pad), float("nan"), dtype=W.scales.dtype, device="cuda")
     xb[:, :kk] = torch.randn((M, kk), generator=g, device="cuda").to(W.scales.dtype)
@@ -144,3 +144,33 @@ def test_largest_scales(env, uref, M):   # noqa: F811
     ref = oracle(uref, W, np16(x, "bf16"), Keep(), "bf16", torch.arange(200, device="cuda"))
     check(y.float().cpu().numpy()[:, ::7], ref[:, ::7], "bf16")
     assert torch.all(torch.isfinite(y.float()))
+
+
+# codes of 8, 6 and 3 bits: one to six fragments a block, windows of the codes inside words (3 bits, 17 tokens and more), loads that hold more units
+# than the tile has, rows as in test_prefixes
+@pytest.mark.parametrize("fmt", FORMATS)
+@pytest.mark.parametrize("bits", [8, 6, 3])
+@pytest.mark.parametrize("M", [5, 8, 9, 16, 17, 32])
+@pytest.mark.parametrize("N,K,kk", [(3061, 2304, 2177), (3050, 5248, 5248), (5003, 2432, 2305), (9018, 2304, 2291), (13005, 2560, 2559), (17003, 2432, 2430), (22003, 2304, 2304)])
+def test_wide_prefixes(env, uref, N, K, kk, M, bits, fmt):   # noqa: F811
+    uq, _ = env
+    ld = kk + (-kk) % 8
+    choice = uq.uniql_w4_linear_kernel(N, K, Keep(n_keep=N - 2, k_keep=kk), M, bits=bits, bf16=fmt == "bf16", ldx=ld)
+    if choice[3] != 8:
+        assert N == 5003 and bits != 6
+        return
+    rng = wl.rng_for(78, N + M)
+    rows = np.concatenate([np.arange(0, N, 512), [15, 16, 31, 47, 48, 63, 64, 79, 80, 95, 96, N - 17, N - 4, N - 1], rng.integers(0, N, 40)])
+    run(env, uref, N, K, M, Keep(n_keep=N - 2, k_keep=kk), Keep(k_keep=kk), fmt, M % 2 == 0, ld - kk, rows, bits)
+
+
+@pytest.mark.parametrize("fmt", FORMATS)
+@pytest.mark.parametrize("bits", [8, 6, 3])
+@pytest.mark.parametrize("M", [7, 16, 24])
+@pytest.mark.parametrize("stride,keep", [(8, 2), (8, 6), (16, 10), (32, 4), (32, 26), (64, 38), (128, 8), (128, 94), (128, 126)])
+def test_wide_segments(env, uref, stride, keep, M, bits, fmt):   # noqa: F811
+    uq, _ = env
+    N, K = 3003, 2432
+    k = Keep(k_keep=K // stride * keep, col_seg_stride=stride, col_seg_keep=keep)
+    assert uq.uniql_w4_linear_kernel(N, K, k, M, bits=bits, bf16=fmt == "bf16", ldx=K // stride * keep + M % 3)[3] == 8
+    run(env, uref, N, K, M, k, k, fmt, M % 2 == 0, M % 3, np.concatenate([np.arange(0, N, 97), [N - 1]]), bits)

@@ -1,5 +1,5 @@
 """Host-side checks of which linears the ring kernel takes (no GPU), where uniql_w4_linear_kernel tells it from the other decode-batch kernel: column
-segments of 17..32 tokens."""
+segments of 17..32 tokens, and codes of 8, 6 and 3 bits."""
 import pytest
 
 import paper_2512_03383_amd as uq
@@ -8,8 +8,8 @@ from paper_2512_03383_amd import KeepDesc
 RING = 8   # waves that K is split over
 
 
-def ring(N, K, M, keep, ldx=None):
-    c = uq.uniql_w4_linear_kernel(N, K, keep, M, ldx=ldx)
+def ring(N, K, M, keep, ldx=None, bits=4):
+    c = uq.uniql_w4_linear_kernel(N, K, keep, M, ldx=ldx, bits=bits)
     return c[0] == 2 and c[3] == RING
 
 
@@ -21,3 +21,17 @@ def test_segments_of_17_tokens_and_more(M):
     # (short segments of partial blocks stay with the other decode-batch kernel)
     assert not ring(1000, 3584, M, KeepDesc(col_seg_stride=32, col_seg_keep=26)) and ring(1000, 3584, M, KeepDesc(col_seg_stride=32, col_seg_keep=24))
     assert uq.uniql_w4_linear_kernel(4096, 4096, seg, M)[1:3] == (32, 16)
+
+
+@pytest.mark.parametrize("bits", [8, 6, 3])
+def test_wide_codes(bits):
+    def takes(N, K, M):
+        return ring(N, K, M, None, bits=bits)
+    assert takes(2048, 2048, 8) and takes(2048, 2304, 32) and not takes(2048, 2304, 33) and not takes(2048, 1920, 8)
+    assert takes(2048, 2176, 17) == (bits != 8)
+    assert takes(4096, 4096, 32) and not takes(4096, 4224, 8) and not takes(4096, 5120, 8) and takes(4096, 5248, 24)
+    assert takes(3072, 8192, 32) and takes(3088, 8192, 25) == takes(4096, 8192, 32) == (bits == 6)
+    assert takes(4112, 4096, 8) == takes(8192, 10240, 24) == (bits == 6) and not takes(8192, 10368, 17) and takes(8208, 10368, 17)
+    assert takes(13120, 4096, 8) and takes(13136, 4096, 8) == takes(16640, 4096, 8) == (bits != 3) and takes(16656, 4096, 8)
+    assert takes(24576, 4096, 8) and not takes(24577, 4096, 8)
+    assert not takes(256, 4096, 8)   # (few rows: a token per grid row)
