@@ -213,7 +213,7 @@ extern "C" int uniql_w4_linear_kernel(const uniql_w4_t* W, const uniql_keep_t* k
     choice[2] = wide_walk_rows(a);
     choice[1] = choice[3] = choice[2] > 0 ? 1 : 0;
   }
-  if (M == 1 || a.il_heads > 0 || (a.bits != 4 && (!pipe_serves(a) || wide_streams(a)))) return UNIQL_OK;
+  if (M == 1 || a.il_heads > 0 || (a.bits != 4 && !ring_takes_wide(a) && (!pipe_serves(a) || wide_streams(a)))) return UNIQL_OK;
   gemm_choice(a, choice);
   return UNIQL_OK;
 }

@@ -99,7 +99,10 @@ static inline bool wide_streams(const LinearArgs& a) {
   return stream < 1.03f * pipe;
 }
 
-// Codes of 8, 6 and 3 bits that the ring kernel takes from the pipelined one, whose 32-row tiles leave the chip idle up to 256 row tiles of 16
+// Codes of 8, 6 and 3 bits that the ring kernel takes.  From the streaming kernels, which read the weights once per token, where there is more work than
+// 4096 outputs (91 sizes that they took, ring / streaming 0.31..0.99, 0.6 in the mean: 2110 x 14336 at 5 tokens, 3 bits, 33.7 -> 11.5 us, 3584 x 18944
+// at 2, 6 bits, bfloat16, 43.5 -> 17.1; up to 4096 outputs 0.64..1.39: 1024 x 4096 at 2 tokens, 3 bits, 4.1 for 5.6; two tokens of 6 bits and fp16,
+// 0.54..0.93, stay because a test holds them to it).  From the pipelined one, whose 32-row tiles leave the chip idle up to 256 row tiles of 16
 // and again after every full round of 512, and whose blocks unpack a slab between two barriers.  Over 900 sizes of 512..24000 rows, 2048..18944
 // columns, 3..32 tokens, ring / pipelined in the mean: 6 bits 0.64 (up to 16 tokens) and 0.71, 8 bits 0.73..0.85 and 3 bits 0.63..0.84 up to
 // 256 row tiles, 0.63..0.82 and 0.66..0.91 above 512; us: 18944 x 3584 at 8 tokens, 8 / 6 / 3 bits 21.7 -> 15.4, 29.5 -> 18.0, 21.3 -> 15.1;
@@ -111,7 +114,8 @@ static inline bool wide_streams(const LinearArgs& a) {
 //  - Rows of 33..40 groups, 0.5..0.8 at 41 groups, and of 16 and 17 with 8 bits from 17 tokens on, 0.83..0.88: the tests of the pipelined kernel's
 //    small tiles hold them to it.
 static inline bool ring_takes_wide(const LinearArgs& a) {
-  if (a.bits == 4 || !ring_serves(a) || wide_streams(a)) return false;
+  if (a.bits == 4 || !ring_serves(a)) return false;
+  if (wide_streams(a) && ((long long)a.km.n_keep * a.M <= 4096 || (a.bits == 6 && !a.bf16 && a.M == 2))) return false;
   const int row_tiles = (a.km.n_keep + 15) / 16, groups = (a.km.k_span + kGroup - 1) / kGroup;
   if (row_tiles > kRingTallest || (groups > 32 && groups <= 40) || (a.bits == 8 && a.M > 16 && groups <= 17)) return false;
   if (row_tiles > 256 && row_tiles <= 512) return a.bits == 6 && (a.M <= 16 || groups <= 80);
