@@ -57,7 +57,7 @@ static inline bool ring_serves(const LinearArgs& a) {
 //    the pipelined kernel, segments of 9..32 tokens (1.02..1.12) with whatever has them.
 //  - Taller prefixes with rows of up to 32 groups, by themselves and two of one height in a launch (gate and up).  9..16 tokens: 0.65..0.96
 //    and 0.68..0.91 up to 24000 rows, but 0.95..1.06 (0.75..0.81) from 14000 to 16500; at 32000 rows 1.01..1.09 (1.05..1.08).  17..32
-//    tokens: 0.97..1.08 (0.75..0.82) up to 12200 rows, 0.75..0.82 (0.85..0.99) at 19000 and 24000; between them, where the tiles of the
+//    tokens: 0.97..1.08 (0.75..0.82) up to 12200 rows, 0.75..0.82 (0.85..0.99) at 19000 and 24000; between them (769..1040 row tiles: four fragments a block), where the tiles of the
 //    pipelined kernel fill their rounds, 1.10..1.17 (0.86..0.89): left there; 1.04 (1.02..1.04) at 32000.  Up to 8 tokens 0.9..1.26.
 // Segments of 17..32 tokens beyond 32 groups stay where they were, 0.88..0.93 notwithstanding: the pipelined kernel's tests hold it to them.
 // (33..64 tokens: a block of 16 rows fetches all of the activations, 29 bytes a clock, which is what takes the time: 0.82 to 1.6, and where
@@ -70,7 +70,7 @@ static inline bool ring_takes(const LinearArgs& a, bool segments_keep) {
   if (a.M <= 8) return row_tiles <= 600;
   if (a.km.cs_stride != 0) return a.M <= 16 ? row_tiles <= 320 : row_tiles <= 256 && shorter && !segments_keep;
   if (row_tiles < 400) return true;
-  return shorter && row_tiles <= kRingTallest && (a.M <= 16 || row_tiles <= 820 || row_tiles > 1040);
+  return shorter && row_tiles <= kRingTallest && (a.M <= 16 || row_tiles <= 768 || row_tiles > 1040);
 }
 
 // Codes of 8, 6 and 3 bits: whether the streaming kernel with a token per grid row (w8.hip, wbits.hip) is faster than the pipelined
@@ -110,7 +110,7 @@ static inline bool wide_streams(const LinearArgs& a) {
 //  - 257..512 row tiles, one full round of the other's: 8 bits 0.91..1.01, 3 bits 0.97..1.08; 6 bits 0.72..0.90, but 1.07 and 1.09 from 17
 //    tokens on with rows of more than 80 groups, whose activations every block fetches.
 //  - 8 and 3 bits, 193..256 row tiles, more than 24 tokens and 32 groups, for the same reason: 1.02..1.12.
-//  - 3 bits, 821..1040 row tiles: 0.99..1.13.  More than 1536 row tiles: 0.65..1.09, seven sizes.
+//  - 3 bits, 769..1040 row tiles (four fragments a block, and the other's second round is full): 0.99..1.13.  More than 1536 row tiles: 0.65..1.09, seven sizes.
 //  - Rows of 33..40 groups, 0.5..0.8 at 41 groups, and of 16 and 17 with 8 bits from 17 tokens on, 0.83..0.88: the tests of the pipelined kernel's
 //    small tiles hold them to it.
 static inline bool ring_takes_wide(const LinearArgs& a) {
@@ -121,7 +121,7 @@ static inline bool ring_takes_wide(const LinearArgs& a) {
   if (row_tiles > 256 && row_tiles <= 512) return a.bits == 6 && (a.M <= 16 || groups <= 80);
   if (a.bits == 6) return true;
   if (row_tiles > 192 && row_tiles <= 256 && a.M > 24 && groups > 32) return false;
-  return a.bits == 8 || row_tiles <= 820 || row_tiles > 1040;
+  return a.bits == 8 || row_tiles <= 768 || row_tiles > 1040;
 }
 
 }  // namespace uniql

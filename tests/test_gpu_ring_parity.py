@@ -101,7 +101,7 @@ def test_row_lengths(env, uref, K, M):   # noqa: F811
 # the same bits in a shared launch, whose blocks have more rows (five fragments, seven and eight), as alone
 @pytest.mark.parametrize("fmt", FORMATS)
 @pytest.mark.parametrize("M", [2, 8, 16, 30])
-@pytest.mark.parametrize("sizes", [(5000, 6300, 5003, 4999), (12801, 12799), (16380, 16361), (9001, 16401)])
+@pytest.mark.parametrize("sizes", [(5000, 6300, 5003, 4999), (12285, 12270, 999), (16380, 16361), (9001, 16401)])
 def test_shared_launch(env, uref, sizes, M, fmt):   # noqa: F811
     uq, torch = env
     g = torch.Generator(device="cuda").manual_seed(M)
@@ -157,7 +157,7 @@ def test_wide_prefixes(env, uref, N, K, kk, M, bits, fmt):   # noqa: F811
     ld = kk + (-kk) % 8
     choice = uq.uniql_w4_linear_kernel(N, K, Keep(n_keep=N - 2, k_keep=kk), M, bits=bits, bf16=fmt == "bf16", ldx=ld)
     if choice[3] != 8:
-        assert N == 5003 and bits != 6
+        assert (N == 5003 and bits != 6) or (N == 13005 and bits == 3)
         return
     rng = wl.rng_for(78, N + M)
     rows = np.concatenate([np.arange(0, N, 512), [15, 16, 31, 47, 48, 63, 64, 79, 80, 95, 96, N - 17, N - 4, N - 1], rng.integers(0, N, 40)])
