@@ -56,9 +56,11 @@ static inline bool ring_serves(const LinearArgs& a) {
 //  - 400..600 row tiles: up to 8 tokens 0.77..0.98; 9..32 of prefixes 0.93..1.0 with rows of up to 32 groups; longer rows (0.9..1.15) stay with
 //    the pipelined kernel, segments of 9..32 tokens (1.02..1.12) with whatever has them.
 //  - Taller prefixes with rows of up to 32 groups, by themselves and two of one height in a launch (gate and up).  9..16 tokens: 0.65..0.96
-//    and 0.68..0.91 up to 24000 rows, but 0.95..1.06 (0.75..0.81) from 14000 to 16500; at 32000 rows 1.01..1.09 (1.05..1.08).  17..32
-//    tokens: 0.97..1.08 (0.75..0.82) up to 12200 rows, 0.75..0.82 (0.85..0.99) at 19000 and 24000; between them (769..1040 row tiles: four fragments a block), where the tiles of the
-//    pipelined kernel fill their rounds, 1.10..1.17 (0.86..0.89): left there; 1.04 (1.02..1.04) at 32000.  Up to 8 tokens 0.9..1.26.
+//    and 0.68..0.91 up to 12200 rows and from 16700 to 24000; at 32000 rows 1.01..1.09 (1.05..1.08).  17..32
+//    tokens: 0.97..1.08 (0.75..0.82) up to 12200 rows, 0.75..0.82 (0.85..0.99) at 19000 and 24000; 1.04 (1.02..1.04) at 32000.  Between them
+//    (769..1040 row tiles: four fragments a block) the other kernels fill their rounds: 17..32 tokens 1.10..1.17 (0.86..0.89), 9..16 tokens 0.93..1.12, 1.03 in the
+//    mean of 84 sizes (fp16, 4096 columns 1.05..1.12: 14208 rows at 16 tokens 13.2 -> 14.7 us; two in a launch 0.75..0.81): left there, as a linear by itself and in
+//    a launch has to take the same kernel.  Up to 8 tokens 0.9..1.26.
 // Segments of 17..32 tokens beyond 32 groups stay where they were, 0.88..0.93 notwithstanding: the pipelined kernel's tests hold it to them.
 // (33..64 tokens: a block of 16 rows fetches all of the activations, 29 bytes a clock, which is what takes the time: 0.82 to 1.6, and where
 // it was faster by itself the pass of a layer was not.)
@@ -70,7 +72,7 @@ static inline bool ring_takes(const LinearArgs& a, bool segments_keep) {
   if (a.M <= 8) return row_tiles <= 600;
   if (a.km.cs_stride != 0) return a.M <= 16 ? row_tiles <= 320 : row_tiles <= 256 && shorter && !segments_keep;
   if (row_tiles < 400) return true;
-  return shorter && row_tiles <= kRingTallest && (a.M <= 16 || row_tiles <= 768 || row_tiles > 1040);
+  return shorter && row_tiles <= kRingTallest && (row_tiles <= 768 || row_tiles > 1040);
 }
 
 // Codes of 8, 6 and 3 bits: whether the streaming kernel with a token per grid row (w8.hip, wbits.hip) is faster than the pipelined
