@@ -420,7 +420,8 @@ static hipError_t ring_launch(const LinearArgs* p, int n, hipStream_t stream) {
     b.tiles = tiles;
     const int lds = S::lds(most);
     if (lds > kRingLds) return hipErrorInvalidValue;
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    // (the limit is the kernel's, not the launch's: the same from every thread, or one could lower it between another's set and launch)
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kRingLds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3(tiles), dim3(kRingWaves * kWave), lds, stream, b);
     return hipGetLastError();
