@@ -358,15 +358,18 @@ __device__ __forceinline__ void pipe_block(const LinearArgs& a, int rt, int m0, 
       rt4 = u32x4_t{(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)at), (uint32_t)__builtin_amdgcn_readfirstlane((int)((at >> 32) & 0xffffu)),
                     (uint32_t)__builtin_amdgcn_readfirstlane(a.N_total * row_bytes), kBufferWord3};
     }
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"   // (m0 is the compiler's own)
     auto touch = [&](int w) {
       if constexpr (S::Touches) {
         const int end = (w + 1) * 8 < ngroups ? (w + 1) * (128 * BITS) : ngroups * (16 * BITS);
         for (int b = w * (128 * BITS) + mine * 128; b < end; b += kPipeTokTilesPerPass * 128)
 #pragma unroll
           for (int p = 0; p < P; ++p)
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds" ::"s"(spare), "v"(e0[p] * (16 * BITS)), "s"(rt4), "s"(b) : "memory");
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds" ::"s"(spare), "v"(e0[p] * (16 * BITS)), "s"(rt4), "s"(b) : "memory", "m0");
       }
     };
+#pragma clang diagnostic pop
     fetch(0);
     put(0);
     fetch(1);

@@ -67,18 +67,22 @@ struct RingShape {
 
 // A load of 64 x 16 bytes (ring_load_word: 64 x 4) that writes LDS: the wave's active lanes, lane i at lds + 16 i.  (As asm, so that
 // the compiler does not make every later LDS read of the wave wait for it: the kernel waits for exactly the loads that it needs.  The
-// output is LDS, no register is written.)
+// output is LDS; m0, which the compiler warns of as one of its own, is the only register written.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void ring_load(u32x4_t rsrc, uint32_t lds, int voff, int soff) {
 #ifdef __HIP_DEVICE_COMPILE__
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory", "m0");
 #endif
 }
 
 __device__ __forceinline__ void ring_load_word(u32x4_t rsrc, uint32_t lds, int voff) {
 #ifdef __HIP_DEVICE_COMPILE__
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc) : "memory");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc) : "memory", "m0");
 #endif
 }
+
+#pragma clang diagnostic pop
 
 __device__ __forceinline__ u32x4_t ring_rsrc(const void* base, int bytes) {
   const uint64_t b = (uint64_t)base;

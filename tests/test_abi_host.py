@@ -1,6 +1,7 @@
 """Host-side checks of the C ABI (no GPU): the library loads, exports every
 function the header declares, and rejects bad arguments before any launch."""
 import ctypes as C
+import os
 import re
 
 import numpy as np
@@ -411,3 +412,15 @@ def test_valid_arguments_without_gfx950_fail_loudly():
     assert _glu() in (uq.UNIQL_E_HIP, uq.UNIQL_E_ARCH)
     assert _emb() in (uq.UNIQL_E_HIP, uq.UNIQL_E_ARCH)
     assert _repack() in (uq.UNIQL_E_HIP, uq.UNIQL_E_ARCH)
+
+
+# Inline assembly says what it changes: m0 among it, which the compiler's own loads into LDS take their address from
+def test_assembly_that_writes_m0_declares_it():
+    csrc = os.path.join(os.path.dirname(uq.__file__), "csrc")
+    found = 0
+    for f in sorted(os.listdir(csrc)):
+        for statement in re.findall(r"\basm\b[^;]*;", open(os.path.join(csrc, f)).read()) if f.endswith((".h", ".hip")) else []:
+            if re.search(r"s_mov_b32 m0", statement):
+                found += 1
+                assert re.search(r':[^:]*"m0"[^:]*\)\s*;$', statement), (f, statement)
+    assert found == 3
