@@ -424,10 +424,10 @@ int uniql_w4_gate_up_stream_probe(const uniql_w4_t* W, const uniql_keep_t* keep,
 /*
  * Measurement aid, not part of the method: which kernel uniql_w4_linear runs for this matrix, rule, leading dimension of x and
  * number of tokens on the current device (256 compute units where there is none), without running it.  choice[0]: 0 the
- * streaming kernels (one token per grid row), 1 the decode-batch kernels, 2 those whose loads write LDS ahead of the products (the
- * pipelined one; with codes of 8, 6 and 3 bits and on column segments of 17..32 tokens also the ring kernel: K over 8 waves), 3 the persistent 256 x 256 one, 4
- * the tiled one; choice[1..3]: its tile's tokens and rows and the number of waves K is split over (0 for kernels 0 and 1,
- * but 1, the rows a wave takes at a time and 1 for one token of 8-, 6- or 3-bit codes on the persistent walk over rows).
+ * streaming kernels (one token per grid row), 1 the decode-batch kernels, 2 the pipelined one, 3 the persistent 256 x 256 one, 4
+ * the tiled one; choice[1..3]: its tile's tokens and rows and the number of waves K is split over.  Of the decode-batch kernels the ring
+ * kernel is the one with a tile (tokens, rows and 8 waves, whatever the width and the column rule), the block-staged one reports 0; so do
+ * the streaming kernels, but 1, the rows a wave takes at a time and 1 for one token of 8-, 6- or 3-bit codes on the persistent walk over rows.
  * The choice may change from one version of the library to the next.  The data pointers of W are not used and may be NULL.
  * Errors as uniql_w4_linear's host checks.
  */

@@ -220,7 +220,8 @@ def kept_dims(W: QuantLinear, keep) -> tuple:
 def uniql_w4_linear_kernel(N: int, K: int, keep, M: int, bits: int = 4, bf16: bool = False, ldx: Optional[int] = None,
                            col_interleave: int = 0):
     """(kernel, tile tokens, tile rows, waves along K) that uniql_w4_linear takes for a matrix of this shape, without running
-    it: kernel 0 streaming, 1 decode-batch, 2 pipelined, 3 persistent 256 x 256, 4 tiled (see include/uniql.h)."""
+    it: kernel 0 streaming, 1 decode-batch (the ring kernel with its tile and 8 waves, the block-staged one with zeros), 2 pipelined, 3
+    persistent 256 x 256, 4 tiled (see include/uniql.h)."""
     d = W4(None, None, None, N, K, 128, UNIQL_BF16 if bf16 else UNIQL_F16, col_interleave, bits)
     kd, out = _keep_desc(keep), (C.c_int32 * 4)()
     _check(lib().uniql_w4_linear_kernel(C.byref(d), C.byref(kd) if kd is not None else None, K if ldx is None else ldx, M, out))

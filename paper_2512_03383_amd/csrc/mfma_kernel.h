@@ -527,19 +527,19 @@ static hipError_t launch_gemm_fmt(const LinearArgs& a, hipStream_t stream) {
   return xm == 1 ? launch_m<1, BF16>(a, stream) : xm == 2 ? launch_m<2, BF16>(a, stream) : launch_m<0, BF16>(a, stream);
 }
 
-// What launch_gemm_fmt (4 bits) and the pipelined kernel (every width) do with a linear of 2 tokens and more, as
+// What launch_gemm_fmt (4 bits), the ring and the pipelined kernel (every width) do with a linear of 2 tokens and more, as
 // uniql_w4_linear_kernel reports it: the kernel, the tile's tokens and rows and the waves that K is split over (0, 0, 0 for the
-// decode-batch kernels).
+// block-staged decode-batch kernel).
 static inline void gemm_choice_of(const LinearArgs& a, int out[4]) {
   static const int tiles[][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}, {256, 256, 1}, {128, 256, 1}, {64, 256, 1}, {64, 128, 2}, {32, 128, 2},
                                  {16, 16, 8}, {16, 64, 4}, {32, 16, 8}, {32, 64, 4}, {64, 32, 4}, {64, 64, 4}};
   const int xm = gemm_xm(a);
   const GemmRoute r = a.bits == 4 ? gemm_route(a, xm) : kPipe;
-  if ((r == kRing && xm == 2 && a.M > 16) || (a.bits != 4 && ring_takes_wide(a))) {
+  if (r == kRing || (a.bits != 4 && ring_takes_wide(a))) {
     ring_tile_of(a, out);
     return;
   }
-  out[0] = r == kSmallM || r == kRing ? 1 : r == kPipe ? 2 : r == kPrefill256 ? 3 : 4;
+  out[0] = r == kSmallM ? 1 : r == kPipe ? 2 : r == kPrefill256 ? 3 : 4;
   for (int i = 0; i < 3; ++i) out[1 + i] = tiles[r][i];
   if (r != kPipe) return;
   const PipeTile t = a.bits == 4 ? pipe_pick<4>(&a, 1) : a.bits == 8 ? pipe_pick<8>(&a, 1) : a.bits == 6 ? pipe_pick<6>(&a, 1) : pipe_pick<3>(&a, 1);

@@ -41,9 +41,9 @@ static inline int ring_glu_rows(const LinearArgs* p) {
   return rounds(3) * 7 <= rounds(4) * 9 ? 6 : 8;
 }
 
-// as uniql_w4_linear_kernel reports it: among the kernels whose loads write LDS directly, tokens and rows of a tile, K over eight waves
+// as uniql_w4_linear_kernel reports it, for every width and column rule: a decode-batch kernel, tokens and rows of a tile, K over eight waves
 static inline void ring_tile_of(const LinearArgs& a, int out[4]) {
-  out[0] = 2, out[1] = ring_tokens(a.M, a.bits), out[2] = 16 * ring_rows(&a, 1), out[3] = 8;
+  out[0] = 1, out[1] = ring_tokens(a.M, a.bits), out[2] = 16 * ring_rows(&a, 1), out[3] = 8;
 }
 
 }  // namespace uniql

@@ -2,6 +2,7 @@
 import pytest
 
 import launches as la
+import paper_2512_03383_amd as uq
 
 
 @pytest.fixture(scope="module")
@@ -26,3 +27,28 @@ def test_limit_of_lds_does_not_depend_on_the_call(record):
             assert x.lds <= max(x.limit, 64 * 1024)
             assert limits.setdefault(x.kernel, x.limit) == x.limit, x.kernel
     assert sum("w_ring_kernel" in k for k in limits) > 20
+
+
+def reported(kernel):
+    """What uniql_w4_linear_kernel says of a launch of this kernel."""
+    name, args = kernel.rstrip(">").split("<")
+    a = [int(x) if x.isdigit() else x == "true" for x in args.split(",")]
+    if name == "w_ring_kernel":
+        return (1, a[0], 16 * a[1], 8)
+    if name == "w_pipe_kernel":
+        return (2, 16 * a[0], 16 * a[1] * a[2], a[3] * a[4])
+    return {"w4_smallm_kernel": (1, 0, 0, 0), "w8_gemv_kernel": (0, 0, 0, 0), "wb_gemv_kernel": (0, 0, 0, 0), "w4_prefill_kernel": (3, 256, 256, 1)}.get(name, (4,))
+
+
+@pytest.mark.parametrize("bits", [4, 8, 6, 3])
+@pytest.mark.parametrize("keep", [{}, dict(col_seg_stride=128, col_seg_keep=102), dict(col_seg_stride=32, col_seg_keep=24)])
+def test_the_report_names_the_kernel_that_is_launched(record, keep, bits):
+    sizes = [(N, K, M) for N in (300, 2048, 4096, 6410, 9472, 13000, 18944, 26000) for K in (1152, 2176, 4096, 5120, 8192) for M in (2, 5, 8, 9, 16, 17, 32, 48, 130, 1000)]
+    calls = [linear(N, K, M, keep, bits=bits, bf16=(N + M) % 2 == 1) for N, K, M in sizes]
+    seen = set()
+    for (N, K, M), call, (rc, launches) in zip(sizes, calls, record(calls)):
+        choice = uq.uniql_w4_linear_kernel(N, K, uq.KeepDesc(**keep), M, bits=bits, bf16=call["bf16"])
+        want = reported(launches[0].kernel)
+        assert rc == 0 and len(launches) == 1 and choice[:len(want)] == want, (N, K, M, launches[0].kernel, choice)
+        seen.add(launches[0].kernel.split("<")[0])
+    assert {"w_ring_kernel", "w_pipe_kernel"} <= seen

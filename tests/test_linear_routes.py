@@ -5,7 +5,13 @@ import pytest
 import paper_2512_03383_amd as uq
 from paper_2512_03383_amd import KeepDesc
 
-STREAM, BATCH, PIPE, BIG, TILED = range(5)
+STREAM, STAGED, PIPE, BIG, TILED, RING = range(6)   # as reported, but the decode-batch kernel with a tile is the ring kernel
+
+
+def kernel(*a, **kw):
+    c = uq.uniql_w4_linear_kernel(*a, **kw)
+    assert c[0] != STAGED or c[1:] == (0, 0, 0) or (c[3] == 8 and c[1] in (4, 8, 16, 32) and c[2] % 16 == 0 and c[2] >= 16)
+    return RING if c[0] == STAGED and c[3] == 8 else c[0]
 
 
 def seg(stride, keep):
@@ -15,7 +21,8 @@ def seg(stride, keep):
 def test_reports_without_running():
     assert uq.uniql_w4_linear_kernel(4096, 4096, None, 1) == (STREAM, 0, 0, 0)
     assert uq.uniql_w4_linear_kernel(4096, 4096, None, 8, col_interleave=32)[0] == STREAM
-    assert uq.uniql_w4_linear_kernel(4096, 4096, None, 8) == (BATCH, 0, 0, 0)
+    assert uq.uniql_w4_linear_kernel(4096, 4096, None, 8) == (STAGED, 8, 16, 8)        # the ring kernel
+    assert uq.uniql_w4_linear_kernel(14336, 4096, None, 8) == (STAGED, 0, 0, 0)        # the block-staged one
     assert uq.uniql_w4_linear_kernel(14336, 4096, None, 4096) == (BIG, 256, 256, 1)
     with pytest.raises(uq.UniqlError):
         uq.uniql_w4_linear_kernel(4096, 4100, None, 8)
@@ -48,13 +55,13 @@ def test_tall_matrices_of_unusual_rules(K, keep, first):
         assert uq.uniql_w4_linear_kernel(12288, K, keep, M) == want, M
 
 
-# decode batches of 2..8 tokens stay with one kernel whatever the height, so that q, k and v or gate and up share a launch
+# decode batches of 2..8 tokens are one kernel's up to 600 row tiles, so that q, k and v share a launch, and another's above
 @pytest.mark.parametrize("N", [1024, 6400, 8192, 9472, 18944])
 @pytest.mark.parametrize("K,keep", [(4096, None), (8192, None), (4096, seg(128, 108))])
 def test_small_decode_batches_share_one_kernel(N, K, keep):
     for M in (2, 5, 8):
-        assert uq.uniql_w4_linear_kernel(N, K, keep, M)[0] == BATCH
-    assert uq.uniql_w4_linear_kernel(N, 8192, keep and seg(128, 108), 12)[0] == (BATCH if N < 6400 else PIPE)
+        assert kernel(N, K, keep, M) == (RING if N <= 9600 else STAGED)
+    assert kernel(N, 8192, keep and seg(128, 108), 12) == (RING if N < 6400 else PIPE)
 
 
 # columns behind the last whole block of eight cost the tiled kernels more than the pipelined one (65 against 39 us at 2560 x 1999
@@ -72,7 +79,7 @@ def test_odd_columns_of_prompts():
 @pytest.mark.parametrize("bits", [8, 6, 3])
 def test_wide_codes_stream_where_that_is_faster(bits, bf16):
     def route(N, K, M, keep=None):
-        return uq.uniql_w4_linear_kernel(N, K, keep, M, bits=bits, bf16=bf16)[0]
+        return kernel(N, K, keep, M, bits=bits, bf16=bf16)
     for K in (1024, 4096, 14336):
         for M in (2, 4, 8):
             assert route(256, K, M) == STREAM
@@ -80,7 +87,7 @@ def test_wide_codes_stream_where_that_is_faster(bits, bf16):
     assert route(2048, 14336, 2) == STREAM
     for N, K in ((4096, 4096), (12185, 4096), (4096, 14336)):
         for M in (8, 16, 48, 512):
-            assert route(N, K, M) == PIPE
+            assert route(N, K, M) == (RING if M <= 16 else PIPE)
     if bits == 6 and not bf16:
         for N, K in ((4096, 4096), (4096, 14336), (14336, 2048)):
             assert route(N, K, 2) == STREAM
@@ -124,28 +131,29 @@ def test_height_at_which_wide_codes_change_their_split(bits, last):
             assert uq.uniql_w4_linear_kernel(16 * last + 1, K, None, M, bits=bits)[1] in (48, 64)
 
 
-# decode batches of 17..32 tokens on column segments, and of 9..32 tokens from 400 row tiles on, leave the decode-batch kernel; below that
-# height a matrix stays, so that it shares a launch with short ones (6000 + 1536 rows x 2560 columns at 9 tokens 8.1 us, 13.6 in two)
+# decode batches of 17..32 tokens on column segments of long rows, and of 9..32 tokens on long rows from 400 row tiles on, go to the pipelined
+# kernel; the others are the ring kernel's, so that they share a launch (6000 + 1536 rows x 2560 columns at 9 tokens 8.1 us, 13.6 in two)
 @pytest.mark.parametrize("bf16", [False, True])
 def test_decode_batches_that_the_pipelined_kernel_takes(bf16):
     for N, K, keep in ((512, 4096, seg(128, 96)), (2560, 5120, seg(64, 54)), (4096, 4096, seg(128, 108))):
-        for M, want in ((8, BATCH), (16, BATCH), (17, PIPE), (32, PIPE)):
-            assert uq.uniql_w4_linear_kernel(N, K, keep, M, bf16=bf16)[0] == want, (N, M)
-    for N, want in ((5985, BATCH), (6384, BATCH), (6385, PIPE)):
+        late = PIPE if K > 4096 else RING
+        for M, want in ((8, RING), (16, RING), (17, late), (32, late)):
+            assert kernel(N, K, keep, M, bf16=bf16) == want, (N, M)
+    for N, want in ((5985, RING), (6384, RING), (6385, PIPE)):
         for M in (9, 17, 32):
-            assert uq.uniql_w4_linear_kernel(N, 8192, None, M, bf16=bf16)[0] == want
-        assert uq.uniql_w4_linear_kernel(N, 8192, None, 8, bf16=bf16)[0] == BATCH
+            assert kernel(N, 8192, None, M, bf16=bf16) == want
+        assert kernel(N, 8192, None, 8, bf16=bf16) == RING
 
 
 # column segments of 17..32 tokens whose kept columns are not whole blocks of eight: long rows of up to 4096 stay with the decode batches
 # (512 x 14208, 98 of 128 columns, 17 tokens: 0.82 of the other kernel's time); fp16, or segments of fewer than 64 columns
 @pytest.mark.parametrize("M", [17, 32])
 def test_segments_that_decode_batches_keep(M):
-    for N, K, keep, f16, bf in ((512, 14208, seg(128, 98), BATCH, PIPE), (512, 14208, seg(128, 96), PIPE, PIPE), (1024, 4096, seg(64, 54), PIPE, PIPE),
-                                (1024, 4224, seg(64, 54), BATCH, PIPE), (3584, 7936, seg(64, 54), PIPE, PIPE), (3584, 8192, seg(64, 54), BATCH, PIPE),
-                                (4097, 14208, seg(64, 54), PIPE, PIPE), (1000, 3456, seg(32, 26), PIPE, PIPE), (1000, 3584, seg(32, 26), BATCH, BATCH)):
+    for N, K, keep, f16, bf in ((512, 14208, seg(128, 98), STAGED, PIPE), (512, 14208, seg(128, 96), PIPE, PIPE), (1024, 4096, seg(64, 54), RING, RING),
+                                (1024, 4224, seg(64, 54), STAGED, PIPE), (3584, 7936, seg(64, 54), PIPE, PIPE), (3584, 8192, seg(64, 54), STAGED, PIPE),
+                                (4097, 14208, seg(64, 54), PIPE, PIPE), (1000, 3456, seg(32, 26), RING, RING), (1000, 3584, seg(32, 26), STAGED, STAGED)):
         for bf16, want in ((False, f16), (True, bf)):
-            assert uq.uniql_w4_linear_kernel(N, K, keep, M, bf16=bf16)[0] == want, (N, K, bf16)
+            assert kernel(N, K, keep, M, bf16=bf16) == want, (N, K, bf16)
 
 
 # one token of 8-, 6- and 3-bit codes: the walk's rows at a time, and what it leaves to the other kernels

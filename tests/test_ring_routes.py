@@ -1,5 +1,4 @@
-"""Host-side checks of which linears the ring kernel takes (no GPU), where uniql_w4_linear_kernel tells it from the other decode-batch kernel: column
-segments of 17..32 tokens, and codes of 8, 6 and 3 bits."""
+"""Host-side checks of which linears the ring kernel takes (no GPU): column segments of 17..32 tokens, and codes of 8, 6 and 3 bits."""
 import pytest
 
 import paper_2512_03383_amd as uq
@@ -10,7 +9,7 @@ RING = 8   # waves that K is split over
 
 def ring(N, K, M, keep, ldx=None, bits=4):
     c = uq.uniql_w4_linear_kernel(N, K, keep, M, ldx=ldx, bits=bits)
-    return c[0] == 2 and c[3] == RING
+    return c[0] == 1 and c[3] == RING
 
 
 @pytest.mark.parametrize("M", [17, 32])
