@@ -103,26 +103,21 @@ static inline bool wide_streams(const LinearArgs& a) {
 
 // Codes of 8, 6 and 3 bits that the ring kernel takes.  From the streaming kernels, which read the weights once per token, where there is more work than
 // 4096 outputs (91 sizes that they took, ring / streaming 0.31..0.99, 0.6 in the mean: 2110 x 14336 at 5 tokens, 3 bits, 33.7 -> 11.5 us, 3584 x 18944
-// at 2, 6 bits, bfloat16, 43.5 -> 17.1; up to 4096 outputs 0.64..1.39: 1024 x 4096 at 2 tokens, 3 bits, 4.1 for 5.6; two tokens of 6 bits and fp16,
-// 0.54..0.93, stay because a test holds them to it).  From the pipelined one, whose 32-row tiles leave the chip idle up to 256 row tiles of 16
+// at 2, 6 bits, bfloat16, 43.5 -> 17.1; up to 4096 outputs 0.64..1.39: 1024 x 4096 at 2 tokens, 3 bits, 4.1 for 5.6).  From the pipelined one, whose 32-row tiles leave the chip idle up to 256 row tiles of 16
 // and again after every full round of 512, and whose blocks unpack a slab between two barriers.  Over 900 sizes of 512..24000 rows, 2048..18944
 // columns, 3..32 tokens, ring / pipelined in the mean: 6 bits 0.64 (up to 16 tokens) and 0.71, 8 bits 0.73..0.85 and 3 bits 0.63..0.84 up to
-// 256 row tiles, 0.63..0.82 and 0.66..0.91 above 512; us: 18944 x 3584 at 8 tokens, 8 / 6 / 3 bits 21.7 -> 15.4, 29.5 -> 18.0, 21.3 -> 15.1;
+// 256 row tiles, 0.63..0.82 and 0.66..0.91 above 512 (25..32 tokens on 193..256 row tiles of 33..148 groups 0.68..0.90); us: 18944 x 3584 at 8 tokens, 8 / 6 / 3 bits 21.7 -> 15.4, 29.5 -> 18.0, 21.3 -> 15.1;
 // 3584 x 18944 25.0 -> 16.5, 37.7 -> 17.3, 24.1 -> 15.2.  Left where they were:
 //  - 257..512 row tiles, one full round of the other's: 8 bits 0.91..1.01, 3 bits 0.97..1.08; 6 bits 0.72..0.90, but 1.07 and 1.09 from 17
 //    tokens on with rows of more than 80 groups, whose activations every block fetches.
-//  - 8 and 3 bits, 193..256 row tiles, more than 24 tokens and 32 groups, for the same reason: 1.02..1.12.
 //  - 3 bits, 769..1040 row tiles (four fragments a block, and the other's second round is full): 0.99..1.13.  More than 1536 row tiles: 0.65..1.09, seven sizes.
-//  - Rows of 33..40 groups, 0.5..0.8 at 41 groups, and of 16 and 17 with 8 bits from 17 tokens on, 0.83..0.88: the tests of the pipelined kernel's
-//    small tiles hold them to it.
 static inline bool ring_takes_wide(const LinearArgs& a) {
   if (a.bits == 4 || !ring_serves(a)) return false;
-  if (wide_streams(a) && ((long long)a.km.n_keep * a.M <= 4096 || (a.bits == 6 && !a.bf16 && a.M == 2))) return false;
+  if (wide_streams(a) && (long long)a.km.n_keep * a.M <= 4096) return false;
   const int row_tiles = (a.km.n_keep + 15) / 16, groups = (a.km.k_span + kGroup - 1) / kGroup;
-  if (row_tiles > kRingTallest || (groups > 32 && groups <= 40) || (a.bits == 8 && a.M > 16 && groups <= 17)) return false;
+  if (row_tiles > kRingTallest) return false;
   if (row_tiles > 256 && row_tiles <= 512) return a.bits == 6 && (a.M <= 16 || groups <= 80);
   if (a.bits == 6) return true;
-  if (row_tiles > 192 && row_tiles <= 256 && a.M > 24 && groups > 32) return false;
   return a.bits == 8 || row_tiles <= 768 || row_tiles > 1040;
 }
 

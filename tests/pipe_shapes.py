@@ -5,6 +5,7 @@ from paper_2512_03383_amd import KeepDesc
 # 17 of one)
 SIZES = [(6410, 4224, 11), (8300, 4224, 11), (6410, 4224, 19), (8300, 4224, 19), (3000, 4224, 13), (3000, 4224, 27),
          (6410, 4224, 37), (8300, 4224, 37), (16500, 4224, 37), (6410, 4224, 51), (8300, 4224, 51), (16500, 4224, 51),
+         (24700, 4224, 11), (24700, 4224, 19),   # (more rows than the ring kernel takes)
          (300, 2176, 67), (8300, 2176, 67), (11000, 2176, 67), (16500, 2176, 67), (16500, 2176, 101), (16500, 2176, 127), (5101, 2176, 333)]
 
 

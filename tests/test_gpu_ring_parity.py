@@ -151,7 +151,7 @@ def test_largest_scales(env, uref, M):   # noqa: F811
 @pytest.mark.parametrize("fmt", FORMATS)
 @pytest.mark.parametrize("bits", [8, 6, 3])
 @pytest.mark.parametrize("M", [5, 8, 9, 16, 17, 32])
-@pytest.mark.parametrize("N,K,kk", [(3061, 2304, 2177), (3050, 5248, 5248), (5003, 2432, 2305), (9018, 2304, 2291), (13005, 2560, 2559), (17003, 2432, 2430), (22003, 2304, 2304)])
+@pytest.mark.parametrize("N,K,kk", [(2061, 2176, 2049), (3061, 2304, 2177), (3061, 4608, 4481), (3050, 5248, 5248), (5003, 2432, 2305), (9018, 2304, 2291), (13005, 2560, 2559), (17003, 2432, 2430), (22003, 2304, 2304)])
 def test_wide_prefixes(env, uref, N, K, kk, M, bits, fmt):   # noqa: F811
     uq, _ = env
     ld = kk + (-kk) % 8

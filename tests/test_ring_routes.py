@@ -27,12 +27,12 @@ def test_wide_codes(bits):
     def takes(N, K, M):
         return ring(N, K, M, None, bits=bits)
     assert takes(2048, 2048, 8) and takes(2048, 2304, 32) and not takes(2048, 2304, 33) and not takes(2048, 1920, 8)
-    assert takes(2048, 2176, 17) == (bits != 8)
-    assert takes(4096, 4096, 32) and not takes(4096, 4224, 8) and not takes(4096, 5120, 8) and takes(4096, 5248, 24)
-    assert takes(3072, 8192, 32) and takes(3088, 8192, 25) == takes(4096, 8192, 32) == (bits == 6)
+    assert takes(2048, 2048, 17) and takes(2048, 2176, 17) and takes(16384, 2176, 32) == (bits != 3)
+    assert takes(4096, 4096, 32) and takes(4096, 4224, 8) and takes(4096, 5120, 8) and takes(4096, 5248, 24) and takes(1024, 5120, 17) and takes(2048, 4608, 32)
+    assert takes(3072, 8192, 32) and takes(3088, 8192, 25) and takes(4096, 8192, 32)
     assert takes(4112, 4096, 8) == takes(8192, 10240, 24) == (bits == 6) and not takes(8192, 10368, 17) and takes(8208, 10368, 17)
     assert takes(12288, 4096, 8) and takes(12304, 4096, 8) == takes(16640, 4096, 8) == (bits != 3) and takes(16656, 4096, 8)
     assert takes(24576, 4096, 8) and not takes(24577, 4096, 8)
     # few outputs: a token per grid row
     assert not takes(256, 4096, 8) and not takes(2048, 8192, 2) and not takes(1024, 4096, 4) and takes(1025, 8192, 4) and takes(520, 8192, 8)
-    assert takes(2064, 8192, 2) == (bits != 6)
+    assert takes(2064, 8192, 2)
