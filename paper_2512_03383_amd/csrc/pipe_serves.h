@@ -61,16 +61,25 @@ static inline bool ring_serves(const LinearArgs& a) {
 //    (769..1040 row tiles: four fragments a block) the other kernels fill their rounds: 17..32 tokens 1.10..1.17 (0.86..0.89), 9..16 tokens 0.93..1.12, 1.03 in the
 //    mean of 84 sizes (fp16, 4096 columns 1.05..1.12: 14208 rows at 16 tokens 13.2 -> 14.7 us; two in a launch 0.75..0.81): left there, as a linear by itself and in
 //    a launch has to take the same kernel.  Up to 8 tokens 0.9..1.26.
-// Segments of 17..32 tokens beyond 32 groups stay where they were, 0.88..0.93 notwithstanding: the pipelined kernel's tests hold it to them.
+//  - Segments of 17..32 tokens, up to 256 row tiles, beyond 32 groups (460 sizes): up to 64 groups 0.77..1.01, bfloat16 and whole blocks as fp16 and partial
+//    ones; but 0.94..1.06 on more than 192 row tiles from 25 tokens on, and segments of fewer than 64 columns that keep part of a block (1.04..1.25
+//    on long rows) stay.  65..96 groups up to 192 row tiles 0.77..0.99; partial blocks in fp16 (0.93..1.03), more row tiles (up to 1.09) and longer rows (up to 1.11) stay.
 // (33..64 tokens: a block of 16 rows fetches all of the activations, 29 bytes a clock, which is what takes the time: 0.82 to 1.6, and where
 // it was faster by itself the pass of a layer was not.)
 constexpr int kRingTallest = 1536;   // row tiles
-static inline bool ring_takes(const LinearArgs& a, bool segments_keep) {
+static inline bool ring_takes(const LinearArgs& a, bool segments_keep) {   // segments_keep: the block-staged kernel is faster than the pipelined one
   if (a.bits != 4 || !ring_serves(a)) return false;
-  const int row_tiles = (a.km.n_keep + 15) / 16;
-  const bool shorter = a.km.k_span <= 32 * kGroup;
+  const int row_tiles = (a.km.n_keep + 15) / 16, groups = (a.km.k_span + kGroup - 1) / kGroup;
+  const bool shorter = groups <= 32;
   if (a.M <= 8) return row_tiles <= 600;
-  if (a.km.cs_stride != 0) return a.M <= 16 ? row_tiles <= 320 : row_tiles <= 256 && shorter && !segments_keep;
+  if (a.km.cs_stride != 0) {
+    if (a.M <= 16) return row_tiles <= 320;
+    if (row_tiles > 256) return false;
+    if (shorter) return !segments_keep;
+    if (a.km.cs_stride < 64 && a.km.cs_keep % 8 != 0) return false;
+    if (groups <= 64) return row_tiles <= 192 || a.M <= 24;
+    return groups <= 96 && row_tiles <= 192 && !segments_keep;
+  }
   if (row_tiles < 400) return true;
   return shorter && row_tiles <= kRingTallest && (row_tiles <= 768 || row_tiles > 1040);
 }

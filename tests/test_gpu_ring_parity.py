@@ -88,6 +88,15 @@ def test_segments(env, uref, stride, keep, M, fmt):   # noqa: F811
     run(env, uref, N, K, M, k, k, fmt, M % 2 == 0, M % 3, np.concatenate([np.arange(0, N, 97), [N - 1]]))
 
 
+# the same with rows of 33 to 96 groups and 17 tokens and more
+@pytest.mark.parametrize("fmt", FORMATS)
+@pytest.mark.parametrize("M,N,K,stride,keep", [(17, 207, 4224, 128, 94), (32, 3070, 8192, 64, 50), (24, 4095, 4352, 128, 126), (31, 1001, 12288, 128, 96), (18, 2563, 8320, 32, 24)])
+def test_segments_of_long_rows(env, uref, M, N, K, stride, keep, fmt):   # noqa: F811
+    k = Keep(k_keep=K // stride * keep, col_seg_stride=stride, col_seg_keep=keep)
+    assert env[0].uniql_w4_linear_kernel(N, K, k, M, bf16=fmt == "bf16", ldx=k.k_keep + M % 3)[3] == 8
+    run(env, uref, N, K, M, k, k, fmt, M % 2 == 0, M % 3, np.concatenate([np.arange(0, N, 97), [N - 1]]))
+
+
 # rows of one to three runs of groups a wave, fewer groups than the loads in flight, more, and the windows of eight scales and sixteen zero points
 # at the row's end
 @pytest.mark.parametrize("M", [2, 8, 16, 32])

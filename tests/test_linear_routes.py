@@ -131,12 +131,12 @@ def test_height_at_which_wide_codes_change_their_split(bits, last):
             assert uq.uniql_w4_linear_kernel(16 * last + 1, K, None, M, bits=bits)[1] in (48, 64)
 
 
-# decode batches of 17..32 tokens on column segments of long rows, and of 9..32 tokens on long rows from 400 row tiles on, go to the pipelined
-# kernel; the others are the ring kernel's, so that they share a launch (6000 + 1536 rows x 2560 columns at 9 tokens 8.1 us, 13.6 in two)
+# decode batches of 17..32 tokens on column segments of more than 256 row tiles, and of 9..32 tokens on long rows from 400 row tiles on, go to the
+# pipelined kernel; the others are the ring kernel's, so that they share a launch (6000 + 1536 rows x 2560 columns at 9 tokens 8.1 us, 13.6 in two)
 @pytest.mark.parametrize("bf16", [False, True])
 def test_decode_batches_that_the_pipelined_kernel_takes(bf16):
-    for N, K, keep in ((512, 4096, seg(128, 96)), (2560, 5120, seg(64, 54)), (4096, 4096, seg(128, 108))):
-        late = PIPE if K > 4096 else RING
+    for N, K, keep in ((512, 4096, seg(128, 96)), (2560, 5120, seg(64, 54)), (4096, 4096, seg(128, 108)), (4112, 4096, seg(128, 108))):
+        late = PIPE if N > 4096 else RING
         for M, want in ((8, RING), (16, RING), (17, late), (32, late)):
             assert kernel(N, K, keep, M, bf16=bf16) == want, (N, M)
     for N, want in ((5985, RING), (6384, RING), (6385, PIPE)):
@@ -145,12 +145,16 @@ def test_decode_batches_that_the_pipelined_kernel_takes(bf16):
         assert kernel(N, 8192, None, 8, bf16=bf16) == RING
 
 
-# column segments of 17..32 tokens whose kept columns are not whole blocks of eight: long rows of up to 4096 stay with the decode batches
-# (512 x 14208, 98 of 128 columns, 17 tokens: 0.82 of the other kernel's time); fp16, or segments of fewer than 64 columns
+# column segments of 17..32 tokens: the ring kernel up to 64 groups (more than 192 row tiles: up to 24 tokens), up to 96 where the block-staged one is not the
+# better; where that is better than the pipelined one, segments whose kept columns are not whole blocks of eight in long rows stay with it (512
+# x 14208, 98 of 128 columns, 17 tokens: 0.82 of the other kernel's time): fp16, or segments of fewer than 64 columns
 @pytest.mark.parametrize("M", [17, 32])
 def test_segments_that_decode_batches_keep(M):
     for N, K, keep, f16, bf in ((512, 14208, seg(128, 98), STAGED, PIPE), (512, 14208, seg(128, 96), PIPE, PIPE), (1024, 4096, seg(64, 54), RING, RING),
-                                (1024, 4224, seg(64, 54), STAGED, PIPE), (3584, 7936, seg(64, 54), PIPE, PIPE), (3584, 8192, seg(64, 54), STAGED, PIPE),
+                                (1024, 4224, seg(64, 54), RING, RING), (3000, 8192, seg(64, 54), RING, RING), (3584, 7936, seg(64, 54), *[RING if M == 17 else PIPE] * 2),
+                                (3584, 8192, seg(64, 54), *((RING, RING) if M == 17 else (STAGED, PIPE))), (2560, 10624, seg(128, 108), STAGED, RING),
+                                (3072, 12288, seg(128, 96), RING, RING), (3073, 12288, seg(128, 96), PIPE, PIPE), (3072, 12416, seg(128, 96), PIPE, PIPE),
+                                (1000, 4224, seg(32, 26), STAGED, STAGED), (1000, 4224, seg(32, 24), RING, RING),
                                 (4097, 14208, seg(64, 54), PIPE, PIPE), (1000, 3456, seg(32, 26), RING, RING), (1000, 3584, seg(32, 26), STAGED, STAGED)):
         for bf16, want in ((False, f16), (True, bf)):
             assert kernel(N, K, keep, M, bf16=bf16) == want, (N, K, bf16)

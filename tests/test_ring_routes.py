@@ -15,7 +15,8 @@ def ring(N, K, M, keep, ldx=None, bits=4):
 @pytest.mark.parametrize("M", [17, 32])
 def test_segments_of_17_tokens_and_more(M):
     seg = KeepDesc(col_seg_stride=128, col_seg_keep=108)
-    assert ring(4096, 4096, M, seg) and not ring(4097, 4096, M, seg) and not ring(4096, 4224, M, seg) and not ring(4096, 4096, 33, seg)
+    assert ring(4096, 4096, M, seg) and not ring(4097, 4096, M, seg) and ring(4096, 4224, M, seg) == (M <= 24) and not ring(4096, 4096, 33, seg)
+    assert ring(3072, 8192, M, seg) and not ring(3072, 8320, M, seg) and ring(3072, 8320, M, KeepDesc(col_seg_stride=128, col_seg_keep=104))
     assert ring(4096, 2048, M, seg) and not ring(4096, 1920, M, seg)
     # (short segments of partial blocks stay with the other decode-batch kernel)
     assert not ring(1000, 3584, M, KeepDesc(col_seg_stride=32, col_seg_keep=26)) and ring(1000, 3584, M, KeepDesc(col_seg_stride=32, col_seg_keep=24))
