@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <atomic>
 
 namespace uniql {
 
@@ -369,5 +370,19 @@ struct RopeArgs {
 };
 hipError_t launch_pruned_rope(const RopeArgs& a, hipStream_t stream);
 hipError_t launch_stream_read(const void* src, long long bytes, uint32_t* out, hipStream_t stream);
+
+// Number of compute units of the current device (the size of the persistent grids; what a round of blocks is), looked up once per device (0: not yet;
+// host threads may look it up at once).
+static inline int compute_units() {
+  static std::atomic<int> cus[64];
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
+  int v = cus[dev].load(std::memory_order_relaxed);
+  if (v == 0) {
+    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v <= 0) v = 256;
+    cus[dev].store(v, std::memory_order_relaxed);
+  }
+  return v;
+}
 
 }  // namespace uniql

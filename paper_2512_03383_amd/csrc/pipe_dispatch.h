@@ -3,7 +3,6 @@
 #pragma once
 #include "pipe_kernel.h"
 #include "pipe_serves.h"
-#include "prefill_kernel.h"   // prefill_grid_limit: compute units of the device
 
 namespace uniql {
 
@@ -20,7 +19,7 @@ struct TileCost {
   float us, slope;
 };
 static inline float launch_cost(long long tiles, float steps, TileCost c, float far, float round = 0.f) {
-  const int cus = prefill_grid_limit();
+  const int cus = compute_units();
   const float rounds = (float)((tiles + cus - 1) / cus);
   return 3.f + rounds * (4.f + round + steps * (c.us + c.slope * (float)tiles / (rounds * (float)cus)) * far);
 }
@@ -73,7 +72,7 @@ static inline PipeTile pipe_pick(const LinearArgs* p, int n) {
     // round takes 0.78 (128 tokens) or 0.82 (96) of a whole one, with 500 sizes timed both ways (1.1 .. 8 rounds, all widths): the launch
     // 0.85 to 0.997 of the time.  The costs here are a little above, so that another tile is not left for too small a gain.
     if (way == kPipeHalves && pipe_halves(BITS, t.af) && tiles < (1 << 20)) {
-      const int cus = prefill_grid_limit(), rest = (int)(tiles % cus);
+      const int cus = compute_units(), rest = (int)(tiles % cus);
       if (tiles > cus && rest > 0 && 2 * rest <= cus) {
         const TileCost& c = seg ? t.seg : t.prefix;
         const float steps = (float)((ngroups + t.g - 1) / t.g), far = span > 8192 ? 1.18f : 1.f;

@@ -58,7 +58,7 @@ static inline bool ring_serves(const LinearArgs& a) {
 //  - Taller prefixes with rows of up to 32 groups, by themselves and two of one height in a launch (gate and up).  9..16 tokens: 0.65..0.96
 //    and 0.68..0.91 up to 12200 rows and from 16700 to 24000; at 32000 rows 1.01..1.09 (1.05..1.08).  17..32
 //    tokens: 0.97..1.08 (0.75..0.82) up to 12200 rows, 0.75..0.82 (0.85..0.99) at 19000 and 24000; 1.04 (1.02..1.04) at 32000.  Between them
-//    (769..1040 row tiles: four fragments a block) the other kernels fill their rounds: 17..32 tokens 1.10..1.17 (0.86..0.89), 9..16 tokens 0.93..1.12, 1.03 in the
+//    (769..1024 row tiles: four fragments a block, ring_four) the other kernels fill their rounds: 17..32 tokens 1.10..1.17 (0.86..0.89), 9..16 tokens 0.93..1.12, 1.03 in the
 //    mean of 84 sizes (fp16, 4096 columns 1.05..1.12: 14208 rows at 16 tokens 13.2 -> 14.7 us; two in a launch 0.75..0.81): left there, as a linear by itself and in
 //    a launch has to take the same kernel.  Up to 8 tokens 0.9..1.26.
 //  - Segments of 17..32 tokens, up to 256 row tiles, beyond 32 groups (460 sizes): up to 64 groups 0.77..1.01, bfloat16 and whole blocks as fp16 and partial
@@ -67,6 +67,10 @@ static inline bool ring_serves(const LinearArgs& a) {
 // (33..64 tokens: a block of 16 rows fetches all of the activations, 29 bytes a clock, which is what takes the time: 0.82 to 1.6, and where
 // it was faster by itself the pass of a layer was not.)
 constexpr int kRingTallest = 1536;   // row tiles
+// One round of the compute units with four fragments a block.  (1025 and 1040 row tiles, five fragments, 9..32 tokens of 4 bits 0.65..0.75 of the time and
+// 3 bits 0.63..0.84 where 1024 are 0.98..1.15 and 0.96..1.14.)
+static inline bool ring_four(int row_tiles) { return row_tiles > 3 * compute_units() && row_tiles <= 4 * compute_units(); }
+
 static inline bool ring_takes(const LinearArgs& a, bool segments_keep) {   // segments_keep: the block-staged kernel is faster than the pipelined one
   if (a.bits != 4 || !ring_serves(a)) return false;
   const int row_tiles = (a.km.n_keep + 15) / 16, groups = (a.km.k_span + kGroup - 1) / kGroup;
@@ -81,7 +85,7 @@ static inline bool ring_takes(const LinearArgs& a, bool segments_keep) {   // se
     return groups <= 96 && row_tiles <= 192 && !segments_keep;
   }
   if (row_tiles < 400) return true;
-  return shorter && row_tiles <= kRingTallest && (row_tiles <= 768 || row_tiles > 1040);
+  return shorter && row_tiles <= kRingTallest && !ring_four(row_tiles);
 }
 
 // Codes of 8, 6 and 3 bits: whether the streaming kernel with a token per grid row (w8.hip, wbits.hip) is faster than the pipelined
@@ -119,7 +123,7 @@ static inline bool wide_streams(const LinearArgs& a) {
 // 3584 x 18944 25.0 -> 16.5, 37.7 -> 17.3, 24.1 -> 15.2.  Left where they were:
 //  - 257..512 row tiles, one full round of the other's: 8 bits 0.91..1.01, 3 bits 0.97..1.08; 6 bits 0.72..0.90, but 1.07 and 1.09 from 17
 //    tokens on with rows of more than 80 groups, whose activations every block fetches.
-//  - 3 bits, 769..1040 row tiles (four fragments a block, and the other's second round is full): 0.99..1.13.  More than 1536 row tiles: 0.65..1.09, seven sizes.
+//  - 3 bits, 769..1024 row tiles (four fragments a block, and the other's second round is full): 0.99..1.13.  More than 1536 row tiles: 0.65..1.09, seven sizes.
 static inline bool ring_takes_wide(const LinearArgs& a) {
   if (a.bits == 4 || !ring_serves(a)) return false;
   if (wide_streams(a) && (long long)a.km.n_keep * a.M <= 4096) return false;
@@ -127,7 +131,7 @@ static inline bool ring_takes_wide(const LinearArgs& a) {
   if (row_tiles > kRingTallest) return false;
   if (row_tiles > 256 && row_tiles <= 512) return a.bits == 6 && (a.M <= 16 || groups <= 80);
   if (a.bits == 6) return true;
-  return a.bits == 8 || row_tiles <= 768 || row_tiles > 1040;
+  return a.bits == 8 || !ring_four(row_tiles);
 }
 
 }  // namespace uniql

@@ -23,7 +23,6 @@
 // The sums are formed in the same order as in w4_mfma_kernel: the outputs are bit-identical.
 #pragma once
 #include "common.h"
-#include <atomic>
 
 namespace uniql {
 
@@ -348,20 +347,6 @@ static inline bool prefill_serves(const LinearArgs& a) {
          a.ldx * 256 * 2 + (long long)a.K_total * 2 + 8192 < (1ll << 31);
 }
 
-// Number of compute units of the current device (the size of the persistent grid), looked up once per device (0: not yet;
-// host threads may look it up at once).
-static inline int prefill_grid_limit() {
-  static std::atomic<int> cus[64];
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
-  int v = cus[dev].load(std::memory_order_relaxed);
-  if (v == 0) {
-    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v <= 0) v = 256;
-    cus[dev].store(v, std::memory_order_relaxed);
-  }
-  return v;
-}
-
 template <bool BF16, int AF, int BF, int WN, int S2, int PW, int AH = (AF > 8 ? 8 : AF), int UPP = 8, int ADB = 1>
 static hipError_t launch_prefill_cfg(const LinearArgs& a, hipStream_t stream) {
   constexpr int BM = 16 * AF, BN = WN * BF * 16, SC = S2 * 128;
@@ -374,7 +359,7 @@ static hipError_t launch_prefill_cfg(const LinearArgs& a, hipStream_t stream) {
   const int nrt = (a.km.n_keep + BN - 1) / BN, ntt = (a.M + BM - 1) / BM;
   // whole octets of blocks for the die-aware walk: rounded up where the tiles are fewer than the compute units (a block
   // without a tile ends at once; rounded down, the tiles left over cost a second round: 180 tiles of 4096 columns 194 us)
-  int blocks = prefill_grid_limit();
+  int blocks = compute_units();
   if (blocks >= 8) blocks -= blocks % 8;
   if ((long long)nrt * ntt < blocks) blocks = nrt * ntt < 8 ? nrt * ntt : (nrt * ntt + 7) / 8 * 8;
   hipLaunchKernelGGL(kern, dim3(blocks), dim3(WN * 64), smem, stream, a, nrt, ntt);

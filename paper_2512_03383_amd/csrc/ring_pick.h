@@ -1,7 +1,6 @@
 // Host side of the ring kernel: the rows of a block.
 #pragma once
 #include "common.h"
-#include "prefill_kernel.h"   // prefill_grid_limit: compute units of the device
 
 namespace uniql {
 
@@ -18,7 +17,7 @@ constexpr int kRingLds = 160 * 1024;
 // a launch of column segments has not been found faster; eight of 32 tokens do not fit the LDS; wide codes do
 // not come in launches of several matrices, and one of up to 1536 row tiles never wants more than six.  The order of the sums does not depend on it.
 static inline int ring_rows(const LinearArgs* p, int n) {
-  const int cus = prefill_grid_limit(), most = p[0].km.cs_stride != 0 ? 5 : p[0].bits != 4 ? 6 : p[0].M <= 16 ? 8 : 7;
+  const int cus = compute_units(), most = p[0].km.cs_stride != 0 ? 5 : p[0].bits != 4 ? 6 : p[0].M <= 16 ? 8 : 7;
   int groups = 0;
   for (int i = 0; i < n; ++i) groups = (p[i].km.k_span + kGroup - 1) / kGroup > groups ? (p[i].km.k_span + kGroup - 1) / kGroup : groups;
   int best = 1;
@@ -36,7 +35,7 @@ static inline int ring_rows(const LinearArgs* p, int n) {
 
 // the same for a gated pair: three or four fragments of each matrix (the pairs that are served have 640 .. 1536 row tiles: fewer never are the best)
 static inline int ring_glu_rows(const LinearArgs* p) {
-  const int cus = prefill_grid_limit(), row_tiles = (p[0].km.n_keep + 15) / 16;
+  const int cus = compute_units(), row_tiles = (p[0].km.n_keep + 15) / 16;
   auto rounds = [&](int rows) { return ((row_tiles + rows - 1) / rows + cus - 1) / cus; };
   return rounds(3) * 7 <= rounds(4) * 9 ? 6 : 8;
 }

@@ -47,7 +47,7 @@ def test_prefixes(env, uref, N, K, kk, M, fmt):   # noqa: F811
 # taller matrices: four to six fragments of 16 a block
 @pytest.mark.parametrize("fmt", FORMATS)
 @pytest.mark.parametrize("M", [9, 16, 19, 32])
-@pytest.mark.parametrize("N,kk", [(12801, 2048), (16260, 2048), (19203, 2175), (21001, 2173), (24570, 2050)])
+@pytest.mark.parametrize("N,kk", [(12801, 2048), (16260, 2048), (16393, 2051), (19203, 2175), (21001, 2173), (24570, 2050)])
 def test_tall_prefixes(env, uref, N, kk, M, fmt):   # noqa: F811
     rng = wl.rng_for(77, N + M)
     rows = np.concatenate([np.arange(0, N, 512), [15, 16, 63, 64, 79, 80, 111, 112, 127, 128, N - 17, N - 4, N - 1], rng.integers(0, N, 40)])

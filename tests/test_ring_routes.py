@@ -32,8 +32,15 @@ def test_wide_codes(bits):
     assert takes(4096, 4096, 32) and takes(4096, 4224, 8) and takes(4096, 5120, 8) and takes(4096, 5248, 24) and takes(1024, 5120, 17) and takes(2048, 4608, 32)
     assert takes(3072, 8192, 32) and takes(3088, 8192, 25) and takes(4096, 8192, 32)
     assert takes(4112, 4096, 8) == takes(8192, 10240, 24) == (bits == 6) and not takes(8192, 10368, 17) and takes(8208, 10368, 17)
-    assert takes(12288, 4096, 8) and takes(12304, 4096, 8) == takes(16640, 4096, 8) == (bits != 3) and takes(16656, 4096, 8)
+    assert takes(12288, 4096, 8) and takes(12304, 4096, 8) == takes(16384, 4096, 8) == (bits != 3) and takes(16385, 4096, 8)
     assert takes(24576, 4096, 8) and not takes(24577, 4096, 8)
     # few outputs: a token per grid row
     assert not takes(256, 4096, 8) and not takes(2048, 8192, 2) and not takes(1024, 4096, 4) and takes(1025, 8192, 4) and takes(520, 8192, 8)
     assert takes(2064, 8192, 2)
+
+
+# tall prefixes of short rows: not where the ring kernel would have four fragments a block
+@pytest.mark.parametrize("M", [9, 16, 17, 32])
+def test_tall_prefixes(M):
+    assert ring(12288, 4096, M, None) and not ring(12289, 4096, M, None) and not ring(16384, 4096, M, None) and ring(16385, 4096, M, None)
+    assert ring(24576, 4096, M, None) and not ring(24577, 4096, M, None) and not ring(16385, 4224, M, None)
