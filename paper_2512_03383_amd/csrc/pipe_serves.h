@@ -60,7 +60,15 @@ static inline bool ring_serves(const LinearArgs& a) {
 //    tokens: 0.97..1.08 (0.75..0.82) up to 12200 rows, 0.75..0.82 (0.85..0.99) at 19000 and 24000; 1.04 (1.02..1.04) at 32000.  Between them
 //    (769..1024 row tiles: four fragments a block, ring_four) the other kernels fill their rounds: 17..32 tokens 1.10..1.17 (0.86..0.89), 9..16 tokens 0.93..1.12, 1.03 in the
 //    mean of 84 sizes (fp16, 4096 columns 1.05..1.12: 14208 rows at 16 tokens 13.2 -> 14.7 us; two in a launch 0.75..0.81): left there, as a linear by itself and in
-//    a launch has to take the same kernel.  Up to 8 tokens 0.9..1.26.
+//    a launch has to take the same kernel.
+//  - Up to 8 tokens, prefixes of 601..639 row tiles 0.66..0.99 (160 sizes), and from 640 on, where the block-staged kernel's image of the activations serves
+//    rows of up to 32 groups (0.85..1.32 of its time here), longer rows: 0.62..0.98 up to 768 and from 1025 to 1536 row tiles; with four fragments a block
+//    0.87..1.02 beyond 40 groups, 1.01..1.10 up to there.  A set of tall and short matrices is then one launch again, which it had stopped being when the short
+//    ones came here: 10240 + 1024 rows x 5120 columns at 8 tokens 22.6 -> 14.7 us (16.4 before that), 12288 + 1024 + 1024 x 12288 43.0 -> 32.9 (41.4).
+//    Tall ones of up to 32 groups with short ones stay two launches: 12288 + 1024 + 1024 x 4096 at 2 / 8 tokens 15.8 / 17.5 (14.4 / 15.4 in one of
+//    the block-staged kernel, 14.1 in one of this; 14336 + 1024 16.0 / 17.8, 14.6 / 15.6 and 14.4), as by themselves they would lose more here
+//    (14336 x 4096 at 8 tokens 11.4 -> 14.1).  The same at 9..16 tokens with four fragments (14336 + 1024 x 4096 at 16 tokens 19.4, 16.0, 14.9), and with rows
+//    of fewer than sixteen groups beside longer ones (4096 x 1536 + 4096 x 4096 at 8 tokens 12.1, 9.6 in one of the block-staged kernel).
 //  - Segments of 17..32 tokens, up to 256 row tiles, beyond 32 groups (460 sizes): up to 64 groups 0.77..1.01, bfloat16 and whole blocks as fp16 and partial
 //    ones; but 0.94..1.06 on more than 192 row tiles from 25 tokens on, and segments of fewer than 64 columns that keep part of a block (1.04..1.25
 //    on long rows) stay.  65..96 groups up to 192 row tiles 0.77..0.99; partial blocks in fp16 (0.93..1.03), more row tiles (up to 1.09) and longer rows (up to 1.11) stay.
@@ -75,8 +83,8 @@ static inline bool ring_takes(const LinearArgs& a, bool segments_keep) {   // se
   if (a.bits != 4 || !ring_serves(a)) return false;
   const int row_tiles = (a.km.n_keep + 15) / 16, groups = (a.km.k_span + kGroup - 1) / kGroup;
   const bool shorter = groups <= 32;
-  if (a.M <= 8) return row_tiles <= 600;
   if (a.km.cs_stride != 0) {
+    if (a.M <= 8) return row_tiles <= 600;
     if (a.M <= 16) return row_tiles <= 320;
     if (row_tiles > 256) return false;
     if (shorter) return !segments_keep;
@@ -84,6 +92,7 @@ static inline bool ring_takes(const LinearArgs& a, bool segments_keep) {   // se
     if (groups <= 64) return row_tiles <= 192 || a.M <= 24;
     return groups <= 96 && row_tiles <= 192 && !segments_keep;
   }
+  if (a.M <= 8) return row_tiles < 640 || (!shorter && row_tiles <= kRingTallest && !(ring_four(row_tiles) && groups <= 40));
   if (row_tiles < 400) return true;
   return shorter && row_tiles <= kRingTallest && !ring_four(row_tiles);
 }

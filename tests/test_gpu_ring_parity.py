@@ -54,6 +54,18 @@ def test_tall_prefixes(env, uref, N, kk, M, fmt):   # noqa: F811
     run(env, uref, N, 2176, M, Keep(n_keep=N - 2, k_keep=kk), Keep(k_keep=kk), fmt, M % 2 == 0, (-kk) % 8, rows)
 
 
+# up to 8 tokens, three to six fragments: rows of up to 32 groups up to 639 row tiles, longer ones above
+@pytest.mark.parametrize("fmt", FORMATS)
+@pytest.mark.parametrize("M", [2, 4, 5, 8])
+@pytest.mark.parametrize("N,K,kk", [(10226, 2176, 2171), (10243, 4352, 4225), (12290, 4224, 4224), (16301, 5248, 5131), (16393, 4224, 4222), (22003, 4352, 4350), (24578, 4224, 4098)])
+def test_tall_prefixes_of_few_tokens(env, uref, N, K, kk, M, fmt):   # noqa: F811
+    rng = wl.rng_for(79, N + M)
+    rows = np.concatenate([np.arange(0, N, 512), [15, 16, 63, 64, 79, 80, 111, 112, 127, 128, N - 17, N - 4, N - 1], rng.integers(0, N, 40)])
+    ld = kk + (-kk) % 8
+    assert env[0].uniql_w4_linear_kernel(N, K, Keep(n_keep=N - 2, k_keep=kk), M, bf16=fmt == "bf16", ldx=ld)[3] == 8
+    run(env, uref, N, K, M, Keep(n_keep=N - 2, k_keep=kk), Keep(k_keep=kk), fmt, M % 2 == 0, ld - kk, rows)
+
+
 # gate and up with h = SiLU(g) * u: two to four pairs of fragments a block, one round and more; rows kept apart; one matrix without zero points.
 @pytest.mark.parametrize("fmt", FORMATS)
 @pytest.mark.parametrize("M", [9, 15, 16])

@@ -52,3 +52,11 @@ def test_the_report_names_the_kernel_that_is_launched(record, keep, bits):
         assert rc == 0 and len(launches) == 1 and choice[:len(want)] == want, (N, K, M, launches[0].kernel, choice)
         seen.add(launches[0].kernel.split("<")[0])
     assert {"w_ring_kernel", "w_pipe_kernel"} <= seen
+
+
+# decode batches of tall and short matrices: one launch where one kernel takes them all
+@pytest.mark.parametrize("M", [2, 5, 8])
+def test_decode_batches_of_mixed_heights(record, M):
+    sets = [[(12288, 8192, {}), (1024, 8192, {}), (1024, 8192, {})], [(10240, 5120, {}), (1024, 5120, {})], [(18944, 4224, {}), (3584, 4224, {})],
+            [(9700, 4096, {}), (4096, 4096, {})], [(8192, 4096, {}), (1024, 4096, {}), (1024, 4096, {})]]
+    assert [len(launches) for _, launches in record([dict(specs=s, M=M) for s in sets])] == [1] * len(sets)

@@ -44,3 +44,12 @@ def test_wide_codes(bits):
 def test_tall_prefixes(M):
     assert ring(12288, 4096, M, None) and not ring(12289, 4096, M, None) and not ring(16384, 4096, M, None) and ring(16385, 4096, M, None)
     assert ring(24576, 4096, M, None) and not ring(24577, 4096, M, None) and not ring(16385, 4224, M, None)
+
+
+# up to 8 tokens: prefixes that the block-staged kernel cannot hold whole
+@pytest.mark.parametrize("M", [2, 8])
+def test_tall_prefixes_of_few_tokens(M):
+    assert ring(10224, 4096, M, None) and not ring(10225, 4096, M, None) and ring(10225, 4224, M, None) and ring(12288, 4224, M, None)
+    assert not ring(12289, 4224, M, None) and not ring(16384, 5120, M, None) and ring(12289, 5248, M, None) and ring(16385, 4224, M, None)
+    assert ring(24576, 8192, M, None) and not ring(24577, 8192, M, None)
+    assert ring(9600, 8192, M, KeepDesc(col_seg_stride=128, col_seg_keep=108)) and not ring(9601, 8192, M, KeepDesc(col_seg_stride=128, col_seg_keep=108))
