@@ -401,7 +401,7 @@ static hipError_t glu_batch(const LinearArgs* p, hipStream_t stream, bool* done)
     *done = false;
     return hipSuccess;
   }
-  if (p[0].M >= 9 && (p[0].km.n_keep + 15) / 16 <= kRingTallest && ring_serves(p[0]) && ring_serves(p[1])) {
+  if (p[0].M >= 9 && (p[0].km.n_keep + 15) / 16 <= kRingTallest && ring_serves(p[0]) && ring_serves(p[1]) && p[0].km.k_span > 15 * kGroup) {
     *done = true;
     if constexpr (BF16) return launch_ring_glu_bf16(p, stream);
     else return launch_ring_glu(p, stream);

@@ -40,11 +40,11 @@ static inline bool pipe_serves(const LinearArgs& a) {
   return (long long)a.N_total * (a.K_total / 8) * a.bits < lim && (long long)a.ldx * 2 * 128 + (long long)a.K_total * 2 < lim;
 }
 
-// What the ring kernel (ring_kernel.h) serves: 2..32 tokens, rows of sixteen kept groups and more (the window of zero points;
-// the groups that are kept and not the stored ones, so that a compact copy of the matrix goes the same way) and up to 320, whose scales
-// and zero points fit the LDS beside the rings.
+// What the ring kernel (ring_kernel.h) serves: 2..32 tokens, rows of eight kept groups and more (one for every wave; the groups that are kept and not the
+// stored ones, so that a compact copy of the matrix goes the same way) and up to 320, whose scales and zero points fit the LDS beside the rings; at
+// least two rows of fewer than sixteen groups (a window of zero points).
 static inline bool ring_serves(const LinearArgs& a) {
-  return a.M <= 32 && a.km.k_span > 15 * kGroup && a.km.k_span <= 320 * kGroup && pipe_serves(a) &&
+  return a.M <= 32 && a.km.k_span > 7 * kGroup && (a.km.k_span > 15 * kGroup || a.km.n_keep > 1) && a.km.k_span <= 320 * kGroup && pipe_serves(a) &&
          ((a.M - 1) * a.ldx + a.km.k_keep) * 2 < (1ll << 31);
 }
 
@@ -67,8 +67,10 @@ static inline bool ring_serves(const LinearArgs& a) {
 //    ones came here: 10240 + 1024 rows x 5120 columns at 8 tokens 22.6 -> 14.7 us (16.4 before that), 12288 + 1024 + 1024 x 12288 43.0 -> 32.9 (41.4).
 //    Tall ones of up to 32 groups with short ones stay two launches: 12288 + 1024 + 1024 x 4096 at 2 / 8 tokens 15.8 / 17.5 (14.4 / 15.4 in one of
 //    the block-staged kernel, 14.1 in one of this; 14336 + 1024 16.0 / 17.8, 14.6 / 15.6 and 14.4), as by themselves they would lose more here
-//    (14336 x 4096 at 8 tokens 11.4 -> 14.1).  The same at 9..16 tokens with four fragments (14336 + 1024 x 4096 at 16 tokens 19.4, 16.0, 14.9), and with rows
-//    of fewer than sixteen groups beside longer ones (4096 x 1536 + 4096 x 4096 at 8 tokens 12.1, 9.6 in one of the block-staged kernel).
+//    (14336 x 4096 at 8 tokens 11.4 -> 14.1).  The same at 9..16 tokens with four fragments (14336 + 1024 x 4096 at 16 tokens 19.4, 16.0, 14.9).
+//  - Rows of 8..15 groups, prefixes, go by the same lines: 0.49..0.93 up to 375 row tiles (384 sizes), 0.69..1.06 above.  Without them a set of such rows and longer ones
+//    was two launches where it had been one: 4096 x 1536 + 4096 x 4096 at 8 / 24 tokens 12.4 / 17.3 -> 8.6 / 9.9 us (9.6 / 16.0 in one of the block-staged
+//    kernel), 2048 x 1024 + 1024 x 2048 9.3 / 12.8 -> 4.2 / 5.3 (6.0 / 8.5).  Segments and other widths, which never shared one, stay.
 //  - Segments of 17..32 tokens, up to 256 row tiles, beyond 32 groups (460 sizes): up to 64 groups 0.77..1.01, bfloat16 and whole blocks as fp16 and partial
 //    ones; but 0.94..1.06 on more than 192 row tiles from 25 tokens on, and segments of fewer than 64 columns that keep part of a block (1.04..1.25
 //    on long rows) stay.  65..96 groups up to 192 row tiles 0.77..0.99; partial blocks in fp16 (0.93..1.03), more row tiles (up to 1.09) and longer rows (up to 1.11) stay.
@@ -84,6 +86,7 @@ static inline bool ring_takes(const LinearArgs& a, bool segments_keep) {   // se
   const int row_tiles = (a.km.n_keep + 15) / 16, groups = (a.km.k_span + kGroup - 1) / kGroup;
   const bool shorter = groups <= 32;
   if (a.km.cs_stride != 0) {
+    if (groups < 16) return false;
     if (a.M <= 8) return row_tiles <= 600;
     if (a.M <= 16) return row_tiles <= 320;
     if (row_tiles > 256) return false;
@@ -134,7 +137,7 @@ static inline bool wide_streams(const LinearArgs& a) {
 //    tokens on with rows of more than 80 groups, whose activations every block fetches.
 //  - 3 bits, 769..1024 row tiles (four fragments a block, and the other's second round is full): 0.99..1.13.  More than 1536 row tiles: 0.65..1.09, seven sizes.
 static inline bool ring_takes_wide(const LinearArgs& a) {
-  if (a.bits == 4 || !ring_serves(a)) return false;
+  if (a.bits == 4 || !ring_serves(a) || a.km.k_span <= 15 * kGroup) return false;
   if (wide_streams(a) && (long long)a.km.n_keep * a.M <= 4096) return false;
   const int row_tiles = (a.km.n_keep + 15) / 16, groups = (a.km.k_span + kGroup - 1) / kGroup;
   if (row_tiles > kRingTallest) return false;

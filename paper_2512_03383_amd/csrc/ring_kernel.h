@@ -163,13 +163,15 @@ __global__ __launch_bounds__(kRingWaves * kWave, 2) void w_ring_kernel(RingBatch
   if ((tail & 1) && ng > 0 && g0 + ng == ngroups && lane < a.M) ring_load_word(rx, lds0 + odd0, lane * (int)a.ldx * 2 + (km.k_keep - 2) * 2);
 
   // ---- scales and zero points: window w of eight (sixteen) groups of every row of the tile, windows dealt to the waves.  A window never
-  // leaves the row (at the row's end it starts earlier).
+  // leaves the row (at the row's end it starts earlier); but that of the zero points of a row of fewer than sixteen groups ends in the next row, and the
+  // last row's, whose last word could lie partly past the array, starts earlier and is moved in LDS (below).
   {
 #pragma unroll
     for (int m = 0; m < NM; ++m) {
       const LinearArgs& w = bt.p[GLU ? m : pi];
       const u32x4_t rs = ring_rsrc(w.scales, w.N_total * gpr * 2);
       const u32x4_t rz = ring_rsrc(w.zeros, w.zeros ? w.N_total * gpr : 0);
+      const int zlast = gpr < 16 ? w.N_total * gpr - 16 : (w.N_total - 1) * gpr;   // where the last row's window starts
 #pragma unroll
       for (int p = 0; p < (R + 63) / 64; ++p) {
         const int r = p * 64 + lane, e0 = stored(m, GLU ? n0 + (r >> 5) * 16 + (r & 15) : n0 + r) * gpr;
@@ -178,7 +180,7 @@ __global__ __launch_bounds__(kRingWaves * kWave, 2) void w_ring_kernel(RingBatch
             ring_load(rs, lds0 + sz0 + (i * R + p * 64) * 16, 2 * e0, 2 * (8 * i < gpr - 8 ? 8 * i : gpr - 8));
           if (w.zeros)
             for (int i = kRingWaves - 1 - wave; i < nwz; i += kRingWaves)
-              ring_load(rz, lds0 + zz0 + (i * R + p * 64) * 16, e0, 16 * i < gpr - 16 ? 16 * i : gpr - 16);
+              ring_load(rz, lds0 + zz0 + (i * R + p * 64) * 16, e0 < zlast ? e0 : zlast, gpr < 16 || 16 * i < gpr - 16 ? 16 * i : gpr - 16);
         }
       }
     }
@@ -261,6 +263,16 @@ __global__ __launch_bounds__(kRingWaves * kWave, 2) void w_ring_kernel(RingBatch
 
   // scales and zero points of this wave have landed, then everybody's
   ring_wait<S, H - 1, L>(parts);
+  if (!GLU && gpr < 16 && wave == kRingWaves - 1 && a.zeros) {   // (the wave that has loaded the only window)
+#pragma unroll
+    for (int p = 0; p < (R + 63) / 64; ++p) {
+      const int r = p * 64 + lane;
+      if (r < R && stored(0, n0 + r) == a.N_total - 1) {
+        unsigned __int128* z = reinterpret_cast<unsigned __int128*>(smem + zz0 + r * 16);
+        *z >>= 8 * (16 - gpr);
+      }
+    }
+  }
   pipe_barrier();
 
   // What lies behind the kept columns in a part's last block of a prefix, or in the last blocks of its segments, is cleared: the next
@@ -321,7 +333,7 @@ __global__ __launch_bounds__(kRingWaves * kWave, 2) void w_ring_kernel(RingBatch
           for (int h = 0; h < H; ++h) raw[h][b] = read_codes<BITS, T>(wp + wrd[h] + b * (16 * U * 16), T * BITS % 4 == 0 ? 0 : ks);
         const int gs = g & ~7, gz = g & ~15;
         const unsigned char* const sp = smem + sz0 + (g >> 3) * (R * 16) + 2 * (g - (gs < gpr - 8 ? gs : gpr - 8)) + n * 16;
-        const unsigned char* const zp = smem + zz0 + (g >> 4) * (R * 16) + g - (gz < gpr - 16 ? gz : gpr - 16) + n * 16;
+        const unsigned char* const zp = smem + zz0 + (g >> 4) * (R * 16) + g - (gpr < 16 || gz < gpr - 16 ? gz : gpr - 16) + n * 16;
 #pragma unroll
         for (int b = 0; b < BF; ++b) sb[b] = *reinterpret_cast<const uint16_t*>(sp + b * 256);
 #pragma unroll

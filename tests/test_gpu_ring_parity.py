@@ -109,6 +109,17 @@ def test_segments_of_long_rows(env, uref, M, N, K, stride, keep, fmt):   # noqa:
     run(env, uref, N, K, M, k, k, fmt, M % 2 == 0, M % 3, np.concatenate([np.arange(0, N, 97), [N - 1]]))
 
 
+# rows of 8 to 15 groups, whose window of zero points ends in the next row, or, the last row's, starts in the one before
+@pytest.mark.parametrize("fmt", FORMATS)
+@pytest.mark.parametrize("M", [2, 7, 16, 31])
+@pytest.mark.parametrize("N,K,kk", [(2, 1024, 1024), (17, 1152, 1029), (47, 1408, 1407), (600, 1920, 1921 - 128), (4117, 1280, 1274), (5000, 1920, 1920), (9577, 1664, 1650)])
+def test_short_rows(env, uref, N, K, kk, M, fmt):   # noqa: F811
+    rng = wl.rng_for(80, N + M)
+    ld = kk + (-kk) % 8
+    assert env[0].uniql_w4_linear_kernel(N, K, Keep(k_keep=kk), M, bf16=fmt == "bf16", ldx=ld)[3] == 8
+    run(env, uref, N, K, M, Keep(k_keep=kk), Keep(k_keep=kk), fmt, (N + M) % 4 != 0, ld - kk, np.concatenate([np.arange(0, N, 256), np.arange(max(0, N - 20), N), rng.integers(0, N, 30)]))
+
+
 # rows of one to three runs of groups a wave, fewer groups than the loads in flight, more, and the windows of eight scales and sixteen zero points
 # at the row's end
 @pytest.mark.parametrize("M", [2, 8, 16, 32])

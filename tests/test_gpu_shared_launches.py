@@ -25,9 +25,11 @@ SEG = Keep(k_keep=8 * 108, col_seg_stride=128, col_seg_keep=108)
 @pytest.mark.parametrize("fmt", ["f16", "bf16"])
 @pytest.mark.parametrize("M,specs,launches", [
     (8, [(6500, 1024, Keep()), (200, 1024, Keep()), (129, 1024, Keep())], 1),          # a decode batch, tall and short
-    (12, [(6500, 1024, Keep()), (200, 1024, Keep()), (129, 1024, Keep())], 1),         # (short rows: staged once per block)
-    (12, [(6500, 2304, Keep()), (200, 1024, Keep()), (129, 1024, Keep())], 2),         # the tall one by itself
-    (24, [(6500, 1152, Keep()), (200, 1024, Keep()), (6401, 1024, Keep(k_keep=1001)), (48, 1024, Keep())], 2),
+    (12, [(6500, 1024, Keep()), (200, 1024, Keep()), (129, 1024, Keep())], 1),
+    (12, [(6500, 2304, Keep()), (200, 1024, Keep()), (129, 1024, Keep())], 1),         # (rows of different lengths)
+    (12, [(6500, 4224, Keep()), (200, 1024, Keep()), (129, 1024, Keep())], 2),         # the tall one, whose rows are long, by itself
+    (24, [(6500, 1152, Keep()), (200, 1024, Keep()), (6401, 1024, Keep(k_keep=1001)), (48, 1024, Keep())], 1),
+    (24, [(6500, 4352, Keep()), (200, 1024, Keep()), (6401, 4224, Keep(k_keep=4201)), (48, 1024, Keep())], 2),   # two and two
     (12, [(200, 1024, SEG), (129, 1024, Keep()), (97, 1152, Keep(k_keep=1100))], 2),   # segments do not share a decode batch
     (40, [(6500, 1024, Keep()), (200, 1024, Keep()), (129, 1024, Keep())], 2),         # two ways to split K
     (40, [(200, 1024, Keep()), (129, 1024, Keep())], 1),

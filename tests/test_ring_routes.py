@@ -53,3 +53,12 @@ def test_tall_prefixes_of_few_tokens(M):
     assert not ring(12289, 4224, M, None) and not ring(16384, 5120, M, None) and ring(12289, 5248, M, None) and ring(16385, 4224, M, None)
     assert ring(24576, 8192, M, None) and not ring(24577, 8192, M, None)
     assert ring(9600, 8192, M, KeepDesc(col_seg_stride=128, col_seg_keep=108)) and not ring(9601, 8192, M, KeepDesc(col_seg_stride=128, col_seg_keep=108))
+
+
+# 4-bit prefixes from eight groups on (one for every wave), of one row from sixteen; segments and other widths from sixteen
+@pytest.mark.parametrize("M", [2, 16, 32])
+def test_shortest_rows(M):
+    assert ring(2048, 1024, M, None) and not ring(2048, 896, M, None) and ring(2048, 2048, M, KeepDesc(k_keep=897)) and not ring(2048, 2048, M, KeepDesc(k_keep=896))
+    assert ring(2, 1024, M, None) and not ring(1, 1920, M, None) and not ring(7, 1920, M, KeepDesc(n_keep=1)) and ring(1, 2048, M, None)
+    assert not ring(2048, 1920, M, KeepDesc(col_seg_stride=128, col_seg_keep=104)) and ring(2048, 2048, M, KeepDesc(col_seg_stride=128, col_seg_keep=104))
+    assert not ring(3000, 1920, M, None, bits=8) and ring(3000, 2048, M, None, bits=8)
