@@ -27,3 +27,23 @@ def tiles(bits, segments):
     if narrow:
         t |= {(16, 64, 4), (32, 64, 4), (64, 96, 4), (112, 128, 2)}
     return t
+
+
+# (bits, K, N, M, segments, tokens of a tile): grids whose last round goes out as halves of its tiles; in those with at most half a tile of tokens left over
+# (8170 x 1170, 19027 x 700, 5068 x 777) second halves have no token.  Codes of 8 bits in 128-token tiles are also brought into the L2 ahead.
+HALVES = [(8, 1024, 6102, 1000, False, 128), (8, 1024, 6102, 1000, True, 128), (8, 1024, 8170, 1170, False, 128), (8, 1024, 8170, 1170, True, 128), (8, 1152, 12185, 500, False, 128),
+          (6, 1024, 8170, 1170, False, 128), (6, 1024, 8170, 1170, True, 128), (6, 1024, 5068, 777, False, 96), (6, 1024, 5068, 777, True, 96)]
+HALVES += [(bits, *size) for bits in (4, 3) for size in ((1024, 8170, 1170, False, 128), (1152, 12185, 500, False, 128), (1024, 16442, 1500, True, 128), (1024, 19027, 700, True, 128),
+                                                         (1024, 5068, 777, False, 96), (1024, 5068, 777, True, 96))]
+
+
+def halves_rule(K, N, segments):
+    """The rule of a case of HALVES: all rows but three, 102 of 128 columns or all but thirteen."""
+    return dict(n_keep=N - 3, k_keep=K // 128 * 102, col_seg_stride=128, col_seg_keep=102) if segments else dict(n_keep=N - 3, k_keep=K - 13)
+
+
+def half_tiles(rows, M, tile, cus=256):
+    """Tiles of a grid that go out as halves, and all of them, for a tile of (tokens, rows)."""
+    tiles = -(-rows // tile[1]) * -(-M // tile[0])
+    rest = tiles % cus
+    return (rest if tiles > cus and 2 * rest <= cus else 0), tiles

@@ -2,6 +2,7 @@
 import pytest
 
 import launches as la
+import pipe_shapes as ps
 import paper_2512_03383_amd as uq
 
 
@@ -67,3 +68,13 @@ def test_decode_batches_of_mixed_heights(record, M):
 def test_decode_batches_of_mixed_lengths(record, M):
     sets = [[(4096, 1536, {}), (4096, 4096, {})], [(2048, 1024, {}), (1024, 2048, {})], [(6384, 1920, {}), (6384, 14336, {}), (200, 1024, {})]]
     assert [len(launches) for _, launches in record([dict(specs=s, M=M) for s in sets])] == [1] * len(sets)
+
+
+# the last round of a grid as halves: two blocks for each of its tiles
+@pytest.mark.parametrize("bf16", [False, True])
+def test_last_round_goes_out_as_halves(record, bf16):
+    calls = [linear(N, K, M, ps.halves_rule(K, N, segments), bits=bits, bf16=bf16) for bits, K, N, M, segments, _ in ps.HALVES]
+    for (bits, K, N, M, segments, tokens), (rc, launches) in zip(ps.HALVES, record(calls)):
+        tile = reported(launches[0].kernel)[1:3]
+        halves, tiles = ps.half_tiles(N - 3, M, tile)
+        assert rc == 0 and tile[0] == tokens and halves > 0 and launches[0].blocks == tiles + halves, (bits, K, N, M, launches)
