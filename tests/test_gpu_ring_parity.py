@@ -44,7 +44,7 @@ def test_prefixes(env, uref, N, K, kk, M, fmt):   # noqa: F811
     run(env, uref, N, K, M, Keep(n_keep=N - 2, k_keep=kk), Keep(k_keep=kk), fmt, M % 2 == 0, ld - kk, rows)
 
 
-# taller matrices: four to six fragments of 16 a block
+# taller matrices: five and six fragments of 16 a block, and 12801 and 16260 rows, which would have four and go to other kernels
 @pytest.mark.parametrize("fmt", FORMATS)
 @pytest.mark.parametrize("M", [9, 16, 19, 32])
 @pytest.mark.parametrize("N,kk", [(12801, 2048), (16260, 2048), (16393, 2051), (19203, 2175), (21001, 2173), (24570, 2050)])
@@ -66,7 +66,7 @@ def test_tall_prefixes_of_few_tokens(env, uref, N, K, kk, M, fmt):   # noqa: F81
     run(env, uref, N, K, M, Keep(n_keep=N - 2, k_keep=kk), Keep(k_keep=kk), fmt, M % 2 == 0, ld - kk, rows)
 
 
-# gate and up with h = SiLU(g) * u: two to four pairs of fragments a block, one round and more; rows kept apart; one matrix without zero points.
+# gate and up with h = SiLU(g) * u: three or four pairs of fragments a block, one round and more; rows kept apart; one matrix without zero points.
 @pytest.mark.parametrize("fmt", FORMATS)
 @pytest.mark.parametrize("M", [9, 15, 16])
 @pytest.mark.parametrize("N,K,keep", [(10233, 2048, Keep(k_keep=1921)), (12185, 4096, Keep(k_keep=3968)), (16300, 2176, Keep(n_keep=16299)), (20011, 2304, Keep(k_keep=2302)),
@@ -89,6 +89,30 @@ def test_gated_pair(env, uref, N, K, keep, M, fmt):   # noqa: F811
     ref = go * up / (1.0 + np.exp(-go))
     # (element by element alone: a few products carry a token's norm, and the rounding of one is up to 2^-8 of it in bfloat16)
     assert linear_err(hb[1:M + 1, :nk].float().cpu().numpy()[:, rows], ref) <= (TOL_BF16 if fmt == "bf16" else TOL)
+
+
+# the two matrices with row rules of their own (the same number of kept rows) and of different heights
+@pytest.mark.parametrize("fmt", FORMATS)
+@pytest.mark.parametrize("M", [9, 16])
+@pytest.mark.parametrize("K,heights,keeps", [
+    (2048, (12000, 14400), (Keep(n_keep=12000, k_keep=2045), Keep(n_keep=12000, k_keep=2045, row_seg_stride=96, row_seg_keep=80, row_seg_limit=14400))),
+    (2176, (20480, 16005), (Keep(n_keep=16000, row_seg_stride=128, row_seg_keep=100, row_seg_limit=20480), Keep(n_keep=16000))),
+    (2304, (15000, 16000), (Keep(n_keep=11000, row_seg_stride=60, row_seg_keep=44, row_seg_limit=15000), Keep(n_keep=11000, row_seg_stride=64, row_seg_keep=44, row_seg_limit=16000)))])
+def test_gated_pair_of_two_row_rules(env, uref, K, heights, keeps, M, fmt):   # noqa: F811
+    uq, torch = env
+    g = torch.Generator(device="cuda").manual_seed(K + M)
+    ws = [weight(env, g, N, K, 4, fmt, zeros=i == 1) for i, N in enumerate(heights)]
+    nk, kk = uq.kept_dims(ws[0], keeps[0])
+    assert (nk, kk) == uq.kept_dims(ws[1], keeps[1])
+    x = torch.zeros((M, kk + (-kk) % 8), dtype=ws[0].scales.dtype, device="cuda")[:, :kk]
+    x.copy_(torch.randn((M, kk), generator=g, device="cuda"))
+    h = torch.empty((M, nk), dtype=x.dtype, device="cuda")
+    uq.uniql_w4_gate_up_silu_batch(ws, list(keeps), x, h)
+    rows = np.unique(np.concatenate([np.arange(0, nk, 256), np.arange(40, 240, 20), [15, 16, 31, 32, nk - 17, nk - 1]])).astype(np.int64)
+    go, up = (oracle(uref, w, np.ascontiguousarray(np16(x, fmt)), Keep(k_keep=kk), fmt,
+                     torch.from_numpy(rows // k.row_seg_keep * k.row_seg_stride + rows % k.row_seg_keep if k.row_seg_stride else rows).cuda()).astype(np.float64) for w, k in zip(ws, keeps))
+    # (element by element alone, as above)
+    assert linear_err(h.float().cpu().numpy()[:, rows], go * up / (1.0 + np.exp(-go))) <= (TOL_BF16 if fmt == "bf16" else TOL)
 
 
 @pytest.mark.parametrize("fmt", FORMATS)
@@ -144,6 +168,25 @@ def test_shared_launch(env, uref, sizes, M, fmt):   # noqa: F811
     uq.MultiCall(ws, [None] * len(ws), [x] * len(ws), ys).run()
     for w, y in zip(ws, ys):
         assert torch.equal(y, uq.uniql_w4_linear(w, None, x))
+
+
+# the same for tall matrices of long rows at up to 8 tokens, and for rows of fewer than sixteen groups beside longer ones
+@pytest.mark.parametrize("fmt", FORMATS)
+@pytest.mark.parametrize("M,shapes", [(2, ((12285, 4352), (999, 4224))), (8, ((22003, 4224), (5003, 4224), (300, 5248))), (16, ((9001, 2176), (16401, 2176))), (30, ((16401, 2176), (5003, 1152))),
+                                      (8, ((4096, 1152), (4096, 2176), (77, 1024))), (24, ((6003, 1920), (2048, 4096)))])
+def test_shared_launch_of_tall_and_short(env, uref, M, shapes, fmt):   # noqa: F811
+    uq, torch = env
+    g = torch.Generator(device="cuda").manual_seed(M)
+    ws = [weight(env, g, N, K, 4, fmt, zeros=i != 1) for i, (N, K) in enumerate(shapes)]
+    assert all(uq.uniql_w4_linear_kernel(N, K, None, M, bf16=fmt == "bf16")[3] == 8 for N, K in shapes)
+    xs = [torch.randn((M, K), generator=g, device="cuda").to(ws[0].scales.dtype) for _, K in shapes]
+    ys = [torch.empty((M, w.N), dtype=x.dtype, device="cuda") for w, x in zip(ws, xs)]
+    uq.MultiCall(ws, [None] * len(ws), xs, ys).run()
+    for w, x, y in zip(ws, xs, ys):
+        assert torch.equal(y, uq.uniql_w4_linear(w, None, x))
+    rows = np.unique(np.array([0, 15, 16, ws[0].N // 2, ws[0].N - 1]))
+    ref = oracle(uref, ws[0], np.ascontiguousarray(np16(xs[0], fmt)), Keep(k_keep=shapes[0][1]), fmt, torch.from_numpy(rows).cuda())
+    check(ys[0].float().cpu().numpy()[:, rows], ref, fmt)
 
 
 @pytest.mark.parametrize("fmt", FORMATS)
