@@ -53,8 +53,13 @@ static inline bool ring_serves(const LinearArgs& a) {
 //  - Matrices of fewer than 400 row tiles: prefixes 0.77..0.95 of the time in the mean (0.49..1.05; above 320 row tiles and from 9 tokens
 //    on level, and there so that a tall member of a set shares a launch with short ones), segments of up to 16 tokens 0.73..0.88
 //    (above 320 row tiles and 8 tokens 1.02).  17..32 tokens of segments 0.82..1.03 up to 256 row tiles, 1.07 above.
-//  - 400..600 row tiles: up to 8 tokens 0.77..0.98; 9..32 of prefixes 0.93..1.0 with rows of up to 32 groups; longer rows (0.9..1.15) stay with
-//    the pipelined kernel, segments of 9..32 tokens (1.02..1.12) with whatever has them.
+//  - 400..600 row tiles: up to 8 tokens 0.77..0.98; 9..32 of prefixes with rows of up to 32 groups 0.88..0.98 above 512, and up to there, one round of the
+//    pipelined kernel's 32-row tiles, 0.90..0.99 with up to 20 groups, beyond them 0.97..1.03 at 9..16 tokens and 1.0..1.09 at 17..32.  But two of
+//    them in a launch (gate and up) are a full round of the pipelined kernel's 64-row tiles too and four fragments a block here: 9..16 tokens beyond 20 groups
+//    1.10..1.20 (8192 x 4096 at 16 tokens 12.1 -> 14.5 us, 7168 x 4096 12.0 -> 14.2), so these are left there, although a set with short ones is then two
+//    launches (8192 + 1024 + 1024 x 4096 at 16 tokens 15.7 us, 11.0 in one of this; 16.6 with the short ones in the block-staged kernel).  At 17..32 tokens two are
+//    0.94..1.05 and the set 0.65..0.67: they come here.  Longer rows (0.9..1.15) stay with the pipelined kernel, segments of 9..32 tokens (1.02..1.12) with
+//    whatever has them.
 //  - Taller prefixes with rows of up to 32 groups, by themselves and two of one height in a launch (gate and up).  9..16 tokens: 0.65..0.96
 //    and 0.68..0.91 up to 12200 rows and from 16700 to 24000; at 32000 rows 1.01..1.09 (1.05..1.08).  17..32
 //    tokens: 0.97..1.08 (0.75..0.82) up to 12200 rows, 0.75..0.82 (0.85..0.99) at 19000 and 24000; 1.04 (1.02..1.04) at 32000.  Between them
@@ -97,6 +102,7 @@ static inline bool ring_takes(const LinearArgs& a, bool segments_keep) {   // se
   }
   if (a.M <= 8) return row_tiles < 640 || (!shorter && row_tiles <= kRingTallest && !(ring_four(row_tiles) && groups <= 40));
   if (row_tiles < 400) return true;
+  if (a.M <= 16 && row_tiles <= 2 * compute_units() && groups > 20) return false;
   return shorter && row_tiles <= kRingTallest && !ring_four(row_tiles);
 }
 

@@ -62,3 +62,12 @@ def test_shortest_rows(M):
     assert ring(2, 1024, M, None) and not ring(1, 1920, M, None) and not ring(7, 1920, M, KeepDesc(n_keep=1)) and ring(1, 2048, M, None)
     assert not ring(2048, 1920, M, KeepDesc(col_seg_stride=128, col_seg_keep=104)) and ring(2048, 2048, M, KeepDesc(col_seg_stride=128, col_seg_keep=104))
     assert not ring(3000, 1920, M, None, bits=8) and ring(3000, 2048, M, None, bits=8)
+
+
+# 9 to 16 tokens: not one round of the pipelined kernel's 32-row tiles, 400 to 512 row tiles, with rows of more than 20 groups, two of which are slower here in a launch
+@pytest.mark.parametrize("M", [9, 16, 17, 32])
+def test_one_round_of_the_pipelined_kernel(M):
+    for N, K in ((6384, 4096), (6385, 2560), (8192, 2560), (8193, 2688), (8193, 4096)):
+        assert ring(N, K, M, None)
+    for N, K in ((6385, 2688), (7168, 4096), (8192, 4096), (8192, 3072)):
+        assert ring(N, K, M, None) == (M > 16) and ring(N, K, 8, None)
