@@ -67,12 +67,14 @@ static inline bool ring_serves(const LinearArgs& a) {
 //    mean of 84 sizes (fp16, 4096 columns 1.05..1.12: 14208 rows at 16 tokens 13.2 -> 14.7 us; two in a launch 0.75..0.81): left there, as a linear by itself and in
 //    a launch has to take the same kernel.
 //  - Up to 8 tokens, prefixes of 601..639 row tiles 0.66..0.99 (160 sizes), and from 640 on, where the block-staged kernel's image of the activations serves
-//    rows of up to 32 groups (0.85..1.32 of its time here), longer rows: 0.62..0.98 up to 768 and from 1025 to 1536 row tiles; with four fragments a block
-//    0.87..1.02 beyond 40 groups, 1.01..1.10 up to there.  A set of tall and short matrices is then one launch again, which it had stopped being when the short
-//    ones came here: 10240 + 1024 rows x 5120 columns at 8 tokens 22.6 -> 14.7 us (16.4 before that), 12288 + 1024 + 1024 x 12288 43.0 -> 32.9 (41.4).
-//    Tall ones of up to 32 groups with short ones stay two launches: 12288 + 1024 + 1024 x 4096 at 2 / 8 tokens 15.8 / 17.5 (14.4 / 15.4 in one of
+//    rows of up to 32 groups (0.85..1.32 of its time here), longer rows up to 768 row tiles 0.70..0.87, two in a launch 0.64..1.01.  Above that one by itself still is
+//    the faster (0.61..1.07), but not two (gate and up; 330 sizes): 769..1024 row tiles 0.80..1.32 (13416 x 11392 at 3 tokens 38.3 -> 50.4 us), 1025..1280 0.70..1.14, and
+//    beyond 0.84..1.10 at 2..4 tokens; there from 5 tokens on 0.67..0.98.  Rows of 8..15 groups up to 768 row tiles 0.84..1.04, two 0.84..1.04, beyond 0.75..1.23.
+//    Where a tall matrix comes here its set with short ones, which are here, is one launch again, which it had stopped being: 10240 + 1024 rows x 5120 columns at
+//    8 tokens 22.6 -> 14.7 us (16.4 in one of the block-staged kernel), 12288 + 1024 + 1024 x 12288 43.0 -> 32.9 (41.4).  Others stay two launches:
+//    12288 + 1024 + 1024 x 4096 at 2 / 8 tokens 15.8 / 17.5 (14.4 / 15.4 in one of
 //    the block-staged kernel, 14.1 in one of this; 14336 + 1024 16.0 / 17.8, 14.6 / 15.6 and 14.4), as by themselves they would lose more here
-//    (14336 x 4096 at 8 tokens 11.4 -> 14.1).  The same at 9..16 tokens with four fragments (14336 + 1024 x 4096 at 16 tokens 19.4, 16.0, 14.9).
+//    (14336 x 4096 at 8 tokens 11.4 -> 14.1), and 21350 + 2666 + 2666 x 1024 at 5 tokens 11.4 (7.9 in one of the block-staged kernel).  The same at 9..16 tokens with four fragments (14336 + 1024 x 4096 at 16 tokens 19.4, 16.0, 14.9).
 //  - Rows of 8..15 groups, prefixes, go by the same lines: 0.49..0.93 up to 375 row tiles (384 sizes), 0.69..1.06 above.  Without them a set of such rows and longer ones
 //    was two launches where it had been one: 4096 x 1536 + 4096 x 4096 at 8 / 24 tokens 12.4 / 17.3 -> 8.6 / 9.9 us (9.6 / 16.0 in one of the block-staged
 //    kernel), 2048 x 1024 + 1024 x 2048 9.3 / 12.8 -> 4.2 / 5.3 (6.0 / 8.5).  Segments and other widths, which never shared one, stay.
@@ -100,7 +102,11 @@ static inline bool ring_takes(const LinearArgs& a, bool segments_keep) {   // se
     if (groups <= 64) return row_tiles <= 192 || a.M <= 24;
     return groups <= 96 && row_tiles <= 192 && !segments_keep;
   }
-  if (a.M <= 8) return row_tiles < 640 || (!shorter && row_tiles <= kRingTallest && !(ring_four(row_tiles) && groups <= 40));
+  if (a.M <= 8) {
+    if (row_tiles < 640) return true;
+    if (row_tiles <= 3 * compute_units()) return !shorter || groups < 16;
+    return !shorter && a.M > 4 && row_tiles > 5 * compute_units() && row_tiles <= kRingTallest;
+  }
   if (row_tiles < 400) return true;
   if (a.M <= 16 && row_tiles <= 2 * compute_units() && groups > 20) return false;
   return shorter && row_tiles <= kRingTallest && !ring_four(row_tiles);

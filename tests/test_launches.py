@@ -58,7 +58,7 @@ def test_the_report_names_the_kernel_that_is_launched(record, keep, bits):
 # decode batches of tall and short matrices: one launch where one kernel takes them all
 @pytest.mark.parametrize("M", [2, 5, 8])
 def test_decode_batches_of_mixed_heights(record, M):
-    sets = [[(12288, 8192, {}), (1024, 8192, {}), (1024, 8192, {})], [(10240, 5120, {}), (1024, 5120, {})], [(18944, 4224, {}), (3584, 4224, {})],
+    sets = [[(12288, 8192, {}), (1024, 8192, {}), (1024, 8192, {})], [(10240, 5120, {}), (1024, 5120, {})], [(12200, 1920, {}), (1024, 1920, {})],
             [(9700, 4096, {}), (4096, 4096, {})], [(4096, 1536, {}), (4096, 4096, {})], [(2048, 1024, {}), (1024, 2048, {}), (300, 1920, {})], [(8192, 4096, {}), (1024, 4096, {}), (1024, 4096, {})]]
     assert [len(launches) for _, launches in record([dict(specs=s, M=M) for s in sets])] == [1] * len(sets)
 

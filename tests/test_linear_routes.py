@@ -55,13 +55,12 @@ def test_tall_matrices_of_unusual_rules(K, keep, first):
         assert uq.uniql_w4_linear_kernel(12288, K, keep, M) == want, M
 
 
-# decode batches of 2..8 tokens are one kernel's whatever the height, so that q, k and v share a launch, but for tall prefixes whose activations the
-# block-staged kernel can hold
+# decode batches of 2..8 tokens are one kernel's up to 600 row tiles, so that q, k and v share a launch
 @pytest.mark.parametrize("N", [1024, 6400, 8192, 9472, 18944])
 @pytest.mark.parametrize("K,keep", [(4096, None), (8192, None), (4096, seg(128, 108))])
 def test_small_decode_batches_share_one_kernel(N, K, keep):
     for M in (2, 5, 8):
-        assert kernel(N, K, keep, M) == (RING if N <= 9600 or K > 4096 else STAGED)
+        assert kernel(N, K, keep, M) == (RING if N <= 9600 else STAGED)
     assert kernel(N, 8192, keep and seg(128, 108), 12) == (RING if N < 6400 else PIPE)
 
 
