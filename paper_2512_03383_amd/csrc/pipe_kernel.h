@@ -45,7 +45,6 @@ constexpr int kBeyond = (int)0x80000000u;   // as an unsigned offset: past the e
 constexpr int kPipeConsumers = 8;
 constexpr int kPipeTouch = 256;   // bytes of LDS that loads write which only bring lines into the L2
 constexpr bool pipe_touches(int bits, int af) { return bits == 8 && af == 8; }
-constexpr int kPipeRound = 256;   // tiles of a round
 constexpr int kPipeDies = 8, kPipeTokTilesPerPass = 4;
 
 // Up to four linears with the same token count and format; tiles are numbered through the whole batch.
@@ -54,6 +53,7 @@ struct PipeBatch {
   int first[kMaxBatch];   // first tile of problem i
   int n, tiles, ntt;      // problems, all tiles, token tiles (the same for every problem)
   int whole;              // tiles that a block takes whole; the rest go out as two halves of the tokens each
+  int round;              // tiles of a round: the compute units
 };
 
 // HALF: half a tile of a kernel whose blocks have twelve waves
@@ -602,7 +602,7 @@ __global__ __launch_bounds__((PipeShape<AF, BF, WN, KG, KQ, G, NX, NW, BITS, SEG
       const int pass = L / (nrt * kPipeTokTilesPerPass), r = L - pass * (nrt * kPipeTokTilesPerPass);
       rt = r / kPipeTokTilesPerPass;
       mine = r - rt * kPipeTokTilesPerPass;
-      share = bt.tiles > kPipeRound ? kPipeTokTilesPerPass : 0;   // (as far as touches go)
+      share = bt.tiles > bt.round ? kPipeTokTilesPerPass : 0;   // (as far as touches go)
       tt = pass * kPipeTokTilesPerPass + mine;
     } else {
       const int w = ntt - full, r = L - nrt * full;
@@ -656,6 +656,7 @@ static hipError_t pipe_launch(const LinearArgs* p, int n, hipStream_t stream, in
   }
   b.tiles = tiles;
   b.whole = whole < 0 ? tiles : whole;
+  b.round = compute_units();
   hipLaunchKernelGGL(kern, dim3(b.whole + 2 * (tiles - b.whole)), dim3(S::Threads), lds, stream, b);
   return hipGetLastError();
 }

@@ -153,7 +153,7 @@ static inline bool ring_takes_wide(const LinearArgs& a) {
   if (wide_streams(a) && (long long)a.km.n_keep * a.M <= 4096) return false;
   const int row_tiles = (a.km.n_keep + 15) / 16, groups = (a.km.k_span + kGroup - 1) / kGroup;
   if (row_tiles > kRingTallest) return false;
-  if (row_tiles > 256 && row_tiles <= 512) return a.bits == 6 && (a.M <= 16 || groups <= 80);
+  if (row_tiles > compute_units() && row_tiles <= 2 * compute_units()) return a.bits == 6 && (a.M <= 16 || groups <= 80);
   if (a.bits == 6) return true;
   return a.bits == 8 || !ring_four(row_tiles);
 }

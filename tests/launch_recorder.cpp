@@ -3,6 +3,7 @@
 #include <hip/hip_runtime_api.h>
 #include <map>
 #include <string>
+#include <stdlib.h>
 #include <string.h>
 #include <vector>
 
@@ -55,7 +56,8 @@ hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_tR0600* p, int) {
   return hipSuccess;
 }
 hipError_t hipDeviceGetAttribute(int* value, hipDeviceAttribute_t, int) {
-  *value = 256;   // compute units
+  const char* cus = getenv("RECORDER_COMPUTE_UNITS");
+  *value = cus ? atoi(cus) : 256;
   return hipSuccess;
 }
 hipError_t hipGetLastError(void) { return hipSuccess; }

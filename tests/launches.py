@@ -15,12 +15,13 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 Launch = namedtuple("Launch", "kernel blocks threads lds limit")
 
 
-def record(calls, directory):
+def record(calls, directory, compute_units=256):
     so = os.path.join(str(directory), "librecorder.so")
     if not os.path.exists(so):
         rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
         subprocess.run(["g++", "-shared", "-fPIC", "-O1", "-D__HIP_PLATFORM_AMD__", "-I" + os.path.join(rocm, "include"), os.path.join(HERE, "launch_recorder.cpp"), "-o", so], check=True)
-    r = subprocess.run([sys.executable, os.path.abspath(__file__), so], input=json.dumps(calls), capture_output=True, text=True, timeout=120)
+    r = subprocess.run([sys.executable, os.path.abspath(__file__), so], input=json.dumps(calls), capture_output=True, text=True, timeout=120,
+                       env=dict(os.environ, RECORDER_COMPUTE_UNITS=str(compute_units)))
     assert r.returncode == 0, r.stderr
     out = json.loads(r.stdout)
     mangled = sorted({k for _, ls in out for k, *_ in ls})

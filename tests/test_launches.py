@@ -9,7 +9,7 @@ import paper_2512_03383_amd as uq
 @pytest.fixture(scope="module")
 def record(tmp_path_factory):
     directory = tmp_path_factory.mktemp("recorder")
-    return lambda calls: la.record(calls, directory)
+    return lambda calls, **kw: la.record(calls, directory, **kw)
 
 
 def linear(N, K, M, keep={}, **kw):
@@ -78,3 +78,13 @@ def test_last_round_goes_out_as_halves(record, bf16):
         tile = reported(launches[0].kernel)[1:3]
         halves, tiles = ps.half_tiles(N - 3, M, tile)
         assert rc == 0 and tile[0] == tokens and halves > 0 and launches[0].blocks == tiles + halves, (bits, K, N, M, launches)
+
+
+# lines that are rounds of the compute units follow the device's number of them
+@pytest.mark.parametrize("cus", [256, 128])
+def test_rounds_are_the_devices(record, cus):
+    def ring(bits, M, *row_tiles):
+        return ["w_ring_kernel" in launches[0].kernel for _, launches in record([linear(16 * n, 4096, M, bits=bits) for n in row_tiles], compute_units=cus)]
+    for bits in (8, 3):   # one round of the pipelined kernel's 32-row tiles
+        assert ring(bits, 16, cus, cus + 1, 2 * cus, 2 * cus + 1) == [True, False, False, True]
+    assert ring(3, 16, 3 * cus, 3 * cus + 1, 4 * cus, 4 * cus + 1) == [True, False, False, True]   # four fragments a block
