@@ -70,8 +70,10 @@ static inline bool ring_serves(const LinearArgs& a) {
 //    rows of up to 32 groups (0.85..1.32 of its time here), longer rows up to 768 row tiles 0.70..0.87, two in a launch 0.64..1.01.  Above that one by itself still is
 //    the faster (0.61..1.07), but not two (gate and up; 330 sizes): 769..1024 row tiles 0.80..1.32 (13416 x 11392 at 3 tokens 38.3 -> 50.4 us), 1025..1280 0.70..1.14, and
 //    beyond 0.84..1.10 at 2..4 tokens; there from 5 tokens on 0.67..0.98.  Rows of 8..15 groups up to 768 row tiles 0.84..1.04, two 0.84..1.04, beyond 0.75..1.23.
+//    Rows of 16..32 groups up to 768 row tiles (576 sizes) where two of these hold: five tokens and more, bfloat16, at most 20 groups: 0.88..1.01, two 0.81..1.02, but
+//    others 1.0..1.15 and 0.93..1.08.
 //    Where a tall matrix comes here its set with short ones, which are here, is one launch again, which it had stopped being: 10240 + 1024 rows x 5120 columns at
-//    8 tokens 22.6 -> 14.7 us (16.4 in one of the block-staged kernel), 12288 + 1024 + 1024 x 12288 43.0 -> 32.9 (41.4).  Others stay two launches:
+//    8 tokens 22.6 -> 14.7 us (16.4 in one of the block-staged kernel), 12288 + 1024 + 1024 x 12288 43.0 -> 32.9 (41.4), x 2560 12.9 -> 9.9 (10.0).  Others stay two launches:
 //    12288 + 1024 + 1024 x 4096 at 2 / 8 tokens 15.8 / 17.5 (14.4 / 15.4 in one of
 //    the block-staged kernel, 14.1 in one of this; 14336 + 1024 16.0 / 17.8, 14.6 / 15.6 and 14.4), as by themselves they would lose more here
 //    (14336 x 4096 at 8 tokens 11.4 -> 14.1), and 21350 + 2666 + 2666 x 1024 at 5 tokens 11.4 (7.9 in one of the block-staged kernel).  The same at 9..16 tokens with four fragments (14336 + 1024 x 4096 at 16 tokens 19.4, 16.0, 14.9).
@@ -104,7 +106,7 @@ static inline bool ring_takes(const LinearArgs& a, bool segments_keep) {   // se
   }
   if (a.M <= 8) {
     if (row_tiles < 640) return true;
-    if (row_tiles <= 3 * compute_units()) return !shorter || groups < 16;
+    if (row_tiles <= 3 * compute_units()) return !shorter || groups < 16 || (a.M > 4) + (a.bf16 != 0) + (groups <= 20) >= 2;
     return !shorter && a.M > 4 && row_tiles > 5 * compute_units() && row_tiles <= kRingTallest;
   }
   if (row_tiles < 400) return true;

@@ -61,6 +61,8 @@ def test_decode_batches_of_mixed_heights(record, M):
     sets = [[(12288, 8192, {}), (1024, 8192, {}), (1024, 8192, {})], [(10240, 5120, {}), (1024, 5120, {})], [(12200, 1920, {}), (1024, 1920, {})],
             [(9700, 4096, {}), (4096, 4096, {})], [(4096, 1536, {}), (4096, 4096, {})], [(2048, 1024, {}), (1024, 2048, {}), (300, 1920, {})], [(8192, 4096, {}), (1024, 4096, {}), (1024, 4096, {})]]
     assert [len(launches) for _, launches in record([dict(specs=s, M=M) for s in sets])] == [1] * len(sets)
+    tall = [[(12288, K, {}), (1024, K, {}), (1024, K, {})] for K in (2048, 2560, 4096)]
+    assert [[len(launches) for _, launches in record([dict(specs=s, M=M, bf16=b) for s in tall])] for b in (False, True)] == ([[1, 1, 2], [1, 1, 1]] if M > 4 else [[2, 2, 2], [1, 1, 2]])
 
 
 # rows of fewer than sixteen groups and longer ones in one launch

@@ -7,8 +7,8 @@ from paper_2512_03383_amd import KeepDesc
 RING = 8   # waves that K is split over
 
 
-def ring(N, K, M, keep, ldx=None, bits=4):
-    c = uq.uniql_w4_linear_kernel(N, K, keep, M, ldx=ldx, bits=bits)
+def ring(N, K, M, keep, ldx=None, bits=4, bf16=False):
+    c = uq.uniql_w4_linear_kernel(N, K, keep, M, ldx=ldx, bits=bits, bf16=bf16)
     return c[0] == 1 and c[3] == RING
 
 
@@ -46,12 +46,15 @@ def test_tall_prefixes(M):
     assert ring(24576, 4096, M, None) and not ring(24577, 4096, M, None) and not ring(16385, 4224, M, None)
 
 
-# up to 8 tokens: prefixes that the block-staged kernel cannot hold whole, and rows of fewer than sixteen groups, up to three rounds of the compute units; from
+# up to 8 tokens: prefixes that the block-staged kernel cannot hold whole, rows of fewer than sixteen groups and some longer ones, up to three rounds of the compute units; from
 # five tokens on also long rows beyond five
 @pytest.mark.parametrize("M", [2, 4, 5, 8])
 def test_tall_prefixes_of_few_tokens(M):
     assert ring(10224, 4096, M, None) and not ring(10225, 4096, M, None) and ring(10225, 4224, M, None) and ring(12288, 4224, M, None)
-    assert ring(12288, 1920, M, None) and not ring(12289, 1920, M, None) and not ring(10225, 2048, M, None)
+    assert ring(12288, 1920, M, None) and not ring(12289, 1920, M, None)
+    for K in (2048, 2560, 2688, 4096):   # two of five tokens and more, bfloat16, at most 20 groups
+        for bf16 in (False, True):
+            assert ring(10225, K, M, None, bf16=bf16) == ring(12288, K, M, None, bf16=bf16) == ((M > 4) + bf16 + (K <= 2560) >= 2) and not ring(12289, K, M, None, bf16=bf16)
     assert not ring(12289, 4224, M, None) and not ring(16384, 5248, M, None) and not ring(16385, 8192, M, None) and not ring(20480, 8192, M, None)
     assert ring(20481, 4224, M, None) == ring(24576, 8192, M, None) == (M > 4) and not ring(24577, 8192, M, None) and not ring(20481, 4096, M, None)
     assert ring(9600, 8192, M, KeepDesc(col_seg_stride=128, col_seg_keep=108)) and not ring(9601, 8192, M, KeepDesc(col_seg_stride=128, col_seg_keep=108))
