@@ -148,10 +148,10 @@ typedef struct uniql_keep {
  *   ldx >= k_keep, ldy >= n_keep (elements); x and y must not overlap (this is not checked:
  *   with overlapping buffers the result is undefined).
  * M = 1 runs the streaming GEMV; M >= 2 the MFMA dequant-GEMMs: 2..32 tokens the decode-batch
- * kernels (up to 600 tiles of 16 rows, and most matrices up to 1536 from 9 tokens on or of codes
- * of 8, 6 and 3 bits, the ring kernel: K over eight waves that each load for themselves; others: a
- * wave owns 16 rows and part of K), more tokens, the remaining tall matrices from 9 tokens on and
- * the remaining ones of codes of 8, 6 and 3 bits the pipelined kernel (loads in waves of their own; few rows or very few tokens of those widths the
+ * kernels (most matrices of up to 600 tiles of 16 rows, and many of up to 1536, the ring kernel: K over
+ * eight waves that each load for themselves; others: a wave owns 16 rows and part of K), more tokens, the
+ * remaining tall matrices from 9 tokens on and the remaining ones of codes of 8, 6 and 3 bits the pipelined
+ * kernel (loads in waves of their own; few rows or very few tokens of those widths the
  * streaming one), long prompts 256 x 256 tiles, rules that these do not take tiles with K split over waves.
  * Errors: E_NULL, E_SHAPE, E_KEEP, E_ALIGN, E_ARCH, E_HIP.  E_SHAPE also at M = 1 when the last
  * kept column lies past stored column 81920 (the block's image of the activations in LDS holds

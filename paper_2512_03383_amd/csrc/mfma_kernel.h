@@ -416,11 +416,11 @@ enum GemmRoute {
   kTile16x16k8, kTile16x64k4, kTile32x16k8, kTile32x64k4, kTile64x32k4, kTile64x64k4
 };
 
-// Column segments of 17..32 tokens that the decode-batch kernel keeps: those whose kept columns are not whole blocks of eight, which the
-// pipelined kernel's movers clear slab after slab, in long rows of up to 256 row tiles (more are two rounds of the other kernel's waves:
-// 5120 x 8192 23.3 us there, 16.6 here).  24 tokens, there against here, fp16: 98..108 of 128 or 54 of 64 columns 1024 x 4096 9.3 / 9.5,
+// Column segments of 17..32 tokens that the block-staged kernel keeps, before the pipelined one and, with longer rows, before the ring kernel (ring_takes): those
+// whose kept columns are not whole blocks of eight, which the pipelined kernel's movers clear slab after slab, in long rows of up to 256 row tiles (more are two rounds
+// of the other kernel's waves: 5120 x 8192 23.3 us there, 16.6 here).  24 tokens, there against here, fp16: 98..108 of 128 or 54 of 64 columns
 // 1024 x 14208 20.6 / 23.6, 3584 x 8192 16.6 / 16.6, 3584 x 14208 23.2 / 25.2; 26 of 32 columns 1024 x 8192 14.1 / 17.9.  bfloat16, whose
-// unpack is longer there, 54 of 64 1024 x 8192 14.8 / 13.6, 1024 x 14208 21.5 / 20.6; 26 of 32 1024 x 8192 14.8 / 16.8.
+// unpack is longer there, 54 of 64 1024 x 14208 21.5 / 20.6; 26 of 32 1024 x 8192 14.8 / 16.8.
 static inline bool segments_stay(const LinearArgs& a) {
   const KeepMap& km = a.km;
   if (km.cs_keep % 8 == 0 || km.n_keep > 4096) return false;
@@ -433,21 +433,13 @@ static inline GemmRoute gemm_route(const LinearArgs& a, int xm) {
   const int row_tiles = (a.km.n_keep + 15) / 16;
   const bool pipe = xm != 0 && pipe_serves(a);
   if (xm != 0 && ring_takes(a, segments_stay(a))) return kRing;
-  // Decode batches (M <= 32) are bound by the weight stream and have a kernel of their own (smallm_kernel.h), except
-  // tall matrices from 9 tokens on whose activations it cannot stage once per block: a wave that stages its own 16 x 128
-  // activations per group costs more than the pipelined kernel's slabs (9472 x 4096 at 12 / 24 tokens 16.9 / 23.3 us there,
-  // 11.4 / 14.1 here, 6400 x 4096 9.6 / 12.7 and 8.7 / 9.4; with 256 row tiles it is the other way round at 9..16 tokens and level
-  // beyond: 4096 x 9344 at 12 / 24 tokens 12.3 / 16.7 there, 13.9 / 16.6 here).  Up to 8 tokens the two are closer (6400 x 4096 8.6 in
-  // both, 9472 x 4096 13.4 there, 11.4 here), and a tall matrix in the other kernel would no longer share a launch with short ones: 8192 +
-  // 1024 + 1024 rows x 8192 columns at 8 tokens 21.4 us in one launch, 28 in three.  From 9 tokens on such a set is two launches, 0.85..1.1 of
-  // the time of one at 17..32 tokens and 0.94..1.2 at 9..16 (8192 + 1024 + 1024 at 9 / 24 tokens, one -> two: x 8192 25.4 / 35.3 -> 25.4 / 30.7,
-  // x 4096 15.9 / 21.8 -> 16.8 / 20.2, x 2560 14.0 / 19.3 -> 15.9 / 19.2); a set of 6400 + 1536 x 2560, which stages its activations once
-  // a block where it is one launch, takes 1.6..1.75 times as long in two (9 / 32 tokens 8.3 / 10.9 -> 14.3 / 17.7).
-  // (Below 400 row tiles a tall matrix by itself is still faster here, 6000 x 4096 at 9 / 16 / 32 tokens 9.5 / 9.6 / 12.8 there, 8.5 / 8.8 /
-  // 9.6 here, but in a set with short ones it costs a launch of its own: 6000 + 1536 rows x 2560 columns at 9 / 32 tokens 8.1 / 10.3 in
-  // one launch, 13.6 / 16.5 in two, x 4096 12.2 / 16.9 and 14.8 / 17.9, x 8192 18.7 / 26.0 and 22.0 / 28.1.)  Column segments, whose activations a wave
-  // of the other kernel gathers for itself, come here from 17 tokens on (but see segments_stay): 4096 x 4096, 108 of 128, at 24 / 32
-  // tokens 10.3 / 10.7 there, 9.2 / 9.3 here, 2560 x 5120, 54 of 64, 11.2 / 11.6 and 10.8 / 10.8; at 9..16 tokens level.
+  // What the ring kernel leaves of the decode batches (M <= 32): up to 8 tokens most prefixes of 640 row tiles and more, segments of more row tiles than it takes,
+  // rows of fewer than eight groups, from 9 tokens on long rows of 400 row tiles and more.  They are bound by the weight stream and have another kernel of
+  // their own (smallm_kernel.h), except tall matrices from 9 tokens on whose activations it cannot stage once per block: a wave that stages its own 16 x 128
+  // activations per group costs more than the pipelined kernel's slabs (before the ring kernel 9472 x 4096 at 12 / 24 tokens 16.9 / 23.3 us there,
+  // 11.4 / 14.1 here).  A set of such a matrix and short ones, which are the ring kernel's, is two launches: 8192 + 1024 + 1024 rows x 8192 columns at 9 / 24 tokens
+  // 21.7 / 27.5 us, 25.4 / 35.3 in one of the block-staged kernel.  Column segments, whose activations a wave of the pipelined kernel gathers for itself, come here
+  // from 17 tokens on (but see segments_stay); at 9..16 tokens the two are level.
   const bool tall = row_tiles >= 400 && a.M >= 9 && !(xm == 1 && smallm_pre(a));
   if (smallm_takes(a, xm == 1) && !(pipe && (tall || (xm == 2 && a.M >= 17 && !segments_stay(a))))) return kSmallM;
   if (pipe && a.M <= 64) return kPipe;

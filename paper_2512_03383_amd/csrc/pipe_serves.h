@@ -80,9 +80,10 @@ static inline bool ring_serves(const LinearArgs& a) {
 //  - Rows of 8..15 groups, prefixes, go by the same lines: 0.49..0.93 up to 375 row tiles (384 sizes), 0.69..1.06 above.  Without them a set of such rows and longer ones
 //    was two launches where it had been one: 4096 x 1536 + 4096 x 4096 at 8 / 24 tokens 12.4 / 17.3 -> 8.6 / 9.9 us (9.6 / 16.0 in one of the block-staged
 //    kernel), 2048 x 1024 + 1024 x 2048 9.3 / 12.8 -> 4.2 / 5.3 (6.0 / 8.5).  Segments and other widths, which never shared one, stay.
-//  - Segments of 17..32 tokens, up to 256 row tiles, beyond 32 groups (460 sizes): up to 64 groups 0.77..1.01, bfloat16 and whole blocks as fp16 and partial
-//    ones; but 0.94..1.06 on more than 192 row tiles from 25 tokens on, and segments of fewer than 64 columns that keep part of a block (1.04..1.25
-//    on long rows) stay.  65..96 groups up to 192 row tiles 0.77..0.99; partial blocks in fp16 (0.93..1.03), more row tiles (up to 1.09) and longer rows (up to 1.11) stay.
+//  - Segments of 17..32 tokens, up to 256 row tiles, beyond 32 groups (460 and 420 sizes): up to 64 groups 0.77..1.05, 0.90 in the mean, bfloat16 and whole blocks as
+//    fp16 and partial ones; but 0.94..1.06 on more than 192 row tiles from 25 tokens on, and segments of fewer than 64 columns that keep part of a block
+//    (1.04..1.25 on long rows) stay.  65..96 groups up to 192 row tiles 0.77..1.08, 0.90 in the mean; partial blocks in fp16 (0.93..1.03), more row tiles (up to 1.09)
+//    and longer rows (up to 1.11) stay.
 // (33..64 tokens: a block of 16 rows fetches all of the activations, 29 bytes a clock, which is what takes the time: 0.82 to 1.6, and where
 // it was faster by itself the pass of a layer was not.)
 constexpr int kRingTallest = 1536;   // row tiles
@@ -123,7 +124,8 @@ static inline bool ring_takes(const LinearArgs& a, bool segments_keep) {   // se
 // of 256 tiles of 32 rows (3 bits, which have 64-row tiles too: in proportion).  Ties go to the streaming kernel.  The p are
 // of an earlier form of the pipelined kernel, which has become faster.  Over 2500 sizes the kernel picked takes 0.2 to 0.9 % longer than
 // the faster one in the mean on prefixes and 1.1 to 2.0 % on segments; the worst are matrices of 1000..2000 rows and long segmented
-// rows, which stay with the streaming kernel (3 bits, 1024 x 12160, 108 of 128 columns, 11 tokens 35.5 us for 18.9).
+// rows (3 bits, 1024 x 12160, 108 of 128 columns, 11 tokens 35.5 us for 18.9).  Since then the ring kernel has taken what it serves of both from 4096 outputs on
+// (ring_takes_wide, below), so this decides up to there, and for rows of up to fifteen groups, matrices of more than 1536 row tiles and the bands that it leaves.
 static inline bool wide_streams(const LinearArgs& a) {
   struct Line { float s0, s1, s2, s3, s4, p0, p1, p2, p3, p4; };
   static const Line lines[3][2] = {   // 8, 6, 3 bits; fp16, bfloat16
