@@ -70,13 +70,15 @@ static inline PipeTile pipe_pick(const LinearArgs* p, int n) {
     t.us = tiles * kPipeMostThreads >= (1ll << 32) ? 1e30f : launch_cost(tiles, (float)((ngroups + t.g - 1) / t.g), seg ? t.seg : t.prefix, span > 8192 ? 1.18f : 1.f);
     // A last round of at most half as many tiles as there are compute units goes out as halves of the tokens, two blocks a tile.  Such a
     // round takes 0.78 (128 tokens) or 0.82 (96) of a whole one, with 500 sizes timed both ways (1.1 .. 8 rounds, all widths): the launch
-    // 0.85 to 0.997 of the time.  The costs here are a little above, so that another tile is not left for too small a gain.
+    // 0.85 to 0.997 of the time.  The costs here are a little above, so that another tile is not left for too small a gain.  Prefixes of 4 and 3 bits have 112-token
+    // tiles, whose two rounds were rated level with one of 128 tokens and its halves but are the faster on long rows (54 such sizes 0.91 to 1.04 of their time; 11642 x
+    // 5376 at 491 tokens 85.9 us, 94.8 in halves): one more, and halves are left to where they gain (11843 x 3200 twice at 255 tokens 73.3 -> 61.5).
     if (way == kPipeHalves && pipe_halves(BITS, t.af) && tiles < (1 << 20)) {
       const int cus = compute_units(), rest = (int)(tiles % cus);
       if (tiles > cus && rest > 0 && 2 * rest <= cus) {
         const TileCost& c = seg ? t.seg : t.prefix;
         const float steps = (float)((ngroups + t.g - 1) / t.g), far = span > 8192 ? 1.18f : 1.f;
-        const float us = launch_cost(tiles - rest, steps, c, far) + (t.af == 8 ? 0.8f : 0.88f) * (4.f + steps * (c.us + c.slope) * far);
+        const float us = launch_cost(tiles - rest, steps, c, far) + (t.af != 8 ? 0.88f : BITS <= 4 && !seg ? 0.87f : 0.8f) * (4.f + steps * (c.us + c.slope) * far);
         if (us < t.us) t.us = us, t.whole = (int)tiles - rest;
       }
     }

@@ -30,10 +30,10 @@ def tiles(bits, segments):
 
 
 # (bits, K, N, M, segments, tokens of a tile): grids whose last round goes out as halves of its tiles; in those with at most half a tile of tokens left over
-# (8170 x 1170, 19027 x 700, 5068 x 777) second halves have no token.  Codes of 8 bits in 128-token tiles are also brought into the L2 ahead.
+# (8170 x 1170, 23680 and 19027 x 700, 5068 x 777) second halves have no token.  Codes of 8 bits in 128-token tiles are also brought into the L2 ahead.
 HALVES = [(8, 1024, 6102, 1000, False, 128), (8, 1024, 6102, 1000, True, 128), (8, 1024, 8170, 1170, False, 128), (8, 1024, 8170, 1170, True, 128), (8, 1152, 12185, 500, False, 128),
           (6, 1024, 8170, 1170, False, 128), (6, 1024, 8170, 1170, True, 128), (6, 1024, 5068, 777, False, 96), (6, 1024, 5068, 777, True, 96)]
-HALVES += [(bits, *size) for bits in (4, 3) for size in ((1024, 8170, 1170, False, 128), (1152, 12185, 500, False, 128), (1024, 16442, 1500, True, 128), (1024, 19027, 700, True, 128),
+HALVES += [(bits, *size) for bits in (4, 3) for size in ((1024, 11789, 1500, False, 128), (1024, 23680, 700, False, 128), (1024, 16442, 1500, True, 128), (1024, 19027, 700, True, 128),
                                                          (1024, 5068, 777, False, 96), (1024, 5068, 777, True, 96))]
 
 
